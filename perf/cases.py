@@ -164,7 +164,8 @@ def _cells(case, gen, dev, chunk=1 << 20):
 _PATTERNS = {"band": _band, "blocks": _blocks, "graph": _graph, "cells": _cells}
 
 
-def prepare(case, seed):
+def _inputs(case, seed):
+    """CSR arrays, B, and for "update" the next time step's values (else the same values)."""
     dev = torch.device("cuda:0")
     gen = torch.Generator(device=dev)
     gen.manual_seed(seed)
@@ -175,14 +176,34 @@ def prepare(case, seed):
         vals = torch.ones(nnz, device=dev)                          # adjacency
     else:
         vals = torch.rand(nnz, generator=gen, device=dev) * 2 - 1
-    state = {"mode": case["mode"], "M": M, "rowptr": rowptr, "colind": colind, "vals": vals,
-             "B": torch.randn((M, N), generator=gen, device=dev),
-             "C": torch.empty((M, N), device=dev)}
+    B = torch.randn((M, N), generator=gen, device=dev)
+    new_vals = vals
+    if case["mode"] == "update":
+        new_vals = torch.rand(nnz, generator=gen, device=dev) * 2 - 1
+    return rowptr, colind, vals, B, new_vals
+
+
+def prepare(case, seed):
+    M, N = case["M"], case["N"]
+    rowptr, colind, vals, B, new_vals = _inputs(case, seed)
+    state = {"mode": case["mode"], "M": M, "rowptr": rowptr, "colind": colind, "vals": new_vals,
+             "B": B, "C": torch.empty((M, N), device=B.device)}
     if case["mode"] != "oneshot":
         state["plan"] = spmm.spmm_plan(M, M, rowptr, colind, vals)
-    if case["mode"] == "update":                                    # the next time step's values
-        state["vals"] = torch.rand(nnz, generator=gen, device=dev) * 2 - 1
     return state
+
+
+def exact(case, seed, chunk=1 << 27):
+    """The same product in 64 bits, a range of entries (about `chunk` products) at a time."""
+    M, N = case["M"], case["N"]
+    rowptr, colind, _, B, vals = _inputs(case, seed)
+    rows = torch.repeat_interleave(torch.arange(M, device=B.device), rowptr.diff().long())
+    C = torch.zeros((M, N), dtype=torch.float64, device=B.device)
+    step = max(1, chunk // N)
+    for e in range(0, rows.numel(), step):
+        part = B[colind[e:e + step].long()].double() * vals[e:e + step, None].double()
+        C.index_add_(0, rows[e:e + step], part)
+    return C
 
 
 def run(state):
