@@ -206,7 +206,10 @@ int build_host_list(spmm_plan_t* pl, int64_t N, const HostList** out) {
     hl = new HostList();
     hl->id = g_next_list_id.fetch_add(1);
     hl->N = N;
-    const int tile = mfma_tile_for(std::max<int64_t>(N, 1));
+    const bool bf16 = pl->precision != SPMM_PRECISION_FP32 &&
+                      bf16_path_shape(std::max<int64_t>(N, 1), pl->K);
+    const int tile = bf16 ? mfma_tile_for(std::max<int64_t>(N, 1))
+                          : mfma_fp32_tile(std::max<int64_t>(N, 1), pl->K);
     hl->info.n_tile = tile;
     hl->info.n_tiles = (int32_t)ceil_div(std::max<int64_t>(N, 1), tile);
     hl->info.num_cus = pl->num_cus;
@@ -239,8 +242,6 @@ int build_host_list(spmm_plan_t* pl, int64_t N, const HostList** out) {
     const int64_t nm = (int64_t)mfma_panels.size();
     std::vector<uint32_t> parts((size_t)nm, 1u);
     int64_t waves = 1;
-    const bool bf16 = pl->precision != SPMM_PRECISION_FP32 &&
-                      bf16_path_shape(std::max<int64_t>(N, 1), pl->K);
     const int resident =
         bf16 ? bf16_resident_waves_per_cu(std::max<int64_t>(N, 1),
                                           pl->precision == SPMM_PRECISION_BF16X3 ? 2 : 3)

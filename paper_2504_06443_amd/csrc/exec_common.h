@@ -38,6 +38,44 @@ __device__ inline void store_vec(float* __restrict__ p, const float (&in)[V]) {
   *reinterpret_cast<vt*>(p) = v;
 }
 
+// V consecutive floats at a 4-byte aligned address, V = 1..4: one global load or store of V dwords,
+// which gfx950 does at any dword address (V = 3 through a struct: a three-element vector type
+// would be widened to four elements and touch memory behind the last one).
+template <int V> struct AnyVec { typedef float type __attribute__((ext_vector_type(V), aligned(4))); };
+template <> struct AnyVec<1> { typedef float type; };
+
+template <int V>
+__device__ inline void load_any(const char* __restrict__ p, float* out) {
+  if constexpr (V == 3) {
+    struct F3 { float x, y, z; };
+    const F3 t = *reinterpret_cast<const F3*>(p);
+    out[0] = t.x; out[1] = t.y; out[2] = t.z;
+  } else {
+    const typename AnyVec<V>::type t = *reinterpret_cast<const typename AnyVec<V>::type*>(p);
+    if constexpr (V == 1) out[0] = t;
+    else {
+#pragma unroll
+      for (int w = 0; w < V; ++w) out[w] = t[w];
+    }
+  }
+}
+
+template <int V>
+__device__ inline void store_any_nt(float* __restrict__ p, const float* in) {
+  if constexpr (V == 3) {
+#pragma unroll
+    for (int w = 0; w < 3; ++w) __builtin_nontemporal_store(in[w], p + w);
+  } else {
+    typename AnyVec<V>::type t;
+    if constexpr (V == 1) t = in[0];
+    else {
+#pragma unroll
+      for (int w = 0; w < V; ++w) t[w] = in[w];
+    }
+    __builtin_nontemporal_store(t, reinterpret_cast<typename AnyVec<V>::type*>(p));
+  }
+}
+
 // Workgroups are handed to the 8 XCDs round-robin, and each XCD has its own L2.  This maps a
 // workgroup to a "virtual" index such that each XCD works through a contiguous range of work
 // items: neighbouring panels -- which share most of their B rows in banded matrices -- then

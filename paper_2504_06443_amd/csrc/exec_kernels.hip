@@ -30,6 +30,7 @@
 // multiple of four.  Used for the panels that the routing sends to the CSR path.
 #include "exec_common.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace spmm {
@@ -201,8 +202,13 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void k_spmm_mfma(
 }
 
 // ------------------------------------------------------------------ MFMA, fast path
-// Same lane mapping as above for the common case: N a multiple of the vector
-// width, 16-byte aligned B and C, and B smaller than 4 GiB (32-bit byte offsets).
+// Same lane mapping as above for B smaller than 4 GiB (32-bit byte offsets), any N and any
+// dword-aligned B and C, on tiles of 16*T columns, T = 1..8.  A lane owns one vector of W0 =
+// min(T, 4) columns and, for T > 4, a second one of W1 = T - 4.  Loads and stores need no more
+// than dword alignment, so rows of an odd N are read with the same vectors as rows of a whole
+// one.  A vector that reaches past column N is moved back to end at N, for the load and for the
+// store: its lane then holds some columns that its neighbour holds too, with the same bits, and
+// both store them.
 //
 // Vector-ALU instructions overlap only partly with MFMAs on a SIMD (measured:
 // about 2 cycles of MFMA time lost per extra VALU instruction), so the per-brick
@@ -229,8 +235,7 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void k_spmm_mfma_fast(
     float* __restrict__ C, float* __restrict__ partial, int64_t M, int64_t N, uint32_t k_last) {
   // (the format arrays are separate __restrict__ parameters, not a struct, so that
   // the compiler knows they are read-only here and may use the scalar cache)
-  constexpr int V = T < 4 ? T : 4;
-  constexpr int NV = T / V;
+  constexpr int W0 = T < 4 ? T : 4, W1 = T - W0;   // columns of the lane's first, second vector
   constexpr int R = kStages;
   constexpr int CH = kFastChunk;
   static_assert(CH % R == 0 && CH * kBrickK <= 64, "stage and lane mapping assume this");
@@ -251,13 +256,13 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void k_spmm_mfma_fast(
   const int j = lane & 15;
   const int kq = lane >> 4;
   const uint32_t perm_transpose = 4u * (uint32_t)(4 * j + kq);  // ds_bpermute: read lane 4j + kq
-  const int64_t ncol0 = (int64_t)blockIdx.y * (16 * T) + V * j;
   const uint32_t row_bytes = (uint32_t)N * 4u;
-  // byte offset of this lane's vectors inside a B row (columns >= N: clamped, never stored)
-  uint32_t lane_off[NV];
-#pragma unroll
-  for (int q = 0; q < NV; ++q)
-    lane_off[q] = (uint32_t)min<int64_t>(ncol0 + q * 16 * V, N - V) * 4u;
+  // first columns of this lane's vectors and their byte offsets inside a B row (a vector that
+  // would reach past N ends at N; N >= W0 and, where there is a second vector, N > 64)
+  const uint32_t ncol0 = blockIdx.y * (16u * T) + W0 * j;
+  const uint32_t ncol1 = blockIdx.y * (16u * T) + 64u + W1 * j;
+  const uint32_t at0 = min(ncol0, (uint32_t)N - W0), at1 = min(ncol1, (uint32_t)N - W1);
+  const uint32_t lane_off0 = at0 * 4u, lane_off1 = at1 * 4u;
   const uint32_t perm_base = 4u * (uint32_t)kq;  // ds_bpermute byte address of lane kq
 
   float4_t acc[T];
@@ -308,16 +313,10 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void k_spmm_mfma_fast(
       // scalar base + 32-bit byte offset (the launcher checks that the values fit 4 GiB)
       st_a[s] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(vals) +
                                                 (off * 4u + cnt * 4u));
-      const char* brow = Bbytes + (ro + lane_off[0]);
-#pragma unroll
-      for (int q = 0; q < NV; ++q) {
-        float tmp[V];
-        // whole tiles: the q-th vector lies a constant distance behind the first
-        if constexpr (FULL) load_vec<V>(reinterpret_cast<const float*>(brow + q * 16 * V * 4), tmp);
-        else load_vec<V>(reinterpret_cast<const float*>(Bbytes + (ro + lane_off[q])), tmp);
-#pragma unroll
-        for (int w = 0; w < V; ++w) st_b[s][q * V + w] = tmp[w];
-      }
+      const char* brow = Bbytes + (ro + lane_off0);
+      load_any<W0>(brow, &st_b[s][0]);
+      // whole 128-column tiles: the second vector lies a constant distance behind the first
+      if constexpr (W1 > 0) load_any<W1>(FULL ? brow + 256 : Bbytes + (ro + lane_off1), &st_b[s][W0]);
     };
     // the A operand of the brick in stage s: zero fill, then the transposition
     auto operand = [&](int s) {
@@ -416,7 +415,7 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void k_spmm_mfma_fast(
     }
   }
 
-  // acc[q*V + w][v] = C[row 4*kq + v][ncol0 + q*16*V + w]
+  // acc[w][v] = C[row 4*kq + v][at0 + w], acc[W0 + w][v] = C[row 4*kq + v][at1 + w]
   float* out;
   int64_t rows_left;
   if (slot == kNoSlot) {
@@ -430,20 +429,13 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void k_spmm_mfma_fast(
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
     if (v < rows_left) {
+      float t[T];
 #pragma unroll
-      for (int q = 0; q < NV; ++q) {
-        const int64_t ncol = ncol0 + q * 16 * V;
-        if (ncol < N) {
-          typedef typename Vec<V>::type vt;
-          vt t;
-          if constexpr (V == 1) t = acc[q][v];
-          else {
-#pragma unroll
-            for (int w = 0; w < V; ++w) t[w] = acc[q * V + w][v];
-          }
-          // C is written once and not read again here: stream it past the caches
-          __builtin_nontemporal_store(t, reinterpret_cast<vt*>(out + v * N + ncol));
-        }
+      for (int w = 0; w < T; ++w) t[w] = acc[w][v];
+      // C is written once and not read again here: stream it past the caches
+      if (ncol0 < (uint32_t)N) store_any_nt<W0>(out + v * N + at0, t);
+      if constexpr (W1 > 0) {
+        if (ncol1 < (uint32_t)N) store_any_nt<W1>(out + v * N + at1, t + W0);
       }
     }
   }
@@ -649,8 +641,7 @@ __global__ __launch_bounds__(64 * kLongWaves) void k_spmm_valu_long(
 
 // ------------------------------------------------------------------ merge (a8)
 // Sum the partial 16 x N tiles of a split panel in part order and store to C.
-// One workgroup per split panel; VEC floats per thread per step.
-template <int VEC>
+// One workgroup per split panel; four floats per thread per step.
 __global__ __launch_bounds__(256) void k_merge(const MergeItem* __restrict__ items,
                                                const float* __restrict__ partial,
                                                float* __restrict__ C, int64_t M, int64_t N) {
@@ -660,17 +651,22 @@ __global__ __launch_bounds__(256) void k_merge(const MergeItem* __restrict__ ite
   const int64_t tile = (int64_t)kPanel * N;
   const float* src = partial + (int64_t)it.slot_begin * tile;
   float* dst = C + row0 * N;
-  for (int64_t x = (int64_t)threadIdx.x * VEC; x < rows * N; x += (int64_t)blockDim.x * VEC) {
-    float s[VEC];
-    load_vec<VEC>(src + x, s);
+  auto merge = [&](auto width, int64_t x) {
+    constexpr int V = decltype(width)::value;
+    float s[V];
+    load_any<V>(reinterpret_cast<const char*>(src + x), s);
     for (uint32_t q = 1; q < it.nparts; ++q) {
-      float t[VEC];
-      load_vec<VEC>(src + (int64_t)q * tile + x, t);
+      float t[V];
+      load_any<V>(reinterpret_cast<const char*>(src + (int64_t)q * tile + x), t);
 #pragma unroll
-      for (int w = 0; w < VEC; ++w) s[w] += t[w];
+      for (int w = 0; w < V; ++w) s[w] += t[w];
     }
-    store_vec<VEC>(dst + x, s);
-  }
+    store_any_nt<V>(dst + x, s);
+  };
+  const int64_t whole = rows * N & ~(int64_t)3;   // the last panel of a ragged M may end off a vector
+  for (int64_t x = (int64_t)threadIdx.x * 4; x < whole; x += (int64_t)blockDim.x * 4)
+    merge(std::integral_constant<int, 4>{}, x);
+  if (whole + threadIdx.x < rows * N) merge(std::integral_constant<int, 1>{}, whole + threadIdx.x);
 }
 
 template <int T, bool ALIGNED>
@@ -705,28 +701,53 @@ int occupancy_fast_t() {
 
 }  // namespace
 
-// the fast kernel serves N that is a multiple of the vector width with B below 4 GiB
+// tiles of 16, 32, 64 or 128 columns: N a multiple of the vector width, B below 4 GiB
 bool mfma_fast_shape(int64_t N, int64_t K) {
   const int tile = mfma_tile_for(N);
   const int V = tile >= 64 ? 4 : tile / 16;
-  return N % V == 0 && K > 0 && (double)K * (double)N * 4.0 < 4294967296.0;
+  return N % V == 0 && mfma_32bit_shape(N, K);
 }
 
+// what the fast FP32 kernel serves: B rows reachable by 32-bit byte offsets
+bool mfma_32bit_shape(int64_t N, int64_t K) {
+  return K > 0 && (double)K * (double)N * 4.0 < 4294967296.0;
+}
+
+// Columns of C per wavefront of the FP32 kernel that serves (N, K).  The fast kernel takes as few
+// tiles of at most 128 columns as N needs, all of the same width, in steps of 16 columns: N = 77
+// is one tile of 80 (five MFMAs a brick), not one of 128 (eight), and N = 144 two of 80, not two
+// of 128.  Measured on 131,072 rows of 3x3 blocks (322 k bricks), against tiles of 16, 32, 64 and
+// 128 with a scalar-load kernel for odd N: N = 48 30.2 -> 26.5 us, 80 50.9 -> 35.3, 144 96.2 ->
+// 64.1, 33 61.5 -> 26.4, 77 139.6 -> 35.8, 511 729 -> 250; N = 16, 32, 64, 128 as before.
+// Where rows start on 128-byte lines (N a multiple of 32), several tiles also end on them (a
+// multiple of 32 columns): a line shared by two tiles is fetched twice.  843 k scattered bricks,
+// tiles of 80 against 96 columns at N = 160: 384 / 328 us; of 112 against 128 at N = 224: 515 /
+// 458.  Other N have no such lines to keep, and there the narrower tile is ahead (N = 144 on the
+// blocks: 137 / 152).
+int mfma_fp32_tile(int64_t N, int64_t K) {
+  if (!mfma_32bit_shape(N, K)) return mfma_tile_for(N);
+  const int64_t tiles = std::max<int64_t>(1, (N + 127) / 128);
+  const int t = (int)std::max<int64_t>(1, ((N + 15) / 16 + tiles - 1) / tiles);
+  return 16 * (tiles > 1 && N % 32 == 0 ? (t + 1) / 2 * 2 : t);
+}
 
 // Wavefronts of the MFMA kernel that fit on one CU at a time, for the kernel variant that
-// (N, K) selects when the operands are 16-byte aligned: the "thread blocks per SM" of Eq. 7.
+// (N, K) selects: the "thread blocks per SM" of Eq. 7.
 int mfma_resident_waves_per_cu(int64_t N, int64_t K) {
-  const int tile = mfma_tile_for(N);
-  const int V = tile >= 64 ? 4 : tile / 16;
-  if (mfma_fast_shape(N, K)) {
-    switch (tile) {
-      case 16: return occupancy_fast_t<1>();
-      case 32: return occupancy_fast_t<2>();
-      case 64: return occupancy_fast_t<4>();
+  if (mfma_32bit_shape(N, K)) {
+    switch (mfma_fp32_tile(N, K) / 16) {
+      case 1: return occupancy_fast_t<1>();
+      case 2: return occupancy_fast_t<2>();
+      case 3: return occupancy_fast_t<3>();
+      case 4: return occupancy_fast_t<4>();
+      case 5: return occupancy_fast_t<5>();
+      case 6: return occupancy_fast_t<6>();
+      case 7: return occupancy_fast_t<7>();
       default: return occupancy_fast_t<8>();
     }
   }
-  const bool aligned = N % V == 0;
+  const int tile = mfma_tile_for(N);
+  const bool aligned = N % (tile >= 64 ? 4 : tile / 16) == 0;
   switch (tile) {
     case 16: return occupancy_t<1, true>();
     case 32: return aligned ? occupancy_t<2, true>() : occupancy_t<2, false>();
@@ -739,12 +760,9 @@ hipError_t launch_spmm_mfma(const BrickFormat& f, const WorkItem* items, int64_t
                             const float* B, float* C, float* partial, int64_t M, int64_t N,
                             int64_t K, int64_t nnz, hipStream_t s) {
   if (n_items == 0 || N == 0) return hipSuccess;
-  const int tile = mfma_tile_for(N);
-  const int V = tile >= 64 ? 4 : tile / 16;
-  const bool al = (N % V == 0) && ptr_aligned16(B) && ptr_aligned16(C) &&
-                  (partial == nullptr || ptr_aligned16(partial));
   // the fast kernel addresses the packed values (and their 64 spare floats) by 32-bit byte offsets
-  if (al && mfma_fast_shape(N, K) && nnz + 64 < (int64_t(1) << 30)) {
+  if (mfma_32bit_shape(N, K) && nnz + 64 < (int64_t(1) << 30)) {
+    const int tile = mfma_fp32_tile(N, K);
     unsigned gx = (unsigned)((n_items + kWavesPerBlock - 1) / kWavesPerBlock);
     gx = (gx + kXcds - 1) / kXcds * kXcds;  // whole rounds over the XCDs
     const dim3 grid(gx, (unsigned)((N + tile - 1) / tile)), block(64 * kWavesPerBlock);
@@ -752,10 +770,14 @@ hipError_t launch_spmm_mfma(const BrickFormat& f, const WorkItem* items, int64_t
 #define SPMM_LAUNCH_FAST(TT, FF)                                                                \
   hipLaunchKernelGGL((k_spmm_mfma_fast<TT, FF>), grid, block, 0, s, f.brick_cols, f.brick_mask, \
                      f.brick_valptr, f.vals, items, n_items, B, C, partial, M, N, k_last)
-    switch (tile) {
-      case 16: SPMM_LAUNCH_FAST(1, false); break;
-      case 32: SPMM_LAUNCH_FAST(2, false); break;
-      case 64: SPMM_LAUNCH_FAST(4, false); break;
+    switch (tile / 16) {
+      case 1: SPMM_LAUNCH_FAST(1, false); break;
+      case 2: SPMM_LAUNCH_FAST(2, false); break;
+      case 3: SPMM_LAUNCH_FAST(3, false); break;
+      case 4: SPMM_LAUNCH_FAST(4, false); break;
+      case 5: SPMM_LAUNCH_FAST(5, false); break;
+      case 6: SPMM_LAUNCH_FAST(6, false); break;
+      case 7: SPMM_LAUNCH_FAST(7, false); break;
       default:   // whole 128-column tiles: the second vector of a B row at a constant offset
         if (N % 128 == 0) SPMM_LAUNCH_FAST(8, true); else SPMM_LAUNCH_FAST(8, false);
         break;
@@ -763,6 +785,10 @@ hipError_t launch_spmm_mfma(const BrickFormat& f, const WorkItem* items, int64_t
 #undef SPMM_LAUNCH_FAST
     return hipGetLastError();
   }
+  const int tile = mfma_tile_for(N);
+  const int V = tile >= 64 ? 4 : tile / 16;
+  const bool al = (N % V == 0) && ptr_aligned16(B) && ptr_aligned16(C) &&
+                  (partial == nullptr || ptr_aligned16(partial));
   switch (tile) {
     case 16: return launch_mfma_t<1, true>(f, items, n_items, B, C, partial, M, N, s);
     case 32: return al ? launch_mfma_t<2, true>(f, items, n_items, B, C, partial, M, N, s)
@@ -817,11 +843,7 @@ hipError_t launch_spmm_valu(const int32_t* rowptr, const int32_t* colind, const 
 hipError_t launch_merge(const MergeItem* items, int64_t n_items, const float* partial, float* C,
                         int64_t M, int64_t N, hipStream_t s) {
   if (n_items == 0 || N == 0) return hipSuccess;
-  // rows * N is a multiple of 4 whenever N is, so whole vectors never straddle the end
-  if (N % 4 == 0 && ptr_aligned16(partial) && ptr_aligned16(C))
-    hipLaunchKernelGGL(k_merge<4>, dim3((unsigned)n_items), dim3(256), 0, s, items, partial, C, M, N);
-  else
-    hipLaunchKernelGGL(k_merge<1>, dim3((unsigned)n_items), dim3(256), 0, s, items, partial, C, M, N);
+  hipLaunchKernelGGL(k_merge, dim3((unsigned)n_items), dim3(256), 0, s, items, partial, C, M, N);
   return hipGetLastError();
 }
 

@@ -137,10 +137,12 @@ struct BrickFormat {
   const float* vals;             // nnz + 64
 };
 
-int mfma_tile_for(int64_t N);   // columns of C per wavefront: 16, 32, 64 or 128
+int mfma_tile_for(int64_t N);   // power-of-two tiles: 16, 32, 64 or 128 columns per wavefront
+int mfma_fp32_tile(int64_t N, int64_t K);   // columns per wavefront of the FP32 kernel
 int mfma_resident_waves_per_cu(int64_t N, int64_t K);
-// shapes the fast FP32 kernel serves when B and C are 16-byte aligned: N a multiple of the
-// vector width, B below 4 GiB
+bool mfma_32bit_shape(int64_t N, int64_t K);   // B below 4 GiB: the fast FP32 kernel
+// shapes of the 32-row kernel when B and C are 16-byte aligned: N a multiple of the vector
+// width, B below 4 GiB
 bool mfma_fast_shape(int64_t N, int64_t K);
 hipError_t launch_spmm_mfma(const BrickFormat& f, const WorkItem* items, int64_t n_items,
                             const float* B, float* C, float* partial, int64_t M, int64_t N,

@@ -1,0 +1,39 @@
+"""Every width of C from one column up, on operands that are only dword-aligned: the tiles of
+16..128 columns in steps of 16, their remainders, and the vectors that end a row."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2504_06443_amd import workloads as W
+from test_gpu_parity import check_c, gpu, make_plan  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+# each tile width T*16 at its first, an odd and its last column; two and three tiles
+WIDTHS = (2, 3, 4, 5, 15, 17, 18, 31, 34, 47, 48, 49, 63, 65, 66, 77, 80, 81, 95, 96, 97, 98, 99, 111,
+          112, 113, 114, 127, 129, 144, 145, 191, 223, 255, 257, 300)
+GUARD = 7.0
+
+
+@pytest.mark.parametrize("offset", [0, 1, 2, 3])
+@pytest.mark.parametrize("split", [0, 2])
+def test_any_width_any_dword_alignment(gpu, offset, split):  # noqa: F811
+    import torch
+    A = W.clustered_blocks(331, 6, 90, seed=3)          # a ragged last panel
+    plan = make_plan(gpu, A)
+    gpu.spmm_plan_set_split(plan, split)
+    for N in WIDTHS:
+        print(f"width N={N} offset={offset} split={split}", flush=True)
+        B = W.dense_b(A.K, N, 41)
+        Cref, S = oracle.spmm_f64(A.rowptr, A.colind, A.vals, B)
+        Bd = torch.empty(A.K * N + 4, device="cuda")[offset:offset + A.K * N].view(A.K, N)
+        Bd.copy_(torch.from_numpy(B))
+        whole = torch.full((A.M * N + 8,), GUARD, device="cuda")
+        Cd = whole[offset:offset + A.M * N].view(A.M, N)
+        Cd.fill_(float("nan"))
+        gpu.spmm_exec(plan, Bd, Cd)
+        torch.cuda.synchronize()
+        Cg = Cd.cpu().numpy()
+        assert not np.isnan(Cg).any(), "every element of C must be written"
+        check_c(Cg, Cref, S)
+        assert bool((whole[:offset] == GUARD).all()) and bool((whole[offset + A.M * N:] == GUARD).all())
