@@ -86,7 +86,8 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t *rowptr, const in
  *           from; read by a kernel enqueued on `stream`, so it must stay valid
  *           until that kernel has run
  *
- * Replaces the packed brick values and the plan's CSR copy; pattern, masks,
+ * Replaces the packed brick values (and the values in CSR order that a plan holds
+ * while its route sends panels to the CSR kernel); pattern, masks,
  * offsets, synergy counts and work lists are unchanged (an entry whose new value
  * is 0 stays a stored entry).  Enqueues only; allocates nothing.  Must not run
  * concurrently with spmm_exec on the same plan.
@@ -187,7 +188,9 @@ int spmm_plan_export(const spmm_plan_t *plan, uint32_t *panel_ptr /* host [P+1] 
 /* ---------------------------------------------------------------------------
  * Routing and load balancing (Section 5).  Both setters drop cached work lists.
  *
- * spmm_plan_set_route: which kernel handles which panel (enum spmm_route).
+ * spmm_plan_set_route: which kernel handles which panel (enum spmm_route).  VALU and CLASS
+ *   make what the CSR kernel reads from the bricks (8 B/nnz; SPMM_ENOMEM if that fails, the
+ *   route is then unchanged).
  * spmm_plan_set_split: how heavy panels are split along K into virtual panels
  *   (Eq. 6-7: ratio_p = blocks_p / avg_blocks / num_waves, with
  *   num_waves = ceil(work items / (CUs * resident waves per CU)); the paper gives no

@@ -83,11 +83,15 @@ struct spmm_plan {
   uint64_t* brick_mask = nullptr;
   uint32_t* brick_valptr = nullptr;
   float* vals = nullptr;          // nnz + 1
-  // plan-owned CSR copy for the vector-ALU kernel (device)
+  uint32_t* src = nullptr;        // CSR entry of each packed value (value-only updates)
+  // what the vector-ALU CSR kernels read (device): rowptr is kept from the start, the rest is made
+  // when a route first sends panels there (csr_on), and kept up to date while one does
   int32_t* rowptr = nullptr;
+  bool csr_on = false;
+  bool csr_may_lag = false;       // an update captured while it was off may be replayed at any time
+  char* csr_arena = nullptr;
   int32_t* colind = nullptr;
   float* csr_vals = nullptr;
-  uint32_t* ent_pos = nullptr;    // packed position of each CSR entry (value-only updates)
   uint32_t* long_rows = nullptr;  // rows with more than long_row_threshold() entries
   int64_t n_long_rows = 0;
   // host copies used by the work-list builder and the synergy model
@@ -130,12 +134,13 @@ struct spmm_plan {
     host_lists.clear();
   }
   // the arrays above are carved out of two device allocations
-  char* fixed_arena = nullptr;   // panel_ptr, rowptr, colind, csr_vals, ent_pos
+  char* fixed_arena = nullptr;   // panel_ptr, rowptr, src
   char* brick_arena = nullptr;   // brick_cols, brick_mask, brick_valptr, vals
   ~spmm_plan() {
     drop_lists();
     if (fixed_arena) (void)hipFree(fixed_arena);
     if (brick_arena) (void)hipFree(brick_arena);
+    if (csr_arena) (void)hipFree(csr_arena);
     if (tm32.arena) (void)hipFree(tm32.arena);
   }
 };
@@ -364,6 +369,36 @@ done:
   return SPMM_OK;
 }
 
+// What the CSR kernels read besides rowptr, from the brick format (the caller's CSR arrays may be
+// gone).  The default route sends no panel to them, so a plan is made without: 8 B/nnz of memory,
+// two copies at plan time and a third of an update's stores.  Called with the device idle.
+int enable_csr(spmm_plan_t* pl) {
+  int status = SPMM_OK;
+  const int64_t cap = pl->nnz / long_row_threshold() + 1;
+  unsigned long long* counter;
+  unsigned long long h_count = 0;
+  Arena a;
+  a.cap = 2 * Arena::pad((size_t)std::max<int64_t>(pl->nnz, 1) * 4) + Arena::pad((size_t)cap * 4) +
+          Arena::pad(sizeof(unsigned long long));
+  if (!pl->csr_arena) HIP_TRY(hipMalloc((void**)&pl->csr_arena, a.cap));
+  a.base = pl->csr_arena;
+  pl->colind = a.take<int32_t>(pl->nnz);
+  pl->csr_vals = a.take<float>(pl->nnz);
+  pl->long_rows = a.take<uint32_t>(cap);
+  counter = a.take<unsigned long long>(1);
+  HIP_TRY(launch_restore_csr(BrickFormat{pl->brick_cols, pl->brick_mask, pl->brick_valptr, pl->vals},
+                             pl->src, pl->nb, pl->colind, pl->csr_vals, nullptr));
+  HIP_TRY(launch_fill_u64(reinterpret_cast<uint64_t*>(counter), 1, 0, nullptr));
+  HIP_TRY(launch_find_long_rows(pl->rowptr, pl->M, long_row_threshold(), pl->long_rows, counter,
+                                nullptr));
+  HIP_TRY(hipMemcpy(&h_count, counter, sizeof(h_count), hipMemcpyDeviceToHost));
+  HIP_TRY(hipDeviceSynchronize());
+  pl->n_long_rows = (int64_t)h_count;
+  pl->csr_on = true;
+done:
+  return status;
+}
+
 // Builds the 32-row panel format from the 16-row one (device kernels; two size read-backs).
 int build_tm32(spmm_plan_t* pl, uint32_t num, uint32_t den, hipStream_t s) {
   int status = SPMM_OK;
@@ -588,16 +623,12 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
   counters = work.take<unsigned long long>(kNumCounters);
   d_active = work.take<unsigned long long>(1);
 
-  fixed.cap = need(P + 1, 4) + need(M + 1, 4) + 3 * need(nnz, 4) +
-              need(nnz / long_row_threshold() + 1, 4);
+  fixed.cap = need(P + 1, 4) + need(M + 1, 4) + need(nnz, 4);
   HIP_TRY(hipMalloc((void**)&fixed.base, fixed.cap));
   pl->fixed_arena = fixed.base;
   pl->panel_ptr = fixed.take<uint32_t>(P + 1);
   pl->rowptr = fixed.take<int32_t>(M + 1);
-  pl->colind = fixed.take<int32_t>(nnz);
-  pl->csr_vals = fixed.take<float>(nnz);
-  pl->ent_pos = fixed.take<uint32_t>(nnz);
-  pl->long_rows = fixed.take<uint32_t>(nnz / long_row_threshold() + 1);
+  pl->src = fixed.take<uint32_t>(nnz);
 
   // ---- rowptr validation and the widest panel span (device), before anything trusts rowptr
   HIP_TRY(hipMemsetAsync(d_err, 0, 4 * sizeof(uint32_t), s));
@@ -637,7 +668,7 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
                                 ncols_p, d_active, d_maxnb, s));
   } else if (path == kPathSort) {
     HIP_TRY(launch_panel_sort_census(rowptr, colind, M, K, P, sort_cap, d_err, nbricks_p,
-                                     panel_nnzptr, ncols_p, pl->ent_pos, d_active, d_maxnb, s));
+                                     panel_nnzptr, ncols_p, pl->src, d_active, d_maxnb, s));
   } else {
     // ---- search-based path for every other matrix.  Its a1
     // kernels only compare columns, so they may run before the host has seen the verdict of
@@ -651,15 +682,8 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
   HIP_TRY(hipMemcpyAsync(&h_err, d_err, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
   if (path != kPathSearch)
     HIP_TRY(hipMemcpyAsync(&h_maxnb, d_maxnb, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-  // plan-owned CSR copy for the vector-ALU kernel, while the host waits for the counts
   HIP_TRY(hipMemcpyAsync(pl->rowptr, rowptr, (size_t)(M + 1) * sizeof(int32_t),
                          hipMemcpyDeviceToDevice, s));
-  if (nnz > 0) {
-    HIP_TRY(hipMemcpyAsync(pl->colind, colind, (size_t)nnz * sizeof(int32_t),
-                           hipMemcpyDeviceToDevice, s));
-    HIP_TRY(hipMemcpyAsync(pl->csr_vals, vals, (size_t)nnz * sizeof(float),
-                           hipMemcpyDeviceToDevice, s));
-  }
   HIP_TRY(hipStreamSynchronize(s));
   if (h_err) {
     status = fail(SPMM_EFORMAT, "invalid colind (%s)",
@@ -701,14 +725,14 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
   if (path == kPathSort) {
     HIP_TRY(launch_panel_sort_build(rowptr, colind, vals, M, K, P, sort_cap,
                                     std::max<uint32_t>(h_maxnb, 1), pl->panel_ptr, pl->brick_cols,
-                                    pl->brick_mask, pl->brick_valptr, pl->vals, pl->ent_pos,
+                                    pl->brick_mask, pl->brick_valptr, pl->vals, pl->src,
                                     col_seen, s));
   } else if (path == kPathBitmap) {
     // ---- a2 (placing), a3, a4, one wavefront per panel
     HIP_TRY(launch_panel_build(rowptr, colind, vals, M, K, P, words_cap,
                                std::max<uint32_t>(h_maxnb, 1), pl->panel_ptr,
                                pl->brick_cols, pl->brick_mask, pl->brick_valptr, pl->vals,
-                               pl->ent_pos, col_seen, s));
+                               pl->src, col_seen, s));
   } else {
     // the arrays of the search-based path, in the order they were carved above
     Arena again = wide;
@@ -728,14 +752,12 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
                                 pl->brick_mask, ent_brick, ent_bit, col_seen, s));
     HIP_TRY(launch_scan_popc64(pl->brick_mask, pl->nb, pl->brick_valptr, scan_tmp, s));
     HIP_TRY(launch_pack_values(vals, ent_brick, ent_bit, pl->brick_mask, pl->brick_valptr, nnz,
-                               pl->vals, pl->ent_pos, s));
+                               pl->vals, pl->src, s));
   }
   // ---- a5: per-panel classes and the synergy counts
   HIP_TRY(launch_panel_classes(pl->panel_ptr, panel_nnzptr, P, panel_class, counters, s));
   HIP_TRY(launch_brick_hist(pl->brick_mask, pl->nb, counters, s));
   HIP_TRY(launch_count_flags(col_seen, K, counters + kCntDistinctCols, s));
-  HIP_TRY(launch_find_long_rows(rowptr, M, long_row_threshold(), pl->long_rows,
-                                counters + kCntLongRows, s));
 
   // ---- host copies for the work-list builder and the model
   try {
@@ -756,7 +778,6 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
   HIP_TRY(hipMemcpyAsync(pl->h_counters, counters, kNumCounters * sizeof(unsigned long long),
                          hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
-  pl->n_long_rows = (int64_t)pl->h_counters[kCntLongRows];
 
 done:
   if (status != SPMM_OK) (void)hipStreamSynchronize(s);
@@ -774,7 +795,15 @@ int spmm_plan_update_values(spmm_plan_t* pl, const float* vals, void* stream_) {
   if (!pl) return fail(SPMM_EINVAL, "plan is NULL");
   if (pl->nnz > 0 && !vals) return fail(SPMM_EINVAL, "vals is NULL with nnz > 0");
   int status = SPMM_OK;
-  HIP_TRY(launch_update_values(vals, pl->ent_pos, pl->nnz, pl->vals, pl->csr_vals,
+  if (!pl->csr_on && !pl->csr_may_lag) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing((hipStream_t)stream_, &capture) != hipSuccess) {
+      (void)hipGetLastError();
+      capture = hipStreamCaptureStatusActive;
+    }
+    pl->csr_may_lag = capture != hipStreamCaptureStatusNone;
+  }
+  HIP_TRY(launch_update_values(vals, pl->src, pl->nnz, pl->vals, pl->csr_on ? pl->csr_vals : nullptr,
                                (hipStream_t)stream_));
   if (pl->tm32.arena)   // the 32-row format holds its own copy of the packed values
     HIP_TRY(launch_tm32_values(pl->brick_mask, pl->brick_valptr, pl->vals, pl->tm32.new_slot,
@@ -838,6 +867,8 @@ int launch_product(const spmm_plan_t* pl, const HostList* hl, const WorkItem* d_
       HIP_TRY(launch_spmm_mfma(f, d_items, hl->info.n_mfma_items, B, C, d_partial, pl->M, N, pl->K,
                                pl->nnz, s));
   }
+  if (pl->csr_may_lag && hl->info.n_valu_panels > 0)
+    HIP_TRY(launch_restore_csr(f, pl->src, pl->nb, pl->colind, pl->csr_vals, s));
   HIP_TRY(launch_spmm_valu(pl->rowptr, pl->colind, pl->csr_vals, d_valu_panels,
                            hl->info.n_valu_panels, pl->long_rows, pl->n_long_rows, B, C, pl->M, N,
                            s));
@@ -976,6 +1007,12 @@ int spmm_plan_set_route(spmm_plan_t* pl, int route) {
   if (!pl) return fail(SPMM_EINVAL, "plan is NULL");
   if (route < SPMM_ROUTE_AUTO || route > SPMM_ROUTE_CLASS) return fail(SPMM_EINVAL, "bad route");
   if (hipDeviceSynchronize() != hipSuccess) return fail(SPMM_EHIP, "hipDeviceSynchronize failed");
+  const bool csr = route == SPMM_ROUTE_VALU || route == SPMM_ROUTE_CLASS;
+  if (csr && !pl->csr_on) {
+    const int status = enable_csr(pl);
+    if (status != SPMM_OK) return status;
+  }
+  pl->csr_on = csr;   // (updates write the CSR copy only while a route reads it)
   pl->route = route;
   pl->drop_lists();
   return SPMM_OK;

@@ -185,26 +185,60 @@ __global__ void k_pack_values(const float* __restrict__ vals,
                               const uint8_t* __restrict__ ent_bit,
                               const uint64_t* __restrict__ brick_mask,
                               const uint32_t* __restrict__ brick_valptr, int64_t nnz,
-                              float* __restrict__ packed, uint32_t* __restrict__ ent_pos) {
+                              float* __restrict__ packed, uint32_t* __restrict__ src) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= nnz) return;
   const uint32_t b = ent_brick[e];
   const uint64_t below = brick_mask[b] & ((1ull << ent_bit[e]) - 1ull);
   const uint32_t pos = brick_valptr[b] + (uint32_t)__popcll(below);
   packed[pos] = vals[e];
-  ent_pos[e] = pos;
+  src[pos] = (uint32_t)e;
 }
 
-// New values for an unchanged pattern: entry e of the CSR goes to the packed position
-// recorded when the plan was built, and into the plan's CSR copy.
-__global__ void k_update_values(const float* __restrict__ vals,
-                                const uint32_t* __restrict__ ent_pos, int64_t nnz,
-                                float* __restrict__ packed, float* __restrict__ csr_vals) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= nnz) return;
-  const float v = vals[e];
-  packed[ent_pos[e]] = v;
-  csr_vals[e] = v;
+// New values for an unchanged pattern: packed position p takes the CSR entry src[p] recorded when
+// the plan was built.  Bound by memory: 4 bytes each of values, positions and packed values per
+// entry.  Gathering by packed position keeps the stores whole (the entries of a panel are 2 KB or
+// so, and their reads hit a cache); four positions per thread.  CSR: the plan also keeps the values
+// in CSR order, for the vector-ALU kernels.  7.86 M entries: scattering by entry and always writing
+// the CSR copy 28.9 us; this way about 15, 94 MB at 6.3 TB/s.
+template <bool CSR>
+__global__ __launch_bounds__(kThreads) void k_update_values(
+    const float* __restrict__ vals, const uint32_t* __restrict__ src, int64_t nnz,
+    float* __restrict__ packed, float* __restrict__ csr_vals) {
+  const int64_t p = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * 4;
+  if (p + 4 <= nnz) {
+    const uint4 e = *reinterpret_cast<const uint4*>(src + p);
+    float4 v;
+    v.x = vals[e.x]; v.y = vals[e.y]; v.z = vals[e.z]; v.w = vals[e.w];
+    *reinterpret_cast<float4*>(packed + p) = v;
+    if constexpr (CSR) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) csr_vals[p + k] = vals[p + k];
+    }
+  } else {
+    for (int64_t q = p; q < nnz; ++q) {
+      packed[q] = vals[src[q]];
+      if constexpr (CSR) csr_vals[q] = vals[q];
+    }
+  }
+}
+
+// Columns and values in CSR order again, from the bricks: one wavefront per brick, lane l holds the
+// element of pattern bit l.
+__global__ __launch_bounds__(kThreads) void k_restore_csr(
+    const uint32_t* __restrict__ brick_cols, const uint64_t* __restrict__ brick_mask,
+    const uint32_t* __restrict__ brick_valptr, const float* __restrict__ packed,
+    const uint32_t* __restrict__ src, int64_t nb, int32_t* __restrict__ colind,
+    float* __restrict__ csr_vals) {
+  const int lane = threadIdx.x & 63;
+  const int64_t b = (int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
+  if (b >= nb) return;
+  const uint64_t mask = brick_mask[b];
+  if (!((mask >> lane) & 1ull)) return;
+  const uint32_t pos = brick_valptr[b] + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
+  const uint32_t e = src[pos];
+  colind[e] = (int32_t)brick_cols[b * kBrickK + (lane & (kBrickK - 1))];
+  csr_vals[e] = packed[pos];
 }
 
 // a5: per-panel class (Table 1, integer compare) and class totals.
@@ -622,14 +656,14 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_sort_census(
 }
 
 // a2 (placing half), a3 and a4 for one panel from the sorted order left by the census in
-// `ent_pos` (which this kernel then overwrites with the value positions).  Dynamic LDS: keys
+// `src` (which this kernel then overwrites with the entry of each packed value).  Dynamic LDS: keys
 // (n_cap x u64), patterns (nb_cap x u64), value offsets (nb_cap words).
 __global__ __launch_bounds__(kPanelThreads) void k_panel_sort_build(
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind,
     const float* __restrict__ vals, int64_t M, int64_t K, uint32_t n_cap, uint32_t nb_cap,
     const uint32_t* __restrict__ panel_ptr, uint32_t* __restrict__ brick_cols,
     uint64_t* __restrict__ brick_mask, uint32_t* __restrict__ brick_valptr,
-    float* __restrict__ packed, uint32_t* ent_pos, uint8_t* __restrict__ col_seen) {
+    float* __restrict__ packed, uint32_t* src, uint8_t* __restrict__ col_seen) {
   extern __shared__ unsigned long long lds64[];
   __shared__ int32_t rp[kPanel + 1];
   unsigned long long* keys = lds64;                                  // [n_cap]
@@ -644,7 +678,7 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_sort_build(
   if (n > n_cap || nb > nb_cap) return;   // (cannot happen: both caps are maxima over the panels)
   for (uint32_t k = threadIdx.x; k < nb; k += kPanelThreads) pat[k] = 0;
   for (uint32_t i = threadIdx.x; i < n; i += kPanelThreads) {
-    const uint32_t idx = min(ent_pos[x.e0 + i], n - 1);   // (always below n)
+    const uint32_t idx = min(src[x.e0 + i], n - 1);   // (always below n)
     keys[i] = ((unsigned long long)(uint32_t)colind[x.e0 + idx] << 32) | idx;
   }
   __syncthreads();
@@ -714,7 +748,7 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_sort_build(
     const uint32_t pos = vptr[k] + (uint32_t)__popcll(pat[k] & ((1ull << bit) - 1ull));
     if (pos < (uint32_t)x.e1) {   // (always, for a census and a build that agree)
       packed[pos] = vals[e];
-      ent_pos[e] = pos;
+      src[pos] = (uint32_t)e;
     }
   }
 }
@@ -751,7 +785,7 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_build(
     const float* __restrict__ vals, int64_t M, int64_t K, uint32_t words_cap, uint32_t nb_cap,
     const uint32_t* __restrict__ panel_ptr, uint32_t* __restrict__ brick_cols,
     uint64_t* __restrict__ brick_mask, uint32_t* __restrict__ brick_valptr,
-    float* __restrict__ packed, uint32_t* __restrict__ ent_pos, uint8_t* __restrict__ col_seen) {
+    float* __restrict__ packed, uint32_t* __restrict__ src, uint8_t* __restrict__ col_seen) {
   extern __shared__ unsigned long long lds64[];
   __shared__ int32_t rp[kPanel + 1];
   unsigned long long* pat = lds64;                                   // [nb_cap]
@@ -844,7 +878,7 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_build(
     const uint32_t pos = vptr[k] + (uint32_t)__popcll(pat[k] & ((1ull << bit) - 1ull));
     if (pos < (uint32_t)x.e1) {   // (always, for a census and a build that agree)
       packed[pos] = vals[e];
-      ent_pos[e] = pos;
+      src[pos] = (uint32_t)e;
     }
   }
 }
@@ -944,18 +978,29 @@ hipError_t launch_scatter_bits(const int32_t* colind, const uint32_t* ent_row, c
 
 hipError_t launch_pack_values(const float* vals, const uint32_t* ent_brick, const uint8_t* ent_bit,
                               const uint64_t* brick_mask, const uint32_t* brick_valptr,
-                              int64_t nnz, float* packed, uint32_t* ent_pos, hipStream_t s) {
+                              int64_t nnz, float* packed, uint32_t* src, hipStream_t s) {
   if (nnz == 0) return hipSuccess;
   hipLaunchKernelGGL(k_pack_values, dim3(grid_for(nnz)), dim3(kThreads), 0, s, vals, ent_brick,
-                     ent_bit, brick_mask, brick_valptr, nnz, packed, ent_pos);
+                     ent_bit, brick_mask, brick_valptr, nnz, packed, src);
   return hipGetLastError();
 }
 
-hipError_t launch_update_values(const float* vals, const uint32_t* ent_pos, int64_t nnz,
-                                float* packed, float* csr_vals, hipStream_t s) {
+hipError_t launch_update_values(const float* vals, const uint32_t* src, int64_t nnz, float* packed,
+                                float* csr_vals, hipStream_t s) {
   if (nnz == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_update_values, dim3(grid_for(nnz)), dim3(kThreads), 0, s, vals, ent_pos,
-                     nnz, packed, csr_vals);
+  const dim3 grid(grid_for((nnz + 3) / 4)), block(kThreads);
+  if (csr_vals)
+    hipLaunchKernelGGL(k_update_values<true>, grid, block, 0, s, vals, src, nnz, packed, csr_vals);
+  else
+    hipLaunchKernelGGL(k_update_values<false>, grid, block, 0, s, vals, src, nnz, packed, csr_vals);
+  return hipGetLastError();
+}
+
+hipError_t launch_restore_csr(const BrickFormat& f, const uint32_t* src, int64_t nb, int32_t* colind,
+                              float* csr_vals, hipStream_t s) {
+  if (nb == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_restore_csr, dim3(grid_for(nb, kThreads / 64)), dim3(kThreads), 0, s,
+                     f.brick_cols, f.brick_mask, f.brick_valptr, f.vals, src, nb, colind, csr_vals);
   return hipGetLastError();
 }
 
@@ -1046,7 +1091,7 @@ hipError_t launch_panel_sort_build(const int32_t* rowptr, const int32_t* colind,
                                    int64_t M, int64_t K, int64_t P, uint32_t n_cap, uint32_t nb_cap,
                                    const uint32_t* panel_ptr, uint32_t* brick_cols,
                                    uint64_t* brick_mask, uint32_t* brick_valptr, float* packed,
-                                   uint32_t* ent_pos, uint8_t* col_seen, hipStream_t s) {
+                                   uint32_t* src, uint8_t* col_seen, hipStream_t s) {
   if (P == 0) return hipSuccess;
   const size_t lds = panel_sort_build_lds(n_cap, nb_cap);
   if (lds > 48 * 1024) {
@@ -1056,7 +1101,7 @@ hipError_t launch_panel_sort_build(const int32_t* rowptr, const int32_t* colind,
   }
   hipLaunchKernelGGL(k_panel_sort_build, dim3((unsigned)P), dim3(kPanelThreads), lds, s, rowptr,
                      colind, vals, M, K, n_cap, nb_cap, panel_ptr, brick_cols, brick_mask,
-                     brick_valptr, packed, ent_pos, col_seen);
+                     brick_valptr, packed, src, col_seen);
   return hipGetLastError();
 }
 
@@ -1097,7 +1142,7 @@ hipError_t launch_panel_census(const int32_t* rowptr, const int32_t* colind, int
 hipError_t launch_panel_build(const int32_t* rowptr, const int32_t* colind, const float* vals,
                               int64_t M, int64_t K, int64_t P, uint32_t words_cap, uint32_t nb_cap,
                               const uint32_t* panel_ptr, uint32_t* brick_cols, uint64_t* brick_mask,
-                              uint32_t* brick_valptr, float* packed, uint32_t* ent_pos,
+                              uint32_t* brick_valptr, float* packed, uint32_t* src,
                               uint8_t* col_seen, hipStream_t s) {
   if (P == 0) return hipSuccess;
   const size_t lds = panel_build_lds(words_cap, nb_cap);
@@ -1108,7 +1153,7 @@ hipError_t launch_panel_build(const int32_t* rowptr, const int32_t* colind, cons
   }
   hipLaunchKernelGGL(k_panel_build, dim3((unsigned)P), dim3(kPanelThreads), lds, s, rowptr, colind,
                      vals, M, K, words_cap, nb_cap, panel_ptr, brick_cols, brick_mask, brick_valptr,
-                     packed, ent_pos, col_seen);
+                     packed, src, col_seen);
   return hipGetLastError();
 }
 

@@ -27,8 +27,7 @@ enum : int {
   kCntNonEmptyPanels = 9,
   kCntDistinctCols = 10,
   kCntPopHist = 11,         // 65
-  kCntLongRows = 76,        // rows with more entries than the CSR kernel handles side by side
-  kNumCounters = 77
+  kNumCounters = 76
 };
 
 struct WorkItem {           // one wavefront's share of the MFMA kernel
@@ -70,9 +69,10 @@ hipError_t launch_scatter_bits(const int32_t* colind, const uint32_t* ent_row, c
                                uint8_t* col_seen, hipStream_t s);
 hipError_t launch_pack_values(const float* vals, const uint32_t* ent_brick, const uint8_t* ent_bit,
                               const uint64_t* brick_mask, const uint32_t* brick_valptr,
-                              int64_t nnz, float* packed, uint32_t* ent_pos, hipStream_t s);
-hipError_t launch_update_values(const float* vals, const uint32_t* ent_pos, int64_t nnz,
-                                float* packed, float* csr_vals, hipStream_t s);
+                              int64_t nnz, float* packed, uint32_t* src, hipStream_t s);
+// csr_vals: null where the plan keeps no values in CSR order
+hipError_t launch_update_values(const float* vals, const uint32_t* src, int64_t nnz, float* packed,
+                                float* csr_vals, hipStream_t s);
 hipError_t launch_panel_classes(const uint32_t* panel_ptr, const uint32_t* panel_nnzptr, int64_t P,
                                 uint8_t* panel_class, unsigned long long* counters, hipStream_t s);
 hipError_t launch_brick_hist(const uint64_t* brick_mask, int64_t nb, unsigned long long* counters,
@@ -94,14 +94,14 @@ bool panel_sort_build_fits(uint32_t n_cap, uint32_t nb_cap);
 hipError_t launch_panel_sort_census(const int32_t* rowptr, const int32_t* colind, int64_t M,
                                     int64_t K, int64_t P, uint32_t n_cap, uint32_t* err,
                                     uint32_t* nbricks_p, uint32_t* panel_nnzptr, uint32_t* ncols_p,
-                                    uint32_t* order /* [nnz]; read back by the build as ent_pos */,
+                                    uint32_t* order /* [nnz]; read back by the build from src */,
                                     unsigned long long* n_active, uint32_t* max_cols,
                                     hipStream_t s);
 hipError_t launch_panel_sort_build(const int32_t* rowptr, const int32_t* colind, const float* vals,
                                    int64_t M, int64_t K, int64_t P, uint32_t n_cap, uint32_t nb_cap,
                                    const uint32_t* panel_ptr, uint32_t* brick_cols,
                                    uint64_t* brick_mask, uint32_t* brick_valptr, float* packed,
-                                   uint32_t* ent_pos, uint8_t* col_seen, hipStream_t s);
+                                   uint32_t* src, uint8_t* col_seen, hipStream_t s);
 uint32_t panel_bitmap_words(uint32_t span);   // 0: span too wide for the per-panel path
 hipError_t launch_panel_census(const int32_t* rowptr, const int32_t* colind, int64_t M, int64_t K,
                                int64_t P, uint32_t words_cap, uint32_t* err, uint32_t* nbricks_p,
@@ -111,7 +111,7 @@ bool panel_build_fits(uint32_t words_cap, uint32_t nb_cap);   // LDS of launch_p
 hipError_t launch_panel_build(const int32_t* rowptr, const int32_t* colind, const float* vals,
                               int64_t M, int64_t K, int64_t P, uint32_t words_cap, uint32_t nb_cap,
                               const uint32_t* panel_ptr, uint32_t* brick_cols, uint64_t* brick_mask,
-                              uint32_t* brick_valptr, float* packed, uint32_t* ent_pos,
+                              uint32_t* brick_valptr, float* packed, uint32_t* src,
                               uint8_t* col_seen, hipStream_t s);
 
 // exclusive scans; out has n+1 entries (out[n] = total); tmp holds block sums
@@ -136,6 +136,10 @@ struct BrickFormat {
   const uint32_t* brick_valptr;  // nb + 1 + kFormatPad
   const float* vals;             // nnz + 64
 };
+
+// colind and values in CSR order from the brick format; src[p] = CSR entry of packed value p
+hipError_t launch_restore_csr(const BrickFormat& f, const uint32_t* src, int64_t nb, int32_t* colind,
+                              float* csr_vals, hipStream_t s);
 
 int mfma_tile_for(int64_t N);   // power-of-two tiles: 16, 32, 64 or 128 columns per wavefront
 int mfma_fp32_tile(int64_t N, int64_t K);   // columns per wavefront of the FP32 kernel

@@ -624,3 +624,46 @@ def test_heavy_first_order_gives_the_same_product(gpu):
     assert sizes == sorted(sizes, reverse=True) and len(set(sizes)) > 3
     with pytest.raises(gpu.SpmmError):
         gpu.spmm_plan_set_order(plan, 5)
+
+
+def test_updates_reach_the_csr_kernel_whenever_they_run(gpu):
+    """The values in CSR order exist only while a route reads them: updates before the route is
+    set, while it is set, after it was left and come back to, and replayed from a graph that was
+    captured before it was ever set."""
+    import torch
+    A = W.power_law(M=1500, target_nnz=None, cap=700, seed=57)     # rows above 256 entries too
+    N = 32
+    B = W.dense_b(A.K, N, 8)
+    plan = make_plan(gpu, A)
+    vals = torch.from_numpy(A.vals).cuda()
+    rng = np.random.default_rng(4)
+
+    def fresh():
+        return rng.uniform(-1, 1, A.nnz).astype(np.float32)
+
+    def expect(v, route):
+        Cref, S = oracle.spmm_f64(A.rowptr, A.colind, v, B)
+        check_c(run_product(gpu, plan, A, B, route=route), Cref, S)
+
+    v = fresh()
+    gpu.spmm_plan_update_values(plan, torch.from_numpy(v).cuda())
+    expect(v, gpu.ROUTE_VALU)
+    v = fresh()
+    gpu.spmm_plan_update_values(plan, torch.from_numpy(v).cuda())
+    expect(v, None)
+    gpu.spmm_plan_set_route(plan, gpu.ROUTE_AUTO)
+    v = fresh()
+    gpu.spmm_plan_update_values(plan, torch.from_numpy(v).cuda())
+    expect(v, gpu.ROUTE_CLASS)
+
+    plan = make_plan(gpu, A)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        gpu.spmm_plan_update_values(plan, vals)
+    gpu.spmm_plan_set_route(plan, gpu.ROUTE_VALU)
+    for _ in range(3):
+        v = fresh()
+        vals.copy_(torch.from_numpy(v))
+        graph.replay()
+        torch.cuda.synchronize()
+        expect(v, None)
