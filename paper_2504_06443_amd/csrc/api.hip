@@ -87,6 +87,7 @@ struct spmm_plan {
   // what the vector-ALU CSR kernels read (device): rowptr is kept from the start, the rest is made
   // when a route first sends panels there (csr_on), and kept up to date while one does
   int32_t* rowptr = nullptr;
+  uint32_t* panel_nnzptr = nullptr;       // first CSR entry of each panel
   bool csr_on = false;
   bool csr_may_lag = false;       // an update captured while it was off may be replayed at any time
   char* csr_arena = nullptr;
@@ -96,8 +97,7 @@ struct spmm_plan {
   int64_t n_long_rows = 0;
   // host copies used by the work-list builder and the synergy model
   std::vector<uint32_t> h_panel_ptr;
-  std::vector<uint32_t> h_panel_nnzptr;   // first CSR entry of each panel
-  std::vector<uint8_t> h_panel_class;
+  std::vector<uint8_t> h_panel_class;     // filled with the CSR arrays, for the routes that ask
   unsigned long long h_counters[kNumCounters] = {};
   int64_t n_active_cols = 0;
   int route = SPMM_ROUTE_AUTO;
@@ -134,7 +134,7 @@ struct spmm_plan {
     host_lists.clear();
   }
   // the arrays above are carved out of two device allocations
-  char* fixed_arena = nullptr;   // panel_ptr, rowptr, src
+  char* fixed_arena = nullptr;   // panel_ptr, rowptr, panel_nnzptr, src
   char* brick_arena = nullptr;   // brick_cols, brick_mask, brick_valptr, vals
   ~spmm_plan() {
     drop_lists();
@@ -223,7 +223,6 @@ int build_host_list(spmm_plan_t* pl, int64_t N, const HostList** out) {
     std::vector<uint32_t> mfma_panels;
     std::vector<uint32_t> nbricks;
     for (int64_t p = 0; p < pl->P; ++p) {
-      const uint8_t cls = pl->h_panel_class[p];
       bool to_mfma;
       // AUTO is the measured policy for MI355X: the brick kernel loads each B row of a panel
       // once where CSR loads it once per entry, and on the benchmark's sweep of brick fill
@@ -234,7 +233,7 @@ int build_host_list(spmm_plan_t* pl, int64_t N, const HostList** out) {
       // under CLASS it goes to the CSR kernel, whose launch the Low panels cause anyway.
       if (pl->route == SPMM_ROUTE_AUTO || pl->route == SPMM_ROUTE_MFMA) to_mfma = true;
       else if (pl->route == SPMM_ROUTE_VALU) to_mfma = false;
-      else to_mfma = cls != SPMM_LOW && cls != 255;
+      else to_mfma = pl->h_panel_class[p] != SPMM_LOW && pl->h_panel_class[p] != 255;
       if (to_mfma) {
         mfma_panels.push_back((uint32_t)p);
         nbricks.push_back(pl->h_panel_ptr[p + 1] - pl->h_panel_ptr[p]);
@@ -377,6 +376,7 @@ int enable_csr(spmm_plan_t* pl) {
   const int64_t cap = pl->nnz / long_row_threshold() + 1;
   unsigned long long* counter;
   unsigned long long h_count = 0;
+  std::vector<uint32_t> nnzptr;
   Arena a;
   a.cap = 2 * Arena::pad((size_t)std::max<int64_t>(pl->nnz, 1) * 4) + Arena::pad((size_t)cap * 4) +
           Arena::pad(sizeof(unsigned long long));
@@ -394,6 +394,19 @@ int enable_csr(spmm_plan_t* pl) {
   HIP_TRY(hipMemcpy(&h_count, counter, sizeof(h_count), hipMemcpyDeviceToHost));
   HIP_TRY(hipDeviceSynchronize());
   pl->n_long_rows = (int64_t)h_count;
+  try {
+    nnzptr.resize((size_t)pl->P + 1);
+    pl->h_panel_class.resize((size_t)pl->P);
+  } catch (const std::bad_alloc&) {
+    return fail(SPMM_ENOMEM, "host allocation failed");
+  }
+  HIP_TRY(hipMemcpy(nnzptr.data(), pl->panel_nnzptr, nnzptr.size() * sizeof(uint32_t),
+                    hipMemcpyDeviceToHost));
+  for (int64_t p = 0; p < pl->P; ++p) {
+    const int cls = classify((int64_t)nnzptr[p + 1] - nnzptr[p],
+                             (int64_t)pl->h_panel_ptr[p + 1] - pl->h_panel_ptr[p]);
+    pl->h_panel_class[p] = cls == SPMM_NONE ? 255 : (uint8_t)cls;
+  }
   pl->csr_on = true;
 done:
   return status;
@@ -562,16 +575,15 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
   // count is known.  Sub-arrays are 256-byte aligned.
   auto need = [](int64_t n, size_t elem) { return Arena::pad((size_t)std::max<int64_t>(n, 1) * elem); };
   Arena work, wide, fixed, bricks;
-  uint32_t *d_err, *d_span, *d_maxnb, *scan_tmp, *nbricks_p, *panel_nnzptr, *ncols_p;
+  PlanControl* ctl;                  // the first array of `work`
+  PlanControl h_ctl{};
+  uint32_t *scan_tmp, *ncols_p;
   enum { kPathSearch, kPathBitmap, kPathSort } path = kPathSearch;
   uint32_t sort_cap = 0;
-  uint32_t h_maxnb = 0;
-  uint8_t *col_seen, *panel_class;
-  unsigned long long *counters, *d_active;
-  uint32_t h_small[3] = {0, 0, 0};   // error bits, widest panel span, most entries of a panel
-  uint32_t h_err = 0, h_nb = 0, words_cap = 0;
-  unsigned long long h_active = 0;
-  const int64_t scan_elems = (int64_t)scan_tmp_elems(std::max(nnz, P + 1));  // bricks <= nnz
+  uint32_t h_maxnb = 0, words_cap = 0;
+  uint8_t* col_seen;
+  const int64_t scan_elems =
+      std::max((int64_t)scan_tmp_elems(nnz), (int64_t)panel_scan_tmp_elems());  // bricks <= nnz
 
   // a1 of the search-based path: row of every entry (with the column check), first occurrences,
   // their scan and compacted list, bricks per panel
@@ -587,13 +599,11 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
     first_scan = wide.take<uint32_t>(nnz + 1);
     link = wide.take<uint32_t>(nnz);
     first_list = wide.take<uint32_t>(nnz);
-    HIP_TRY(launch_validate_cols(rowptr, colind, M, K, nnz, ent_row, d_err, s));
+    HIP_TRY(launch_validate_cols(rowptr, colind, M, K, nnz, ent_row, &ctl->err, s));
     HIP_TRY(launch_first_in_panel(rowptr, colind, ent_row, nnz, first, link, s));
     HIP_TRY(launch_scan_u8(first, nnz, first_scan, scan_tmp, s));
     HIP_TRY(launch_compact_first(first, first_scan, nnz, first_list, s));
-    HIP_TRY(launch_panel_counts(rowptr, first_scan, M, P, nbricks_p, panel_nnzptr, s));
-    HIP_TRY(hipMemsetAsync(d_active, 0, sizeof(unsigned long long), s));
-    HIP_TRY(hipMemcpyAsync(d_active, first_scan + nnz, sizeof(uint32_t), hipMemcpyDeviceToDevice, s));
+    HIP_TRY(launch_panel_counts(rowptr, first_scan, M, P, ncols_p, s));
   done:
     return status;
   };
@@ -608,46 +618,36 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
   HIP_TRY(hipDeviceGetAttribute(&pl->num_cus, hipDeviceAttributeMultiprocessorCount, pl->device));
   pl->num_cus = std::max(1, pl->num_cus);
 
-  work.cap = need(4, 4) + need(scan_elems, 4) + 2 * need(P, 4) + need(P + 1, 4) + need(K, 1) +
-                need(P, 1) + need(kNumCounters, 8) + need(1, 8);
+  work.cap = need(1, sizeof(PlanControl)) + need(K, 1) + need(scan_elems, 4) + need(P, 4);
   HIP_TRY(hipMalloc((void**)&work.base, work.cap));
-  d_err = work.take<uint32_t>(4);   // error bits, widest span, most entries, most columns
-  d_span = d_err + 1;
-  d_maxnb = d_err + 3;
+  ctl = work.take<PlanControl>(1);
+  col_seen = work.take<uint8_t>(K);   // next to the control block: cleared together
   scan_tmp = work.take<uint32_t>(scan_elems);
-  nbricks_p = work.take<uint32_t>(P);
   ncols_p = work.take<uint32_t>(P);
-  panel_nnzptr = work.take<uint32_t>(P + 1);
-  col_seen = work.take<uint8_t>(K);
-  panel_class = work.take<uint8_t>(P);
-  counters = work.take<unsigned long long>(kNumCounters);
-  d_active = work.take<unsigned long long>(1);
 
-  fixed.cap = need(P + 1, 4) + need(M + 1, 4) + need(nnz, 4);
+  fixed.cap = 2 * need(P + 1, 4) + need(M + 1, 4) + need(nnz, 4);
   HIP_TRY(hipMalloc((void**)&fixed.base, fixed.cap));
   pl->fixed_arena = fixed.base;
   pl->panel_ptr = fixed.take<uint32_t>(P + 1);
+  pl->panel_nnzptr = fixed.take<uint32_t>(P + 1);
   pl->rowptr = fixed.take<int32_t>(M + 1);
   pl->src = fixed.take<uint32_t>(nnz);
 
   // ---- rowptr validation and the widest panel span (device), before anything trusts rowptr
-  HIP_TRY(hipMemsetAsync(d_err, 0, 4 * sizeof(uint32_t), s));
-  HIP_TRY(hipMemsetAsync(d_active, 0, sizeof(unsigned long long), s));
-  HIP_TRY(launch_validate_rowptr(rowptr, M, nnz, d_err, s));
-  HIP_TRY(launch_panel_span(rowptr, colind, M, P, d_err, d_span, s));
-  HIP_TRY(hipMemcpyAsync(h_small, d_err, 3 * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipMemsetAsync(work.base, 0, (size_t)(reinterpret_cast<char*>(scan_tmp) - work.base), s));
+  HIP_TRY(launch_rows(rowptr, colind, M, P, nnz, pl->rowptr, pl->panel_nnzptr, ctl, s));
+  HIP_TRY(hipMemcpyAsync(&h_ctl, ctl, sizeof(PlanControl), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
-  h_err = h_small[0];
-  if (h_err & (kErrRowptrEnds | kErrRowptrOrder)) {
+  if (h_ctl.err & (kErrRowptrEnds | kErrRowptrOrder)) {
     status = fail(SPMM_EFORMAT, "invalid rowptr (%s)",
-                  (h_err & kErrRowptrEnds) ? "rowptr[0] != 0 or rowptr[M] != nnz" : "not monotone");
+                  (h_ctl.err & kErrRowptrEnds) ? "rowptr[0] != 0 or rowptr[M] != nnz" : "not monotone");
     goto done;
   }
-  if (h_err & (kErrColRange | kErrColOrder)) {   // a panel whose column span is inverted
+  if (h_ctl.err & (kErrColRange | kErrColOrder)) {   // a panel whose column span is inverted
     status = fail(SPMM_EFORMAT, "invalid colind (columns of a row not strictly ascending)");
     goto done;
   }
-  words_cap = panel_bitmap_words(h_small[1]);
+  words_cap = panel_bitmap_words(h_ctl.span);
 
   // Three ways to the same format.  The bitmap kernels walk a bitmap over the panel's column
   // span; that pays while the bitmaps are not much longer than the entry lists (band-like
@@ -659,16 +659,15 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
   // (67 x) 31 vs 3.8 ms against it; sort against search: 1M-row sweep f = 0.4 (488 entries
   // per panel) 2.4 vs 4.5 ms, f = 0.8 3.8 vs 3.8 ms, config 3 (46 per panel, largest 3000+)
   // 1.45 vs 0.99 ms.
-  sort_cap = panel_sort_keys(h_small[2]);
+  sort_cap = panel_sort_keys(h_ctl.max_nnz);
   if (words_cap != 0 && (int64_t)words_cap * P <= 8 * nnz) path = kPathBitmap;
   else if (sort_cap != 0 && sort_cap <= 2048 && nnz >= 128 * P) path = kPathSort;
   if (path == kPathBitmap) {
     // ---- a1/a2: census (also validates colind) -> bricks per panel
-    HIP_TRY(launch_panel_census(rowptr, colind, M, K, P, words_cap, d_err, nbricks_p, panel_nnzptr,
-                                ncols_p, d_active, d_maxnb, s));
+    HIP_TRY(launch_panel_census(rowptr, colind, M, K, P, words_cap, &ctl->err, ncols_p, s));
   } else if (path == kPathSort) {
-    HIP_TRY(launch_panel_sort_census(rowptr, colind, M, K, P, sort_cap, d_err, nbricks_p,
-                                     panel_nnzptr, ncols_p, pl->src, d_active, d_maxnb, s));
+    HIP_TRY(launch_panel_sort_census(rowptr, colind, M, K, P, sort_cap, &ctl->err, ncols_p,
+                                     pl->src, s));
   } else {
     // ---- search-based path for every other matrix.  Its a1
     // kernels only compare columns, so they may run before the host has seen the verdict of
@@ -676,29 +675,23 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
     status = wide_a1();
     if (status != SPMM_OK) goto done;
   }
-  HIP_TRY(launch_scan_u32(nbricks_p, P, pl->panel_ptr, scan_tmp, s));
-  HIP_TRY(hipMemcpyAsync(&h_nb, pl->panel_ptr + P, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipMemcpyAsync(&h_active, d_active, sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipMemcpyAsync(&h_err, d_err, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-  if (path != kPathSearch)
-    HIP_TRY(hipMemcpyAsync(&h_maxnb, d_maxnb, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipMemcpyAsync(pl->rowptr, rowptr, (size_t)(M + 1) * sizeof(int32_t),
-                         hipMemcpyDeviceToDevice, s));
+  HIP_TRY(launch_panel_scan(ncols_p, P, pl->panel_ptr, scan_tmp, ctl, s));
+  HIP_TRY(hipMemcpyAsync(&h_ctl, ctl, sizeof(PlanControl), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
-  if (h_err) {
+  if (h_ctl.err) {
     status = fail(SPMM_EFORMAT, "invalid colind (%s)",
-                  (h_err & kErrColRange) ? "column out of range"
-                                         : "columns of a row not strictly ascending");
+                  (h_ctl.err & kErrColRange) ? "column out of range"
+                                             : "columns of a row not strictly ascending");
     goto done;
   }
-  pl->nb = h_nb;
-  pl->n_active_cols = (int64_t)h_active;
-  if ((int64_t)h_nb * kBrickK >= (int64_t(1) << 32)) {
+  pl->nb = h_ctl.nb;
+  pl->n_active_cols = (int64_t)h_ctl.n_active;
+  if (pl->nb * kBrickK >= (int64_t(1) << 32)) {
     status = fail(SPMM_ELIMIT, "4 * bricks must be below 2^32");
     goto done;
   }
 
-  h_maxnb = (h_maxnb + kBrickK - 1) / kBrickK;   // read back as the largest column count of a panel
+  h_maxnb = (h_ctl.max_cols + kBrickK - 1) / kBrickK;
   if ((path == kPathBitmap && !panel_build_fits(words_cap, std::max<uint32_t>(h_maxnb, 1))) ||
       (path == kPathSort && !panel_sort_build_fits(sort_cap, std::max<uint32_t>(h_maxnb, 1)))) {
     path = kPathSearch;   // a panel with more bricks than fit in LDS: finish on the search-based path
@@ -715,12 +708,7 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
   pl->brick_mask = bricks.take<uint64_t>(pl->nb + kFormatPad);
   pl->brick_valptr = bricks.take<uint32_t>(pl->nb + 1 + kFormatPad);
   pl->vals = bricks.take<float>(nnz + 64);
-  HIP_TRY(hipMemsetAsync(pl->brick_cols + pl->nb * kBrickK, 0, kFormatPad * kBrickK * 4, s));
-  HIP_TRY(hipMemsetAsync(pl->brick_mask, 0, (size_t)(pl->nb + kFormatPad) * 8, s));
-  HIP_TRY(launch_fill_u32(pl->brick_valptr + pl->nb, kFormatPad + 1, (uint32_t)nnz, s));
-  HIP_TRY(hipMemsetAsync(pl->vals + nnz, 0, 64 * sizeof(float), s));
-  HIP_TRY(hipMemsetAsync(col_seen, 0, (size_t)std::max<int64_t>(K, 1), s));
-  HIP_TRY(hipMemsetAsync(counters, 0, kNumCounters * sizeof(unsigned long long), s));
+  HIP_TRY(launch_format_pad(pl->brick_cols, pl->brick_mask, pl->brick_valptr, pl->vals, pl->nb, nnz, s));
 
   if (path == kPathSort) {
     HIP_TRY(launch_panel_sort_build(rowptr, colind, vals, M, K, P, sort_cap,
@@ -746,6 +734,7 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
     uint8_t* ent_bit = again.take<uint8_t>(nnz);
     uint32_t* ent_rank = again.take<uint32_t>(nnz);
     HIP_TRY(launch_fill_u32(pl->brick_cols, pl->nb * kBrickK, kPadCol, s));
+    HIP_TRY(launch_fill_u64(pl->brick_mask, pl->nb, 0, s));
     HIP_TRY(launch_rank_first(rowptr, colind, ent_row, first_list, first_scan, pl->panel_ptr, M,
                               pl->n_active_cols, ent_rank, pl->brick_cols, s));
     HIP_TRY(launch_scatter_bits(colind, ent_row, link, ent_rank, pl->panel_ptr, nnz,
@@ -755,29 +744,21 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
                                pl->vals, pl->src, s));
   }
   // ---- a5: per-panel classes and the synergy counts
-  HIP_TRY(launch_panel_classes(pl->panel_ptr, panel_nnzptr, P, panel_class, counters, s));
-  HIP_TRY(launch_brick_hist(pl->brick_mask, pl->nb, counters, s));
-  HIP_TRY(launch_count_flags(col_seen, K, counters + kCntDistinctCols, s));
+  HIP_TRY(launch_plan_stats(pl->panel_ptr, pl->panel_nnzptr, P, pl->brick_mask, pl->nb, col_seen, K,
+                            ctl->counters, s));
 
   // ---- host copies for the work-list builder and the model
   try {
     pl->h_panel_ptr.resize((size_t)P + 1);
-    pl->h_panel_nnzptr.resize((size_t)P + 1);
-    pl->h_panel_class.resize((size_t)std::max<int64_t>(P, 1));
   } catch (const std::bad_alloc&) {
     status = fail(SPMM_ENOMEM, "host allocation failed");
     goto done;
   }
   HIP_TRY(hipMemcpyAsync(pl->h_panel_ptr.data(), pl->panel_ptr, (size_t)(P + 1) * sizeof(uint32_t),
                          hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipMemcpyAsync(pl->h_panel_nnzptr.data(), panel_nnzptr, (size_t)(P + 1) * sizeof(uint32_t),
-                         hipMemcpyDeviceToHost, s));
-  if (P > 0)
-    HIP_TRY(hipMemcpyAsync(pl->h_panel_class.data(), panel_class, (size_t)P,
-                           hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipMemcpyAsync(pl->h_counters, counters, kNumCounters * sizeof(unsigned long long),
-                         hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipMemcpyAsync(&h_ctl, ctl, sizeof(PlanControl), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
+  memcpy(pl->h_counters, h_ctl.counters, sizeof(pl->h_counters));
 
 done:
   if (status != SPMM_OK) (void)hipStreamSynchronize(s);

@@ -40,21 +40,91 @@ __device__ inline int64_t lower_bound_col(const int32_t* __restrict__ colind, in
   return lo;
 }
 
-// ---------------------------------------------------------------- validation
-__global__ void k_validate_rowptr(const int32_t* __restrict__ rowptr, int64_t M, int64_t nnz,
-                                  uint32_t* err) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i > M) return;
-  uint32_t e = 0;
-  const int64_t a = rowptr[i];
-  if (i == 0 && a != 0) e |= kErrRowptrEnds;
-  if (i == M && a != nnz) e |= kErrRowptrEnds;
-  if (a < 0 || a > nnz) e |= kErrRowptrOrder;
-  if (i < M) {
-    const int64_t b = rowptr[i + 1];
-    if (b < a) e |= kErrRowptrOrder;
+// reductions across the wavefront (every lane takes part; all get the result)
+template <typename T> __device__ inline T wave_sum(T v) {
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+  return v;
+}
+template <typename T> __device__ inline T wave_max(T v) {
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) v = max(v, __shfl_xor(v, d, 64));
+  return v;
+}
+template <typename T> __device__ inline T wave_or(T v) {
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) v |= __shfl_xor(v, d, 64);
+  return v;
+}
+// raises *p to v; the plain look first spares the atomic that would change nothing
+__device__ inline void raise_to(uint32_t* p, uint32_t v) {
+  if (v > __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(p, v);
+}
+
+// ---------------------------------------------------------------- rows
+// One pass over the rows, a thread each, sixteen neighbouring lanes a panel: checks rowptr, copies
+// it into the plan, writes the entry offset of each panel, and finds the widest column span and the
+// largest entry count of a panel, from which the plan chooses how to build.  A row's columns are
+// bounded by its first and last entry; they are read only where the row's own offsets are in order
+// and inside [0, nnz].  A panel with entries and an inverted span (the last column of every row
+// below the first column of some row) is not sorted or has a negative column.
+// Bound by the latency of two dependent loads, hence a thread per row; one block maximum per 1024
+// rows in flight keeps the atomics on one address few.  262,144 rows: 33 us as a thread per panel
+// and a separate check, 12 us so.
+constexpr int kRowThreads = 1024;
+constexpr int kRowBlocks = 256;
+
+__global__ __launch_bounds__(kRowThreads) void k_rows(
+    const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind, int64_t M, int64_t P,
+    int64_t nnz, int32_t* __restrict__ rowptr_copy, uint32_t* __restrict__ panel_nnzptr,
+    PlanControl* ctl) {
+  __shared__ uint32_t s_err, s_span, s_nnz;
+  if (threadIdx.x == 0) { s_err = 0; s_span = 0; s_nnz = 0; }
+  __syncthreads();
+  uint32_t err = 0, span = 0, most = 0;
+  const int64_t stride = (int64_t)gridDim.x * kRowThreads;
+  for (int64_t base = (int64_t)blockIdx.x * kRowThreads; base <= M; base += stride) {
+    const int64_t i = base + threadIdx.x;
+    int32_t lo = 0x7FFFFFFF, hi = -1;
+    uint32_t cnt = 0;
+    if (i <= M) {
+      const int32_t a = rowptr[i], b = i < M ? rowptr[i + 1] : a;
+      rowptr_copy[i] = a;
+      if (i % kPanel == 0) panel_nnzptr[i / kPanel] = (uint32_t)a;
+      else if (i == M) panel_nnzptr[P] = (uint32_t)a;
+      if (i == 0 && a != 0) err |= kErrRowptrEnds;
+      if (i == M && a != nnz) err |= kErrRowptrEnds;
+      if (a < 0 || a > nnz || b < a) err |= kErrRowptrOrder;
+      else if (a < b && b <= nnz) {
+        lo = colind[a];
+        hi = colind[b - 1];
+        cnt = (uint32_t)(b - a);
+      }
+    }
+#pragma unroll
+    for (int d = 8; d > 0; d >>= 1) {
+      lo = min(lo, __shfl_xor(lo, d, 64));
+      hi = max(hi, __shfl_xor(hi, d, 64));
+      cnt += __shfl_xor(cnt, d, 64);
+    }
+    if (hi >= lo) span = max(span, (uint32_t)((int64_t)hi - lo + 1));
+    else if (cnt) err |= kErrColOrder;
+    most = max(most, cnt);
   }
-  if (e) atomicOr(err, e);
+  err = wave_or(err);
+  span = wave_max(span);
+  most = wave_max(most);
+  if ((threadIdx.x & 63) == 0) {
+    if (err) atomicOr(&s_err, err);
+    atomicMax(&s_span, span);
+    atomicMax(&s_nnz, most);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    if (s_err) atomicOr(&ctl->err, s_err);
+    raise_to(&ctl->span, s_span);
+    raise_to(&ctl->max_nnz, s_nnz);
+  }
 }
 
 // Requires a valid rowptr.  Also records the row of every entry.
@@ -107,21 +177,14 @@ __global__ void k_compact_first(const uint8_t* __restrict__ first,
   if (e < nnz && first[e]) first_list[first_scan[e]] = (uint32_t)e;
 }
 
-// a2: bricks per panel and the entry offset of each panel.
+// a2: active columns of each panel.
 __global__ void k_panel_counts(const int32_t* __restrict__ rowptr,
                                const uint32_t* __restrict__ first_scan, int64_t M, int64_t P,
-                               uint32_t* __restrict__ nbricks_p,
-                               uint32_t* __restrict__ panel_nnzptr) {
+                               uint32_t* __restrict__ ncols_p) {
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p > P) return;
-  const int64_t r0 = min(p * kPanel, M);
-  const int64_t e0 = rowptr[r0];
-  panel_nnzptr[p] = (uint32_t)e0;
-  if (p < P) {
-    const int64_t r1 = min(r0 + kPanel, M);
-    const uint32_t ncols = first_scan[rowptr[r1]] - first_scan[e0];
-    nbricks_p[p] = (ncols + kBrickK - 1) / kBrickK;
-  }
+  if (p >= P) return;
+  const int64_t r0 = p * kPanel, r1 = min(r0 + kPanel, M);
+  ncols_p[p] = first_scan[rowptr[r1]] - first_scan[rowptr[r0]];
 }
 
 template <typename T>
@@ -241,56 +304,95 @@ __global__ __launch_bounds__(kThreads) void k_restore_csr(
   csr_vals[e] = packed[pos];
 }
 
-// a5: per-panel class (Table 1, integer compare) and class totals.
-__global__ void k_panel_classes(const uint32_t* __restrict__ panel_ptr,
-                                const uint32_t* __restrict__ panel_nnzptr, int64_t P,
-                                uint8_t* __restrict__ panel_class, unsigned long long* counters) {
-  __shared__ unsigned long long acc[10];
-  if (threadIdx.x < 10) acc[threadIdx.x] = 0;
+// a5: per-panel class (Table 1, integer compare) and class totals, histogram of bricks by stored
+// elements, columns that occur.  Few, large workgroups: each adds its totals to the counters once,
+// and same-address atomics of many workgroups were what the separate kernels for these three spent
+// their time on (630 k bricks of 16,384 panels: 55 us in three launches, 8 us in
+// this one).
+constexpr int kStatThreads = 1024;
+constexpr int kStatBlocks = 128;
+
+__global__ __launch_bounds__(kStatThreads) void k_plan_stats(
+    const uint32_t* __restrict__ panel_ptr, const uint32_t* __restrict__ panel_nnzptr, int64_t P,
+    const uint64_t* __restrict__ brick_mask, int64_t nb, const uint8_t* __restrict__ col_seen,
+    int64_t K, unsigned long long* counters) {
+  constexpr int kWaves = kStatThreads / 64;
+  __shared__ uint32_t hist[kWaves][65];          // a histogram per wavefront: fewer collisions
+  __shared__ unsigned long long acc[kCntPopHist];
+  for (int t = threadIdx.x; t < kWaves * 65; t += kStatThreads) (&hist[0][0])[t] = 0;
+  if (threadIdx.x < kCntPopHist) acc[threadIdx.x] = 0;
   __syncthreads();
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p < P) {
-    const unsigned long long nb = panel_ptr[p + 1] - panel_ptr[p];
-    const unsigned long long nz = panel_nnzptr[p + 1] - panel_nnzptr[p];
-    uint8_t cls = 255;
-    if (nb) {
-      cls = nz < 8 * nb ? 0 : (nz < 16 * nb ? 1 : 2);
-      atomicAdd(&acc[kCntPanelsByClass + cls], 1ull);
-      atomicAdd(&acc[kCntBricksByClass + cls], nb);
-      atomicAdd(&acc[kCntNnzByClass + cls], nz);
-      atomicAdd(&acc[kCntNonEmptyPanels], 1ull);
-    }
-    panel_class[p] = cls;
+  const int64_t first = (int64_t)blockIdx.x * kStatThreads + threadIdx.x;
+  const int64_t stride = (int64_t)gridDim.x * kStatThreads;
+
+  uint32_t* mine = hist[threadIdx.x >> 6];
+  int64_t b = first;
+  for (; b + 3 * stride < nb; b += 4 * stride) {   // four loads in flight
+    uint64_t m[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) m[k] = brick_mask[b + k * stride];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) atomicAdd(&mine[__popcll(m[k])], 1u);
   }
+  for (; b < nb; b += stride) atomicAdd(&mine[__popcll(brick_mask[b])], 1u);
+
+  // class totals in registers: bricks and entries of a thread's panels
+  unsigned long long panels[3] = {0, 0, 0}, bricks[3] = {0, 0, 0}, entries[3] = {0, 0, 0};
+  for (int64_t p = first; p < P; p += stride) {
+    const unsigned long long n = panel_ptr[p + 1] - panel_ptr[p];
+    const unsigned long long nz = panel_nnzptr[p + 1] - panel_nnzptr[p];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const bool is = n && (nz < 8 * n ? 0 : (nz < 16 * n ? 1 : 2)) == c;
+      panels[c] += is;
+      bricks[c] += is ? n : 0;
+      entries[c] += is ? nz : 0;
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    panels[c] = wave_sum(panels[c]);
+    if (!panels[c]) continue;   // (the same in every lane)
+    bricks[c] = wave_sum(bricks[c]);
+    entries[c] = wave_sum(entries[c]);
+    if ((threadIdx.x & 63) == 0) {
+      atomicAdd(&acc[kCntPanelsByClass + c], panels[c]);
+      atomicAdd(&acc[kCntBricksByClass + c], bricks[c]);
+      atomicAdd(&acc[kCntNnzByClass + c], entries[c]);
+      atomicAdd(&acc[kCntNonEmptyPanels], panels[c]);
+    }
+  }
+
+  // flags of 0 or 1, sixteen at a time (the array is 256-byte aligned)
+  uint32_t seen = 0;
+  const int64_t vecs = K / 16;
+  for (int64_t v = first; v < vecs; v += stride) {
+    const uint4 f = reinterpret_cast<const uint4*>(col_seen)[v];
+    seen += __popc(f.x) + __popc(f.y) + __popc(f.z) + __popc(f.w);
+  }
+  if (first < K - vecs * 16) seen += col_seen[vecs * 16 + first];
+  seen = wave_sum(seen);
+  if (seen && (threadIdx.x & 63) == 0) atomicAdd(&acc[kCntDistinctCols], (unsigned long long)seen);
+
   __syncthreads();
-  if (threadIdx.x < 10 && acc[threadIdx.x]) atomicAdd(&counters[threadIdx.x], acc[threadIdx.x]);
+  if (threadIdx.x < kCntPopHist && acc[threadIdx.x])
+    atomicAdd(&counters[threadIdx.x], acc[threadIdx.x]);
+  if (threadIdx.x < 65) {
+    unsigned long long h = 0;
+    for (int w = 0; w < kWaves; ++w) h += hist[w][threadIdx.x];
+    if (h) atomicAdd(&counters[kCntPopHist + threadIdx.x], h);
+  }
 }
 
-__global__ void k_brick_hist(const uint64_t* __restrict__ brick_mask, int64_t nb,
-                             unsigned long long* counters) {
-  __shared__ unsigned int h[65];
-  for (int t = threadIdx.x; t < 65; t += blockDim.x) h[t] = 0;
-  __syncthreads();
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < nb; b += stride)
-    atomicAdd(&h[__popcll(brick_mask[b])], 1u);
-  __syncthreads();
-  for (int t = threadIdx.x; t < 65; t += blockDim.x)
-    if (h[t]) atomicAdd(&counters[kCntPopHist + t], (unsigned long long)h[t]);
-}
-
-__global__ void k_count_flags(const uint8_t* __restrict__ flags, int64_t n,
-                              unsigned long long* counter) {
-  __shared__ unsigned int total;
-  if (threadIdx.x == 0) total = 0;
-  __syncthreads();
-  unsigned int mine = 0;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
-    mine += flags[i];
-  if (mine) atomicAdd(&total, mine);
-  __syncthreads();
-  if (threadIdx.x == 0 && total) atomicAdd(counter, (unsigned long long)total);
+// the spare entries behind the brick arrays (see BrickFormat); one workgroup of kThreads
+__global__ void k_format_pad(uint32_t* __restrict__ brick_cols, uint64_t* __restrict__ brick_mask,
+                             uint32_t* __restrict__ brick_valptr, float* __restrict__ vals,
+                             int64_t nb, int64_t nnz) {
+  const int t = threadIdx.x;
+  if (t < kFormatPad * kBrickK) brick_cols[nb * kBrickK + t] = 0;
+  if (t < kFormatPad) brick_mask[nb + t] = 0;
+  if (t < kFormatPad + 1) brick_valptr[nb + t] = (uint32_t)nnz;
+  if (t < 64) vals[nnz + t] = 0.f;
 }
 
 // Rows with more than `threshold` entries, compacted in any order (the CSR kernel gives each of
@@ -397,6 +499,72 @@ hipError_t scan_impl(Load load, int64_t n, uint32_t* out, uint32_t* tmp, hipStre
   return hipGetLastError();
 }
 
+// ---------------------------------------------------------------- panel_ptr
+// Bricks of each panel (a quarter of its active columns, rounded up), scanned; two launches of at
+// most kPanelScanBlocks workgroups, each thread a run of `run` panels.  The first also totals the
+// active columns and finds the largest column count; in the second every workgroup adds up the
+// sums before its own, which saves the launch that would scan them.
+constexpr int kPanelScanBlocks = 1024;
+
+inline int64_t panel_scan_run(int64_t P) {
+  return std::max<int64_t>(4, (P + (int64_t)kPanelScanBlocks * kScanThreads - 1) /
+                                  ((int64_t)kPanelScanBlocks * kScanThreads));
+}
+
+__global__ __launch_bounds__(kScanThreads) void k_panel_sums(const uint32_t* __restrict__ ncols_p,
+                                                             int64_t P, int64_t run,
+                                                             uint32_t* __restrict__ block_sums,
+                                                             PlanControl* ctl) {
+  __shared__ unsigned long long s_cols;
+  __shared__ uint32_t s_max;
+  if (threadIdx.x == 0) { s_cols = 0; s_max = 0; }
+  const int64_t p0 = min(((int64_t)blockIdx.x * kScanThreads + threadIdx.x) * run, P);
+  const int64_t p1 = min(p0 + run, P);
+  uint32_t bricks = 0, most = 0;
+  unsigned long long cols = 0;
+  for (int64_t p = p0; p < p1; ++p) {
+    const uint32_t n = ncols_p[p];
+    bricks += (n + kBrickK - 1) / kBrickK;
+    cols += n;
+    most = max(most, n);
+  }
+  uint32_t total;
+  block_exclusive(bricks, &total);   // (its barriers also cover the zeroing above)
+  cols = wave_sum(cols);
+  most = wave_max(most);
+  if (cols && (threadIdx.x & 63) == 0) { atomicAdd(&s_cols, cols); atomicMax(&s_max, most); }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    block_sums[blockIdx.x] = total;
+    if (s_cols) { atomicAdd(&ctl->n_active, s_cols); raise_to(&ctl->max_cols, s_max); }
+  }
+}
+
+__global__ __launch_bounds__(kScanThreads) void k_panel_scan(const uint32_t* __restrict__ ncols_p,
+                                                             int64_t P, int64_t run,
+                                                             const uint32_t* __restrict__ block_sums,
+                                                             uint32_t* __restrict__ panel_ptr,
+                                                             PlanControl* ctl) {
+  uint32_t before = 0;
+  for (uint32_t b = threadIdx.x; b < blockIdx.x; b += kScanThreads) before += block_sums[b];
+  uint32_t base;
+  block_exclusive(before, &base);
+  const int64_t p0 = min(((int64_t)blockIdx.x * kScanThreads + threadIdx.x) * run, P);
+  const int64_t p1 = min(p0 + run, P);
+  uint32_t bricks = 0;
+  for (int64_t p = p0; p < p1; ++p) bricks += (ncols_p[p] + kBrickK - 1) / kBrickK;
+  uint32_t total;
+  uint32_t at = base + block_exclusive(bricks, &total);
+  for (int64_t p = p0; p < p1; ++p) {
+    panel_ptr[p] = at;
+    at += (ncols_p[p] + kBrickK - 1) / kBrickK;
+  }
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+    panel_ptr[P] = base + total;
+    ctl->nb = base + total;
+  }
+}
+
 // ---------------------------------------------------------------- per-panel path
 // One wavefront (a 64-thread workgroup) per panel, the panel's active columns as a bitmap in
 // LDS over the panel's column span [cmin, cmax]: setting a bit per entry is the census (a1),
@@ -463,36 +631,6 @@ __device__ inline int row_in_panel(const int32_t* rp, int64_t e) {
   return r;
 }
 
-// widest column span and largest entry count of any panel (0 for an empty matrix); requires
-// a valid rowptr.  out[0] = span, out[1] = entries.
-__global__ void k_panel_span(const int32_t* __restrict__ rowptr,
-                             const int32_t* __restrict__ colind, int64_t M, int64_t P,
-                             uint32_t* err, uint32_t* out) {
-  __shared__ uint32_t s_span, s_nnz, s_bad;
-  if (*err & (kErrRowptrEnds | kErrRowptrOrder)) return;
-  if (threadIdx.x == 0) { s_span = 0; s_nnz = 0; s_bad = 0; }
-  __syncthreads();
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p < P) {
-    int32_t lo = 0x7FFFFFFF, hi = -1;
-    const int64_t r0 = p * kPanel, r1 = min((p + 1) * kPanel, M);
-    for (int64_t r = r0; r < r1; ++r) {
-      const int32_t s = rowptr[r], t = rowptr[r + 1];
-      if (s < t) { lo = min(lo, colind[s]); hi = max(hi, colind[t - 1]); }
-    }
-    if (hi >= lo) atomicMax(&s_span, (uint32_t)((int64_t)hi - lo + 1));
-    else if (rowptr[r1] > rowptr[r0]) atomicOr(&s_bad, 1u);   // entries, but an inverted span
-    atomicMax(&s_nnz, (uint32_t)(rowptr[r1] - rowptr[r0]));
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    if (s_span) atomicMax(&out[0], s_span);
-    if (s_nnz) atomicMax(&out[1], s_nnz);
-    // a panel whose rows end below where they start is not sorted (or has a negative column)
-    if (s_bad) atomicOr(err, (uint32_t)kErrColOrder);
-  }
-}
-
 // sets the panel's bitmap; checks the columns on the way (range, order, inside the span)
 __device__ inline void panel_bitmap(const int32_t* __restrict__ colind, const PanelExtent& x,
                                     const int32_t* rp, int64_t K, uint32_t words, uint32_t* bm,
@@ -517,35 +655,28 @@ __device__ inline void panel_bitmap(const int32_t* __restrict__ colind, const Pa
   __syncthreads();
 }
 
-// a1/a2 (counting half): bricks of each panel, entry offset of each panel, total of active
-// columns, largest brick count of a panel; validates colind.  Dynamic LDS: the bitmap.
+// a1/a2 (counting half): active columns of each panel; validates colind.  Dynamic LDS: the bitmap.
 __global__ __launch_bounds__(kPanelThreads) void k_panel_census(
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind, int64_t M, int64_t K,
-    int64_t P, uint32_t words_cap, uint32_t* err, uint32_t* __restrict__ nbricks_p,
-    uint32_t* __restrict__ panel_nnzptr, uint32_t* __restrict__ ncols_p) {
+    int64_t P, uint32_t words_cap, uint32_t* err, uint32_t* __restrict__ ncols_p) {
   extern __shared__ uint32_t lds[];
   __shared__ int32_t rp[kPanel + 1];
   if (*err & (kErrRowptrEnds | kErrRowptrOrder)) return;   // uniform: nothing below is safe
   const int64_t p = blockIdx.x;
   const PanelExtent x = panel_extent(rowptr, colind, M, p, rp);
-  if (threadIdx.x == 0) {
-    panel_nnzptr[p] = (uint32_t)x.e0;
-    if (p == P - 1) panel_nnzptr[P] = (uint32_t)x.e1;
-  }
   if (x.e0 >= x.e1 || x.cmax < x.cmin) {
     // Entries but an inverted span (the last column of every row lies below the first column
     // of some row): a row is stored in descending order, or a column is negative.  No bitmap
     // can hold that, so the per-entry checks below would never see it.
     if (threadIdx.x == 0) {
       if (x.e0 < x.e1) atomicOr(err, (uint32_t)kErrColOrder);
-      nbricks_p[p] = 0;
       ncols_p[p] = 0;
     }
     return;
   }
   const uint32_t words = (uint32_t)(x.cmax - x.cmin) / 32u + 1u;
-  if (words > words_cap) {   // cannot happen for sorted rows (the cap comes from k_panel_span)
-    if (threadIdx.x == 0) { atomicOr(err, (uint32_t)kErrColOrder); nbricks_p[p] = 0; ncols_p[p] = 0; }
+  if (words > words_cap) {   // cannot happen for sorted rows (the cap comes from k_rows)
+    if (threadIdx.x == 0) { atomicOr(err, (uint32_t)kErrColOrder); ncols_p[p] = 0; }
     return;
   }
   panel_bitmap(colind, x, rp, K, words, lds, err);
@@ -553,10 +684,7 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_census(
   for (uint32_t w = threadIdx.x; w < words; w += kPanelThreads) cnt += __popc(lds[w]);
   uint32_t total;
   wave_exclusive(cnt, &total);
-  if (threadIdx.x == 0) {
-    nbricks_p[p] = (total + kBrickK - 1) / kBrickK;
-    ncols_p[p] = total;
-  }
+  if (threadIdx.x == 0) ncols_p[p] = total;
 }
 
 // ---- per-panel path for scattered matrices: sort instead of a bitmap
@@ -623,8 +751,7 @@ __device__ inline uint32_t sort_size(uint32_t n) {
 template <typename KT>
 __global__ __launch_bounds__(kPanelThreads) void k_panel_sort_census(
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind, int64_t M, int64_t K,
-    int64_t P, uint32_t n_cap, uint32_t* err, uint32_t* __restrict__ nbricks_p,
-    uint32_t* __restrict__ panel_nnzptr, uint32_t* __restrict__ ncols_p,
+    int64_t P, uint32_t n_cap, uint32_t* err, uint32_t* __restrict__ ncols_p,
     uint32_t* __restrict__ order) {
   extern __shared__ unsigned long long lds64[];
   KT* keys = reinterpret_cast<KT*>(lds64);
@@ -632,13 +759,9 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_sort_census(
   if (*err & (kErrRowptrEnds | kErrRowptrOrder)) return;   // uniform: nothing below is safe
   const int64_t p = blockIdx.x;
   const PanelExtent x = panel_extent(rowptr, colind, M, p, rp);
-  if (threadIdx.x == 0) {
-    panel_nnzptr[p] = (uint32_t)x.e0;
-    if (p == P - 1) panel_nnzptr[P] = (uint32_t)x.e1;
-  }
   const uint32_t n = (uint32_t)(x.e1 - x.e0);
-  if (n == 0 || n > n_cap) {   // (n > n_cap cannot happen: the cap comes from k_panel_span)
-    if (threadIdx.x == 0) { nbricks_p[p] = 0; ncols_p[p] = 0; }
+  if (n == 0 || n > n_cap) {   // (n > n_cap cannot happen: the cap comes from k_rows)
+    if (threadIdx.x == 0) ncols_p[p] = 0;
     return;
   }
   panel_sort<KT>(colind, x, rp, K, sort_size(n), keys, err);
@@ -649,10 +772,7 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_sort_census(
   }
   uint32_t total;
   wave_exclusive(cnt, &total);
-  if (threadIdx.x == 0) {
-    nbricks_p[p] = (total + kBrickK - 1) / kBrickK;
-    ncols_p[p] = total;
-  }
+  if (threadIdx.x == 0) ncols_p[p] = total;
 }
 
 // a2 (placing half), a3 and a4 for one panel from the sorted order left by the census in
@@ -750,30 +870,6 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_sort_build(
       packed[pos] = vals[e];
       src[pos] = (uint32_t)e;
     }
-  }
-}
-
-// sum and maximum of ncols_p (one atomic pair per workgroup: per-panel atomics on one address
-// serialise at more than 100 ns each)
-__global__ void k_cols_sum_max(const uint32_t* __restrict__ ncols_p, int64_t P,
-                               unsigned long long* sum, uint32_t* max_cols) {
-  __shared__ unsigned long long s_sum;
-  __shared__ uint32_t s_max;
-  if (threadIdx.x == 0) { s_sum = 0; s_max = 0; }
-  __syncthreads();
-  unsigned long long mine = 0;
-  uint32_t mx = 0;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < P; p += stride) {
-    mine += ncols_p[p];
-    mx = max(mx, ncols_p[p]);
-  }
-  if (mine) atomicAdd(&s_sum, mine);
-  if (mx) atomicMax(&s_max, mx);
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    if (s_sum) atomicAdd(sum, s_sum);
-    if (s_max) atomicMax(max_cols, s_max);
   }
 }
 
@@ -904,10 +1000,31 @@ hipError_t launch_scan_nonzero64(const uint64_t* in, int64_t n, uint32_t* out, u
   return scan_impl(LoadNonZero{in}, n, out, tmp, s);
 }
 
-hipError_t launch_validate_rowptr(const int32_t* rowptr, int64_t M, int64_t nnz, uint32_t* err,
-                                  hipStream_t s) {
-  hipLaunchKernelGGL(k_validate_rowptr, dim3(grid_for(M + 1)), dim3(kThreads), 0, s, rowptr, M, nnz,
-                     err);
+hipError_t launch_rows(const int32_t* rowptr, const int32_t* colind, int64_t M, int64_t P, int64_t nnz,
+                       int32_t* rowptr_copy, uint32_t* panel_nnzptr, PlanControl* ctl,
+                       hipStream_t s) {
+  const unsigned g = (unsigned)std::min<int64_t>(grid_for(M + 1, kRowThreads), kRowBlocks);
+  hipLaunchKernelGGL(k_rows, dim3(g), dim3(kRowThreads), 0, s, rowptr, colind, M, P, nnz,
+                     rowptr_copy, panel_nnzptr, ctl);
+  return hipGetLastError();
+}
+
+size_t panel_scan_tmp_elems() { return kPanelScanBlocks; }
+
+hipError_t launch_panel_scan(const uint32_t* ncols_p, int64_t P, uint32_t* panel_ptr, uint32_t* tmp,
+                             PlanControl* ctl, hipStream_t s) {
+  const int64_t run = panel_scan_run(P);
+  const dim3 grid(grid_for((P + run - 1) / run, kScanThreads)), block(kScanThreads);
+  hipLaunchKernelGGL(k_panel_sums, grid, block, 0, s, ncols_p, P, run, tmp, ctl);
+  hipLaunchKernelGGL(k_panel_scan, grid, block, 0, s, ncols_p, P, run, tmp, panel_ptr, ctl);
+  return hipGetLastError();
+}
+
+hipError_t launch_format_pad(uint32_t* brick_cols, uint64_t* brick_mask, uint32_t* brick_valptr,
+                             float* vals, int64_t nb, int64_t nnz, hipStream_t s) {
+  static_assert(kFormatPad * kBrickK <= kThreads && kFormatPad < 64, "one workgroup writes the pads");
+  hipLaunchKernelGGL(k_format_pad, dim3(1), dim3(kThreads), 0, s, brick_cols, brick_mask,
+                     brick_valptr, vals, nb, nnz);
   return hipGetLastError();
 }
 
@@ -937,10 +1054,10 @@ hipError_t launch_compact_first(const uint8_t* first, const uint32_t* first_scan
 }
 
 hipError_t launch_panel_counts(const int32_t* rowptr, const uint32_t* first_scan, int64_t M,
-                               int64_t P, uint32_t* nbricks_p, uint32_t* panel_nnzptr,
-                               hipStream_t s) {
-  hipLaunchKernelGGL(k_panel_counts, dim3(grid_for(P + 1)), dim3(kThreads), 0, s, rowptr,
-                     first_scan, M, P, nbricks_p, panel_nnzptr);
+                               int64_t P, uint32_t* ncols_p, hipStream_t s) {
+  if (P == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_panel_counts, dim3(grid_for(P)), dim3(kThreads), 0, s, rowptr, first_scan, M,
+                     P, ncols_p);
   return hipGetLastError();
 }
 
@@ -1004,27 +1121,14 @@ hipError_t launch_restore_csr(const BrickFormat& f, const uint32_t* src, int64_t
   return hipGetLastError();
 }
 
-hipError_t launch_panel_classes(const uint32_t* panel_ptr, const uint32_t* panel_nnzptr, int64_t P,
-                                uint8_t* panel_class, unsigned long long* counters, hipStream_t s) {
-  if (P == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_panel_classes, dim3(grid_for(P)), dim3(kThreads), 0, s, panel_ptr,
-                     panel_nnzptr, P, panel_class, counters);
-  return hipGetLastError();
-}
-
-hipError_t launch_brick_hist(const uint64_t* brick_mask, int64_t nb, unsigned long long* counters,
-                             hipStream_t s) {
-  if (nb == 0) return hipSuccess;
-  const unsigned g = (unsigned)std::min<int64_t>(grid_for(nb), 2048);
-  hipLaunchKernelGGL(k_brick_hist, dim3(g), dim3(kThreads), 0, s, brick_mask, nb, counters);
-  return hipGetLastError();
-}
-
-hipError_t launch_count_flags(const uint8_t* flags, int64_t n, unsigned long long* counter,
-                              hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  const unsigned g = (unsigned)std::min<int64_t>(grid_for(n), 2048);
-  hipLaunchKernelGGL(k_count_flags, dim3(g), dim3(kThreads), 0, s, flags, n, counter);
+hipError_t launch_plan_stats(const uint32_t* panel_ptr, const uint32_t* panel_nnzptr, int64_t P,
+                             const uint64_t* brick_mask, int64_t nb, const uint8_t* col_seen,
+                             int64_t K, unsigned long long* counters, hipStream_t s) {
+  if (nb == 0) return hipSuccess;   // no brick: every count is zero
+  const int64_t most = std::max(std::max(nb, P), K / 16 + 16);
+  const unsigned g = (unsigned)std::min<int64_t>(grid_for(most, kStatThreads), kStatBlocks);
+  hipLaunchKernelGGL(k_plan_stats, dim3(g), dim3(kStatThreads), 0, s, panel_ptr, panel_nnzptr, P,
+                     brick_mask, nb, col_seen, K, counters);
   return hipGetLastError();
 }
 
@@ -1033,15 +1137,6 @@ hipError_t launch_find_long_rows(const int32_t* rowptr, int64_t M, int threshold
   if (M == 0) return hipSuccess;
   hipLaunchKernelGGL(k_find_long_rows, dim3(grid_for(M)), dim3(kThreads), 0, s, rowptr, M,
                      threshold, list, counter);
-  return hipGetLastError();
-}
-
-// ---- per-panel path
-hipError_t launch_panel_span(const int32_t* rowptr, const int32_t* colind, int64_t M, int64_t P,
-                             uint32_t* err, uint32_t* span_and_nnz, hipStream_t s) {
-  if (P == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_panel_span, dim3(grid_for(P)), dim3(kThreads), 0, s, rowptr, colind, M, P,
-                     err, span_and_nnz);
   return hipGetLastError();
 }
 
@@ -1061,9 +1156,7 @@ bool panel_sort_build_fits(uint32_t n_cap, uint32_t nb_cap) {
 
 hipError_t launch_panel_sort_census(const int32_t* rowptr, const int32_t* colind, int64_t M,
                                     int64_t K, int64_t P, uint32_t n_cap, uint32_t* err,
-                                    uint32_t* nbricks_p, uint32_t* panel_nnzptr, uint32_t* ncols_p,
-                                    uint32_t* order, unsigned long long* n_active,
-                                    uint32_t* max_cols, hipStream_t s) {
+                                    uint32_t* ncols_p, uint32_t* order, hipStream_t s) {
   if (P == 0) return hipSuccess;
   const bool narrow = K < (int64_t(1) << 21) && n_cap <= 2048;   // (column, index) fits 32 bits
   const size_t lds = (size_t)n_cap * (narrow ? 4 : 8);
@@ -1076,14 +1169,11 @@ hipError_t launch_panel_sort_census(const int32_t* rowptr, const int32_t* colind
   }
   if (narrow)
     hipLaunchKernelGGL(k_panel_sort_census<uint32_t>, dim3((unsigned)P), dim3(kPanelThreads), lds,
-                       s, rowptr, colind, M, K, P, n_cap, err, nbricks_p, panel_nnzptr, ncols_p,
-                       order);
+                       s, rowptr, colind, M, K, P, n_cap, err, ncols_p, order);
   else
     hipLaunchKernelGGL(k_panel_sort_census<unsigned long long>, dim3((unsigned)P),
-                       dim3(kPanelThreads), lds, s, rowptr, colind, M, K, P, n_cap, err, nbricks_p,
-                       panel_nnzptr, ncols_p, order);
-  hipLaunchKernelGGL(k_cols_sum_max, dim3((unsigned)std::min<int64_t>(grid_for(P), 1024)),
-                     dim3(kThreads), 0, s, ncols_p, P, n_active, max_cols);
+                       dim3(kPanelThreads), lds, s, rowptr, colind, M, K, P, n_cap, err, ncols_p,
+                       order);
   return hipGetLastError();
 }
 
@@ -1122,9 +1212,8 @@ bool panel_build_fits(uint32_t words_cap, uint32_t nb_cap) {
 }
 
 hipError_t launch_panel_census(const int32_t* rowptr, const int32_t* colind, int64_t M, int64_t K,
-                               int64_t P, uint32_t words_cap, uint32_t* err, uint32_t* nbricks_p,
-                               uint32_t* panel_nnzptr, uint32_t* ncols_p,
-                               unsigned long long* n_active, uint32_t* max_cols, hipStream_t s) {
+                               int64_t P, uint32_t words_cap, uint32_t* err, uint32_t* ncols_p,
+                               hipStream_t s) {
   if (P == 0) return hipSuccess;
   const size_t lds = (size_t)words_cap * 4;
   if (lds > 48 * 1024) {
@@ -1133,9 +1222,7 @@ hipError_t launch_panel_census(const int32_t* rowptr, const int32_t* colind, int
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL(k_panel_census, dim3((unsigned)P), dim3(kPanelThreads), lds, s, rowptr, colind,
-                     M, K, P, words_cap, err, nbricks_p, panel_nnzptr, ncols_p);
-  hipLaunchKernelGGL(k_cols_sum_max, dim3((unsigned)std::min<int64_t>(grid_for(P), 1024)),
-                     dim3(kThreads), 0, s, ncols_p, P, n_active, max_cols);
+                     M, K, P, words_cap, err, ncols_p);
   return hipGetLastError();
 }
 

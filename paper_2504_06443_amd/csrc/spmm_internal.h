@@ -30,6 +30,16 @@ enum : int {
   kNumCounters = 76
 };
 
+struct PlanControl {        // device, zeroed when a plan begins; read back at its synchronisations
+  uint32_t err;             // error bits
+  uint32_t span, max_nnz;   // widest column span, most entries of a panel
+  uint32_t max_cols;        // most active columns of a panel
+  uint32_t nb;              // bricks
+  uint32_t pad;
+  unsigned long long n_active;   // active columns, summed over the panels
+  unsigned long long counters[kNumCounters];
+};
+
 struct WorkItem {           // one wavefront's share of the MFMA kernel
   uint32_t panel;
   uint32_t brick_begin;     // global brick index
@@ -45,8 +55,15 @@ struct MergeItem {          // one split panel
 };
 
 // ---- plan (a1..a5) -------------------------------------------------------
-hipError_t launch_validate_rowptr(const int32_t* rowptr, int64_t M, int64_t nnz, uint32_t* err,
-                                  hipStream_t s);
+hipError_t launch_rows(const int32_t* rowptr, const int32_t* colind, int64_t M, int64_t P, int64_t nnz,
+                       int32_t* rowptr_copy, uint32_t* panel_nnzptr, PlanControl* ctl,
+                       hipStream_t s);
+// ncols_p -> panel_ptr[P+1] (bricks, scanned), ctl->nb, ctl->n_active, ctl->max_cols
+size_t panel_scan_tmp_elems();
+hipError_t launch_panel_scan(const uint32_t* ncols_p, int64_t P, uint32_t* panel_ptr, uint32_t* tmp,
+                             PlanControl* ctl, hipStream_t s);
+hipError_t launch_format_pad(uint32_t* brick_cols, uint64_t* brick_mask, uint32_t* brick_valptr,
+                             float* vals, int64_t nb, int64_t nnz, hipStream_t s);
 hipError_t launch_validate_cols(const int32_t* rowptr, const int32_t* colind, int64_t M, int64_t K,
                                 int64_t nnz, uint32_t* ent_row, uint32_t* err, hipStream_t s);
 hipError_t launch_first_in_panel(const int32_t* rowptr, const int32_t* colind,
@@ -55,8 +72,7 @@ hipError_t launch_first_in_panel(const int32_t* rowptr, const int32_t* colind,
 hipError_t launch_compact_first(const uint8_t* first, const uint32_t* first_scan, int64_t nnz,
                                 uint32_t* first_list, hipStream_t s);
 hipError_t launch_panel_counts(const int32_t* rowptr, const uint32_t* first_scan, int64_t M,
-                               int64_t P, uint32_t* nbricks_p, uint32_t* panel_nnzptr,
-                               hipStream_t s);
+                               int64_t P, uint32_t* ncols_p, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t s);
 hipError_t launch_fill_u64(uint64_t* p, int64_t n, uint64_t v, hipStream_t s);
 hipError_t launch_rank_first(const int32_t* rowptr, const int32_t* colind, const uint32_t* ent_row,
@@ -73,29 +89,21 @@ hipError_t launch_pack_values(const float* vals, const uint32_t* ent_brick, cons
 // csr_vals: null where the plan keeps no values in CSR order
 hipError_t launch_update_values(const float* vals, const uint32_t* src, int64_t nnz, float* packed,
                                 float* csr_vals, hipStream_t s);
-hipError_t launch_panel_classes(const uint32_t* panel_ptr, const uint32_t* panel_nnzptr, int64_t P,
-                                uint8_t* panel_class, unsigned long long* counters, hipStream_t s);
-hipError_t launch_brick_hist(const uint64_t* brick_mask, int64_t nb, unsigned long long* counters,
-                             hipStream_t s);
-hipError_t launch_count_flags(const uint8_t* flags, int64_t n, unsigned long long* counter,
-                              hipStream_t s);
+hipError_t launch_plan_stats(const uint32_t* panel_ptr, const uint32_t* panel_nnzptr, int64_t P,
+                             const uint64_t* brick_mask, int64_t nb, const uint8_t* col_seen,
+                             int64_t K, unsigned long long* counters, hipStream_t s);
 // rows with more than `threshold` entries -> list (any order), count added to *counter
 hipError_t launch_find_long_rows(const int32_t* rowptr, int64_t M, int threshold,
                                  uint32_t* list, unsigned long long* counter, hipStream_t s);
 
 // per-panel path (LDS bitmap over the panel's column span)
-// out[0] = widest column span of a panel, out[1] = most entries of a panel
-// (also flags a panel whose column span is inverted: unsorted rows or negative columns)
-hipError_t launch_panel_span(const int32_t* rowptr, const int32_t* colind, int64_t M, int64_t P,
-                             uint32_t* err, uint32_t* span_and_nnz, hipStream_t s);
 // per-panel path by sorting (any column span, panels of limited size)
 uint32_t panel_sort_keys(uint32_t max_nnz);   // 0: a panel has too many entries
 bool panel_sort_build_fits(uint32_t n_cap, uint32_t nb_cap);
 hipError_t launch_panel_sort_census(const int32_t* rowptr, const int32_t* colind, int64_t M,
                                     int64_t K, int64_t P, uint32_t n_cap, uint32_t* err,
-                                    uint32_t* nbricks_p, uint32_t* panel_nnzptr, uint32_t* ncols_p,
+                                    uint32_t* ncols_p,
                                     uint32_t* order /* [nnz]; read back by the build from src */,
-                                    unsigned long long* n_active, uint32_t* max_cols,
                                     hipStream_t s);
 hipError_t launch_panel_sort_build(const int32_t* rowptr, const int32_t* colind, const float* vals,
                                    int64_t M, int64_t K, int64_t P, uint32_t n_cap, uint32_t nb_cap,
@@ -104,9 +112,8 @@ hipError_t launch_panel_sort_build(const int32_t* rowptr, const int32_t* colind,
                                    uint32_t* src, uint8_t* col_seen, hipStream_t s);
 uint32_t panel_bitmap_words(uint32_t span);   // 0: span too wide for the per-panel path
 hipError_t launch_panel_census(const int32_t* rowptr, const int32_t* colind, int64_t M, int64_t K,
-                               int64_t P, uint32_t words_cap, uint32_t* err, uint32_t* nbricks_p,
-                               uint32_t* panel_nnzptr, uint32_t* ncols_p,
-                               unsigned long long* n_active, uint32_t* max_cols, hipStream_t s);
+                               int64_t P, uint32_t words_cap, uint32_t* err, uint32_t* ncols_p,
+                               hipStream_t s);
 bool panel_build_fits(uint32_t words_cap, uint32_t nb_cap);   // LDS of launch_panel_build
 hipError_t launch_panel_build(const int32_t* rowptr, const int32_t* colind, const float* vals,
                               int64_t M, int64_t K, int64_t P, uint32_t words_cap, uint32_t nb_cap,
