@@ -718,7 +718,7 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
   } else if (path == kPathBitmap) {
     // ---- a2 (placing), a3, a4, one wavefront per panel
     HIP_TRY(launch_panel_build(rowptr, colind, vals, M, K, P, words_cap,
-                               std::max<uint32_t>(h_maxnb, 1), pl->panel_ptr,
+                               std::max<uint32_t>(h_maxnb, 1), h_ctl.max_nnz, pl->panel_ptr,
                                pl->brick_cols, pl->brick_mask, pl->brick_valptr, pl->vals,
                                pl->src, col_seen, s));
   } else {

@@ -575,6 +575,8 @@ __global__ __launch_bounds__(kScanThreads) void k_panel_scan(const uint32_t* __r
 // brick count of a panel fit in LDS; other matrices take the search-based kernels above.
 constexpr int kPanelThreads = 64;
 constexpr int kGroupWords = 8;   // bitmap words per entry of the coarse rank table
+constexpr uint32_t kPanelFineWords = 2048;          // bitmaps with a rank per word (16 KiB with it)
+constexpr uint32_t kPanelStageMax = 2048;           // entries of a panel staged in LDS (12 KiB)
 constexpr uint32_t kPanelMaxWords = 32768;          // 1 Mi columns of span
 constexpr size_t kPanelMaxLds = 150 * 1024;         // of the 160 KiB of a CU
 constexpr uint32_t kPanelMaxSortKeys = 8192;        // entries of a panel on the sort-based path
@@ -640,10 +642,8 @@ __device__ inline void panel_bitmap(const int32_t* __restrict__ colind, const Pa
   uint32_t bad = 0;
   for (int64_t e = x.e0 + threadIdx.x; e < x.e1; e += kPanelThreads) {
     const int32_t j = colind[e];
-    if (err) {
-      if (j < 0 || j >= K) bad |= kErrColRange;
-      if (e > rp[row_in_panel(rp, e)] && colind[e - 1] >= j) bad |= kErrColOrder;
-    }
+    if (j < 0 || j >= K) bad |= kErrColRange;
+    if (e > rp[row_in_panel(rp, e)] && colind[e - 1] >= j) bad |= kErrColOrder;
     if (j >= x.cmin && j <= x.cmax) {
       const uint32_t d = (uint32_t)(j - x.cmin);
       atomicOr(&bm[d >> 5], 1u << (d & 31));
@@ -651,7 +651,7 @@ __device__ inline void panel_bitmap(const int32_t* __restrict__ colind, const Pa
       bad |= kErrColOrder;   // outside the span its sorted row promised
     }
   }
-  if (err && bad) atomicOr(err, bad);
+  if (bad) atomicOr(err, bad);
   __syncthreads();
 }
 
@@ -777,7 +777,8 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_sort_census(
 
 // a2 (placing half), a3 and a4 for one panel from the sorted order left by the census in
 // `src` (which this kernel then overwrites with the entry of each packed value).  Dynamic LDS: keys
-// (n_cap x u64), patterns (nb_cap x u64), value offsets (nb_cap words).
+// (n_cap x u64), patterns (nb_cap x u64), value offsets (nb_cap words), the order of the packed
+// values (n_cap x two bytes), through which they leave in order, whole lines at a time.
 __global__ __launch_bounds__(kPanelThreads) void k_panel_sort_build(
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind,
     const float* __restrict__ vals, int64_t M, int64_t K, uint32_t n_cap, uint32_t nb_cap,
@@ -789,6 +790,7 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_sort_build(
   unsigned long long* keys = lds64;                                  // [n_cap]
   unsigned long long* pat = lds64 + n_cap;                           // [nb_cap]
   uint32_t* vptr = reinterpret_cast<uint32_t*>(pat + nb_cap);        // [nb_cap]
+  uint16_t* at = reinterpret_cast<uint16_t*>(vptr + nb_cap);         // [n_cap]
   const int64_t p = blockIdx.x;
   const uint32_t pp = panel_ptr[p];
   const uint32_t nb = panel_ptr[p + 1] - pp;
@@ -865,29 +867,43 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_sort_build(
     const int64_t e = x.e0 + (uint32_t)keys[i];
     const uint32_t bit = (uint32_t)row_in_panel(rp, e) * kBrickK + rank % kBrickK;
     const uint32_t k = min(rank / kBrickK, nb - 1);
-    const uint32_t pos = vptr[k] + (uint32_t)__popcll(pat[k] & ((1ull << bit) - 1ull));
-    if (pos < (uint32_t)x.e1) {   // (always, for a census and a build that agree)
-      packed[pos] = vals[e];
-      src[pos] = (uint32_t)e;
-    }
+    const uint32_t pos = vptr[k] - (uint32_t)x.e0 +
+                         (uint32_t)__popcll(pat[k] & ((1ull << bit) - 1ull));
+    if (pos < n) at[pos] = (uint16_t)(uint32_t)keys[i];   // (always, for a census and a build that agree)
+  }
+  __syncthreads();
+  for (uint32_t i = threadIdx.x; i < n; i += kPanelThreads) {
+    const uint32_t e = (uint32_t)x.e0 + min((uint32_t)at[i], n - 1);
+    packed[x.e0 + i] = vals[e];
+    src[x.e0 + i] = e;
   }
 }
 
-// a2 (placing half), a3 and a4 for one panel.  Dynamic LDS: patterns of the
-// panel's bricks (nb_cap x u64), the bitmap (words_cap words), the coarse rank table
-// (words_cap / 8 + 1 words), value offsets of the panel's bricks (nb_cap words).
+// a2 (placing half), a3 and a4 for one panel.  Dynamic LDS: patterns of the panel's bricks (nb_cap x
+// u64), the bitmap (words_cap words), the rank table (words_cap / G + 1 words: set bits before every
+// G-th word), value offsets of the panel's bricks (nb_cap words), and for panels of at most
+// stage_cap entries a word per entry and their order (two bytes per entry).
+// Bound by the latency of what one wavefront does in turn, so the columns are read once, four loads
+// in flight, and an entry's row and rank are worked out once and kept in LDS; the packed values and
+// their sources leave in order, whole lines at a time.  Panels above stage_cap go through the same
+// steps without the staging: they read the columns again and scatter their values.
+// 7.86 M entries in 16,384 panels: 92 us unstaged and walking groups of bitmap words, 50 us so;
+// 41 M entries in 57,696 panels 434 -> 250 us (0.76 GB).
+template <int G>
 __global__ __launch_bounds__(kPanelThreads) void k_panel_build(
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind,
     const float* __restrict__ vals, int64_t M, int64_t K, uint32_t words_cap, uint32_t nb_cap,
-    const uint32_t* __restrict__ panel_ptr, uint32_t* __restrict__ brick_cols,
+    uint32_t stage_cap, const uint32_t* __restrict__ panel_ptr, uint32_t* __restrict__ brick_cols,
     uint64_t* __restrict__ brick_mask, uint32_t* __restrict__ brick_valptr,
     float* __restrict__ packed, uint32_t* __restrict__ src, uint8_t* __restrict__ col_seen) {
   extern __shared__ unsigned long long lds64[];
   __shared__ int32_t rp[kPanel + 1];
   unsigned long long* pat = lds64;                                   // [nb_cap]
   uint32_t* bm = reinterpret_cast<uint32_t*>(lds64 + nb_cap);        // [words_cap]
-  uint32_t* pre = bm + words_cap;     // [words_cap / 8 + 1]; pre[g] = set bits in words [0, 8g)
-  uint32_t* vptr = pre + words_cap / kGroupWords + 1;                // [nb_cap]
+  uint32_t* pre = bm + words_cap;     // [words_cap / G + 1]; pre[g] = set bits in words [0, G*g)
+  uint32_t* vptr = pre + words_cap / G + 1;                          // [nb_cap]
+  uint32_t* key = vptr + nb_cap;                                     // [stage_cap]
+  uint16_t* at = reinterpret_cast<uint16_t*>(key + stage_cap);       // [stage_cap]
   const int64_t p = blockIdx.x;
   const uint32_t pp = panel_ptr[p];
   const uint32_t nb = panel_ptr[p + 1] - pp;
@@ -895,17 +911,45 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_build(
   if (nb == 0) return;
   const uint32_t words = (uint32_t)(x.cmax - x.cmin) / 32u + 1u;
   if (words > words_cap || nb > nb_cap) return;   // (cannot happen: both caps are maxima)
-  for (uint32_t k = threadIdx.x; k < nb; k += kPanelThreads) pat[k] = 0;
-  panel_bitmap(colind, x, rp, K, words, bm, nullptr);
+  const uint32_t n = (uint32_t)(x.e1 - x.e0);
+  const bool staged = n <= stage_cap;
+  // row starts as scalars, relative to the panel's first entry
+  uint32_t row_start[kPanel];
+#pragma unroll
+  for (int r = 0; r < kPanel; ++r)
+    row_start[r] = __builtin_amdgcn_readfirstlane((uint32_t)(rp[r] - rp[0]));
+  auto row_of = [&](uint32_t i) {   // last row that starts at or before entry i
+    uint32_t r = 0;
+#pragma unroll
+    for (int k = 1; k < kPanel; ++k) r += i >= row_start[k] ? 1u : 0u;
+    return r;
+  };
 
-  // coarse rank table: exclusive scan over groups of 8 words, a contiguous run per lane
-  const uint32_t ngroups = (words + kGroupWords - 1) / kGroupWords;
+  for (uint32_t k = threadIdx.x; k < nb; k += kPanelThreads) pat[k] = 0;
+  for (uint32_t w = threadIdx.x; w < words; w += kPanelThreads) bm[w] = 0;
+  __syncthreads();
+  for (uint32_t i0 = threadIdx.x; i0 < n; i0 += 4 * kPanelThreads) {
+    uint32_t d[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)   // past the end: the last entry again
+      d[u] = (uint32_t)(colind[x.e0 + min(i0 + u * kPanelThreads, n - 1)] - x.cmin);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const uint32_t i = i0 + u * kPanelThreads;
+      if (i < n && d[u] / 32u < words) atomicOr(&bm[d[u] >> 5], 1u << (d[u] & 31));
+      if (i < n && staged) key[i] = d[u];
+    }
+  }
+  __syncthreads();
+
+  // rank table: exclusive scan over groups of G words, a contiguous run per lane
+  const uint32_t ngroups = (words + G - 1) / G;
   const uint32_t per = (ngroups + kPanelThreads - 1) / kPanelThreads;
   const uint32_t g0 = min(threadIdx.x * per, ngroups), g1 = min(g0 + per, ngroups);
   uint32_t mine = 0;
   for (uint32_t g = g0; g < g1; ++g) {
     uint32_t s = 0;
-    for (uint32_t w = g * kGroupWords; w < min((g + 1) * kGroupWords, words); ++w) s += __popc(bm[w]);
+    for (uint32_t w = g * G; w < min((g + 1) * G, words); ++w) s += __popc(bm[w]);
     pre[g] = s;
     mine += s;
   }
@@ -917,38 +961,48 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_build(
     run += s;
   }
   __syncthreads();
-  auto bits_before_word = [&](uint32_t w) {
-    uint32_t r = pre[w / kGroupWords];
-    for (uint32_t v = w & ~(uint32_t)(kGroupWords - 1); v < w; ++v) r += __popc(bm[v]);
+  auto rank_of = [&](uint32_t d) {   // set bits before bit d
+    const uint32_t w = d >> 5;
+    uint32_t r = pre[w / G] + __popc(bm[w] & ((1u << (d & 31)) - 1u));
+    if constexpr (G > 1)
+      for (uint32_t v = w & ~(uint32_t)(G - 1); v < w; ++v) r += __popc(bm[v]);
     return r;
   };
 
-  // a2: active columns in ascending order, four per brick, the tail padded
-  for (uint32_t w = threadIdx.x; w < words; w += kPanelThreads) {
-    uint32_t bits = bm[w];
+  // a2: active columns in ascending order, four per brick, the tail padded; a lane takes the
+  // columns of eight bits at a time
+  for (uint32_t q = threadIdx.x; q < 4 * words; q += kPanelThreads) {
+    uint32_t bits = (bm[q >> 2] >> (8 * (q & 3))) & 0xFFu;
     if (!bits) continue;
-    uint32_t r = bits_before_word(w);
-    while (bits) {
-      const uint32_t col = (uint32_t)x.cmin + 32u * w + (uint32_t)__builtin_ctz(bits);
+    uint32_t r = rank_of(8 * q);
+    do {
+      const uint32_t col = (uint32_t)x.cmin + 8u * q + (uint32_t)__builtin_ctz(bits);
       brick_cols[(int64_t)pp * kBrickK + r++] = col;
       col_seen[col] = 1;
       bits &= bits - 1;
-    }
+    } while (bits);
   }
   for (uint32_t k = ncols + threadIdx.x; k < nb * kBrickK; k += kPanelThreads)
     brick_cols[(int64_t)pp * kBrickK + k] = kPadCol;
 
-  // a3: pattern bits, accumulated in LDS
-  for (int64_t e = x.e0 + threadIdx.x; e < x.e1; e += kPanelThreads) {
-    const uint32_t d = (uint32_t)(colind[e] - x.cmin);
-    const uint32_t rank = bits_before_word(d >> 5) + __popc(bm[d >> 5] & ((1u << (d & 31)) - 1u));
-    const uint32_t bit = (uint32_t)row_in_panel(rp, e) * kBrickK + rank % kBrickK;
-    if (rank / kBrickK < nb) atomicOr(&pat[rank / kBrickK], 1ull << bit);
+  // a3: pattern bits, accumulated in LDS; a staged entry keeps rank and row, 16 * rank + row
+  auto entry_key = [&](uint32_t i, uint32_t d) {
+    return min(rank_of(d), nb * kBrickK - 1) * kPanel + row_of(i);
+  };
+  auto unstaged_key = [&](uint32_t i) {
+    return entry_key(i, (uint32_t)(colind[x.e0 + i] - x.cmin));
+  };
+  auto brick_of = [](uint32_t k) { return k / (kPanel * kBrickK); };
+  auto bit_of = [](uint32_t k) { return k % kPanel * kBrickK + k / kPanel % kBrickK; };
+  for (uint32_t i = threadIdx.x; i < n; i += kPanelThreads) {
+    const uint32_t k = staged ? entry_key(i, key[i]) : unstaged_key(i);
+    if (staged) key[i] = k;
+    atomicOr(&pat[brick_of(k)], 1ull << bit_of(k));
   }
   __syncthreads();
 
   // a4: value offsets = entries before the panel + popcounts of the panel's earlier bricks
-  uint32_t carry = (uint32_t)x.e0;
+  uint32_t carry = 0;
   for (uint32_t base = 0; base < nb; base += kPanelThreads) {
     const uint32_t k = base + threadIdx.x;
     uint32_t c = 0;
@@ -961,20 +1015,44 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_build(
     const uint32_t ex = wave_exclusive(c, &total);
     if (k < nb) {
       vptr[k] = carry + ex;
-      brick_valptr[pp + k] = carry + ex;
+      brick_valptr[pp + k] = (uint32_t)x.e0 + carry + ex;
     }
     carry += total;
   }
   __syncthreads();
-  for (int64_t e = x.e0 + threadIdx.x; e < x.e1; e += kPanelThreads) {
-    const uint32_t d = (uint32_t)(colind[e] - x.cmin);
-    const uint32_t rank = bits_before_word(d >> 5) + __popc(bm[d >> 5] & ((1u << (d & 31)) - 1u));
-    const uint32_t bit = (uint32_t)row_in_panel(rp, e) * kBrickK + rank % kBrickK;
-    const uint32_t k = min(rank / kBrickK, nb - 1);
-    const uint32_t pos = vptr[k] + (uint32_t)__popcll(pat[k] & ((1ull << bit) - 1ull));
-    if (pos < (uint32_t)x.e1) {   // (always, for a census and a build that agree)
-      packed[pos] = vals[e];
-      src[pos] = (uint32_t)e;
+  auto place_of = [&](uint32_t k) {   // inside the panel's values
+    return vptr[brick_of(k)] + (uint32_t)__popcll(pat[brick_of(k)] & ((1ull << bit_of(k)) - 1ull));
+  };
+  if (staged) {
+    for (uint32_t i = threadIdx.x; i < n; i += kPanelThreads) {
+      const uint32_t pos = place_of(key[i]);
+      if (pos < n) at[pos] = (uint16_t)i;   // (always, for a census and a build that agree)
+    }
+    __syncthreads();
+    for (uint32_t i0 = threadIdx.x; i0 < n; i0 += 4 * kPanelThreads) {
+      uint32_t from[4];
+      float v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        from[u] = min((uint32_t)at[min(i0 + u * kPanelThreads, n - 1)], n - 1);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = vals[x.e0 + from[u]];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const uint32_t i = i0 + u * kPanelThreads;
+        if (i < n) {
+          packed[x.e0 + i] = v[u];
+          src[x.e0 + i] = (uint32_t)x.e0 + from[u];
+        }
+      }
+    }
+  } else {
+    for (uint32_t i = threadIdx.x; i < n; i += kPanelThreads) {
+      const uint32_t pos = place_of(unstaged_key(i));
+      if (pos < n) {
+        packed[x.e0 + pos] = vals[x.e0 + i];
+        src[x.e0 + pos] = (uint32_t)x.e0 + i;
+      }
     }
   }
 }
@@ -1148,7 +1226,7 @@ uint32_t panel_sort_keys(uint32_t max_nnz) {
   return n >= max_nnz ? n : 0;
 }
 static size_t panel_sort_build_lds(uint32_t n_cap, uint32_t nb_cap) {
-  return (size_t)n_cap * 8 + (size_t)nb_cap * 12;
+  return (size_t)n_cap * 10 + (size_t)nb_cap * 12;
 }
 bool panel_sort_build_fits(uint32_t n_cap, uint32_t nb_cap) {
   return n_cap != 0 && panel_sort_build_lds(n_cap, nb_cap) <= kPanelMaxLds;
@@ -1203,12 +1281,14 @@ uint32_t panel_bitmap_words(uint32_t span) {
   return (uint64_t)words * 32 >= span ? words : 0;
 }
 
-// LDS bytes of k_panel_build for a bitmap of words_cap words and panels of up to nb_cap bricks
-static size_t panel_build_lds(uint32_t words_cap, uint32_t nb_cap) {
-  return (size_t)nb_cap * 8 + ((size_t)words_cap + words_cap / kGroupWords + 1 + nb_cap) * 4;
+// LDS bytes of k_panel_build for a bitmap of words_cap words, panels of up to nb_cap bricks, rank
+// table entries every `group` words and up to stage_cap staged entries
+static size_t panel_build_lds(uint32_t words_cap, uint32_t nb_cap, uint32_t group, uint32_t stage_cap) {
+  return (size_t)nb_cap * 8 + ((size_t)words_cap + words_cap / group + 1 + nb_cap) * 4 +
+         (size_t)stage_cap * 6;
 }
 bool panel_build_fits(uint32_t words_cap, uint32_t nb_cap) {
-  return words_cap != 0 && panel_build_lds(words_cap, nb_cap) <= kPanelMaxLds;
+  return words_cap != 0 && panel_build_lds(words_cap, nb_cap, kGroupWords, 0) <= kPanelMaxLds;
 }
 
 hipError_t launch_panel_census(const int32_t* rowptr, const int32_t* colind, int64_t M, int64_t K,
@@ -1228,19 +1308,33 @@ hipError_t launch_panel_census(const int32_t* rowptr, const int32_t* colind, int
 
 hipError_t launch_panel_build(const int32_t* rowptr, const int32_t* colind, const float* vals,
                               int64_t M, int64_t K, int64_t P, uint32_t words_cap, uint32_t nb_cap,
-                              const uint32_t* panel_ptr, uint32_t* brick_cols, uint64_t* brick_mask,
-                              uint32_t* brick_valptr, float* packed, uint32_t* src,
-                              uint8_t* col_seen, hipStream_t s) {
+                              uint32_t max_nnz, const uint32_t* panel_ptr, uint32_t* brick_cols,
+                              uint64_t* brick_mask, uint32_t* brick_valptr, float* packed,
+                              uint32_t* src, uint8_t* col_seen, hipStream_t s) {
   if (P == 0) return hipSuccess;
-  const size_t lds = panel_build_lds(words_cap, nb_cap);
+  // A rank per word of the bitmap while that is short (no walk through a group of words for every
+  // entry); staging for panels of up to kPanelStageMax entries, where LDS has room for it.
+  const bool fine = words_cap <= kPanelFineWords;
+  const uint32_t group = fine ? 1 : kGroupWords;
+  uint32_t stage_cap = (std::min(max_nnz, kPanelStageMax) + 1) & ~1u;
+  if (panel_build_lds(words_cap, nb_cap, group, stage_cap) > kPanelMaxLds) stage_cap = 0;
+  const size_t lds = panel_build_lds(words_cap, nb_cap, group, stage_cap);
+  const void* fn = fine ? reinterpret_cast<const void*>(k_panel_build<1>)
+                        : reinterpret_cast<const void*>(k_panel_build<kGroupWords>);
   if (lds > 48 * 1024) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_panel_build),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    const hipError_t e =
+        hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(k_panel_build, dim3((unsigned)P), dim3(kPanelThreads), lds, s, rowptr, colind,
-                     vals, M, K, words_cap, nb_cap, panel_ptr, brick_cols, brick_mask, brick_valptr,
-                     packed, src, col_seen);
+  const dim3 grid((unsigned)P), block(kPanelThreads);
+  if (fine)
+    hipLaunchKernelGGL(k_panel_build<1>, grid, block, lds, s, rowptr, colind, vals, M, K, words_cap,
+                       nb_cap, stage_cap, panel_ptr, brick_cols, brick_mask, brick_valptr, packed,
+                       src, col_seen);
+  else
+    hipLaunchKernelGGL(k_panel_build<kGroupWords>, grid, block, lds, s, rowptr, colind, vals, M, K,
+                       words_cap, nb_cap, stage_cap, panel_ptr, brick_cols, brick_mask, brick_valptr,
+                       packed, src, col_seen);
   return hipGetLastError();
 }
 

@@ -117,9 +117,9 @@ hipError_t launch_panel_census(const int32_t* rowptr, const int32_t* colind, int
 bool panel_build_fits(uint32_t words_cap, uint32_t nb_cap);   // LDS of launch_panel_build
 hipError_t launch_panel_build(const int32_t* rowptr, const int32_t* colind, const float* vals,
                               int64_t M, int64_t K, int64_t P, uint32_t words_cap, uint32_t nb_cap,
-                              const uint32_t* panel_ptr, uint32_t* brick_cols, uint64_t* brick_mask,
-                              uint32_t* brick_valptr, float* packed, uint32_t* src,
-                              uint8_t* col_seen, hipStream_t s);
+                              uint32_t max_nnz, const uint32_t* panel_ptr, uint32_t* brick_cols,
+                              uint64_t* brick_mask, uint32_t* brick_valptr, float* packed,
+                              uint32_t* src, uint8_t* col_seen, hipStream_t s);
 
 // exclusive scans; out has n+1 entries (out[n] = total); tmp holds block sums
 size_t scan_tmp_elems(int64_t n);
