@@ -47,6 +47,9 @@ struct HostList {
   uint64_t id = 0;                          // unique per list (tags the contents of the static scratch)
   int64_t N = 0;
   spmm_worklist_info_t info{};
+  // Every panel to the brick kernel, whole and in order: item i is panel i, the lists below are
+  // empty and the kernels read panel_ptr instead.
+  bool direct = false;
   std::vector<spmm_work_item_t> h_items;   // exported form
   std::vector<WorkItem> items;             // device form
   std::vector<MergeItem> merges;
@@ -96,7 +99,8 @@ struct spmm_plan {
   uint32_t* long_rows = nullptr;  // rows with more than long_row_threshold() entries
   int64_t n_long_rows = 0;
   // host copies used by the work-list builder and the synergy model
-  std::vector<uint32_t> h_panel_ptr;
+  std::vector<uint32_t> h_panel_ptr;      // empty until a list needs it (need_panel_ptr)
+  int64_t max_bricks = 0, n_blocks = 0;   // of a panel; of the matrix (Eq. 6-7's unit)
   std::vector<uint8_t> h_panel_class;     // filled with the CSR arrays, for the routes that ask
   unsigned long long h_counters[kNumCounters] = {};
   int64_t n_active_cols = 0;
@@ -175,6 +179,11 @@ int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 constexpr int64_t kMinBlocksPerPart = 4;   // Eq. 6-7 splits never go below this (16 bricks)
 
+// Eq. 7's waves of work
+int64_t waves_of(int64_t work_items, int64_t capacity) {
+  return std::max<int64_t>(1, ceil_div(work_items, std::max<int64_t>(1, capacity)));
+}
+
 // Eq. 6-7 in integers: partition_ratio_p = blocks_p * P / (total_blocks * waves).
 // SPMM_SPLIT_EQ7_FROM2 (the default): one part while the ratio is below 2, else the ratio
 // rounded to the nearest integer, halves up.  SPMM_SPLIT_EQ7_NEAREST: the ratio rounded to
@@ -183,7 +192,7 @@ void partition_counts(int64_t P, const uint32_t* nbricks, int64_t work_items, in
                       int policy, uint32_t* parts, int64_t* waves_out) {
   int64_t total = 0;
   for (int64_t p = 0; p < P; ++p) total += ceil_div(nbricks[p], kBrickK);
-  const int64_t waves = std::max<int64_t>(1, ceil_div(work_items, std::max<int64_t>(1, capacity)));
+  const int64_t waves = waves_of(work_items, capacity);
   for (int64_t p = 0; p < P; ++p) {
     const int64_t blocks = ceil_div(nbricks[p], kBrickK);
     int64_t q = 1;
@@ -197,6 +206,31 @@ void partition_counts(int64_t P, const uint32_t* nbricks, int64_t work_items, in
     parts[p] = (uint32_t)std::max<int64_t>(1, q);
   }
   if (waves_out) *waves_out = waves;
+}
+
+// Whether the plan's split policy leaves every panel whole: the number of parts never falls
+// with the number of blocks, so the largest panel decides.
+bool splits_nothing(const spmm_plan_t* pl, int64_t waves) {
+  const int64_t blocks = ceil_div(pl->max_bricks, kBrickK);
+  if (pl->split > 1) return blocks < pl->split;
+  if (pl->split == SPMM_SPLIT_NEVER || blocks < 2 * kMinBlocksPerPart) return true;
+  const __int128 num = (__int128)blocks * pl->P, den = (__int128)pl->n_blocks * waves;
+  return pl->split == SPMM_SPLIT_EQ7_FROM2 ? num < 2 * den : 2 * num < 3 * den;
+}
+
+// The host's copy of panel_ptr.  spmm_plan fetches it where the default policy may split a panel,
+// the setters (which wait for the device anyway) wherever a list may be built after them; so no
+// call that only enqueues has to.
+int need_panel_ptr(spmm_plan_t* pl) {
+  int status = SPMM_OK;
+  if (!pl->h_panel_ptr.empty()) return SPMM_OK;
+  try { pl->h_panel_ptr.resize((size_t)pl->P + 1); }
+  catch (const std::bad_alloc&) { return fail(SPMM_ENOMEM, "host allocation failed"); }
+  HIP_TRY(hipMemcpy(pl->h_panel_ptr.data(), pl->panel_ptr, (size_t)(pl->P + 1) * sizeof(uint32_t),
+                    hipMemcpyDeviceToHost));
+done:
+  if (status != SPMM_OK) pl->h_panel_ptr.clear();
+  return status;
 }
 
 // Routing and load balancing for N (host only, no device memory).  Cached in the plan.
@@ -218,6 +252,29 @@ int build_host_list(spmm_plan_t* pl, int64_t N, const HostList** out) {
     hl->info.n_tile = tile;
     hl->info.n_tiles = (int32_t)ceil_div(std::max<int64_t>(N, 1), tile);
     hl->info.num_cus = pl->num_cus;
+
+    const int resident =
+        bf16 ? bf16_resident_waves_per_cu(std::max<int64_t>(N, 1),
+                                          pl->precision == SPMM_PRECISION_BF16X3 ? 2 : 3)
+             : mfma_resident_waves_per_cu(std::max<int64_t>(N, 1), pl->K);
+    hl->info.resident_waves_per_cu = resident;
+
+    if ((pl->route == SPMM_ROUTE_AUTO || pl->route == SPMM_ROUTE_MFMA) && pl->order == SPMM_ORDER_PANEL) {
+      const bool eq7 = pl->split == SPMM_SPLIT_EQ7_FROM2 || pl->split == SPMM_SPLIT_EQ7_NEAREST;
+      const int64_t waves = eq7 && pl->P > 0 ? waves_of(pl->P * hl->info.n_tiles, (int64_t)pl->num_cus * resident) : 1;
+      if (splits_nothing(pl, waves)) {
+        hl->direct = true;
+        hl->info.num_waves = waves;
+        hl->info.n_mfma_items = pl->P;
+        pl->host_lists[N] = hl;
+        *out = hl;
+        return SPMM_OK;
+      }
+    }
+    if (const int status = need_panel_ptr(pl)) {
+      delete hl;
+      return status;
+    }
 
     // routing: which panels go to the MFMA kernel
     std::vector<uint32_t> mfma_panels;
@@ -246,11 +303,6 @@ int build_host_list(spmm_plan_t* pl, int64_t N, const HostList** out) {
     const int64_t nm = (int64_t)mfma_panels.size();
     std::vector<uint32_t> parts((size_t)nm, 1u);
     int64_t waves = 1;
-    const int resident =
-        bf16 ? bf16_resident_waves_per_cu(std::max<int64_t>(N, 1),
-                                          pl->precision == SPMM_PRECISION_BF16X3 ? 2 : 3)
-             : mfma_resident_waves_per_cu(std::max<int64_t>(N, 1), pl->K);
-    hl->info.resident_waves_per_cu = resident;
     if (nm > 0) {
       if (pl->split == SPMM_SPLIT_EQ7_FROM2 || pl->split == SPMM_SPLIT_EQ7_NEAREST) {
         partition_counts(nm, nbricks.data(), nm * hl->info.n_tiles,
@@ -325,7 +377,7 @@ int build_host_list(spmm_plan_t* pl, int64_t N, const HostList** out) {
   return SPMM_OK;
 }
 
-// Device copy of the work list for N (allocates; synchronises the stream once).
+// Device copy of the work list for N (where there is a list: allocates, synchronises the stream once).
 int build_worklist(spmm_plan_t* pl, int64_t N, hipStream_t stream, WorkList** out) {
   auto found = pl->lists.find(N);
   if (found != pl->lists.end()) {
@@ -338,9 +390,9 @@ int build_worklist(spmm_plan_t* pl, int64_t N, hipStream_t stream, WorkList** ou
   WorkList* wl = new (std::nothrow) WorkList();
   if (!wl) return fail(SPMM_ENOMEM, "host allocation failed");
   wl->host = hl;
-  HIP_TRY(dev_alloc(&wl->d_items, (int64_t)hl->items.size()));
-  HIP_TRY(dev_alloc(&wl->d_valu_panels, (int64_t)hl->valu_panels.size()));
-  HIP_TRY(dev_alloc(&wl->d_merge, (int64_t)hl->merges.size()));
+  if (!hl->direct) HIP_TRY(dev_alloc(&wl->d_items, (int64_t)hl->items.size()));
+  if (!hl->valu_panels.empty()) HIP_TRY(dev_alloc(&wl->d_valu_panels, (int64_t)hl->valu_panels.size()));
+  if (!hl->merges.empty()) HIP_TRY(dev_alloc(&wl->d_merge, (int64_t)hl->merges.size()));
   if (hl->n_slots > 0)
     HIP_TRY(dev_alloc(&wl->d_partial, hl->n_slots * kPanel * std::max<int64_t>(N, 1)));
   if (!hl->items.empty())
@@ -353,7 +405,7 @@ int build_worklist(spmm_plan_t* pl, int64_t N, hipStream_t stream, WorkList** ou
   if (!hl->merges.empty())
     HIP_TRY(hipMemcpyAsync(wl->d_merge, hl->merges.data(), hl->merges.size() * sizeof(MergeItem),
                            hipMemcpyHostToDevice, stream));
-  HIP_TRY(hipStreamSynchronize(stream));
+  if (!hl->direct) HIP_TRY(hipStreamSynchronize(stream));
   try {
     pl->lists[N] = wl;
   } catch (const std::bad_alloc&) {
@@ -373,6 +425,7 @@ done:
 // two copies at plan time and a third of an update's stores.  Called with the device idle.
 int enable_csr(spmm_plan_t* pl) {
   int status = SPMM_OK;
+  if ((status = need_panel_ptr(pl)) != SPMM_OK) return status;
   const int64_t cap = pl->nnz / long_row_threshold() + 1;
   unsigned long long* counter;
   unsigned long long h_count = 0;
@@ -386,7 +439,7 @@ int enable_csr(spmm_plan_t* pl) {
   pl->csr_vals = a.take<float>(pl->nnz);
   pl->long_rows = a.take<uint32_t>(cap);
   counter = a.take<unsigned long long>(1);
-  HIP_TRY(launch_restore_csr(BrickFormat{pl->brick_cols, pl->brick_mask, pl->brick_valptr, pl->vals},
+  HIP_TRY(launch_restore_csr(BrickFormat{pl->panel_ptr, pl->brick_cols, pl->brick_mask, pl->brick_valptr, pl->vals},
                              pl->src, pl->nb, pl->colind, pl->csr_vals, nullptr));
   HIP_TRY(launch_fill_u64(reinterpret_cast<uint64_t*>(counter), 1, 0, nullptr));
   HIP_TRY(launch_find_long_rows(pl->rowptr, pl->M, long_row_threshold(), pl->long_rows, counter,
@@ -748,14 +801,18 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
                             ctl->counters, s));
 
   // ---- host copies for the work-list builder and the model
-  try {
-    pl->h_panel_ptr.resize((size_t)P + 1);
-  } catch (const std::bad_alloc&) {
-    status = fail(SPMM_ENOMEM, "host allocation failed");
-    goto done;
+  pl->max_bricks = h_maxnb;
+  pl->n_blocks = (int64_t)h_ctl.n_blocks;
+  if (!splits_nothing(pl, 1)) {   // for some N the default policy may split a panel
+    try {
+      pl->h_panel_ptr.resize((size_t)P + 1);
+    } catch (const std::bad_alloc&) {
+      status = fail(SPMM_ENOMEM, "host allocation failed");
+      goto done;
+    }
+    HIP_TRY(hipMemcpyAsync(pl->h_panel_ptr.data(), pl->panel_ptr,
+                           (size_t)(P + 1) * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
   }
-  HIP_TRY(hipMemcpyAsync(pl->h_panel_ptr.data(), pl->panel_ptr, (size_t)(P + 1) * sizeof(uint32_t),
-                         hipMemcpyDeviceToHost, s));
   HIP_TRY(hipMemcpyAsync(&h_ctl, ctl, sizeof(PlanControl), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
   memcpy(pl->h_counters, h_ctl.counters, sizeof(pl->h_counters));
@@ -826,7 +883,7 @@ int launch_product(const spmm_plan_t* pl, const HostList* hl, const WorkItem* d_
                    const uint32_t* d_valu_panels, const MergeItem* d_merge, float* d_partial,
                    const float* B, int64_t N, float* C, hipStream_t s) {
   int status = SPMM_OK;
-  const BrickFormat f{pl->brick_cols, pl->brick_mask, pl->brick_valptr, pl->vals};
+  const BrickFormat f{pl->panel_ptr, pl->brick_cols, pl->brick_mask, pl->brick_valptr, pl->vals};
   if (uses_tm32(pl, B, N, C)) {
     // 32-row panels: one wavefront per super-panel and column tile, no work list
     HIP_TRY(launch_spmm_tm32(pl->tm32.sp_ptr, pl->tm32.bc_cols, pl->tm32.meta, pl->tm32.vals,
@@ -879,7 +936,8 @@ int spmm_exec_noalloc(spmm_plan_t* pl, const float* B, int64_t N, float* C, void
   status = build_host_list(pl, N, &hl);   // host arithmetic only; cached per N
   if (status != SPMM_OK) return status;
 
-  const size_t items_b = pad256(hl->items.size() * sizeof(WorkItem));
+  // (what a list takes, also where none is needed: the same sizes are refused either way)
+  const size_t items_b = pad256((size_t)hl->info.n_mfma_items * sizeof(WorkItem));
   const size_t valu_b = pad256(hl->valu_panels.size() * sizeof(uint32_t));
   const size_t merge_b = pad256(hl->merges.size() * sizeof(MergeItem));
   const size_t partial_b = (size_t)hl->n_slots * kPanel * (size_t)N * sizeof(float);
@@ -889,6 +947,8 @@ int spmm_exec_noalloc(spmm_plan_t* pl, const float* B, int64_t N, float* C, void
                 "exceed the static scratch of %zu B; use spmm_exec",
                 items_b + valu_b + merge_b, partial_b, kScratchBytes);
 
+  if (hl->direct)   // nothing to keep in the scratch
+    return launch_product(pl, hl, nullptr, nullptr, nullptr, nullptr, B, N, C, s);
   {
     std::lock_guard<std::mutex> lock(g_scratch_mutex);
     ScratchState* stp = nullptr;
@@ -993,6 +1053,7 @@ int spmm_plan_set_route(spmm_plan_t* pl, int route) {
     const int status = enable_csr(pl);
     if (status != SPMM_OK) return status;
   }
+  if (const int status = need_panel_ptr(pl)) return status;
   pl->csr_on = csr;   // (updates write the CSR copy only while a route reads it)
   pl->route = route;
   pl->drop_lists();
@@ -1003,6 +1064,7 @@ int spmm_plan_set_split(spmm_plan_t* pl, int parts) {
   if (!pl) return fail(SPMM_EINVAL, "plan is NULL");
   if (parts < SPMM_SPLIT_EQ7_NEAREST) return fail(SPMM_EINVAL, "unknown split policy");
   if (hipDeviceSynchronize() != hipSuccess) return fail(SPMM_EHIP, "hipDeviceSynchronize failed");
+  if (const int status = need_panel_ptr(pl)) return status;
   pl->split = parts;
   pl->drop_lists();
   return SPMM_OK;
@@ -1075,6 +1137,7 @@ int spmm_plan_set_order(spmm_plan_t* pl, int order) {
   if (order != SPMM_ORDER_PANEL && order != SPMM_ORDER_HEAVY_FIRST)
     return fail(SPMM_EINVAL, "unknown order");
   if (hipDeviceSynchronize() != hipSuccess) return fail(SPMM_EHIP, "hipDeviceSynchronize failed");
+  if (const int status = need_panel_ptr(pl)) return status;
   pl->order = order;
   pl->drop_lists();
   return SPMM_OK;
@@ -1100,6 +1163,11 @@ int spmm_plan_worklist(spmm_plan_t* pl, int64_t N, spmm_worklist_info_t* info,
   const int status = build_host_list(pl, N, &hl);
   if (status != SPMM_OK) return status;
   *info = hl->info;
+  if (items && hl->direct && pl->P > 0) {
+    if (const int st = need_panel_ptr(pl)) return st;
+    for (int64_t p = 0; p < pl->P; ++p)
+      items[p] = spmm_work_item_t{(uint32_t)p, pl->h_panel_ptr[p], pl->h_panel_ptr[p + 1], 0, 1};
+  }
   if (items && !hl->h_items.empty())
     memcpy(items, hl->h_items.data(), hl->h_items.size() * sizeof(spmm_work_item_t));
   if (valu_panels && !hl->valu_panels.empty())

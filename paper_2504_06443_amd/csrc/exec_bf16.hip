@@ -70,9 +70,9 @@ __device__ inline void split_pair(float x0, float x1, uint32_t (&planes)[NP]) {
 
 template <int T, int NP>
 __global__ __launch_bounds__(64 * kWavesPerBlock) __attribute__((amdgpu_waves_per_eu(2))) void k_spmm_bf16(
-    const uint32_t* __restrict__ brick_cols, const uint64_t* __restrict__ brick_mask,
-    const uint32_t* __restrict__ brick_valptr, const float* __restrict__ vals,
-    const WorkItem* __restrict__ items, int64_t n_items, const float* __restrict__ B,
+    const uint32_t* __restrict__ panel_ptr, const uint32_t* __restrict__ brick_cols,
+    const uint64_t* __restrict__ brick_mask, const uint32_t* __restrict__ brick_valptr,
+    const float* __restrict__ vals, const WorkItem* __restrict__ items, int64_t n_items, const float* __restrict__ B,
     float* __restrict__ C, float* __restrict__ partial, int64_t M, int64_t N, uint32_t k_last,
     uint32_t /* reserved */) {
   constexpr int V = T < 4 ? T : 4;
@@ -86,7 +86,7 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) __attribute__((amdgpu_waves_pe
   const uint32_t vblock = xcd_contiguous_block();
   const int64_t item_id = (int64_t)vblock * kWavesPerBlock + wave;
   if (item_id >= n_items) return;  // whole wavefront leaves together
-  const WorkItem it = items[item_id];
+  const WorkItem it = work_item(items, panel_ptr, item_id);
   const uint32_t panel = __builtin_amdgcn_readfirstlane(it.panel);
   const uint32_t b_begin = __builtin_amdgcn_readfirstlane(it.brick_begin);
   const uint32_t b_end = __builtin_amdgcn_readfirstlane(it.brick_end);
@@ -343,8 +343,8 @@ hipError_t launch_spmm_bf16(const BrickFormat& f, const WorkItem* items, int64_t
   const dim3 grid(gx, (unsigned)((N + tile - 1) / tile)), block(64 * kWavesPerBlock);
   const uint32_t k_last = (uint32_t)(K - 1);
 #define SPMM_LAUNCH_BF16(TT, PP)                                                            \
-  hipLaunchKernelGGL((k_spmm_bf16<TT, PP>), grid, block, 0, s, f.brick_cols, f.brick_mask,  \
-                     f.brick_valptr, f.vals, items, n_items, B, C, partial, M, N, k_last, zero_idx)
+  hipLaunchKernelGGL((k_spmm_bf16<TT, PP>), grid, block, 0, s, f.panel_ptr, f.brick_cols,   \
+                     f.brick_mask, f.brick_valptr, f.vals, items, n_items, B, C, partial, M, N, k_last, zero_idx)
   if (planes == 2) {
     switch (tile) {
       case 16: SPMM_LAUNCH_BF16(1, 2); break;

@@ -81,7 +81,7 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void k_spmm_mfma(
   const uint32_t vblock = xcd_contiguous_block();   // contiguous range of work items per XCD
   const int64_t item_id = (int64_t)vblock * kWavesPerBlock + (threadIdx.x >> 6);
   if (item_id >= n_items) return;  // whole wavefront leaves together
-  const WorkItem it = items[item_id];
+  const WorkItem it = work_item(items, f.panel_ptr, item_id);
   const uint32_t panel = __builtin_amdgcn_readfirstlane(it.panel);
   const uint32_t b_begin = __builtin_amdgcn_readfirstlane(it.brick_begin);
   const uint32_t b_end = __builtin_amdgcn_readfirstlane(it.brick_end);
@@ -229,10 +229,11 @@ constexpr int kFastChunk = 8;
 
 template <int T, bool FULL>
 __global__ __launch_bounds__(64 * kWavesPerBlock) void k_spmm_mfma_fast(
-    const uint32_t* __restrict__ brick_cols, const uint64_t* __restrict__ brick_mask,
-    const uint32_t* __restrict__ brick_valptr, const float* __restrict__ vals,
-    const WorkItem* __restrict__ items, int64_t n_items, const float* __restrict__ B,
-    float* __restrict__ C, float* __restrict__ partial, int64_t M, int64_t N, uint32_t k_last) {
+    const uint32_t* __restrict__ panel_ptr, const uint32_t* __restrict__ brick_cols,
+    const uint64_t* __restrict__ brick_mask, const uint32_t* __restrict__ brick_valptr,
+    const float* __restrict__ vals, const WorkItem* __restrict__ items, int64_t n_items,
+    const float* __restrict__ B, float* __restrict__ C, float* __restrict__ partial, int64_t M,
+    int64_t N, uint32_t k_last) {
   // (the format arrays are separate __restrict__ parameters, not a struct, so that
   // the compiler knows they are read-only here and may use the scalar cache)
   constexpr int W0 = T < 4 ? T : 4, W1 = T - W0;   // columns of the lane's first, second vector
@@ -247,7 +248,7 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void k_spmm_mfma_fast(
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t item_id = (int64_t)vblock * kWavesPerBlock + wave;
   if (item_id >= n_items) return;  // whole wavefront leaves together
-  const WorkItem it = items[item_id];
+  const WorkItem it = work_item(items, panel_ptr, item_id);
   const uint32_t panel = it.panel;
   const uint32_t b_begin = it.brick_begin;
   const uint32_t b_end = it.brick_end;
@@ -768,8 +769,9 @@ hipError_t launch_spmm_mfma(const BrickFormat& f, const WorkItem* items, int64_t
     const dim3 grid(gx, (unsigned)((N + tile - 1) / tile)), block(64 * kWavesPerBlock);
     const uint32_t k_last = (uint32_t)(K - 1);
 #define SPMM_LAUNCH_FAST(TT, FF)                                                                \
-  hipLaunchKernelGGL((k_spmm_mfma_fast<TT, FF>), grid, block, 0, s, f.brick_cols, f.brick_mask, \
-                     f.brick_valptr, f.vals, items, n_items, B, C, partial, M, N, k_last)
+  hipLaunchKernelGGL((k_spmm_mfma_fast<TT, FF>), grid, block, 0, s, f.panel_ptr, f.brick_cols,  \
+                     f.brick_mask, f.brick_valptr, f.vals, items, n_items, B, C, partial, M, N, \
+                     k_last)
     switch (tile / 16) {
       case 1: SPMM_LAUNCH_FAST(1, false); break;
       case 2: SPMM_LAUNCH_FAST(2, false); break;

@@ -21,10 +21,11 @@ constexpr int kChunk = 8;    // bricks per decode chunk
 
 template <int W>
 __global__ __launch_bounds__(64 * W) void k_spmm_mfma_wide(
-    const uint32_t* __restrict__ brick_cols, const uint64_t* __restrict__ brick_mask,
-    const uint32_t* __restrict__ brick_valptr, const float* __restrict__ vals,
-    const WorkItem* __restrict__ items, int64_t n_items, const float* __restrict__ B,
-    float* __restrict__ C, float* __restrict__ partial, int64_t M, int64_t N, uint32_t k_last) {
+    const uint32_t* __restrict__ panel_ptr, const uint32_t* __restrict__ brick_cols,
+    const uint64_t* __restrict__ brick_mask, const uint32_t* __restrict__ brick_valptr,
+    const float* __restrict__ vals, const WorkItem* __restrict__ items, int64_t n_items,
+    const float* __restrict__ B, float* __restrict__ C, float* __restrict__ partial, int64_t M,
+    int64_t N, uint32_t k_last) {
   constexpr int T = 8, V = 4, NV = 2;
   constexpr int R = kStages;
   constexpr int CH = kChunk;
@@ -37,7 +38,7 @@ __global__ __launch_bounds__(64 * W) void k_spmm_mfma_wide(
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t item_id = xcd_contiguous_block();   // one work item per workgroup
   if (item_id >= n_items) return;                   // the whole workgroup leaves together
-  const WorkItem it = items[item_id];   // uniform index: through the scalar cache
+  const WorkItem it = work_item(items, panel_ptr, item_id);   // uniform index: through the scalar cache
   const uint32_t panel = it.panel;
   const uint32_t b_begin = it.brick_begin;
   const uint32_t b_end = it.brick_end;
@@ -204,11 +205,11 @@ hipError_t launch_spmm_mfma_wide(const BrickFormat& f, const WorkItem* items, in
   const dim3 grid(gx, (unsigned)(tiles / W));
   const uint32_t k_last = (uint32_t)(K - 1);
   if (W == 4)
-    hipLaunchKernelGGL(k_spmm_mfma_wide<4>, grid, dim3(256), 0, s, f.brick_cols, f.brick_mask,
-                       f.brick_valptr, f.vals, items, n_items, B, C, partial, M, N, k_last);
+    hipLaunchKernelGGL(k_spmm_mfma_wide<4>, grid, dim3(256), 0, s, f.panel_ptr, f.brick_cols,
+                       f.brick_mask, f.brick_valptr, f.vals, items, n_items, B, C, partial, M, N, k_last);
   else
-    hipLaunchKernelGGL(k_spmm_mfma_wide<2>, grid, dim3(128), 0, s, f.brick_cols, f.brick_mask,
-                       f.brick_valptr, f.vals, items, n_items, B, C, partial, M, N, k_last);
+    hipLaunchKernelGGL(k_spmm_mfma_wide<2>, grid, dim3(128), 0, s, f.panel_ptr, f.brick_cols,
+                       f.brick_mask, f.brick_valptr, f.vals, items, n_items, B, C, partial, M, N, k_last);
   return hipGetLastError();
 }
 

@@ -515,28 +515,38 @@ __global__ __launch_bounds__(kScanThreads) void k_panel_sums(const uint32_t* __r
                                                              int64_t P, int64_t run,
                                                              uint32_t* __restrict__ block_sums,
                                                              PlanControl* ctl) {
-  __shared__ unsigned long long s_cols;
+  __shared__ unsigned long long s_cols, s_blocks;
   __shared__ uint32_t s_max;
-  if (threadIdx.x == 0) { s_cols = 0; s_max = 0; }
+  if (threadIdx.x == 0) { s_cols = 0; s_blocks = 0; s_max = 0; }
   const int64_t p0 = min(((int64_t)blockIdx.x * kScanThreads + threadIdx.x) * run, P);
   const int64_t p1 = min(p0 + run, P);
   uint32_t bricks = 0, most = 0;
-  unsigned long long cols = 0;
+  unsigned long long cols = 0, blocks = 0;
   for (int64_t p = p0; p < p1; ++p) {
     const uint32_t n = ncols_p[p];
     bricks += (n + kBrickK - 1) / kBrickK;
+    blocks += ((n + kBrickK - 1) / kBrickK + kBrickK - 1) / kBrickK;
     cols += n;
     most = max(most, n);
   }
   uint32_t total;
   block_exclusive(bricks, &total);   // (its barriers also cover the zeroing above)
   cols = wave_sum(cols);
+  blocks = wave_sum(blocks);
   most = wave_max(most);
-  if (cols && (threadIdx.x & 63) == 0) { atomicAdd(&s_cols, cols); atomicMax(&s_max, most); }
+  if (cols && (threadIdx.x & 63) == 0) {
+    atomicAdd(&s_cols, cols);
+    atomicAdd(&s_blocks, blocks);
+    atomicMax(&s_max, most);
+  }
   __syncthreads();
   if (threadIdx.x == 0) {
     block_sums[blockIdx.x] = total;
-    if (s_cols) { atomicAdd(&ctl->n_active, s_cols); raise_to(&ctl->max_cols, s_max); }
+    if (s_cols) {
+      atomicAdd(&ctl->n_active, s_cols);
+      atomicAdd(&ctl->n_blocks, s_blocks);
+      raise_to(&ctl->max_cols, s_max);
+    }
   }
 }
 

@@ -37,6 +37,7 @@ struct PlanControl {        // device, zeroed when a plan begins; read back at i
   uint32_t nb;              // bricks
   uint32_t pad;
   unsigned long long n_active;   // active columns, summed over the panels
+  unsigned long long n_blocks;   // blocks of four bricks, every panel rounded up
   unsigned long long counters[kNumCounters];
 };
 
@@ -132,12 +133,14 @@ hipError_t launch_scan_nonzero64(const uint64_t* in, int64_t n, uint32_t* out, u
                                  hipStream_t s);
 
 // ---- exec (a6..a8) -------------------------------------------------------
+// `items` may be null: one item per panel, n_items panels.
 // Device arrays of the brick format.  Each carries spare entries past its end
 // (kFormatPad bricks' worth: zero columns and patterns, value offsets equal to
 // nnz, zero values) so that kernels may fetch metadata a few bricks past a work
 // item's last brick without clamping.
 constexpr int kFormatPad = 32;
 struct BrickFormat {
+  const uint32_t* panel_ptr;     // P + 1: the work list where there is no other
   const uint32_t* brick_cols;    // 4 * (nb + kFormatPad)
   const uint64_t* brick_mask;    // nb + kFormatPad
   const uint32_t* brick_valptr;  // nb + 1 + kFormatPad
