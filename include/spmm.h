@@ -335,7 +335,9 @@ int spmm_plan_worklist(spmm_plan_t *plan, int64_t N, spmm_worklist_info_t *info 
 int spmm_calibrate_gather(const float *buf, int64_t n_rows, int64_t loads_per_wave,
                           int64_t n_waves, float *sink, void *stream);
 
-void spmm_plan_destroy(spmm_plan_t *plan); /* NULL is allowed */
+/* Waits for the device.  The library keeps up to 512 MiB a device of the memory that plans let go
+ * for the plans that follow; with NULL nothing is destroyed and that memory is given back. */
+void spmm_plan_destroy(spmm_plan_t *plan);
 
 const char *spmm_last_error(void); /* thread-local, valid until the next failing call */
 

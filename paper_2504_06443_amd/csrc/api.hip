@@ -13,6 +13,8 @@
 #include <map>
 #include <mutex>
 #include <new>
+#include <optional>
+#include <unordered_map>
 #include <vector>
 
 using namespace spmm;
@@ -42,6 +44,163 @@ int fail(int code, const char* fmt, ...) {
 constexpr double kHbmBytesPerS = 8.0e12;    // MI355X published HBM3E bandwidth
 constexpr double kMfmaFp32Flops = 157.3e12; // MI355X published dense fp32 matrix peak
 
+// Device memory of plans and of their construction, kept for the next plan when it is let go.
+// hipMalloc and hipFree of tens of megabytes take 25 to 300 us each (they map and unmap), together
+// more than building a plan of 8 M entries; a program that makes a plan per matrix, or drops and
+// makes work lists, asks for the same sizes again.  Only memory that nothing uses any more comes
+// here: its owner has waited for the device, or for the one stream that used it.  At most kKeepBytes
+// a device are kept (0.2 % of it), each block for kKeepCalls later requests; all of it is given back
+// when an allocation here fails, and by spmm_plan_destroy(NULL).  Blocks below kKeepMin go straight to the
+// runtime, which hands those out without mapping.
+constexpr size_t kKeepBytes = size_t(512) << 20, kKeepMin = size_t(256) << 10;
+constexpr uint64_t kKeepCalls = 256;
+
+class DeviceKeep {
+ public:
+  static DeviceKeep& instance() {
+    static DeviceKeep* keep = new DeviceKeep();   // never destroyed: plans may outlive static data
+    return *keep;
+  }
+  hipError_t get(void** p, size_t bytes) {
+    if (bytes < kKeepMin) return hipMalloc(p, bytes);
+    const size_t page = bytes < (size_t(2) << 20) ? size_t(64) << 10 : size_t(2) << 20;
+    bytes = (bytes + page - 1) / page * page;   // what the runtime takes for it
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (take(p, bytes, dev)) return hipSuccess;
+    e = hipMalloc(p, bytes);
+    if (e == hipErrorOutOfMemory) {
+      (void)hipGetLastError();
+      give_back(dev);
+      e = hipMalloc(p, bytes);
+    }
+    if (e != hipSuccess) return e;
+    std::lock_guard<std::mutex> lock(mutex_);
+    try { live_[*p] = Block{*p, bytes, dev, 0}; }
+    catch (const std::bad_alloc&) { }             // put() then frees it
+    return hipSuccess;
+  }
+  // idle: nothing that was enqueued still uses the block
+  void put(void* p, bool idle) {
+    if (!p) return;
+    int dev = -1;
+    if (idle && hipGetDevice(&dev) != hipSuccess) idle = false;
+    {
+      std::lock_guard<std::mutex> lock(mutex_);
+      const auto it = live_.find(p);
+      if (it != live_.end()) {
+        Block b = it->second;
+        live_.erase(it);
+        size_t kept = b.bytes;
+        for (const Block& k : kept_) kept += k.dev == b.dev ? k.bytes : 0;
+        if (idle && dev == b.dev && kept <= kKeepBytes) {
+          b.stamp = clock_;
+          try { kept_.push_back(b); return; }
+          catch (const std::bad_alloc&) { }
+        }
+      }
+    }
+    (void)hipFree(p);
+  }
+  void give_back(int dev /* -1: all */) {
+    while (void* p = evict([&](const Block& b) { return dev < 0 || b.dev == dev; })) (void)hipFree(p);
+  }
+
+ private:
+  struct Block { void* p; size_t bytes; int dev; uint64_t stamp; };
+
+  bool take(void** p, size_t bytes, int dev) {
+    bool found = false;
+    uint64_t now;
+    {
+      std::lock_guard<std::mutex> lock(mutex_);
+      now = ++clock_;
+      size_t best = kept_.size();
+      for (size_t i = 0; i < kept_.size(); ++i) {
+        const Block& b = kept_[i];
+        if (b.dev == dev && b.bytes >= bytes && b.bytes <= bytes + bytes / 2 &&
+            (best == kept_.size() || b.bytes < kept_[best].bytes))
+          best = i;
+      }
+      if (best < kept_.size()) {
+        const Block b = kept_[best];
+        try {
+          live_[b.p] = b;
+          kept_.erase(kept_.begin() + (ptrdiff_t)best);
+          *p = b.p;
+          found = true;
+        } catch (const std::bad_alloc&) { }
+      }
+    }
+    while (void* old = evict([&](const Block& b) { return now > b.stamp + kKeepCalls; })) (void)hipFree(old);
+    return found;
+  }
+  template <typename Which> void* evict(Which which) {
+    std::lock_guard<std::mutex> lock(mutex_);
+    for (size_t i = 0; i < kept_.size(); ++i)
+      if (which(kept_[i])) {
+        void* p = kept_[i].p;
+        kept_.erase(kept_.begin() + (ptrdiff_t)i);
+        return p;
+      }
+    return nullptr;
+  }
+
+  std::mutex mutex_;
+  std::vector<Block> kept_;
+  std::unordered_map<void*, Block> live_;
+  uint64_t clock_ = 0;
+};
+
+hipError_t keep_get(char** p, size_t bytes) { return DeviceKeep::instance().get((void**)p, bytes); }
+void keep_put(void* p, bool idle) { DeviceKeep::instance().put(p, idle); }
+
+// Pinned host memory for what plans and work lists exchange with the device (a copy to or from
+// pageable memory is staged by the runtime, 25 to 150 us a call): buffers of kStageBytes, one per
+// call that needs one, at most kStages kept.  Without one (null) the copy goes the pageable way.
+constexpr size_t kStageBytes = size_t(1) << 20, kStages = 4;
+
+class HostStage {
+ public:
+  HostStage() {
+    {
+      std::lock_guard<std::mutex> lock(pool().mutex);
+      if (!pool().free.empty()) {
+        p_ = pool().free.back();
+        pool().free.pop_back();
+        return;
+      }
+    }
+    void* p = nullptr;
+    if (hipHostMalloc(&p, kStageBytes, hipHostMallocPortable) == hipSuccess) p_ = static_cast<char*>(p);
+    else (void)hipGetLastError();
+  }
+  // (the owner has waited for the copies by now)
+  ~HostStage() {
+    if (!p_) return;
+    {
+      std::lock_guard<std::mutex> lock(pool().mutex);
+      if (pool().free.size() < kStages) {
+        try { pool().free.push_back(p_); return; }
+        catch (const std::bad_alloc&) { }
+      }
+    }
+    (void)hipHostFree(p_);
+  }
+  HostStage(const HostStage&) = delete;
+  HostStage& operator=(const HostStage&) = delete;
+  char* get() const { return p_; }
+
+ private:
+  struct Pool { std::mutex mutex; std::vector<char*> free; };
+  static Pool& pool() {
+    static Pool* pool = new Pool();
+    return *pool;
+  }
+  char* p_ = nullptr;
+};
+
 // Host half of a work list: what the routing and Eq. 6-7 decide for one N.
 struct HostList {
   uint64_t id = 0;                          // unique per list (tags the contents of the static scratch)
@@ -50,8 +209,7 @@ struct HostList {
   // Every panel to the brick kernel, whole and in order: item i is panel i, the lists below are
   // empty and the kernels read panel_ptr instead.
   bool direct = false;
-  std::vector<spmm_work_item_t> h_items;   // exported form
-  std::vector<WorkItem> items;             // device form
+  std::vector<WorkItem> items;
   std::vector<MergeItem> merges;
   std::vector<uint32_t> valu_panels;
   int64_t n_slots = 0;                      // partial 16 x N tiles of split panels
@@ -64,11 +222,9 @@ struct WorkList {
   uint32_t* d_valu_panels = nullptr;
   MergeItem* d_merge = nullptr;
   float* d_partial = nullptr;               // n_slots tiles of 16 x N
-  ~WorkList() {
-    if (d_items) (void)hipFree(d_items);
-    if (d_valu_panels) (void)hipFree(d_valu_panels);
-    if (d_merge) (void)hipFree(d_merge);
-    if (d_partial) (void)hipFree(d_partial);
+  void release(bool idle) {
+    for (void* p : {(void*)d_items, (void*)d_valu_panels, (void*)d_merge, (void*)d_partial})
+      keep_put(p, idle);
   }
 };
 
@@ -131,8 +287,12 @@ struct spmm_plan {
   std::map<int64_t, HostList*> host_lists;
   std::map<int64_t, WorkList*> lists;
 
-  void drop_lists() {
-    for (auto& kv : lists) delete kv.second;
+  // idle: nothing that was enqueued still uses the plan
+  void drop_lists(bool idle) {
+    for (auto& kv : lists) {
+      kv.second->release(idle);
+      delete kv.second;
+    }
     lists.clear();
     for (auto& kv : host_lists) delete kv.second;
     host_lists.clear();
@@ -140,11 +300,12 @@ struct spmm_plan {
   // the arrays above are carved out of two device allocations
   char* fixed_arena = nullptr;   // panel_ptr, rowptr, panel_nnzptr, src
   char* brick_arena = nullptr;   // brick_cols, brick_mask, brick_valptr, vals
+  bool idle = false;             // set before the end: as in drop_lists
   ~spmm_plan() {
-    drop_lists();
-    if (fixed_arena) (void)hipFree(fixed_arena);
-    if (brick_arena) (void)hipFree(brick_arena);
-    if (csr_arena) (void)hipFree(csr_arena);
+    drop_lists(idle);
+    keep_put(fixed_arena, idle);
+    keep_put(brick_arena, idle);
+    keep_put(csr_arena, idle);
     if (tm32.arena) (void)hipFree(tm32.arena);
   }
 };
@@ -165,7 +326,7 @@ struct Arena {
 
 template <typename T>
 hipError_t dev_alloc(T** p, int64_t n) {
-  return hipMalloc((void**)p, (size_t)std::max<int64_t>(n, 1) * sizeof(T));
+  return DeviceKeep::instance().get((void**)p, (size_t)std::max<int64_t>(n, 1) * sizeof(T));
 }
 
 int classify(int64_t nnz, int64_t nb) {
@@ -188,23 +349,22 @@ int64_t waves_of(int64_t work_items, int64_t capacity) {
 // SPMM_SPLIT_EQ7_FROM2 (the default): one part while the ratio is below 2, else the ratio
 // rounded to the nearest integer, halves up.  SPMM_SPLIT_EQ7_NEAREST: the ratio rounded to
 // the nearest integer from the start (a panel is split from ratio 1.5), at least one part.
+int64_t eq7_parts(int64_t blocks, int64_t P, int64_t total, int64_t waves, int policy) {
+  if (total <= 0 || blocks <= 0) return 1;
+  // blocks * P can exceed 2^63 only for absurd sizes; use 128-bit to be safe
+  const __int128 num = (__int128)blocks * P;
+  const __int128 den = (__int128)total * waves;
+  if (2 * num < 3 * den || (policy == SPMM_SPLIT_EQ7_FROM2 && num < 2 * den)) return 1;
+  return (int64_t)((2 * num + den) / (2 * den));
+}
+
 void partition_counts(int64_t P, const uint32_t* nbricks, int64_t work_items, int64_t capacity,
                       int policy, uint32_t* parts, int64_t* waves_out) {
   int64_t total = 0;
   for (int64_t p = 0; p < P; ++p) total += ceil_div(nbricks[p], kBrickK);
   const int64_t waves = waves_of(work_items, capacity);
-  for (int64_t p = 0; p < P; ++p) {
-    const int64_t blocks = ceil_div(nbricks[p], kBrickK);
-    int64_t q = 1;
-    if (total > 0 && blocks > 0) {
-      // blocks * P can exceed 2^63 only for absurd sizes; use 128-bit to be safe
-      const __int128 num = (__int128)blocks * P;
-      const __int128 den = (__int128)total * waves;
-      const int64_t nearest = (int64_t)((2 * num + den) / (2 * den));
-      q = (policy == SPMM_SPLIT_EQ7_FROM2 && num < 2 * den) ? 1 : nearest;
-    }
-    parts[p] = (uint32_t)std::max<int64_t>(1, q);
-  }
+  for (int64_t p = 0; p < P; ++p)
+    parts[p] = (uint32_t)eq7_parts(ceil_div(nbricks[p], kBrickK), P, total, waves, policy);
   if (waves_out) *waves_out = waves;
 }
 
@@ -276,93 +436,74 @@ int build_host_list(spmm_plan_t* pl, int64_t N, const HostList** out) {
       return status;
     }
 
-    // routing: which panels go to the MFMA kernel
-    std::vector<uint32_t> mfma_panels;
-    std::vector<uint32_t> nbricks;
+    // Routing: which panels go to the MFMA kernel.
+    // AUTO is the measured policy for MI355X: the brick kernel loads each B row of a panel
+    // once where CSR loads it once per entry, and on the benchmark's sweep of brick fill
+    // (0.05..0.8) and width (16..512) the CSR kernel is nowhere faster by more than a few
+    // percent (a tie at fill 0.05, N = 16), so every panel goes to the brick kernel.  SPMM_ROUTE_CLASS is the
+    // paper's per-class rule.
+    // An empty panel (class 255) only needs its rows of C zeroed; either kernel does that, so
+    // under CLASS it goes to the CSR kernel, whose launch the Low panels cause anyway.
+    const uint32_t* ptr = pl->h_panel_ptr.data();
+    auto to_mfma = [&](int64_t p) {
+      if (pl->route == SPMM_ROUTE_AUTO || pl->route == SPMM_ROUTE_MFMA) return true;
+      if (pl->route == SPMM_ROUTE_VALU) return false;
+      return pl->h_panel_class[p] != SPMM_LOW && pl->h_panel_class[p] != 255;
+    };
+    int64_t nm = 0, total = 0;   // panels of the MFMA kernel and their blocks
     for (int64_t p = 0; p < pl->P; ++p) {
-      bool to_mfma;
-      // AUTO is the measured policy for MI355X: the brick kernel loads each B row of a panel
-      // once where CSR loads it once per entry, and on the benchmark's sweep of brick fill
-      // (0.05..0.8) and width (16..512) the CSR kernel is nowhere faster by more than a few
-      // percent (a tie at fill 0.05, N = 16), so every panel goes to the brick kernel.  SPMM_ROUTE_CLASS is the
-      // paper's per-class rule.
-      // An empty panel (class 255) only needs its rows of C zeroed; either kernel does that, so
-      // under CLASS it goes to the CSR kernel, whose launch the Low panels cause anyway.
-      if (pl->route == SPMM_ROUTE_AUTO || pl->route == SPMM_ROUTE_MFMA) to_mfma = true;
-      else if (pl->route == SPMM_ROUTE_VALU) to_mfma = false;
-      else to_mfma = pl->h_panel_class[p] != SPMM_LOW && pl->h_panel_class[p] != 255;
-      if (to_mfma) {
-        mfma_panels.push_back((uint32_t)p);
-        nbricks.push_back(pl->h_panel_ptr[p + 1] - pl->h_panel_ptr[p]);
+      if (to_mfma(p)) {
+        ++nm;
+        total += ceil_div(ptr[p + 1] - ptr[p], kBrickK);
       } else {
         hl->valu_panels.push_back((uint32_t)p);
       }
     }
 
     // load balancing over the MFMA panels
-    const int64_t nm = (int64_t)mfma_panels.size();
-    std::vector<uint32_t> parts((size_t)nm, 1u);
-    int64_t waves = 1;
-    if (nm > 0) {
-      if (pl->split == SPMM_SPLIT_EQ7_FROM2 || pl->split == SPMM_SPLIT_EQ7_NEAREST) {
-        partition_counts(nm, nbricks.data(), nm * hl->info.n_tiles,
-                         (int64_t)pl->num_cus * resident, pl->split, parts.data(), &waves);
-        // A part keeps at least kMinBlocksPerPart blocks: splitting a panel of a few blocks saves
-        // less than the merge launch it causes (measured on the 65,536-row sweep, fill 0.8: three panels of
-        // about 20 bricks split in two, 24.8 us against 20.9 us unsplit).
-        for (int64_t i = 0; i < nm; ++i) {
-          const int64_t blocks = ceil_div(nbricks[i], kBrickK);
-          parts[i] = (uint32_t)std::min<int64_t>(parts[i], std::max<int64_t>(1, blocks / kMinBlocksPerPart));
-        }
-      } else if (pl->split > 1) {
-        for (int64_t i = 0; i < nm; ++i)
-          if (ceil_div(nbricks[i], kBrickK) >= pl->split) parts[i] = (uint32_t)pl->split;
+    const bool eq7 = pl->split == SPMM_SPLIT_EQ7_FROM2 || pl->split == SPMM_SPLIT_EQ7_NEAREST;
+    const int64_t waves = eq7 && nm > 0 ? waves_of(nm * hl->info.n_tiles, (int64_t)pl->num_cus * resident) : 1;
+    auto parts_of = [&](int64_t blocks) -> int64_t {
+      // A part keeps at least kMinBlocksPerPart blocks: splitting a panel of a few blocks saves
+      // less than the merge launch it causes (measured on the 65,536-row sweep, fill 0.8: three panels of
+      // about 20 bricks split in two, 24.8 us against 20.9 us unsplit).
+      if (eq7) {
+        if (blocks < 2 * kMinBlocksPerPart) return 1;
+        return std::min(eq7_parts(blocks, nm, total, waves, pl->split), blocks / kMinBlocksPerPart);
       }
-    }
+      return pl->split > 1 && blocks >= pl->split ? pl->split : 1;
+    };
     hl->info.num_waves = waves;
 
     int64_t slots = 0;
-    for (int64_t i = 0; i < nm; ++i) {
-      const uint32_t p = mfma_panels[i];
-      const uint32_t b0 = pl->h_panel_ptr[p];
-      const int64_t nbp = nbricks[i];
+    hl->items.reserve((size_t)nm);
+    for (int64_t p = 0; p < pl->P; ++p) {
+      if (!to_mfma(p)) continue;
+      const uint32_t b0 = ptr[p];
+      const int64_t nbp = ptr[p + 1] - b0;
       const int64_t blocks = ceil_div(nbp, kBrickK);
-      const int64_t want = std::max<int64_t>(1, std::min<int64_t>(parts[i], blocks));
-      const int64_t per = std::max<int64_t>(1, ceil_div(blocks, want));   // blocks per part
-      const int64_t nparts = ceil_div(blocks, per);        // parts that are not empty
-      if (nparts <= 1) {   // also an empty panel: one work item without bricks
-        hl->items.push_back(WorkItem{p, b0, b0 + (uint32_t)nbp, kNoSlot});
-        hl->h_items.push_back(spmm_work_item_t{p, b0, b0 + (uint32_t)nbp, 0, 1});
+      const int64_t want = parts_of(blocks);
+      if (want <= 1) {   // also an empty panel: one work item without bricks
+        hl->items.push_back(WorkItem{(uint32_t)p, b0, b0 + (uint32_t)nbp, kNoSlot});
         continue;
       }
-      hl->merges.push_back(MergeItem{p, (uint32_t)slots, (uint32_t)nparts});
+      const int64_t per = ceil_div(blocks, want);          // blocks per part
+      const int64_t nparts = ceil_div(blocks, per);        // parts that are not empty
+      hl->merges.push_back(MergeItem{(uint32_t)p, (uint32_t)slots, (uint32_t)nparts});
       for (int64_t q = 0; q < nparts; ++q) {
         const int64_t lo = std::min<int64_t>(nbp, q * per * kBrickK);
         const int64_t hi = std::min<int64_t>(nbp, (q + 1) * per * kBrickK);
         hl->items.push_back(
-            WorkItem{p, b0 + (uint32_t)lo, b0 + (uint32_t)hi, (uint32_t)(slots + q)});
-        hl->h_items.push_back(
-            spmm_work_item_t{p, b0 + (uint32_t)lo, b0 + (uint32_t)hi, (uint32_t)q, (uint32_t)nparts});
+            WorkItem{(uint32_t)p, b0 + (uint32_t)lo, b0 + (uint32_t)hi, (uint32_t)(slots + q)});
       }
       slots += nparts;
     }
     if (pl->order == SPMM_ORDER_HEAVY_FIRST) {
       // the schedule Section 5 argues against (it gives up the locality of consecutive panels);
       // kept as an experiment
-      std::vector<size_t> perm(hl->items.size());
-      for (size_t i = 0; i < perm.size(); ++i) perm[i] = i;
-      std::stable_sort(perm.begin(), perm.end(), [&](size_t l, size_t r) {
-        return hl->items[l].brick_end - hl->items[l].brick_begin >
-               hl->items[r].brick_end - hl->items[r].brick_begin;
+      std::stable_sort(hl->items.begin(), hl->items.end(), [](const WorkItem& l, const WorkItem& r) {
+        return l.brick_end - l.brick_begin > r.brick_end - r.brick_begin;
       });
-      std::vector<WorkItem> sorted_items(hl->items.size());
-      std::vector<spmm_work_item_t> sorted_h(hl->items.size());
-      for (size_t i = 0; i < perm.size(); ++i) {
-        sorted_items[i] = hl->items[perm[i]];
-        sorted_h[i] = hl->h_items[perm[i]];
-      }
-      hl->items.swap(sorted_items);
-      hl->h_items.swap(sorted_h);
     }
     hl->info.n_mfma_items = (int64_t)hl->items.size();
     hl->info.n_valu_panels = (int64_t)hl->valu_panels.size();
@@ -385,6 +526,7 @@ int build_worklist(spmm_plan_t* pl, int64_t N, hipStream_t stream, WorkList** ou
     return SPMM_OK;
   }
   const HostList* hl = nullptr;
+  std::optional<HostStage> stage;
   int status = build_host_list(pl, N, &hl);
   if (status != SPMM_OK) return status;
   WorkList* wl = new (std::nothrow) WorkList();
@@ -395,17 +537,25 @@ int build_worklist(spmm_plan_t* pl, int64_t N, hipStream_t stream, WorkList** ou
   if (!hl->merges.empty()) HIP_TRY(dev_alloc(&wl->d_merge, (int64_t)hl->merges.size()));
   if (hl->n_slots > 0)
     HIP_TRY(dev_alloc(&wl->d_partial, hl->n_slots * kPanel * std::max<int64_t>(N, 1)));
-  if (!hl->items.empty())
-    HIP_TRY(hipMemcpyAsync(wl->d_items, hl->items.data(), hl->items.size() * sizeof(WorkItem),
-                           hipMemcpyHostToDevice, stream));
-  if (!hl->valu_panels.empty())
-    HIP_TRY(hipMemcpyAsync(wl->d_valu_panels, hl->valu_panels.data(),
-                           hl->valu_panels.size() * sizeof(uint32_t), hipMemcpyHostToDevice,
-                           stream));
-  if (!hl->merges.empty())
-    HIP_TRY(hipMemcpyAsync(wl->d_merge, hl->merges.data(), hl->merges.size() * sizeof(MergeItem),
-                           hipMemcpyHostToDevice, stream));
-  if (!hl->direct) HIP_TRY(hipStreamSynchronize(stream));
+  if (!hl->direct) {
+    stage.emplace();
+    size_t used = 0;
+    auto upload = [&](void* dst, const void* from, size_t bytes) {
+      if (stage->get() && used + bytes <= kStageBytes) {
+        memcpy(stage->get() + used, from, bytes);
+        from = stage->get() + used;
+        used += (bytes + 63) & ~size_t(63);
+      }
+      return hipMemcpyAsync(dst, from, bytes, hipMemcpyHostToDevice, stream);
+    };
+    if (!hl->items.empty())
+      HIP_TRY(upload(wl->d_items, hl->items.data(), hl->items.size() * sizeof(WorkItem)));
+    if (!hl->valu_panels.empty())
+      HIP_TRY(upload(wl->d_valu_panels, hl->valu_panels.data(), hl->valu_panels.size() * sizeof(uint32_t)));
+    if (!hl->merges.empty())
+      HIP_TRY(upload(wl->d_merge, hl->merges.data(), hl->merges.size() * sizeof(MergeItem)));
+    HIP_TRY(hipStreamSynchronize(stream));
+  }
   try {
     pl->lists[N] = wl;
   } catch (const std::bad_alloc&) {
@@ -413,6 +563,7 @@ int build_worklist(spmm_plan_t* pl, int64_t N, hipStream_t stream, WorkList** ou
   }
 done:
   if (status != SPMM_OK) {
+    wl->release(hipStreamSynchronize(stream) == hipSuccess);   // (uploads may be under way)
     delete wl;
     return status;
   }
@@ -433,7 +584,7 @@ int enable_csr(spmm_plan_t* pl) {
   Arena a;
   a.cap = 2 * Arena::pad((size_t)std::max<int64_t>(pl->nnz, 1) * 4) + Arena::pad((size_t)cap * 4) +
           Arena::pad(sizeof(unsigned long long));
-  if (!pl->csr_arena) HIP_TRY(hipMalloc((void**)&pl->csr_arena, a.cap));
+  if (!pl->csr_arena) HIP_TRY(keep_get(&pl->csr_arena, a.cap));
   a.base = pl->csr_arena;
   pl->colind = a.take<int32_t>(pl->nnz);
   pl->csr_vals = a.take<float>(pl->nnz);
@@ -630,6 +781,14 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
   Arena work, wide, fixed, bricks;
   PlanControl* ctl;                  // the first array of `work`
   PlanControl h_ctl{};
+  HostStage stage;
+  auto read_ctl = [&]() -> hipError_t {   // enqueues the copy, waits, h_ctl
+    void* to = stage.get() ? (void*)stage.get() : (void*)&h_ctl;
+    hipError_t e = hipMemcpyAsync(to, ctl, sizeof(PlanControl), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e == hipSuccess && to != &h_ctl) memcpy(&h_ctl, to, sizeof(PlanControl));
+    return e;
+  };
   uint32_t *scan_tmp, *ncols_p;
   enum { kPathSearch, kPathBitmap, kPathSort } path = kPathSearch;
   uint32_t sort_cap = 0;
@@ -646,7 +805,7 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
     uint8_t* first;
     wide.cap = need(nnz, 4) + need(nnz, 1) + need(nnz + 1, 4) + need(nnz, 4) + need(nnz, 1) +
                3 * need(nnz, 4);
-    HIP_TRY(hipMalloc((void**)&wide.base, wide.cap));
+    HIP_TRY(keep_get(&wide.base, wide.cap));
     ent_row = wide.take<uint32_t>(nnz);
     first = wide.take<uint8_t>(nnz);
     first_scan = wide.take<uint32_t>(nnz + 1);
@@ -672,14 +831,14 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
   pl->num_cus = std::max(1, pl->num_cus);
 
   work.cap = need(1, sizeof(PlanControl)) + need(K, 1) + need(scan_elems, 4) + need(P, 4);
-  HIP_TRY(hipMalloc((void**)&work.base, work.cap));
+  HIP_TRY(keep_get(&work.base, work.cap));
   ctl = work.take<PlanControl>(1);
   col_seen = work.take<uint8_t>(K);   // next to the control block: cleared together
   scan_tmp = work.take<uint32_t>(scan_elems);
   ncols_p = work.take<uint32_t>(P);
 
   fixed.cap = 2 * need(P + 1, 4) + need(M + 1, 4) + need(nnz, 4);
-  HIP_TRY(hipMalloc((void**)&fixed.base, fixed.cap));
+  HIP_TRY(keep_get(&fixed.base, fixed.cap));
   pl->fixed_arena = fixed.base;
   pl->panel_ptr = fixed.take<uint32_t>(P + 1);
   pl->panel_nnzptr = fixed.take<uint32_t>(P + 1);
@@ -689,8 +848,7 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
   // ---- rowptr validation and the widest panel span (device), before anything trusts rowptr
   HIP_TRY(hipMemsetAsync(work.base, 0, (size_t)(reinterpret_cast<char*>(scan_tmp) - work.base), s));
   HIP_TRY(launch_rows(rowptr, colind, M, P, nnz, pl->rowptr, pl->panel_nnzptr, ctl, s));
-  HIP_TRY(hipMemcpyAsync(&h_ctl, ctl, sizeof(PlanControl), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
+  HIP_TRY(read_ctl());
   if (h_ctl.err & (kErrRowptrEnds | kErrRowptrOrder)) {
     status = fail(SPMM_EFORMAT, "invalid rowptr (%s)",
                   (h_ctl.err & kErrRowptrEnds) ? "rowptr[0] != 0 or rowptr[M] != nnz" : "not monotone");
@@ -729,8 +887,7 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
     if (status != SPMM_OK) goto done;
   }
   HIP_TRY(launch_panel_scan(ncols_p, P, pl->panel_ptr, scan_tmp, ctl, s));
-  HIP_TRY(hipMemcpyAsync(&h_ctl, ctl, sizeof(PlanControl), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
+  HIP_TRY(read_ctl());
   if (h_ctl.err) {
     status = fail(SPMM_EFORMAT, "invalid colind (%s)",
                   (h_ctl.err & kErrColRange) ? "column out of range"
@@ -755,7 +912,7 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
   // ---- brick arrays (they carry spare entries, see BrickFormat)
   bricks.cap = need((pl->nb + kFormatPad) * kBrickK, 4) + need(pl->nb + kFormatPad, 8) +
                need(pl->nb + 1 + kFormatPad, 4) + need(nnz + 64, 4);
-  HIP_TRY(hipMalloc((void**)&bricks.base, bricks.cap));
+  HIP_TRY(keep_get(&bricks.base, bricks.cap));
   pl->brick_arena = bricks.base;
   pl->brick_cols = bricks.take<uint32_t>((pl->nb + kFormatPad) * kBrickK);
   pl->brick_mask = bricks.take<uint64_t>(pl->nb + kFormatPad);
@@ -810,18 +967,24 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
       status = fail(SPMM_ENOMEM, "host allocation failed");
       goto done;
     }
-    HIP_TRY(hipMemcpyAsync(pl->h_panel_ptr.data(), pl->panel_ptr,
-                           (size_t)(P + 1) * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+    const size_t bytes = (size_t)(P + 1) * sizeof(uint32_t);
+    const bool staged = stage.get() && sizeof(PlanControl) + bytes <= kStageBytes;
+    void* to = staged ? (void*)(stage.get() + sizeof(PlanControl)) : (void*)pl->h_panel_ptr.data();
+    HIP_TRY(hipMemcpyAsync(to, pl->panel_ptr, bytes, hipMemcpyDeviceToHost, s));
+    HIP_TRY(read_ctl());
+    if (staged) memcpy(pl->h_panel_ptr.data(), to, bytes);
+  } else {
+    HIP_TRY(read_ctl());
   }
-  HIP_TRY(hipMemcpyAsync(&h_ctl, ctl, sizeof(PlanControl), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
   memcpy(pl->h_counters, h_ctl.counters, sizeof(pl->h_counters));
 
 done:
-  if (status != SPMM_OK) (void)hipStreamSynchronize(s);
-  if (work.base) (void)hipFree(work.base);
-  if (wide.base) (void)hipFree(wide.base);
+  // (a call that succeeds ends with a wait for `s`, the only stream that used these)
+  const bool idle = status == SPMM_OK || hipStreamSynchronize(s) == hipSuccess;
+  keep_put(work.base, idle);
+  keep_put(wide.base, idle);
   if (status != SPMM_OK) {
+    pl->idle = idle;
     delete pl;
     return status;
   }
@@ -1056,7 +1219,7 @@ int spmm_plan_set_route(spmm_plan_t* pl, int route) {
   if (const int status = need_panel_ptr(pl)) return status;
   pl->csr_on = csr;   // (updates write the CSR copy only while a route reads it)
   pl->route = route;
-  pl->drop_lists();
+  pl->drop_lists(true);
   return SPMM_OK;
 }
 
@@ -1066,7 +1229,7 @@ int spmm_plan_set_split(spmm_plan_t* pl, int parts) {
   if (hipDeviceSynchronize() != hipSuccess) return fail(SPMM_EHIP, "hipDeviceSynchronize failed");
   if (const int status = need_panel_ptr(pl)) return status;
   pl->split = parts;
-  pl->drop_lists();
+  pl->drop_lists(true);
   return SPMM_OK;
 }
 
@@ -1076,7 +1239,7 @@ int spmm_plan_set_precision(spmm_plan_t* pl, int precision) {
     return fail(SPMM_EINVAL, "unknown precision");
   if (hipDeviceSynchronize() != hipSuccess) return fail(SPMM_EHIP, "hipDeviceSynchronize failed");
   pl->precision = precision;
-  pl->drop_lists();   // the kernels differ in occupancy, which Eq. 7 uses
+  pl->drop_lists(true);   // the kernels differ in occupancy, which Eq. 7 uses
   return SPMM_OK;
 }
 
@@ -1139,7 +1302,7 @@ int spmm_plan_set_order(spmm_plan_t* pl, int order) {
   if (hipDeviceSynchronize() != hipSuccess) return fail(SPMM_EHIP, "hipDeviceSynchronize failed");
   if (const int status = need_panel_ptr(pl)) return status;
   pl->order = order;
-  pl->drop_lists();
+  pl->drop_lists(true);
   return SPMM_OK;
 }
 
@@ -1168,16 +1331,30 @@ int spmm_plan_worklist(spmm_plan_t* pl, int64_t N, spmm_worklist_info_t* info,
     for (int64_t p = 0; p < pl->P; ++p)
       items[p] = spmm_work_item_t{(uint32_t)p, pl->h_panel_ptr[p], pl->h_panel_ptr[p + 1], 0, 1};
   }
-  if (items && !hl->h_items.empty())
-    memcpy(items, hl->h_items.data(), hl->h_items.size() * sizeof(spmm_work_item_t));
+  if (items && !hl->direct) {
+    for (size_t i = 0; i < hl->items.size(); ++i) {
+      const WorkItem& it = hl->items[i];
+      uint32_t part = 0, nparts = 1;
+      if (it.slot != kNoSlot) {   // merges are in the order of their slots
+        const auto m = std::upper_bound(hl->merges.begin(), hl->merges.end(), it.slot,
+                                        [](uint32_t slot, const MergeItem& x) { return slot < x.slot_begin; }) - 1;
+        part = it.slot - m->slot_begin;
+        nparts = m->nparts;
+      }
+      items[i] = spmm_work_item_t{it.panel, it.brick_begin, it.brick_end, part, nparts};
+    }
+  }
   if (valu_panels && !hl->valu_panels.empty())
     memcpy(valu_panels, hl->valu_panels.data(), hl->valu_panels.size() * sizeof(uint32_t));
   return SPMM_OK;
 }
 
 void spmm_plan_destroy(spmm_plan_t* pl) {
-  if (!pl) return;
-  (void)hipDeviceSynchronize();
+  if (!pl) {
+    DeviceKeep::instance().give_back(-1);
+    return;
+  }
+  pl->idle = hipDeviceSynchronize() == hipSuccess;
   delete pl;
 }
 
