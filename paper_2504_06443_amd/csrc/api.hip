@@ -789,10 +789,10 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
     if (e == hipSuccess && to != &h_ctl) memcpy(&h_ctl, to, sizeof(PlanControl));
     return e;
   };
-  uint32_t *scan_tmp, *ncols_p;
+  uint32_t *scan_tmp, *ncols_p, *mid_list, *big_list;
   enum { kPathSearch, kPathBitmap, kPathSort } path = kPathSearch;
-  uint32_t sort_cap = 0;
   uint32_t h_maxnb = 0, words_cap = 0;
+  bool sort_fits = false;
   uint8_t* col_seen;
   const int64_t scan_elems =
       std::max((int64_t)scan_tmp_elems(nnz), (int64_t)panel_scan_tmp_elems());  // bricks <= nnz
@@ -830,12 +830,15 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
   HIP_TRY(hipDeviceGetAttribute(&pl->num_cus, hipDeviceAttributeMultiprocessorCount, pl->device));
   pl->num_cus = std::max(1, pl->num_cus);
 
-  work.cap = need(1, sizeof(PlanControl)) + need(K, 1) + need(scan_elems, 4) + need(P, 4);
+  work.cap = need(1, sizeof(PlanControl)) + need(K, 1) + need(scan_elems, 4) + need(P, 4) +
+             need(panel_mid_list_elems(nnz), 4) + need(panel_big_list_elems(nnz), 4);
   HIP_TRY(keep_get(&work.base, work.cap));
   ctl = work.take<PlanControl>(1);
   col_seen = work.take<uint8_t>(K);   // next to the control block: cleared together
   scan_tmp = work.take<uint32_t>(scan_elems);
   ncols_p = work.take<uint32_t>(P);
+  mid_list = work.take<uint32_t>(panel_mid_list_elems(nnz));
+  big_list = work.take<uint32_t>(panel_big_list_elems(nnz));
 
   fixed.cap = 2 * need(P + 1, 4) + need(M + 1, 4) + need(nnz, 4);
   HIP_TRY(keep_get(&fixed.base, fixed.cap));
@@ -863,22 +866,20 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
   // Three ways to the same format.  The bitmap kernels walk a bitmap over the panel's column
   // span; that pays while the bitmaps are not much longer than the entry lists (band-like
   // matrices).  Scattered matrices (power-law graphs, random bricks: spans near K) sort each
-  // panel's entries in LDS instead when panels are well filled and none is large (the sort
-  // costs a fixed network per panel and LDS per wavefront); everything else takes the
-  // search-based kernels.  Measured: config 5 (bitmap words x panels = 4 x nnz) 0.6 vs 1.0 ms
-  // (search) in favour of the bitmap, config 3 (360 x) 4.0 vs 0.9 ms and the 1M-row sweep
-  // (67 x) 31 vs 3.8 ms against it; sort against search: 1M-row sweep f = 0.4 (488 entries
-  // per panel) 2.4 vs 4.5 ms, f = 0.8 3.8 vs 3.8 ms, config 3 (46 per panel, largest 3000+)
-  // 1.45 vs 0.99 ms.
-  sort_cap = panel_sort_keys(h_ctl.max_nnz);
-  if (words_cap != 0 && (int64_t)words_cap * P <= 8 * nnz) path = kPathBitmap;
-  else if (sort_cap != 0 && sort_cap <= 2048 && nnz >= 128 * P) path = kPathSort;
+  // panel's entries instead; a matrix with a panel beyond what one workgroup sorts takes the
+  // search-based kernels.  spmm_plan, bitmap against sort, at bitmap words x panels / nnz:
+  //   0.1 (blocks, 7.9 M entries) 141 / 173 us, 1.3 (cells, 0.4 M) 96 / 111, 1.3 (band of three a row)
+  //   120 / 123, 4.2 (cells, 2 M, fill 0.05) 239 / 140, 4.2 (fill 0.8) 163 / 143.
+  // Bitmap against search at 4: 0.6 / 1.0 ms.
+  sort_fits = panel_sort_fits(h_ctl.max_nnz);
+  if (words_cap != 0 && (int64_t)words_cap * P <= (sort_fits ? 2 : 8) * nnz) path = kPathBitmap;
+  else if (sort_fits) path = kPathSort;
   if (path == kPathBitmap) {
     // ---- a1/a2: census (also validates colind) -> bricks per panel
     HIP_TRY(launch_panel_census(rowptr, colind, M, K, P, words_cap, &ctl->err, ncols_p, s));
   } else if (path == kPathSort) {
-    HIP_TRY(launch_panel_sort_census(rowptr, colind, M, K, P, sort_cap, &ctl->err, ncols_p,
-                                     pl->src, s));
+    HIP_TRY(launch_panel_sort_census(rowptr, colind, M, K, P, nnz, h_ctl.max_nnz,
+                                     pl->panel_nnzptr, mid_list, big_list, ctl, ncols_p, pl->src, s));
   } else {
     // ---- search-based path for every other matrix.  Its a1
     // kernels only compare columns, so they may run before the host has seen the verdict of
@@ -902,8 +903,7 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
   }
 
   h_maxnb = (h_ctl.max_cols + kBrickK - 1) / kBrickK;
-  if ((path == kPathBitmap && !panel_build_fits(words_cap, std::max<uint32_t>(h_maxnb, 1))) ||
-      (path == kPathSort && !panel_sort_build_fits(sort_cap, std::max<uint32_t>(h_maxnb, 1)))) {
+  if (path == kPathBitmap && !panel_build_fits(words_cap, std::max<uint32_t>(h_maxnb, 1))) {
     path = kPathSearch;   // a panel with more bricks than fit in LDS: finish on the search-based path
     status = wide_a1();
     if (status != SPMM_OK) goto done;
@@ -921,10 +921,11 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
   HIP_TRY(launch_format_pad(pl->brick_cols, pl->brick_mask, pl->brick_valptr, pl->vals, pl->nb, nnz, s));
 
   if (path == kPathSort) {
-    HIP_TRY(launch_panel_sort_build(rowptr, colind, vals, M, K, P, sort_cap,
-                                    std::max<uint32_t>(h_maxnb, 1), pl->panel_ptr, pl->brick_cols,
-                                    pl->brick_mask, pl->brick_valptr, pl->vals, pl->src,
-                                    col_seen, s));
+    HIP_TRY(launch_panel_sort_build(rowptr, colind, vals, M, P,
+                                    PanelLists{mid_list, big_list, h_ctl.n_mid, h_ctl.n_big},
+                                    h_ctl.max_nnz, std::max<uint32_t>(h_maxnb, 1), pl->panel_ptr, pl->brick_cols,
+                                    pl->brick_mask, pl->brick_valptr, pl->vals, pl->src, col_seen,
+                                    s));
   } else if (path == kPathBitmap) {
     // ---- a2 (placing), a3, a4, one wavefront per panel
     HIP_TRY(launch_panel_build(rowptr, colind, vals, M, K, P, words_cap,

@@ -589,7 +589,6 @@ constexpr uint32_t kPanelFineWords = 2048;          // bitmaps with a rank per w
 constexpr uint32_t kPanelStageMax = 2048;           // entries of a panel staged in LDS (12 KiB)
 constexpr uint32_t kPanelMaxWords = 32768;          // 1 Mi columns of span
 constexpr size_t kPanelMaxLds = 150 * 1024;         // of the 160 KiB of a CU
-constexpr uint32_t kPanelMaxSortKeys = 8192;        // entries of a panel on the sort-based path
 
 struct PanelExtent {
   int64_t e0, e1;        // entries of the panel
@@ -698,13 +697,40 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_census(
 }
 
 // ---- per-panel path for scattered matrices: sort instead of a bitmap
-// One wavefront per panel sorts the panel's entries by (column, entry) in LDS (bitonic network
-// on 64-bit keys: column in the high half, entry index inside the panel in the low half).
-// Equal columns end up next to each other: flags + a scan give the rank of every column, with
-// no dependence on the width of the panel's column span.
-// Loads the keys (padded with all-ones to n_sort, a power of two >= 64), checks the columns,
-// sorts ascending.  KT = uint32_t packs (column << 11 | index) for matrices with fewer than
-// 2^21 columns and panels of at most 2048 entries: half the LDS traffic of 64-bit keys.
+// A panel's entries are sorted by (column, entry): equal columns end up next to each other, and the
+// number of column changes before an entry is the rank of its column, whatever the width of the
+// panel's column span.  Panels come in three classes of size, so that a few heavy panels cost the many light
+// ones neither registers nor LDS: up to 512 entries a wavefront each, up to 2048 a
+// workgroup of 256, up to 8192 one of 1024.  All sort in registers, up to eight keys a lane: a
+// compare-exchange inside a lane is a min and a max, across lanes one cross-lane read a key, and only
+// steps across wavefronts go through LDS (a sort all through LDS moved four words a pair and step).
+// The census leaves the sorted entries, rank << 16 | index inside the panel, for the build.
+// 20,360 panels of 46 entries, the largest 3000: the search-based kernels 195 us, these 130.
+// 18,750 panels of 430: a sort through LDS by one wavefront 163 + 101 us (census, build), now 84 + 67.
+constexpr uint32_t kSortSmall = 512, kSortMid = 2048, kSortBig = 8192;
+constexpr int kMidThreads = 256, kBigThreads = 1024;
+
+// the panels of more than kSortSmall and of more than kSortMid entries, listed in any order
+__global__ __launch_bounds__(1024) void k_panel_lists(const uint32_t* __restrict__ panel_nnzptr,
+                                                      int64_t P, uint32_t* __restrict__ mid_list,
+                                                      uint32_t* __restrict__ big_list,
+                                                      PlanControl* ctl) {
+  __shared__ uint32_t count[2], base[2];
+  if (threadIdx.x < 2) count[threadIdx.x] = 0;
+  __syncthreads();
+  const int64_t p = (int64_t)blockIdx.x * 1024 + threadIdx.x;
+  const uint32_t n = p < P ? panel_nnzptr[p + 1] - panel_nnzptr[p] : 0;
+  const int which = n > kSortMid ? 1 : (n > kSortSmall ? 0 : -1);
+  uint32_t at = 0;
+  if (which >= 0) at = atomicAdd(&count[which], 1u);
+  __syncthreads();
+  if (threadIdx.x < 2 && count[threadIdx.x])
+    base[threadIdx.x] = atomicAdd(threadIdx.x ? &ctl->n_big : &ctl->n_mid, count[threadIdx.x]);
+  __syncthreads();
+  if (which >= 0) (which ? big_list : mid_list)[base[which] + at] = (uint32_t)p;
+}
+
+// KT = uint32_t packs (column << 11 | index): fewer than 2^21 columns, at most 2048 entries
 template <typename KT> struct SortKey;
 template <> struct SortKey<unsigned long long> {
   static __device__ unsigned long long make(uint32_t col, uint32_t idx) { return ((unsigned long long)col << 32) | idx; }
@@ -717,145 +743,257 @@ template <> struct SortKey<uint32_t> {
   static __device__ uint32_t idx(uint32_t k) { return k & 2047u; }
 };
 
-template <typename KT>
-__device__ inline void panel_sort(const int32_t* __restrict__ colind, const PanelExtent& x,
-                                  const int32_t* rp, int64_t K, uint32_t n_sort, KT* keys,
-                                  uint32_t* err) {
-  const uint32_t n = (uint32_t)(x.e1 - x.e0);
-  uint32_t bad = 0;
-  for (uint32_t i = threadIdx.x; i < n_sort; i += kPanelThreads) {
-    KT key = (KT)~(KT)0;
-    if (i < n) {
-      const int64_t e = x.e0 + i;
-      const int32_t j = colind[e];
-      if (j < 0 || j >= K) bad |= kErrColRange;
-      if (e > rp[row_in_panel(rp, e)] && colind[e - 1] >= j) bad |= kErrColOrder;
-      key = SortKey<KT>::make((uint32_t)j, i);
+// entries and row starts of panel p, as scalars (uniform addresses)
+struct PanelRows {
+  int64_t e0;
+  uint32_t n;
+  uint32_t start[kPanel];   // first entry of each row, relative to e0
+  __device__ PanelRows(const int32_t* __restrict__ rowptr, int64_t M, int64_t p) {
+    const int64_t r0 = p * kPanel;
+    e0 = rowptr[r0];
+    n = (uint32_t)(rowptr[min(r0 + kPanel, M)] - rowptr[r0]);
+#pragma unroll
+    for (int r = 0; r < kPanel; ++r) start[r] = (uint32_t)(rowptr[min(r0 + r, M)] - rowptr[r0]);
+  }
+  __device__ uint32_t row_of(uint32_t i) const {   // last row that starts at or before entry i
+    uint32_t r = 0;
+#pragma unroll
+    for (int k = 1; k < kPanel; ++k) r += i >= start[k] ? 1u : 0u;
+    return r;
+  }
+  __device__ bool starts_row(uint32_t i) const {
+    bool is = false;
+#pragma unroll
+    for (int k = 0; k < kPanel; ++k) is |= i == start[k];
+    return is;
+  }
+  // range and order of entry i's column
+  __device__ uint32_t check(const int32_t* __restrict__ colind, int64_t K, uint32_t i, int32_t j) const {
+    uint32_t bad = (j < 0 || j >= K) ? kErrColRange : 0u;
+    if (!starts_row(i) && colind[e0 + i - 1] >= j) bad |= kErrColOrder;
+    return bad;
+  }
+};
+
+// exclusive scan of one value per thread across a workgroup of T threads (T = 64: across the
+// wavefront); the total in *total_out.  `sums` is LDS for a word per wavefront
+template <int T>
+__device__ inline uint32_t group_exclusive(uint32_t v, uint32_t* total_out, uint32_t* sums) {
+  uint32_t mine;
+  const uint32_t ex = wave_exclusive(v, &mine);
+  if constexpr (T == 64) {
+    *total_out = mine;
+    return ex;
+  } else {
+    __syncthreads();   // (the previous use has been read)
+    if ((threadIdx.x & 63) == 0) sums[threadIdx.x >> 6] = mine;
+    __syncthreads();
+    uint32_t base = 0, total = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < T / 64; ++w) {
+      base += w < (threadIdx.x >> 6) ? sums[w] : 0;
+      total += sums[w];
     }
-    keys[i] = key;
+    *total_out = total;
+    return base + ex;
+  }
+}
+
+// Bitonic sort of T * R keys, ascending in t * R + r for thread t of T (T = 64: for the lanes of a
+// wavefront).  In the halves that a step sorts downwards the keys are held complemented, so every
+// exchange puts the smaller key first.  `lds` holds T * R keys (T = 64: unused).
+template <int T, int R, typename KT>
+__device__ inline void group_sort(KT (&k)[R], KT* lds) {
+  const uint32_t t = threadIdx.x & (T - 1);
+  auto exchange = [&](int a, int b) {
+    const KT lo = min(k[a], k[b]), hi = max(k[a], k[b]);
+    k[a] = lo;
+    k[b] = hi;
+  };
+  auto complement = [&](KT mask) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) k[r] ^= mask;
+  };
+  // inside the lane: sizes 2 .. R (R itself upwards or downwards by lane)
+#pragma unroll
+  for (int size = 2; size <= R; size *= 2) {
+    if (size == R) complement((t & 1) ? ~(KT)0 : (KT)0);
+#pragma unroll
+    for (int j = size / 2; j > 0; j /= 2) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        if (r & j) continue;
+        if (size < R && (r & size)) exchange(r | j, r);
+        else exchange(r, r | j);
+      }
+    }
+    if (size == R) complement((t & 1) ? ~(KT)0 : (KT)0);
+  }
+  // across lanes: sizes 2R .. T * R, that is 2 .. T lanes
+#pragma unroll 1
+  for (uint32_t lanes = 2; lanes <= (uint32_t)T; lanes *= 2) {
+    const KT flip = (t & lanes) ? ~(KT)0 : (KT)0;   // (none at T: the whole is ascending)
+    complement(flip);
+#pragma unroll 1
+    for (uint32_t m = lanes / 2; m > 0; m /= 2) {
+      const bool keep_small = !(t & m);
+      KT other[R];
+      if (T > 64 && m >= 64) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) lds[r * T + t] = k[r];
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < R; ++r) other[r] = lds[r * T + (t ^ m)];
+        __syncthreads();
+      } else {
+#pragma unroll
+        for (int r = 0; r < R; ++r) other[r] = __shfl_xor(k[r], (int)m, 64);
+      }
+#pragma unroll
+      for (int r = 0; r < R; ++r) k[r] = (other[r] < k[r]) == keep_small ? other[r] : k[r];
+    }
+#pragma unroll
+    for (int j = R / 2; j > 0; j /= 2)
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        if (!(r & j)) exchange(r, r | j);
+    complement(flip);
+  }
+}
+
+// one panel of at most T * R entries: sort, count the columns, leave the order; returns the count
+template <int T, int R, typename KT>
+__device__ inline uint32_t group_census(const int32_t* __restrict__ colind, const PanelRows& x,
+                                        int64_t K, uint32_t* err, uint32_t* __restrict__ order,
+                                        KT* lds, uint32_t* sums) {
+  const uint32_t t = threadIdx.x & (T - 1);
+  KT k[R];
+  uint32_t bad = 0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const uint32_t i = r * T + t;
+    k[r] = ~(KT)0;
+    if (i < x.n) {
+      const int32_t j = colind[x.e0 + i];
+      bad |= x.check(colind, K, i, j);
+      k[r] = SortKey<KT>::make((uint32_t)j, i);
+    }
   }
   if (bad) atomicOr(err, bad);
-  __syncthreads();
-  for (uint32_t k = 2; k <= n_sort; k <<= 1) {
-    for (uint32_t j = k >> 1; j > 0; j >>= 1) {
-      for (uint32_t i = threadIdx.x; i < n_sort / 2; i += kPanelThreads) {
-        const uint32_t a = ((i & ~(j - 1)) << 1) | (i & (j - 1));
-        const uint32_t b = a | j;
-        const KT ka = keys[a], kb = keys[b];
-        const bool ascending = (a & k) == 0;
-        if ((ka > kb) == ascending) { keys[a] = kb; keys[b] = ka; }
-      }
-      __syncthreads();
-    }
+  group_sort<T, R, KT>(k, lds);
+  // changes of column: against the key before, the previous thread's last for the first of a thread
+  KT before = __shfl_up(k[R - 1], 1, 64);
+  if constexpr (T > 64) {
+    lds[t] = k[R - 1];
+    __syncthreads();
+    if (t > 0) before = lds[t - 1];
   }
-}
-
-__device__ inline uint32_t sort_size(uint32_t n) {
-  uint32_t m = 64;
-  while (m < n) m <<= 1;
-  return m;
-}
-
-// census by sorting: distinct columns of each panel; validates colind; leaves the sorted order
-// of each panel's entries (indices inside the panel) in `order`.  Dynamic LDS: keys.
-template <typename KT>
-__global__ __launch_bounds__(kPanelThreads) void k_panel_sort_census(
-    const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind, int64_t M, int64_t K,
-    int64_t P, uint32_t n_cap, uint32_t* err, uint32_t* __restrict__ ncols_p,
-    uint32_t* __restrict__ order) {
-  extern __shared__ unsigned long long lds64[];
-  KT* keys = reinterpret_cast<KT*>(lds64);
-  __shared__ int32_t rp[kPanel + 1];
-  if (*err & (kErrRowptrEnds | kErrRowptrOrder)) return;   // uniform: nothing below is safe
-  const int64_t p = blockIdx.x;
-  const PanelExtent x = panel_extent(rowptr, colind, M, p, rp);
-  const uint32_t n = (uint32_t)(x.e1 - x.e0);
-  if (n == 0 || n > n_cap) {   // (n > n_cap cannot happen: the cap comes from k_rows)
-    if (threadIdx.x == 0) ncols_p[p] = 0;
-    return;
-  }
-  panel_sort<KT>(colind, x, rp, K, sort_size(n), keys, err);
-  uint32_t cnt = 0;
-  for (uint32_t i = threadIdx.x; i < n; i += kPanelThreads) {
-    cnt += (i == 0 || SortKey<KT>::col(keys[i]) != SortKey<KT>::col(keys[i - 1])) ? 1u : 0u;
-    order[x.e0 + i] = SortKey<KT>::idx(keys[i]);   // sorted order of the panel's entries
+  uint32_t first = 0;   // bit r: a column begins at element t * R + r
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const bool is = r == 0 ? t == 0 || SortKey<KT>::col(k[0]) != SortKey<KT>::col(before)
+                           : SortKey<KT>::col(k[r]) != SortKey<KT>::col(k[r > 0 ? r - 1 : 0]);
+    first |= (is && t * R + r < x.n ? 1u : 0u) << r;
   }
   uint32_t total;
-  wave_exclusive(cnt, &total);
-  if (threadIdx.x == 0) ncols_p[p] = total;
+  uint32_t rank = group_exclusive<T>((uint32_t)__popc(first), &total, sums) - 1u;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    rank += (first >> r) & 1u;
+    if (t * R + r < x.n) order[x.e0 + t * R + r] = rank << 16 | SortKey<KT>::idx(k[r]);
+  }
+  return total;
 }
 
-// a2 (placing half), a3 and a4 for one panel from the sorted order left by the census in
-// `src` (which this kernel then overwrites with the entry of each packed value).  Dynamic LDS: keys
-// (n_cap x u64), patterns (nb_cap x u64), value offsets (nb_cap words), the order of the packed
-// values (n_cap x two bytes), through which they leave in order, whole lines at a time.
-__global__ __launch_bounds__(kPanelThreads) void k_panel_sort_build(
+// census of the panels of at most kSortSmall entries, a wavefront each
+template <typename KT>
+__global__ __launch_bounds__(256) void k_panel_sort_census(
+    const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind, int64_t M, int64_t K,
+    int64_t P, uint32_t* err, uint32_t* __restrict__ ncols_p, uint32_t* __restrict__ order) {
+  if (*err & (kErrRowptrEnds | kErrRowptrOrder)) return;   // uniform: nothing below is safe
+  const int64_t p = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (p >= P) return;
+  const PanelRows x(rowptr, M, p);
+  if (x.n > kSortSmall) return;
+  uint32_t cols = 0;
+  KT* none = nullptr;
+  if (x.n == 0) cols = 0;
+  else if (x.n <= 64) cols = group_census<64, 1, KT>(colind, x, K, err, order, none, nullptr);
+  else if (x.n <= 128) cols = group_census<64, 2, KT>(colind, x, K, err, order, none, nullptr);
+  else if (x.n <= 256) cols = group_census<64, 4, KT>(colind, x, K, err, order, none, nullptr);
+  else cols = group_census<64, 8, KT>(colind, x, K, err, order, none, nullptr);
+  if ((threadIdx.x & 63) == 0) ncols_p[p] = cols;
+}
+
+// census of the listed panels, of at most T * 8 entries, a workgroup each
+template <typename KT, int T>
+__global__ __launch_bounds__(T) void k_panel_sort_census_listed(
+    const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind, int64_t M, int64_t K,
+    const uint32_t* __restrict__ list, const uint32_t* __restrict__ listed, uint32_t* err,
+    uint32_t* __restrict__ ncols_p, uint32_t* __restrict__ order) {
+  __shared__ KT lds[T * 8];
+  __shared__ uint32_t sums[T / 64];
+  if (blockIdx.x >= *listed) return;   // (the host does not know the count yet)
+  if (*err & (kErrRowptrEnds | kErrRowptrOrder)) return;
+  const int64_t p = list[blockIdx.x];
+  const PanelRows x(rowptr, M, p);
+  uint32_t cols = 0;
+  if (x.n <= T * 4) cols = group_census<T, 4, KT>(colind, x, K, err, order, lds, sums);
+  else if (x.n <= T * 8) cols = group_census<T, 8, KT>(colind, x, K, err, order, lds, sums);
+  if (threadIdx.x == 0) ncols_p[p] = cols;
+}
+
+// a2 (placing half), a3 and a4 of the listed panels (no list: of all) of at most n_cap entries, from the
+// sorted entries that the census left in `src` (which this kernel then overwrites with the entry of
+// each packed value).  T threads a panel.  Dynamic LDS: patterns (nb_cap x u64), the sorted entries
+// (n_cap words), value offsets (nb_cap words), the order of the packed values (n_cap x two bytes),
+// through which they leave in order, whole lines at a time.
+template <int T>
+__global__ __launch_bounds__(T) void k_panel_sort_build(
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind,
-    const float* __restrict__ vals, int64_t M, int64_t K, uint32_t n_cap, uint32_t nb_cap,
+    const float* __restrict__ vals, int64_t M, const uint32_t* __restrict__ list, uint32_t n_cap,
+    uint32_t nb_cap,
     const uint32_t* __restrict__ panel_ptr, uint32_t* __restrict__ brick_cols,
     uint64_t* __restrict__ brick_mask, uint32_t* __restrict__ brick_valptr,
     float* __restrict__ packed, uint32_t* src, uint8_t* __restrict__ col_seen) {
   extern __shared__ unsigned long long lds64[];
-  __shared__ int32_t rp[kPanel + 1];
-  unsigned long long* keys = lds64;                                  // [n_cap]
-  unsigned long long* pat = lds64 + n_cap;                           // [nb_cap]
-  uint32_t* vptr = reinterpret_cast<uint32_t*>(pat + nb_cap);        // [nb_cap]
+  __shared__ uint32_t sums[T / 64];
+  unsigned long long* pat = lds64;                                   // [nb_cap]
+  uint32_t* ent = reinterpret_cast<uint32_t*>(pat + nb_cap);         // [n_cap] rank << 16 | index
+  uint32_t* vptr = ent + n_cap;                                      // [nb_cap]
   uint16_t* at = reinterpret_cast<uint16_t*>(vptr + nb_cap);         // [n_cap]
-  const int64_t p = blockIdx.x;
+  const int64_t p = list ? list[blockIdx.x] : blockIdx.x;
+  const PanelRows x(rowptr, M, p);
+  if (x.n == 0 || x.n > n_cap) return;
+  const uint32_t n = x.n;
   const uint32_t pp = panel_ptr[p];
   const uint32_t nb = panel_ptr[p + 1] - pp;
-  const PanelExtent x = panel_extent(rowptr, colind, M, p, rp);
-  if (nb == 0) return;
-  const uint32_t n = (uint32_t)(x.e1 - x.e0);
-  if (n > n_cap || nb > nb_cap) return;   // (cannot happen: both caps are maxima over the panels)
-  for (uint32_t k = threadIdx.x; k < nb; k += kPanelThreads) pat[k] = 0;
-  for (uint32_t i = threadIdx.x; i < n; i += kPanelThreads) {
-    const uint32_t idx = min(src[x.e0 + i], n - 1);   // (always below n)
-    keys[i] = ((unsigned long long)(uint32_t)colind[x.e0 + idx] << 32) | idx;
-  }
+  if (nb == 0 || nb > nb_cap) return;   // (cannot happen: the cap is a maximum)
+  for (uint32_t k = threadIdx.x; k < nb; k += T) pat[k] = 0;
+  for (uint32_t i = threadIdx.x; i < n; i += T) ent[i] = src[x.e0 + i];
   __syncthreads();
 
-  // rank of each sorted entry's column = number of column changes before it; first
-  // occurrences write brick_cols; then the key's column is replaced by the rank.  The column
-  // before a batch of 64 is carried in a register: its key has been rewritten by then.
-  uint32_t carry = 0;
-  uint32_t col_before = 0xFFFFFFFFu;   // never a column (columns are below 2^31)
-  for (uint32_t base = 0; base < n; base += kPanelThreads) {
-    const uint32_t i = base + threadIdx.x;
-    uint32_t col = 0xFFFFFFFFu, first = 0;
-    if (i < n) col = (uint32_t)(keys[i] >> 32);
-    uint32_t prev = __shfl_up(col, 1, 64);
-    if (threadIdx.x == 0) prev = col_before;
-    if (i < n) first = (col != prev) ? 1u : 0u;
-    uint32_t total;
-    const uint32_t ex = wave_exclusive(first, &total);
-    if (i < n) {
-      const uint32_t rank = carry + ex + first - 1u;   // inclusive count of firsts, minus one
-      if (first && rank < nb * kBrickK) {
-        brick_cols[(int64_t)pp * kBrickK + rank] = col;
-        col_seen[col] = 1;
-      }
-      keys[i] = ((unsigned long long)rank << 32) | (uint32_t)keys[i];
+  // columns, from the first entry of each; the tail of the last brick padded.  Pattern bits.
+  const uint32_t ncols = (ent[n - 1] >> 16) + 1u;
+  auto rank_of = [&](uint32_t w) { return min(w >> 16, nb * kBrickK - 1); };
+  auto index_of = [&](uint32_t w) { return min(w & 0xFFFFu, n - 1); };
+  auto bit_of = [&](uint32_t w) { return x.row_of(index_of(w)) * kBrickK + rank_of(w) % kBrickK; };
+  for (uint32_t i = threadIdx.x; i < n; i += T) {
+    const uint32_t w = ent[i], rank = rank_of(w);
+    if (i == 0 || (ent[i - 1] >> 16) != (w >> 16)) {
+      const uint32_t col = (uint32_t)colind[x.e0 + index_of(w)];
+      brick_cols[(int64_t)pp * kBrickK + rank] = col;
+      col_seen[col] = 1;
     }
-    col_before = __shfl(col, 63, 64);
-    carry += total;
+    atomicOr(&pat[rank / kBrickK], 1ull << bit_of(w));
   }
-  __syncthreads();
-  for (uint32_t k = carry + threadIdx.x; k < nb * kBrickK; k += kPanelThreads)
+  for (uint32_t k = ncols + threadIdx.x; k < nb * kBrickK; k += T)
     brick_cols[(int64_t)pp * kBrickK + k] = kPadCol;
-
-  // a3: pattern bits, accumulated in LDS
-  for (uint32_t i = threadIdx.x; i < n; i += kPanelThreads) {
-    const uint32_t rank = (uint32_t)(keys[i] >> 32);
-    const int64_t e = x.e0 + (uint32_t)keys[i];
-    const uint32_t bit = (uint32_t)row_in_panel(rp, e) * kBrickK + rank % kBrickK;
-    if (rank / kBrickK < nb) atomicOr(&pat[rank / kBrickK], 1ull << bit);
-  }
   __syncthreads();
 
   // a4: value offsets = entries before the panel + popcounts of the panel's earlier bricks
-  uint32_t off = (uint32_t)x.e0;
-  for (uint32_t base = 0; base < nb; base += kPanelThreads) {
+  uint32_t off = 0;
+  for (uint32_t base = 0; base < nb; base += T) {
     const uint32_t k = base + threadIdx.x;
     uint32_t c = 0;
     if (k < nb) {
@@ -864,25 +1002,21 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_sort_build(
       c = (uint32_t)__popcll(m);
     }
     uint32_t total;
-    const uint32_t ex = wave_exclusive(c, &total);
+    const uint32_t ex = group_exclusive<T>(c, &total, sums);
     if (k < nb) {
       vptr[k] = off + ex;
-      brick_valptr[pp + k] = off + ex;
+      brick_valptr[pp + k] = (uint32_t)x.e0 + off + ex;
     }
     off += total;
   }
   __syncthreads();
-  for (uint32_t i = threadIdx.x; i < n; i += kPanelThreads) {
-    const uint32_t rank = (uint32_t)(keys[i] >> 32);
-    const int64_t e = x.e0 + (uint32_t)keys[i];
-    const uint32_t bit = (uint32_t)row_in_panel(rp, e) * kBrickK + rank % kBrickK;
-    const uint32_t k = min(rank / kBrickK, nb - 1);
-    const uint32_t pos = vptr[k] - (uint32_t)x.e0 +
-                         (uint32_t)__popcll(pat[k] & ((1ull << bit) - 1ull));
-    if (pos < n) at[pos] = (uint16_t)(uint32_t)keys[i];   // (always, for a census and a build that agree)
+  for (uint32_t i = threadIdx.x; i < n; i += T) {
+    const uint32_t w = ent[i], k = rank_of(w) / kBrickK;
+    const uint32_t pos = vptr[k] + (uint32_t)__popcll(pat[k] & ((1ull << bit_of(w)) - 1ull));
+    if (pos < n) at[pos] = (uint16_t)index_of(w);   // (always, for a census and a build that agree)
   }
   __syncthreads();
-  for (uint32_t i = threadIdx.x; i < n; i += kPanelThreads) {
+  for (uint32_t i = threadIdx.x; i < n; i += T) {
     const uint32_t e = (uint32_t)x.e0 + min((uint32_t)at[i], n - 1);
     packed[x.e0 + i] = vals[e];
     src[x.e0 + i] = e;
@@ -1229,58 +1363,81 @@ hipError_t launch_find_long_rows(const int32_t* rowptr, int64_t M, int threshold
 }
 
 // ---- sort-based per-panel path
-// keys of the sort for panels of up to max_nnz entries (a power of two), or 0 if too many
-uint32_t panel_sort_keys(uint32_t max_nnz) {
-  uint32_t n = 64;
-  while (n < max_nnz && n < kPanelMaxSortKeys) n *= 2;
-  return n >= max_nnz ? n : 0;
-}
-static size_t panel_sort_build_lds(uint32_t n_cap, uint32_t nb_cap) {
-  return (size_t)n_cap * 10 + (size_t)nb_cap * 12;
-}
-bool panel_sort_build_fits(uint32_t n_cap, uint32_t nb_cap) {
-  return n_cap != 0 && panel_sort_build_lds(n_cap, nb_cap) <= kPanelMaxLds;
-}
+bool panel_sort_fits(uint32_t max_nnz) { return max_nnz <= kSortBig; }
+int64_t panel_mid_list_elems(int64_t nnz) { return nnz / kSortSmall; }
+int64_t panel_big_list_elems(int64_t nnz) { return nnz / kSortMid; }
 
 hipError_t launch_panel_sort_census(const int32_t* rowptr, const int32_t* colind, int64_t M,
-                                    int64_t K, int64_t P, uint32_t n_cap, uint32_t* err,
-                                    uint32_t* ncols_p, uint32_t* order, hipStream_t s) {
+                                    int64_t K, int64_t P, int64_t nnz, uint32_t max_nnz,
+                                    const uint32_t* panel_nnzptr, uint32_t* mid_list,
+                                    uint32_t* big_list, PlanControl* ctl, uint32_t* ncols_p,
+                                    uint32_t* order, hipStream_t s) {
   if (P == 0) return hipSuccess;
-  const bool narrow = K < (int64_t(1) << 21) && n_cap <= 2048;   // (column, index) fits 32 bits
-  const size_t lds = (size_t)n_cap * (narrow ? 4 : 8);
-  const void* fn = narrow ? reinterpret_cast<const void*>(k_panel_sort_census<uint32_t>)
-                          : reinterpret_cast<const void*>(k_panel_sort_census<unsigned long long>);
+  const bool narrow = K < (int64_t(1) << 21);   // column and index (below 2048) fit 32 bits
+  const dim3 grid(grid_for(P, 4)), block(256);
+  if (narrow)
+    hipLaunchKernelGGL(k_panel_sort_census<uint32_t>, grid, block, 0, s, rowptr, colind, M, K, P,
+                       &ctl->err, ncols_p, order);
+  else
+    hipLaunchKernelGGL(k_panel_sort_census<unsigned long long>, grid, block, 0, s, rowptr, colind,
+                       M, K, P, &ctl->err, ncols_p, order);
+  if (max_nnz > kSortSmall) {
+    hipLaunchKernelGGL(k_panel_lists, dim3(grid_for(P, 1024)), dim3(1024), 0, s, panel_nnzptr, P,
+                       mid_list, big_list, ctl);
+    const dim3 at_most((unsigned)std::min(P, panel_mid_list_elems(nnz))), mid(kMidThreads);
+    if (narrow)
+      hipLaunchKernelGGL((k_panel_sort_census_listed<uint32_t, kMidThreads>), at_most, mid, 0, s,
+                         rowptr, colind, M, K, mid_list, &ctl->n_mid, &ctl->err, ncols_p, order);
+    else
+      hipLaunchKernelGGL((k_panel_sort_census_listed<unsigned long long, kMidThreads>), at_most, mid,
+                         0, s, rowptr, colind, M, K, mid_list, &ctl->n_mid, &ctl->err, ncols_p, order);
+  }
+  if (max_nnz > kSortMid)
+    hipLaunchKernelGGL((k_panel_sort_census_listed<unsigned long long, kBigThreads>),
+                       dim3((unsigned)std::min(P, panel_big_list_elems(nnz))), dim3(kBigThreads), 0,
+                       s, rowptr, colind, M, K, big_list, &ctl->n_big, &ctl->err, ncols_p, order);
+  return hipGetLastError();
+}
+
+template <int T>
+static hipError_t sort_build(const int32_t* rowptr, const int32_t* colind, const float* vals,
+                             int64_t M, const uint32_t* list, int64_t n_panels, uint32_t n_cap,
+                             uint32_t nb_cap, const uint32_t* panel_ptr, uint32_t* brick_cols,
+                             uint64_t* brick_mask, uint32_t* brick_valptr, float* packed,
+                             uint32_t* src, uint8_t* col_seen, hipStream_t s) {
+  if (n_panels == 0) return hipSuccess;
+  n_cap = (n_cap + 1) & ~1u;
+  nb_cap = std::min(nb_cap, n_cap);                             // a brick has an entry at least
+  const size_t lds = (size_t)nb_cap * 12 + (size_t)n_cap * 6;   // at most 18 bytes x kSortBig
   if (lds > 48 * 1024) {
-    const hipError_t e =
-        hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_panel_sort_build<T>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  if (narrow)
-    hipLaunchKernelGGL(k_panel_sort_census<uint32_t>, dim3((unsigned)P), dim3(kPanelThreads), lds,
-                       s, rowptr, colind, M, K, P, n_cap, err, ncols_p, order);
-  else
-    hipLaunchKernelGGL(k_panel_sort_census<unsigned long long>, dim3((unsigned)P),
-                       dim3(kPanelThreads), lds, s, rowptr, colind, M, K, P, n_cap, err, ncols_p,
-                       order);
+  hipLaunchKernelGGL(k_panel_sort_build<T>, dim3((unsigned)n_panels), dim3(T), lds, s, rowptr, colind,
+                     vals, M, list, n_cap, nb_cap, panel_ptr, brick_cols, brick_mask, brick_valptr,
+                     packed, src, col_seen);
   return hipGetLastError();
 }
 
 hipError_t launch_panel_sort_build(const int32_t* rowptr, const int32_t* colind, const float* vals,
-                                   int64_t M, int64_t K, int64_t P, uint32_t n_cap, uint32_t nb_cap,
-                                   const uint32_t* panel_ptr, uint32_t* brick_cols,
-                                   uint64_t* brick_mask, uint32_t* brick_valptr, float* packed,
-                                   uint32_t* src, uint8_t* col_seen, hipStream_t s) {
-  if (P == 0) return hipSuccess;
-  const size_t lds = panel_sort_build_lds(n_cap, nb_cap);
-  if (lds > 48 * 1024) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_panel_sort_build),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(k_panel_sort_build, dim3((unsigned)P), dim3(kPanelThreads), lds, s, rowptr,
-                     colind, vals, M, K, n_cap, nb_cap, panel_ptr, brick_cols, brick_mask,
-                     brick_valptr, packed, src, col_seen);
-  return hipGetLastError();
+                                   int64_t M, int64_t P, const PanelLists& l, uint32_t max_nnz,
+                                   uint32_t max_bricks, const uint32_t* panel_ptr,
+                                   uint32_t* brick_cols, uint64_t* brick_mask,
+                                   uint32_t* brick_valptr, float* packed, uint32_t* src,
+                                   uint8_t* col_seen, hipStream_t s) {
+  hipError_t e = sort_build<64>(rowptr, colind, vals, M, nullptr, P, std::min(max_nnz, kSortSmall),
+                                max_bricks, panel_ptr, brick_cols, brick_mask, brick_valptr, packed,
+                                src, col_seen, s);
+  if (e == hipSuccess)
+    e = sort_build<kMidThreads>(rowptr, colind, vals, M, l.mid, l.n_mid, std::min(max_nnz, kSortMid),
+                                max_bricks, panel_ptr, brick_cols, brick_mask, brick_valptr, packed,
+                                src, col_seen, s);
+  if (e == hipSuccess)
+    e = sort_build<kBigThreads>(rowptr, colind, vals, M, l.big, l.n_big, max_nnz, max_bricks,
+                                panel_ptr, brick_cols, brick_mask, brick_valptr, packed, src,
+                                col_seen, s);
+  return e;
 }
 
 // bitmap words (a power of two, at least 64) for a widest panel span of `span` columns, or 0 if

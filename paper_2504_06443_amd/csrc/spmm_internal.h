@@ -35,6 +35,7 @@ struct PlanControl {        // device, zeroed when a plan begins; read back at i
   uint32_t span, max_nnz;   // widest column span, most entries of a panel
   uint32_t max_cols;        // most active columns of a panel
   uint32_t nb;              // bricks
+  uint32_t n_mid, n_big;    // panels in the lists of the sort-based path
   uint32_t pad;
   unsigned long long n_active;   // active columns, summed over the panels
   unsigned long long n_blocks;   // blocks of four bricks, every panel rounded up
@@ -99,18 +100,25 @@ hipError_t launch_find_long_rows(const int32_t* rowptr, int64_t M, int threshold
 
 // per-panel path (LDS bitmap over the panel's column span)
 // per-panel path by sorting (any column span, panels of limited size)
-uint32_t panel_sort_keys(uint32_t max_nnz);   // 0: a panel has too many entries
-bool panel_sort_build_fits(uint32_t n_cap, uint32_t nb_cap);
+struct PanelLists {         // panels above 512 and above 2048 entries
+  const uint32_t *mid, *big;
+  uint32_t n_mid, n_big;
+};
+int64_t panel_mid_list_elems(int64_t nnz);   // room the lists need
+int64_t panel_big_list_elems(int64_t nnz);
+bool panel_sort_fits(uint32_t max_nnz);
 hipError_t launch_panel_sort_census(const int32_t* rowptr, const int32_t* colind, int64_t M,
-                                    int64_t K, int64_t P, uint32_t n_cap, uint32_t* err,
-                                    uint32_t* ncols_p,
+                                    int64_t K, int64_t P, int64_t nnz, uint32_t max_nnz,
+                                    const uint32_t* panel_nnzptr, uint32_t* mid_list,
+                                    uint32_t* big_list, PlanControl* ctl, uint32_t* ncols_p,
                                     uint32_t* order /* [nnz]; read back by the build from src */,
                                     hipStream_t s);
 hipError_t launch_panel_sort_build(const int32_t* rowptr, const int32_t* colind, const float* vals,
-                                   int64_t M, int64_t K, int64_t P, uint32_t n_cap, uint32_t nb_cap,
-                                   const uint32_t* panel_ptr, uint32_t* brick_cols,
-                                   uint64_t* brick_mask, uint32_t* brick_valptr, float* packed,
-                                   uint32_t* src, uint8_t* col_seen, hipStream_t s);
+                                   int64_t M, int64_t P, const PanelLists& l, uint32_t max_nnz,
+                                   uint32_t max_bricks, const uint32_t* panel_ptr,
+                                   uint32_t* brick_cols, uint64_t* brick_mask,
+                                   uint32_t* brick_valptr, float* packed, uint32_t* src,
+                                   uint8_t* col_seen, hipStream_t s);
 uint32_t panel_bitmap_words(uint32_t span);   // 0: span too wide for the per-panel path
 hipError_t launch_panel_census(const int32_t* rowptr, const int32_t* colind, int64_t M, int64_t K,
                                int64_t P, uint32_t words_cap, uint32_t* err, uint32_t* ncols_p,
