@@ -314,8 +314,9 @@ typedef struct spmm_worklist_info {
   int32_t n_tile;         /* columns of C per wavefront (16, 32, ... 128)     */
   int32_t n_tiles;        /* ceil(N / n_tile)                                 */
   int32_t num_cus;        /* compute units of the plan's device               */
-  int32_t resident_waves_per_cu; /* wavefronts of the MFMA kernel variant for
-                             this N that fit on one CU at a time; num_waves =
+  int32_t resident_waves_per_cu; /* wavefronts of the MFMA kernel, at the
+                             power-of-two tile of this N, that fit on one CU at
+                             a time; num_waves =
                              max(1, ceil(panels * n_tiles / (num_cus * this))) */
 } spmm_worklist_info_t;
 

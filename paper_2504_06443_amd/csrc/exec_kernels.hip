@@ -744,22 +744,21 @@ int mfma_fp32_tile(int64_t N, int64_t K) {
   return 16 * (tiles > 1 && N % 32 == 0 ? (t + 1) / 2 * 2 : t);
 }
 
-// Wavefronts of the MFMA kernel that fit on one CU at a time, for the kernel variant that
-// (N, K) selects: the "thread blocks per SM" of Eq. 7.
+// The "thread blocks per SM" of Eq. 7: wavefronts of the MFMA kernel that fit on one CU at a time,
+// taken at the power-of-two tile of N (the fast kernel's where N is a multiple of its vector width,
+// else the general kernel's), not at the narrower tile that runs.  The narrower tiles hold up to
+// half as many wavefronts more (5 x 16 columns: 24 a CU, 8 x 16: 16), and Eq. 7 then splits more
+// panels: more partial tiles, and calls of spmm_exec_noalloc that no longer fit the static scratch.
 int mfma_resident_waves_per_cu(int64_t N, int64_t K) {
-  if (mfma_32bit_shape(N, K)) {
-    switch (mfma_fp32_tile(N, K) / 16) {
-      case 1: return occupancy_fast_t<1>();
-      case 2: return occupancy_fast_t<2>();
-      case 3: return occupancy_fast_t<3>();
-      case 4: return occupancy_fast_t<4>();
-      case 5: return occupancy_fast_t<5>();
-      case 6: return occupancy_fast_t<6>();
-      case 7: return occupancy_fast_t<7>();
+  const int tile = mfma_tile_for(N);
+  if (mfma_fast_shape(N, K)) {
+    switch (tile) {
+      case 16: return occupancy_fast_t<1>();
+      case 32: return occupancy_fast_t<2>();
+      case 64: return occupancy_fast_t<4>();
       default: return occupancy_fast_t<8>();
     }
   }
-  const int tile = mfma_tile_for(N);
   const bool aligned = N % (tile >= 64 ? 4 : tile / 16) == 0;
   switch (tile) {
     case 16: return occupancy_t<1, true>();

@@ -37,3 +37,17 @@ def test_any_width_any_dword_alignment(gpu, offset, split):  # noqa: F811
         assert not np.isnan(Cg).any(), "every element of C must be written"
         check_c(Cg, Cref, S)
         assert bool((whole[:offset] == GUARD).all()) and bool((whole[offset + A.M * N:] == GUARD).all())
+
+
+@pytest.mark.parametrize("N,as_wide_as", [(48, 64), (44, 64), (80, 128), (96, 128), (144, 128), (400, 128)])
+def test_narrow_tiles_do_not_split_more(gpu, N, as_wide_as):  # noqa: F811
+    """Eq. 7's capacity is that of the power-of-two tile, so a panel is cut into no more parts (and
+    takes no more of the static scratch of spmm_exec_noalloc) because a narrower tile runs."""
+    A = W.power_law(M=120000, target_nnz=None, cap=2000, alpha=1.6, seed=41)
+    plan = make_plan(gpu, A)
+    mine, wide = gpu.spmm_plan_worklist(plan, N), gpu.spmm_plan_worklist(plan, as_wide_as)
+    assert mine["n_tile"] not in (16, 32, 64, 128)
+    assert mine["resident_waves_per_cu"] == wide["resident_waves_per_cu"]
+    if N <= as_wide_as:   # the same number of tiles, hence the same list
+        assert mine["n_mfma_items"] == wide["n_mfma_items"]
+        assert mine["num_waves"] == wide["num_waves"]
