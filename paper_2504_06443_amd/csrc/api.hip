@@ -571,6 +571,23 @@ done:
   return SPMM_OK;
 }
 
+// Makes `device` current while it lives: the setters take a plan on any current device, and one that
+// allocates or launches has to do so on the plan's.
+class OnDevice {
+ public:
+  explicit OnDevice(int device) : ok_(hipGetDevice(&before_) == hipSuccess) {
+    if (ok_ && before_ != device) moved_ = ok_ = hipSetDevice(device) == hipSuccess;
+  }
+  ~OnDevice() { if (moved_) (void)hipSetDevice(before_); }
+  OnDevice(const OnDevice&) = delete;
+  OnDevice& operator=(const OnDevice&) = delete;
+  bool ok() const { return ok_; }
+
+ private:
+  int before_ = 0;
+  bool ok_, moved_ = false;
+};
+
 // What the CSR kernels read besides rowptr, from the brick format (the caller's CSR arrays may be
 // gone).  The default route sends no panel to them, so a plan is made without: 8 B/nnz of memory,
 // two copies at plan time and a third of an update's stores.  Called with the device idle.
@@ -1211,6 +1228,8 @@ done:
 int spmm_plan_set_route(spmm_plan_t* pl, int route) {
   if (!pl) return fail(SPMM_EINVAL, "plan is NULL");
   if (route < SPMM_ROUTE_AUTO || route > SPMM_ROUTE_CLASS) return fail(SPMM_EINVAL, "bad route");
+  const OnDevice here(pl->device);
+  if (!here.ok()) return fail(SPMM_EHIP, "device %d cannot be made current", pl->device);
   if (hipDeviceSynchronize() != hipSuccess) return fail(SPMM_EHIP, "hipDeviceSynchronize failed");
   const bool csr = route == SPMM_ROUTE_VALU || route == SPMM_ROUTE_CLASS;
   if (csr && !pl->csr_on) {
