@@ -705,10 +705,12 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_census(
 // compare-exchange inside a lane is a min and a max, across lanes one cross-lane read a key, and only
 // steps across wavefronts go through LDS (a sort all through LDS moved four words a pair and step).
 // The census leaves the sorted entries, rank << 16 | index inside the panel, for the build.
-// 20,360 panels of 46 entries, the largest 3000: the search-based kernels 195 us, these 130.
+// 20,360 panels of 46 entries, the largest 3000: the search-based kernels 195 us, these 87 (keys of 32 bits
+// for the 48 panels above 2048: 30 -> 19 us).
 // 18,750 panels of 430: a sort through LDS by one wavefront 163 + 101 us (census, build), now 84 + 67.
 constexpr uint32_t kSortSmall = 512, kSortMid = 2048, kSortBig = 8192;
 constexpr int kMidThreads = 256, kBigThreads = 1024;
+static_assert(kMidThreads * 8 == kSortMid && kBigThreads * 8 == kSortBig, "eight keys a lane");
 
 // the panels of more than kSortSmall and of more than kSortMid entries, listed in any order
 __global__ __launch_bounds__(1024) void k_panel_lists(const uint32_t* __restrict__ panel_nnzptr,
@@ -730,17 +732,15 @@ __global__ __launch_bounds__(1024) void k_panel_lists(const uint32_t* __restrict
   if (which >= 0) (which ? big_list : mid_list)[base[which] + at] = (uint32_t)p;
 }
 
-// KT = uint32_t packs (column << 11 | index): fewer than 2^21 columns, at most 2048 entries
-template <typename KT> struct SortKey;
-template <> struct SortKey<unsigned long long> {
-  static __device__ unsigned long long make(uint32_t col, uint32_t idx) { return ((unsigned long long)col << 32) | idx; }
-  static __device__ uint32_t col(unsigned long long k) { return (uint32_t)(k >> 32); }
-  static __device__ uint32_t idx(unsigned long long k) { return (uint32_t)k; }
-};
-template <> struct SortKey<uint32_t> {
-  static __device__ uint32_t make(uint32_t col, uint32_t idx) { return (col << 11) | idx; }
-  static __device__ uint32_t col(uint32_t k) { return k >> 11; }
-  static __device__ uint32_t idx(uint32_t k) { return k & 2047u; }
+// A key is column << B | index.  In 32 bits, half the moves of a 64-bit one: B = 11 for panels of up to
+// kSortMid entries and fewer than 2^21 columns, B = 13 for up to kSortBig and fewer than 2^19 (fewer,
+// so that no key is all ones, which pads).  In 64 bits: B = 32.
+constexpr int kMidBits = 11, kBigBits = 13;
+static_assert(kSortMid <= 1u << kMidBits && kSortBig <= 1u << kBigBits, "indexes fit");
+template <typename KT, int B> struct SortKey {
+  static __device__ KT make(uint32_t col, uint32_t idx) { return ((KT)col << B) | idx; }
+  static __device__ uint32_t col(KT k) { return (uint32_t)(k >> B); }
+  static __device__ uint32_t idx(KT k) { return (uint32_t)(k & (((KT)1 << B) - 1)); }
 };
 
 // entries and row starts of panel p, as scalars (uniform addresses)
@@ -862,7 +862,7 @@ __device__ inline void group_sort(KT (&k)[R], KT* lds) {
 }
 
 // one panel of at most T * R entries: sort, count the columns, leave the order; returns the count
-template <int T, int R, typename KT>
+template <int T, int R, int B, typename KT>
 __device__ inline uint32_t group_census(const int32_t* __restrict__ colind, const PanelRows& x,
                                         int64_t K, uint32_t* err, uint32_t* __restrict__ order,
                                         KT* lds, uint32_t* sums) {
@@ -876,7 +876,7 @@ __device__ inline uint32_t group_census(const int32_t* __restrict__ colind, cons
     if (i < x.n) {
       const int32_t j = colind[x.e0 + i];
       bad |= x.check(colind, K, i, j);
-      k[r] = SortKey<KT>::make((uint32_t)j, i);
+      k[r] = SortKey<KT, B>::make((uint32_t)j, i);
     }
   }
   if (bad) atomicOr(err, bad);
@@ -891,8 +891,8 @@ __device__ inline uint32_t group_census(const int32_t* __restrict__ colind, cons
   uint32_t first = 0;   // bit r: a column begins at element t * R + r
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    const bool is = r == 0 ? t == 0 || SortKey<KT>::col(k[0]) != SortKey<KT>::col(before)
-                           : SortKey<KT>::col(k[r]) != SortKey<KT>::col(k[r > 0 ? r - 1 : 0]);
+    const bool is = r == 0 ? t == 0 || SortKey<KT, B>::col(k[0]) != SortKey<KT, B>::col(before)
+                           : SortKey<KT, B>::col(k[r]) != SortKey<KT, B>::col(k[r > 0 ? r - 1 : 0]);
     first |= (is && t * R + r < x.n ? 1u : 0u) << r;
   }
   uint32_t total;
@@ -900,50 +900,71 @@ __device__ inline uint32_t group_census(const int32_t* __restrict__ colind, cons
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     rank += (first >> r) & 1u;
-    if (t * R + r < x.n) order[x.e0 + t * R + r] = rank << 16 | SortKey<KT>::idx(k[r]);
+    if (t * R + r < x.n) order[x.e0 + t * R + r] = rank << 16 | SortKey<KT, B>::idx(k[r]);
   }
   return total;
 }
 
-// census of the panels of at most kSortSmall entries, a wavefront each
-template <typename KT>
-__global__ __launch_bounds__(256) void k_panel_sort_census(
+// Census of the panels of at most kSortMid entries.  Those above kSortSmall, which are listed, take
+// the first mid_blocks workgroups, one each (the host does not know their count yet); a wavefront
+// takes each of the others.  One launch: the few hundred listed panels of a graph are a chain of
+// latencies that hides among the many small ones (20,360 panels, 159 of them listed: 24 + 16 us as
+// two launches, 27 so).
+template <typename KT, int B, bool MID>
+__global__ __launch_bounds__(kMidThreads) void k_panel_sort_census(
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind, int64_t M, int64_t K,
-    int64_t P, uint32_t* err, uint32_t* __restrict__ ncols_p, uint32_t* __restrict__ order) {
+    int64_t P, const uint32_t* __restrict__ mid_list, const uint32_t* __restrict__ n_mid,
+    uint32_t mid_blocks, uint32_t* err, uint32_t* __restrict__ ncols_p, uint32_t* __restrict__ order) {
   if (*err & (kErrRowptrEnds | kErrRowptrOrder)) return;   // uniform: nothing below is safe
-  const int64_t p = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if constexpr (MID) {
+    if (blockIdx.x < mid_blocks) {
+      __shared__ KT lds[kSortMid];
+      __shared__ uint32_t sums[kMidThreads / 64];
+      if (blockIdx.x >= *n_mid) return;
+      const int64_t p = mid_list[blockIdx.x];
+      const PanelRows x(rowptr, M, p);
+      uint32_t cols = 0;
+      if (x.n <= kMidThreads * 4) cols = group_census<kMidThreads, 4, B, KT>(colind, x, K, err, order, lds, sums);
+      else if (x.n <= kSortMid) cols = group_census<kMidThreads, 8, B, KT>(colind, x, K, err, order, lds, sums);
+      if (threadIdx.x == 0) ncols_p[p] = cols;
+      return;
+    }
+  }
+  const int64_t p = (int64_t)(blockIdx.x - mid_blocks) * (kMidThreads / 64) +
+                    __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (p >= P) return;
   const PanelRows x(rowptr, M, p);
   if (x.n > kSortSmall) return;
   uint32_t cols = 0;
   KT* none = nullptr;
   if (x.n == 0) cols = 0;
-  else if (x.n <= 64) cols = group_census<64, 1, KT>(colind, x, K, err, order, none, nullptr);
-  else if (x.n <= 128) cols = group_census<64, 2, KT>(colind, x, K, err, order, none, nullptr);
-  else if (x.n <= 256) cols = group_census<64, 4, KT>(colind, x, K, err, order, none, nullptr);
-  else cols = group_census<64, 8, KT>(colind, x, K, err, order, none, nullptr);
+  else if (x.n <= 64) cols = group_census<64, 1, B, KT>(colind, x, K, err, order, none, nullptr);
+  else if (x.n <= 128) cols = group_census<64, 2, B, KT>(colind, x, K, err, order, none, nullptr);
+  else if (x.n <= 256) cols = group_census<64, 4, B, KT>(colind, x, K, err, order, none, nullptr);
+  else cols = group_census<64, 8, B, KT>(colind, x, K, err, order, none, nullptr);
   if ((threadIdx.x & 63) == 0) ncols_p[p] = cols;
 }
 
-// census of the listed panels, of at most T * 8 entries, a workgroup each
-template <typename KT, int T>
-__global__ __launch_bounds__(T) void k_panel_sort_census_listed(
+// census of the listed panels of at most kSortBig entries, a workgroup each
+template <typename KT, int B>
+__global__ __launch_bounds__(kBigThreads) void k_panel_sort_census_big(
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind, int64_t M, int64_t K,
     const uint32_t* __restrict__ list, const uint32_t* __restrict__ listed, uint32_t* err,
     uint32_t* __restrict__ ncols_p, uint32_t* __restrict__ order) {
-  __shared__ KT lds[T * 8];
-  __shared__ uint32_t sums[T / 64];
+  __shared__ KT lds[kSortBig];
+  __shared__ uint32_t sums[kBigThreads / 64];
   if (blockIdx.x >= *listed) return;   // (the host does not know the count yet)
   if (*err & (kErrRowptrEnds | kErrRowptrOrder)) return;
   const int64_t p = list[blockIdx.x];
   const PanelRows x(rowptr, M, p);
   uint32_t cols = 0;
-  if (x.n <= T * 4) cols = group_census<T, 4, KT>(colind, x, K, err, order, lds, sums);
-  else if (x.n <= T * 8) cols = group_census<T, 8, KT>(colind, x, K, err, order, lds, sums);
+  if (x.n <= kBigThreads * 4) cols = group_census<kBigThreads, 4, B, KT>(colind, x, K, err, order, lds, sums);
+  else if (x.n <= kSortBig) cols = group_census<kBigThreads, 8, B, KT>(colind, x, K, err, order, lds, sums);
   if (threadIdx.x == 0) ncols_p[p] = cols;
 }
 
-// a2 (placing half), a3 and a4 of the listed panels (no list: of all) of at most n_cap entries, from the
+// a2 (placing half), a3 and a4 of the listed panels (n_first of `list`, then those of `rest`; no list:
+// of all) of at most n_cap entries, from the
 // sorted entries that the census left in `src` (which this kernel then overwrites with the entry of
 // each packed value).  T threads a panel.  Dynamic LDS: patterns (nb_cap x u64), the sorted entries
 // (n_cap words), value offsets (nb_cap words), the order of the packed values (n_cap x two bytes),
@@ -951,8 +972,8 @@ __global__ __launch_bounds__(T) void k_panel_sort_census_listed(
 template <int T>
 __global__ __launch_bounds__(T) void k_panel_sort_build(
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind,
-    const float* __restrict__ vals, int64_t M, const uint32_t* __restrict__ list, uint32_t n_cap,
-    uint32_t nb_cap,
+    const float* __restrict__ vals, int64_t M, const uint32_t* __restrict__ list,
+    const uint32_t* __restrict__ rest, uint32_t n_first, uint32_t n_cap, uint32_t nb_cap,
     const uint32_t* __restrict__ panel_ptr, uint32_t* __restrict__ brick_cols,
     uint64_t* __restrict__ brick_mask, uint32_t* __restrict__ brick_valptr,
     float* __restrict__ packed, uint32_t* src, uint8_t* __restrict__ col_seen) {
@@ -962,7 +983,7 @@ __global__ __launch_bounds__(T) void k_panel_sort_build(
   uint32_t* ent = reinterpret_cast<uint32_t*>(pat + nb_cap);         // [n_cap] rank << 16 | index
   uint32_t* vptr = ent + n_cap;                                      // [nb_cap]
   uint16_t* at = reinterpret_cast<uint16_t*>(vptr + nb_cap);         // [n_cap]
-  const int64_t p = list ? list[blockIdx.x] : blockIdx.x;
+  const int64_t p = !list ? blockIdx.x : blockIdx.x < n_first ? list[blockIdx.x] : rest[blockIdx.x - n_first];
   const PanelRows x(rowptr, M, p);
   if (x.n == 0 || x.n > n_cap) return;
   const uint32_t n = x.n;
@@ -1373,36 +1394,42 @@ hipError_t launch_panel_sort_census(const int32_t* rowptr, const int32_t* colind
                                     uint32_t* big_list, PlanControl* ctl, uint32_t* ncols_p,
                                     uint32_t* order, hipStream_t s) {
   if (P == 0) return hipSuccess;
-  const bool narrow = K < (int64_t(1) << 21);   // column and index (below 2048) fit 32 bits
-  const dim3 grid(grid_for(P, 4)), block(256);
-  if (narrow)
-    hipLaunchKernelGGL(k_panel_sort_census<uint32_t>, grid, block, 0, s, rowptr, colind, M, K, P,
-                       &ctl->err, ncols_p, order);
-  else
-    hipLaunchKernelGGL(k_panel_sort_census<unsigned long long>, grid, block, 0, s, rowptr, colind,
-                       M, K, P, &ctl->err, ncols_p, order);
-  if (max_nnz > kSortSmall) {
+  const bool narrow = K < (int64_t(1) << (32 - kMidBits)), narrow_big = K < (int64_t(1) << (32 - kBigBits));
+  const bool mid = max_nnz > kSortSmall;
+  const unsigned mid_blocks = mid ? (unsigned)std::min(P, panel_mid_list_elems(nnz)) : 0u;
+  if (mid)
     hipLaunchKernelGGL(k_panel_lists, dim3(grid_for(P, 1024)), dim3(1024), 0, s, panel_nnzptr, P,
                        mid_list, big_list, ctl);
-    const dim3 at_most((unsigned)std::min(P, panel_mid_list_elems(nnz))), mid(kMidThreads);
-    if (narrow)
-      hipLaunchKernelGGL((k_panel_sort_census_listed<uint32_t, kMidThreads>), at_most, mid, 0, s,
-                         rowptr, colind, M, K, mid_list, &ctl->n_mid, &ctl->err, ncols_p, order);
-    else
-      hipLaunchKernelGGL((k_panel_sort_census_listed<unsigned long long, kMidThreads>), at_most, mid,
-                         0, s, rowptr, colind, M, K, mid_list, &ctl->n_mid, &ctl->err, ncols_p, order);
+  const dim3 grid(mid_blocks + grid_for(P, kMidThreads / 64)), block(kMidThreads);
+#define SPMM_LAUNCH_CENSUS(KT, BITS, MID)                                                         \
+  hipLaunchKernelGGL((k_panel_sort_census<KT, BITS, MID>), grid, block, 0, s, rowptr, colind, M, K, \
+                     P, mid_list, &ctl->n_mid, mid_blocks, &ctl->err, ncols_p, order)
+  if (narrow) {
+    if (mid) SPMM_LAUNCH_CENSUS(uint32_t, kMidBits, true);
+    else SPMM_LAUNCH_CENSUS(uint32_t, kMidBits, false);
+  } else {
+    if (mid) SPMM_LAUNCH_CENSUS(unsigned long long, 32, true);
+    else SPMM_LAUNCH_CENSUS(unsigned long long, 32, false);
   }
-  if (max_nnz > kSortMid)
-    hipLaunchKernelGGL((k_panel_sort_census_listed<unsigned long long, kBigThreads>),
-                       dim3((unsigned)std::min(P, panel_big_list_elems(nnz))), dim3(kBigThreads), 0,
-                       s, rowptr, colind, M, K, big_list, &ctl->n_big, &ctl->err, ncols_p, order);
+#undef SPMM_LAUNCH_CENSUS
+  if (max_nnz > kSortMid) {
+    const dim3 at_most((unsigned)std::min(P, panel_big_list_elems(nnz))), big(kBigThreads);
+    if (narrow_big)
+      hipLaunchKernelGGL((k_panel_sort_census_big<uint32_t, kBigBits>), at_most, big, 0, s, rowptr,
+                         colind, M, K, big_list, &ctl->n_big, &ctl->err, ncols_p, order);
+    else
+      hipLaunchKernelGGL((k_panel_sort_census_big<unsigned long long, 32>), at_most, big, 0, s, rowptr,
+                         colind, M, K, big_list, &ctl->n_big, &ctl->err, ncols_p, order);
+  }
   return hipGetLastError();
 }
 
+constexpr uint32_t kSortBuildRound = 256;   // a workgroup per CU
+
 template <int T>
 static hipError_t sort_build(const int32_t* rowptr, const int32_t* colind, const float* vals,
-                             int64_t M, const uint32_t* list, int64_t n_panels, uint32_t n_cap,
-                             uint32_t nb_cap, const uint32_t* panel_ptr, uint32_t* brick_cols,
+                             int64_t M, const uint32_t* list, const uint32_t* rest,
+                             uint32_t n_first, int64_t n_panels, uint32_t n_cap, uint32_t nb_cap, const uint32_t* panel_ptr, uint32_t* brick_cols,
                              uint64_t* brick_mask, uint32_t* brick_valptr, float* packed,
                              uint32_t* src, uint8_t* col_seen, hipStream_t s) {
   if (n_panels == 0) return hipSuccess;
@@ -1415,8 +1442,8 @@ static hipError_t sort_build(const int32_t* rowptr, const int32_t* colind, const
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL(k_panel_sort_build<T>, dim3((unsigned)n_panels), dim3(T), lds, s, rowptr, colind,
-                     vals, M, list, n_cap, nb_cap, panel_ptr, brick_cols, brick_mask, brick_valptr,
-                     packed, src, col_seen);
+                     vals, M, list, rest, n_first, n_cap, nb_cap, panel_ptr, brick_cols, brick_mask,
+                     brick_valptr, packed, src, col_seen);
   return hipGetLastError();
 }
 
@@ -1426,17 +1453,21 @@ hipError_t launch_panel_sort_build(const int32_t* rowptr, const int32_t* colind,
                                    uint32_t* brick_cols, uint64_t* brick_mask,
                                    uint32_t* brick_valptr, float* packed, uint32_t* src,
                                    uint8_t* col_seen, hipStream_t s) {
-  hipError_t e = sort_build<64>(rowptr, colind, vals, M, nullptr, P, std::min(max_nnz, kSortSmall),
+  hipError_t e = sort_build<64>(rowptr, colind, vals, M, nullptr, nullptr, 0, P, std::min(max_nnz, kSortSmall),
                                 max_bricks, panel_ptr, brick_cols, brick_mask, brick_valptr, packed,
                                 src, col_seen, s);
+  // Few listed panels are one round of workgroups: together, in the time of the largest (48 panels
+  // above 2048 entries and 159 above 512: 15 + 10 us as two launches, 10 as one).  Many are
+  // ahead with the smaller workgroups and the LDS that the smaller ones need.
+  const bool together = l.n_big > 0 && l.n_big + l.n_mid <= kSortBuildRound;
+  if (e == hipSuccess && !together)
+    e = sort_build<kMidThreads>(rowptr, colind, vals, M, l.mid, nullptr, l.n_mid, l.n_mid,
+                                std::min(max_nnz, kSortMid), max_bricks, panel_ptr, brick_cols,
+                                brick_mask, brick_valptr, packed, src, col_seen, s);
   if (e == hipSuccess)
-    e = sort_build<kMidThreads>(rowptr, colind, vals, M, l.mid, l.n_mid, std::min(max_nnz, kSortMid),
-                                max_bricks, panel_ptr, brick_cols, brick_mask, brick_valptr, packed,
-                                src, col_seen, s);
-  if (e == hipSuccess)
-    e = sort_build<kBigThreads>(rowptr, colind, vals, M, l.big, l.n_big, max_nnz, max_bricks,
-                                panel_ptr, brick_cols, brick_mask, brick_valptr, packed, src,
-                                col_seen, s);
+    e = sort_build<kBigThreads>(rowptr, colind, vals, M, l.big, l.mid, l.n_big,
+                                together ? l.n_big + l.n_mid : l.n_big, max_nnz, max_bricks, panel_ptr,
+                                brick_cols, brick_mask, brick_valptr, packed, src, col_seen, s);
   return e;
 }
 

@@ -19,6 +19,7 @@ def panels_of(sizes, K, seed):
     rows, cols = [], []
     for p, n in enumerate(sizes):
         shared = rng.choice(K, size=max(1, n // 8), replace=False)
+        shared[0] = K - 1                                       # the largest key of the panel
         cells = set()
         while len(cells) < n:
             c = int(shared[rng.integers(len(shared))]) if rng.random() < 0.5 else int(rng.integers(K))
@@ -29,9 +30,11 @@ def panels_of(sizes, K, seed):
                           rng.uniform(-1, 1, len(rows)).astype(np.float32))
 
 
-@pytest.mark.parametrize("K", [1_500_000, 3_000_000], ids=["packed_keys", "wide_keys"])
-@pytest.mark.parametrize("sizes", [SIZES, SIZES[:10], SIZES[:14] + (0, 0), (8193, 5)],
-                         ids=["all", "small", "mid", "beyond"])
+# 2^19 columns and 2^21 are the first that the 32-bit keys of the largest and the other panels refuse
+@pytest.mark.parametrize("K", [(1 << 19) - 1, 1 << 19, (1 << 21) - 1, 1 << 21, 3_000_000])
+@pytest.mark.parametrize("sizes", [SIZES, SIZES[:10], SIZES[:14] + (0, 0), (8193, 5), (600,) * 255 + (2100,),
+                                   (600,) * 256 + (2100,)],
+                         ids=["all", "small", "mid", "beyond", "one_round", "above_a_round"])
 def test_class_edges(gpu, K, sizes):  # noqa: F811
     A = panels_of(sizes, K, seed=len(sizes))
     print(f"panel sizes {sizes} K={K}", flush=True)
