@@ -705,7 +705,7 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_census(
 // compare-exchange inside a lane is a min and a max, across lanes one cross-lane read a key, and only
 // steps across wavefronts go through LDS (a sort all through LDS moved four words a pair and step).
 // The census leaves the sorted entries, rank << 16 | index inside the panel, for the build.
-// 20,360 panels of 46 entries, the largest 3000: the search-based kernels 195 us, these 87 (keys of 32 bits
+// 20,360 panels of 46 entries, the largest 3000: the search-based kernels 195 us, these 81 (keys of 32 bits
 // for the 48 panels above 2048: 30 -> 19 us).
 // 18,750 panels of 430: a sort through LDS by one wavefront 163 + 101 us (census, build), now 84 + 67.
 constexpr uint32_t kSortSmall = 512, kSortMid = 2048, kSortBig = 8192;
@@ -1434,8 +1434,11 @@ static hipError_t sort_build(const int32_t* rowptr, const int32_t* colind, const
                              uint32_t* src, uint8_t* col_seen, hipStream_t s) {
   if (n_panels == 0) return hipSuccess;
   n_cap = (n_cap + 1) & ~1u;
-  nb_cap = std::min(nb_cap, n_cap);                             // a brick has an entry at least
-  const size_t lds = (size_t)nb_cap * 12 + (size_t)n_cap * 6;   // at most 18 bytes x kSortBig
+  // All bricks of a panel but the last have four columns, so four entries at least.  With room for a
+  // brick per entry the small class took 9 KiB a wavefront, 17 on a CU; with 4.6 KiB a CU is full
+  // (20,360 panels 31 -> 25 us; spmm_plan of a million-row graph 302 -> 283).
+  nb_cap = std::min(nb_cap, (n_cap + kBrickK - 1) / kBrickK);
+  const size_t lds = (size_t)nb_cap * 12 + (size_t)n_cap * 6;   // at most 9 bytes x kSortBig
   if (lds > 48 * 1024) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_panel_sort_build<T>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
