@@ -87,7 +87,7 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t *rowptr, const in
  *           until that kernel has run
  *
  * Replaces the packed brick values (and the values in CSR order that a plan holds
- * while its route sends panels to the CSR kernel); pattern, masks,
+ * once a route has sent panels to the CSR kernel); pattern, masks,
  * offsets, synergy counts and work lists are unchanged (an entry whose new value
  * is 0 stays a stored entry).  Enqueues only; allocates nothing.  Must not run
  * concurrently with spmm_exec on the same plan.

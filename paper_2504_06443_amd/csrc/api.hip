@@ -244,11 +244,12 @@ struct spmm_plan {
   float* vals = nullptr;          // nnz + 1
   uint32_t* src = nullptr;        // CSR entry of each packed value (value-only updates)
   // what the vector-ALU CSR kernels read (device): rowptr is kept from the start, the rest is made
-  // when a route first sends panels there (csr_on), and kept up to date while one does
+  // when a route first sends panels there, and every update keeps it up to date from then on
+  // (csr_on), whatever the route: a product captured under that route may be replayed at any time
   int32_t* rowptr = nullptr;
   uint32_t* panel_nnzptr = nullptr;       // first CSR entry of each panel
   bool csr_on = false;
-  bool csr_may_lag = false;       // an update captured while it was off may be replayed at any time
+  bool csr_may_lag = false;       // an update captured before that may be replayed at any time
   char* csr_arena = nullptr;
   int32_t* colind = nullptr;
   float* csr_vals = nullptr;
@@ -590,7 +591,7 @@ class OnDevice {
 
 // What the CSR kernels read besides rowptr, from the brick format (the caller's CSR arrays may be
 // gone).  The default route sends no panel to them, so a plan is made without: 8 B/nnz of memory,
-// two copies at plan time and a third of an update's stores.  Called with the device idle.
+// two copies at plan time and half of an update's stores.  Called with the device idle.
 int enable_csr(spmm_plan_t* pl) {
   int status = SPMM_OK;
   if ((status = need_panel_ptr(pl)) != SPMM_OK) return status;
@@ -1231,13 +1232,11 @@ int spmm_plan_set_route(spmm_plan_t* pl, int route) {
   const OnDevice here(pl->device);
   if (!here.ok()) return fail(SPMM_EHIP, "device %d cannot be made current", pl->device);
   if (hipDeviceSynchronize() != hipSuccess) return fail(SPMM_EHIP, "hipDeviceSynchronize failed");
-  const bool csr = route == SPMM_ROUTE_VALU || route == SPMM_ROUTE_CLASS;
-  if (csr && !pl->csr_on) {
+  if ((route == SPMM_ROUTE_VALU || route == SPMM_ROUTE_CLASS) && !pl->csr_on) {
     const int status = enable_csr(pl);
     if (status != SPMM_OK) return status;
   }
   if (const int status = need_panel_ptr(pl)) return status;
-  pl->csr_on = csr;   // (updates write the CSR copy only while a route reads it)
   pl->route = route;
   pl->drop_lists(true);
   return SPMM_OK;

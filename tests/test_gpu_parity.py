@@ -627,7 +627,7 @@ def test_heavy_first_order_gives_the_same_product(gpu):
 
 
 def test_updates_reach_the_csr_kernel_whenever_they_run(gpu):
-    """The values in CSR order exist only while a route reads them: updates before the route is
+    """The values in CSR order exist from the first route on that reads them: updates before it is
     set, while it is set, after it was left and come back to, and replayed from a graph that was
     captured before it was ever set."""
     import torch
@@ -667,3 +667,47 @@ def test_updates_reach_the_csr_kernel_whenever_they_run(gpu):
         graph.replay()
         torch.cuda.synchronize()
         expect(v, None)
+
+
+@pytest.mark.parametrize("route", ["VALU", "CLASS"])
+def test_captured_csr_products_see_every_later_update(gpu, route):
+    """A product captured while a route sends panels to the CSR kernel multiplies the values of the
+    last update, also of one made after the route was left, and of one captured there and replayed."""
+    import torch
+    A = W.power_law(M=1500, target_nnz=None, cap=700, seed=58)
+    route = getattr(gpu, "ROUTE_" + route)
+    B = W.dense_b(A.K, 32, 8)
+    Bd = torch.from_numpy(B).cuda()
+    Cd = torch.empty((A.M, 32), device="cuda")
+    plan = make_plan(gpu, A)
+    gpu.spmm_plan_set_route(plan, route)
+    assert gpu.spmm_plan_worklist(plan, 32)["n_valu_panels"] > 0
+    gpu.spmm_exec_noalloc(plan, Bd, Cd)          # its list is in the scratch: the graph copies nothing
+    product, update = torch.cuda.CUDAGraph(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(product):
+        gpu.spmm_exec_noalloc(plan, Bd, Cd)
+    rng = np.random.default_rng(5)
+
+    def fresh():
+        return rng.uniform(-1, 1, A.nnz).astype(np.float32)
+
+    def expect(v):
+        Cd.fill_(float("nan"))
+        product.replay()
+        torch.cuda.synchronize()
+        check_c(Cd.cpu().numpy(), *oracle.spmm_f64(A.rowptr, A.colind, v, B))
+
+    gpu.spmm_plan_set_route(plan, gpu.ROUTE_AUTO)
+    for _ in range(2):
+        v = fresh()
+        gpu.spmm_plan_update_values(plan, torch.from_numpy(v).cuda())
+        expect(v)
+    vals = torch.from_numpy(fresh()).cuda()
+    with torch.cuda.graph(update):
+        gpu.spmm_plan_update_values(plan, vals)
+    gpu.spmm_plan_set_route(plan, route)
+    for _ in range(2):
+        v = fresh()
+        vals.copy_(torch.from_numpy(v))
+        update.replay()
+        expect(v)
