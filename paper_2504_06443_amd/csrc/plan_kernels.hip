@@ -288,22 +288,26 @@ __global__ __launch_bounds__(kThreads) void k_update_values(
   }
 }
 
-// Columns and values in CSR order again, from the bricks: one wavefront per brick, lane l holds the
-// element of pattern bit l.
+// Columns and values in CSR order again, from the bricks: a wavefront takes a brick at a time, lane l
+// the element of pattern bit l.  At most kRestoreBlocks workgroups walk the bricks: a launch has
+// fewer than 2^32 threads, a plan up to 2^30 bricks.
+constexpr int kRestoreBlocks = 1 << 16;
+
 __global__ __launch_bounds__(kThreads) void k_restore_csr(
     const uint32_t* __restrict__ brick_cols, const uint64_t* __restrict__ brick_mask,
     const uint32_t* __restrict__ brick_valptr, const float* __restrict__ packed,
     const uint32_t* __restrict__ src, int64_t nb, int32_t* __restrict__ colind,
     float* __restrict__ csr_vals) {
   const int lane = threadIdx.x & 63;
-  const int64_t b = (int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
-  if (b >= nb) return;
-  const uint64_t mask = brick_mask[b];
-  if (!((mask >> lane) & 1ull)) return;
-  const uint32_t pos = brick_valptr[b] + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
-  const uint32_t e = src[pos];
-  colind[e] = (int32_t)brick_cols[b * kBrickK + (lane & (kBrickK - 1))];
-  csr_vals[e] = packed[pos];
+  const int64_t stride = (int64_t)gridDim.x * (kThreads / 64);
+  for (int64_t b = (int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6); b < nb; b += stride) {
+    const uint64_t mask = brick_mask[b];
+    if (!((mask >> lane) & 1ull)) continue;
+    const uint32_t pos = brick_valptr[b] + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
+    const uint32_t e = src[pos];
+    colind[e] = (int32_t)brick_cols[b * kBrickK + (lane & (kBrickK - 1))];
+    csr_vals[e] = packed[pos];
+  }
 }
 
 // a5: per-panel class (Table 1, integer compare) and class totals, histogram of bricks by stored
@@ -1361,8 +1365,9 @@ hipError_t launch_update_values(const float* vals, const uint32_t* src, int64_t 
 hipError_t launch_restore_csr(const BrickFormat& f, const uint32_t* src, int64_t nb, int32_t* colind,
                               float* csr_vals, hipStream_t s) {
   if (nb == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_restore_csr, dim3(grid_for(nb, kThreads / 64)), dim3(kThreads), 0, s,
-                     f.brick_cols, f.brick_mask, f.brick_valptr, f.vals, src, nb, colind, csr_vals);
+  const unsigned g = (unsigned)std::min<int64_t>(grid_for(nb, kThreads / 64), kRestoreBlocks);
+  hipLaunchKernelGGL(k_restore_csr, dim3(g), dim3(kThreads), 0, s, f.brick_cols, f.brick_mask,
+                     f.brick_valptr, f.vals, src, nb, colind, csr_vals);
   return hipGetLastError();
 }
 

@@ -1,0 +1,37 @@
+"""Plans whose counts are at the upper end of what is accepted, where a launch of a wavefront a brick
+would hold 2^32 threads.  The matrices are regular, so that C and the format follow from the
+construction."""
+import pytest
+
+from test_gpu_parity import gpu  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def test_csr_route_with_2_to_26_bricks(gpu):  # noqa: F811
+    """Row r of every panel holds columns 256 r .. 256 r + 255: 1024 bricks a panel, one row each.
+    Columns, values and a later update all reach the CSR kernel."""
+    import torch
+    P, K, N = 1 << 16, 4096, 4
+    M = 16 * P
+    rowptr = torch.arange(M + 1, dtype=torch.int64, device="cuda").mul_(256).to(torch.int32)
+    colind = torch.arange(K, dtype=torch.int32, device="cuda").repeat(P)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+
+    def fresh():
+        return torch.randint(-4, 5, (M * 256,), generator=gen, device="cuda").to(torch.float32)
+
+    B = torch.randint(-4, 5, (K, N), generator=gen, device="cuda").to(torch.float32)
+
+    def expected(vals):   # whole numbers: every order of summation gives the same
+        return torch.bmm(vals.view(P, 16, 256).transpose(0, 1).contiguous(), B.view(16, 256, N)).transpose(0, 1)
+
+    vals = fresh()
+    plan = gpu.spmm_plan(M, K, rowptr, colind, vals)
+    assert gpu.spmm_plan_sizes(plan)["n_bricks"] == 1 << 26
+    print("planned 2^26 bricks", flush=True)
+    gpu.spmm_plan_set_route(plan, gpu.ROUTE_VALU)
+    assert torch.equal(gpu.spmm_exec(plan, B).view(P, 16, N), expected(vals))
+    vals = fresh()
+    gpu.spmm_plan_update_values(plan, vals)
+    assert torch.equal(gpu.spmm_exec(plan, B).view(P, 16, N), expected(vals))
