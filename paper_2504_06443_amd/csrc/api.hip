@@ -879,7 +879,7 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
     status = fail(SPMM_EFORMAT, "invalid colind (columns of a row not strictly ascending)");
     goto done;
   }
-  words_cap = panel_bitmap_words(h_ctl.span);
+  words_cap = panel_bitmap_words(h_ctl.span, P);
 
   // Three ways to the same format.  The bitmap kernels walk a bitmap over the panel's column
   // span; that pays while the bitmaps are not much longer than the entry lists (band-like
@@ -889,7 +889,7 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
   //   0.1 (blocks, 7.9 M entries) 141 / 173 us, 1.3 (cells, 0.4 M) 96 / 111, 1.3 (band of three a row)
   //   120 / 123, 4.2 (cells, 2 M, fill 0.05) 239 / 140, 4.2 (fill 0.8) 163 / 143.
   // Bitmap against search at 4: 0.6 / 1.0 ms.
-  sort_fits = panel_sort_fits(h_ctl.max_nnz);
+  sort_fits = panel_sort_fits(P, nnz, h_ctl.max_nnz);
   if (words_cap != 0 && (int64_t)words_cap * P <= (sort_fits ? 2 : 8) * nnz) path = kPathBitmap;
   else if (sort_fits) path = kPathSort;
   if (path == kPathBitmap) {

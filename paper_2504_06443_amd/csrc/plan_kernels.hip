@@ -26,6 +26,7 @@ namespace spmm {
 namespace {
 
 constexpr int kThreads = 256;
+constexpr int64_t kMaxLaunchThreads = int64_t(1) << 32;   // a launch has fewer than this
 
 inline unsigned grid_for(int64_t n, int threads = kThreads) {
   int64_t g = (n + threads - 1) / threads;
@@ -289,8 +290,8 @@ __global__ __launch_bounds__(kThreads) void k_update_values(
 }
 
 // Columns and values in CSR order again, from the bricks: a wavefront takes a brick at a time, lane l
-// the element of pattern bit l.  At most kRestoreBlocks workgroups walk the bricks: a launch has
-// fewer than 2^32 threads, a plan up to 2^30 bricks.
+// the element of pattern bit l.  At most kRestoreBlocks workgroups walk the bricks: a plan holds up to
+// 2^30 of them, a launch fewer than kMaxLaunchThreads threads.
 constexpr int kRestoreBlocks = 1 << 16;
 
 __global__ __launch_bounds__(kThreads) void k_restore_csr(
@@ -1391,7 +1392,12 @@ hipError_t launch_find_long_rows(const int32_t* rowptr, int64_t M, int threshold
 }
 
 // ---- sort-based per-panel path
-bool panel_sort_fits(uint32_t max_nnz) { return max_nnz <= kSortBig; }
+// (the census is the largest launch: a wavefront a panel and, of 256 threads, a workgroup for each
+// 512 entries; a launch has fewer than 2^32 threads, which M from 2^30 on would take)
+bool panel_sort_fits(int64_t P, int64_t nnz, uint32_t max_nnz) {
+  return max_nnz <= kSortBig &&
+         64 * (P + kMidThreads / 64) + kMidThreads * panel_mid_list_elems(nnz) < kMaxLaunchThreads;
+}
 int64_t panel_mid_list_elems(int64_t nnz) { return nnz / kSortSmall; }
 int64_t panel_big_list_elems(int64_t nnz) { return nnz / kSortMid; }
 
@@ -1482,8 +1488,9 @@ hipError_t launch_panel_sort_build(const int32_t* rowptr, const int32_t* colind,
 }
 
 // bitmap words (a power of two, at least 64) for a widest panel span of `span` columns, or 0 if
-// that does not fit the LDS bitmap
-uint32_t panel_bitmap_words(uint32_t span) {
+// that does not fit the LDS bitmap, or a workgroup a panel does not fit a launch
+uint32_t panel_bitmap_words(uint32_t span, int64_t P) {
+  if (P * kPanelThreads >= kMaxLaunchThreads) return 0;
   uint32_t words = 64;
   while ((uint64_t)words * 32 < span && words < kPanelMaxWords) words *= 2;
   return (uint64_t)words * 32 >= span ? words : 0;

@@ -106,7 +106,7 @@ struct PanelLists {         // panels above 512 and above 2048 entries
 };
 int64_t panel_mid_list_elems(int64_t nnz);   // room the lists need
 int64_t panel_big_list_elems(int64_t nnz);
-bool panel_sort_fits(uint32_t max_nnz);
+bool panel_sort_fits(int64_t P, int64_t nnz, uint32_t max_nnz);
 hipError_t launch_panel_sort_census(const int32_t* rowptr, const int32_t* colind, int64_t M,
                                     int64_t K, int64_t P, int64_t nnz, uint32_t max_nnz,
                                     const uint32_t* panel_nnzptr, uint32_t* mid_list,
@@ -119,7 +119,7 @@ hipError_t launch_panel_sort_build(const int32_t* rowptr, const int32_t* colind,
                                    uint32_t* brick_cols, uint64_t* brick_mask,
                                    uint32_t* brick_valptr, float* packed, uint32_t* src,
                                    uint8_t* col_seen, hipStream_t s);
-uint32_t panel_bitmap_words(uint32_t span);   // 0: span too wide for the per-panel path
+uint32_t panel_bitmap_words(uint32_t span, int64_t P);   // 0: beyond the per-panel path
 hipError_t launch_panel_census(const int32_t* rowptr, const int32_t* colind, int64_t M, int64_t K,
                                int64_t P, uint32_t words_cap, uint32_t* err, uint32_t* ncols_p,
                                hipStream_t s);

@@ -1,8 +1,11 @@
 """Plans whose counts are at the upper end of what is accepted, where a launch of a wavefront a brick
-would hold 2^32 threads.  The matrices are regular, so that C and the format follow from the
-construction."""
+or a panel would hold 2^32 threads.  The matrices are regular or nearly empty, so that C and the
+format follow from the construction."""
+import numpy as np
 import pytest
 
+import oracle
+from paper_2504_06443_amd import workloads as W
 from test_gpu_parity import gpu  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -35,3 +38,27 @@ def test_csr_route_with_2_to_26_bricks(gpu):  # noqa: F811
     vals = fresh()
     gpu.spmm_plan_update_values(plan, vals)
     assert torch.equal(gpu.spmm_exec(plan, B).view(P, 16, N), expected(vals))
+
+
+def test_plan_of_2_to_30_rows(gpu):  # noqa: F811
+    """2^26 panels, nearly all empty: the bricks are those of the few others by themselves."""
+    import torch
+    M, K = 1 << 30, 1000
+    panels = np.array([0, 1, 5, 1 << 22, (1 << 25) + 3, (1 << 26) - 1])
+    A = W.uniform_random(16 * len(panels), K, 0.05, 7)
+    ref = oracle.build_bricks(A.M, A.rowptr, A.colind, A.vals)
+    length = torch.zeros(M, dtype=torch.int32, device="cuda")
+    rows = (panels[:, None] * 16 + np.arange(16)).ravel()
+    length[torch.from_numpy(rows).cuda()] = torch.from_numpy(np.diff(A.rowptr).astype(np.int32)).cuda()
+    rowptr = torch.zeros(M + 1, dtype=torch.int32, device="cuda")
+    torch.cumsum(length, 0, dtype=torch.int32, out=rowptr[1:])
+    del length
+    assert int(rowptr[-1]) == A.nnz
+    print("planning 2^30 rows", flush=True)
+    plan = gpu.spmm_plan(M, K, rowptr, torch.from_numpy(A.colind).cuda(), torch.from_numpy(A.vals).cuda())
+    got = gpu.spmm_plan_export(plan)
+    for k in ("brick_cols", "brick_mask", "brick_valptr", "vals"):
+        assert np.array_equal(got[k], ref[k]), k
+    bricks = np.diff(got["panel_ptr"])
+    assert np.array_equal(bricks[panels], np.diff(ref["panel_ptr"]))
+    assert int(bricks.sum()) == len(ref["brick_mask"]) and got["panel_ptr"][0] == 0
