@@ -3,6 +3,7 @@
 // Section 5 (Eq. 6-7), kernel dispatch, the synergy model of Section 4 /
 // Table 1, and export accessors.
 #include "../../include/spmm.h"
+#include "device_keep.h"
 #include "spmm_internal.h"
 
 #include <algorithm>
@@ -14,7 +15,6 @@
 #include <mutex>
 #include <new>
 #include <optional>
-#include <unordered_map>
 #include <vector>
 
 using namespace spmm;
@@ -44,115 +44,8 @@ int fail(int code, const char* fmt, ...) {
 constexpr double kHbmBytesPerS = 8.0e12;    // MI355X published HBM3E bandwidth
 constexpr double kMfmaFp32Flops = 157.3e12; // MI355X published dense fp32 matrix peak
 
-// Device memory of plans and of their construction, kept for the next plan when it is let go.
-// hipMalloc and hipFree of tens of megabytes take 25 to 300 us each (they map and unmap), together
-// more than building a plan of 8 M entries; a program that makes a plan per matrix, or drops and
-// makes work lists, asks for the same sizes again.  Only memory that nothing uses any more comes
-// here: its owner has waited for the device, or for the one stream that used it.  At most kKeepBytes
-// a device are kept (0.2 % of it), each block for kKeepCalls later requests; all of it is given back
-// when an allocation here fails, and by spmm_plan_destroy(NULL).  Blocks below kKeepMin go straight to the
-// runtime, which hands those out without mapping.
-constexpr size_t kKeepBytes = size_t(512) << 20, kKeepMin = size_t(256) << 10;
-constexpr uint64_t kKeepCalls = 256;
-
-class DeviceKeep {
- public:
-  static DeviceKeep& instance() {
-    static DeviceKeep* keep = new DeviceKeep();   // never destroyed: plans may outlive static data
-    return *keep;
-  }
-  hipError_t get(void** p, size_t bytes) {
-    if (bytes < kKeepMin) return hipMalloc(p, bytes);
-    const size_t page = bytes < (size_t(2) << 20) ? size_t(64) << 10 : size_t(2) << 20;
-    bytes = (bytes + page - 1) / page * page;   // what the runtime takes for it
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    if (take(p, bytes, dev)) return hipSuccess;
-    e = hipMalloc(p, bytes);
-    if (e == hipErrorOutOfMemory) {
-      (void)hipGetLastError();
-      give_back(dev);
-      e = hipMalloc(p, bytes);
-    }
-    if (e != hipSuccess) return e;
-    std::lock_guard<std::mutex> lock(mutex_);
-    try { live_[*p] = Block{*p, bytes, dev, 0}; }
-    catch (const std::bad_alloc&) { }             // put() then frees it
-    return hipSuccess;
-  }
-  // idle: nothing that was enqueued still uses the block
-  void put(void* p, bool idle) {
-    if (!p) return;
-    int dev = -1;
-    if (idle && hipGetDevice(&dev) != hipSuccess) idle = false;
-    {
-      std::lock_guard<std::mutex> lock(mutex_);
-      const auto it = live_.find(p);
-      if (it != live_.end()) {
-        Block b = it->second;
-        live_.erase(it);
-        size_t kept = b.bytes;
-        for (const Block& k : kept_) kept += k.dev == b.dev ? k.bytes : 0;
-        if (idle && dev == b.dev && kept <= kKeepBytes) {
-          b.stamp = clock_;
-          try { kept_.push_back(b); return; }
-          catch (const std::bad_alloc&) { }
-        }
-      }
-    }
-    (void)hipFree(p);
-  }
-  void give_back(int dev /* -1: all */) {
-    while (void* p = evict([&](const Block& b) { return dev < 0 || b.dev == dev; })) (void)hipFree(p);
-  }
-
- private:
-  struct Block { void* p; size_t bytes; int dev; uint64_t stamp; };
-
-  bool take(void** p, size_t bytes, int dev) {
-    bool found = false;
-    uint64_t now;
-    {
-      std::lock_guard<std::mutex> lock(mutex_);
-      now = ++clock_;
-      size_t best = kept_.size();
-      for (size_t i = 0; i < kept_.size(); ++i) {
-        const Block& b = kept_[i];
-        if (b.dev == dev && b.bytes >= bytes && b.bytes <= bytes + bytes / 2 &&
-            (best == kept_.size() || b.bytes < kept_[best].bytes))
-          best = i;
-      }
-      if (best < kept_.size()) {
-        const Block b = kept_[best];
-        try {
-          live_[b.p] = b;
-          kept_.erase(kept_.begin() + (ptrdiff_t)best);
-          *p = b.p;
-          found = true;
-        } catch (const std::bad_alloc&) { }
-      }
-    }
-    while (void* old = evict([&](const Block& b) { return now > b.stamp + kKeepCalls; })) (void)hipFree(old);
-    return found;
-  }
-  template <typename Which> void* evict(Which which) {
-    std::lock_guard<std::mutex> lock(mutex_);
-    for (size_t i = 0; i < kept_.size(); ++i)
-      if (which(kept_[i])) {
-        void* p = kept_[i].p;
-        kept_.erase(kept_.begin() + (ptrdiff_t)i);
-        return p;
-      }
-    return nullptr;
-  }
-
-  std::mutex mutex_;
-  std::vector<Block> kept_;
-  std::unordered_map<void*, Block> live_;
-  uint64_t clock_ = 0;
-};
-
+// memory that is not kept (freed with hipFree), but may take what is
+hipError_t keep_malloc(char** p, size_t bytes) { return DeviceKeep::instance().allocate((void**)p, bytes); }
 hipError_t keep_get(char** p, size_t bytes) { return DeviceKeep::instance().get((void**)p, bytes); }
 void keep_put(void* p, bool idle) { DeviceKeep::instance().put(p, idle); }
 
@@ -650,7 +543,7 @@ int build_tm32(spmm_plan_t* pl, uint32_t num, uint32_t den, hipStream_t s) {
 
   t1.cap = need(4 * nb + P + 1, 4) + need(Q, 4) + need(Q + 1, 4) + need(Q, 1) + need(4 * nb, 4) +
            need(nb, 1) + need((int64_t)scan_tmp_elems(std::max<int64_t>(2 * 4 * nb + 2, Q + 1)), 4);
-  HIP_TRY(hipMalloc((void**)&t1.base, t1.cap));
+  HIP_TRY(keep_malloc(&t1.base, t1.cap));
   cpre = t1.take<uint32_t>(4 * nb + P + 1);
   nbc_q = t1.take<uint32_t>(Q);
   sp_ptr_tmp = t1.take<uint32_t>(Q + 1);
@@ -666,7 +559,7 @@ int build_tm32(spmm_plan_t* pl, uint32_t num, uint32_t den, hipStream_t s) {
   nbc = h_nbc;   // at most the bricks of the 16-row format
 
   t2.cap = need((nbc + kFormatPad) * kBrickK, 4) + need(2 * nbc, 8) + need(2 * nbc + 1, 4);
-  HIP_TRY(hipMalloc((void**)&t2.base, t2.cap));
+  HIP_TRY(keep_malloc(&t2.base, t2.cap));
   bc_cols_tmp = t2.take<uint32_t>((nbc + kFormatPad) * kBrickK);
   tmask = t2.take<unsigned long long>(2 * nbc);
   pos_tmp = t2.take<uint32_t>(2 * nbc + 1);
@@ -688,7 +581,7 @@ int build_tm32(spmm_plan_t* pl, uint32_t num, uint32_t den, hipStream_t s) {
   keep.cap = need(Q + 1, 4) + need(Q, 1) + need((nbc + kFormatPad) * kBrickK, 4) + need(nbc + 1, 4) +
              need(nbr, 1) + need(nbr, 8) + need(nbr + 1, 4) + need(nnz + 64, 4) +
              need(n_meta, sizeof(Tm32Meta)) + need(4 * nb, 4) + need(nb, 1) + need(2 * nbc + 1, 4);
-  HIP_TRY(hipMalloc((void**)&keep.base, keep.cap));
+  HIP_TRY(keep_malloc(&keep.base, keep.cap));
   f.arena = keep.base;
   f.Q = Q; f.nbc = nbc; f.nbr = nbr;
   for (int64_t q = 0; q < Q; ++q) f.n_merged += h_merged[q];
