@@ -17,6 +17,7 @@
 //    array.  The second question is only asked once per active column (the
 //    first-occurrence entries, compacted into a list); the other entries of that column
 //    follow a link to it.  One thread per entry (or per row / panel / brick).
+#include "panel_layout.h"
 #include "spmm_internal.h"
 
 #include <algorithm>
@@ -591,11 +592,7 @@ __global__ __launch_bounds__(kScanThreads) void k_panel_scan(const uint32_t* __r
 // brick_valptr needs no scan across panels).  Used when the widest panel span and the largest
 // brick count of a panel fit in LDS; other matrices take the search-based kernels above.
 constexpr int kPanelThreads = 64;
-constexpr int kGroupWords = 8;   // bitmap words per entry of the coarse rank table
-constexpr uint32_t kPanelFineWords = 2048;          // bitmaps with a rank per word (16 KiB with it)
-constexpr uint32_t kPanelStageMax = 2048;           // entries of a panel staged in LDS (12 KiB)
 constexpr uint32_t kPanelMaxWords = 32768;          // 1 Mi columns of span
-constexpr size_t kPanelMaxLds = 150 * 1024;         // of the 160 KiB of a CU
 
 struct PanelExtent {
   int64_t e0, e1;        // entries of the panel
@@ -1496,14 +1493,8 @@ uint32_t panel_bitmap_words(uint32_t span, int64_t P) {
   return (uint64_t)words * 32 >= span ? words : 0;
 }
 
-// LDS bytes of k_panel_build for a bitmap of words_cap words, panels of up to nb_cap bricks, rank
-// table entries every `group` words and up to stage_cap staged entries
-static size_t panel_build_lds(uint32_t words_cap, uint32_t nb_cap, uint32_t group, uint32_t stage_cap) {
-  return (size_t)nb_cap * 8 + ((size_t)words_cap + words_cap / group + 1 + nb_cap) * 4 +
-         (size_t)stage_cap * 6;
-}
 bool panel_build_fits(uint32_t words_cap, uint32_t nb_cap) {
-  return words_cap != 0 && panel_build_lds(words_cap, nb_cap, kGroupWords, 0) <= kPanelMaxLds;
+  return panel_build_layout(words_cap, nb_cap, 0).bytes != 0;
 }
 
 hipError_t launch_panel_census(const int32_t* rowptr, const int32_t* colind, int64_t M, int64_t K,
@@ -1527,13 +1518,11 @@ hipError_t launch_panel_build(const int32_t* rowptr, const int32_t* colind, cons
                               uint64_t* brick_mask, uint32_t* brick_valptr, float* packed,
                               uint32_t* src, uint8_t* col_seen, hipStream_t s) {
   if (P == 0) return hipSuccess;
-  // A rank per word of the bitmap while that is short (no walk through a group of words for every
-  // entry); staging for panels of up to kPanelStageMax entries, where LDS has room for it.
-  const bool fine = words_cap <= kPanelFineWords;
-  const uint32_t group = fine ? 1 : kGroupWords;
-  uint32_t stage_cap = (std::min(max_nnz, kPanelStageMax) + 1) & ~1u;
-  if (panel_build_lds(words_cap, nb_cap, group, stage_cap) > kPanelMaxLds) stage_cap = 0;
-  const size_t lds = panel_build_lds(words_cap, nb_cap, group, stage_cap);
+  const PanelBuildLayout layout = panel_build_layout(words_cap, nb_cap, max_nnz);
+  if (layout.bytes == 0) return hipErrorInvalidValue;   // (the caller asked panel_build_fits)
+  const bool fine = layout.group == 1;
+  const uint32_t stage_cap = layout.stage_cap;
+  const size_t lds = layout.bytes;
   const void* fn = fine ? reinterpret_cast<const void*>(k_panel_build<1>)
                         : reinterpret_cast<const void*>(k_panel_build<kGroupWords>);
   if (lds > 48 * 1024) {

@@ -79,3 +79,19 @@ def test_bitmap_beyond_the_default_lds_limit(gpu):  # noqa: F811
                        rng.uniform(-1, 1, 16 * 1100).astype(np.float32))
     assert_format_equal(gpu.spmm_plan_export(make_plan(gpu, A)),
                         oracle.build_bricks(A.M, A.rowptr, A.colind, A.vals))
+
+
+# with 2048 words of bitmap: the last count of bricks with a rank for every word, the first without, the
+# last that fits, and the first that the search-based kernels take
+@pytest.mark.parametrize("bricks", [11434, 11435, 12031, 12032])
+def test_bitmap_build_at_its_limits_of_bricks(gpu, bricks):  # noqa: F811
+    rng = np.random.default_rng(bricks)
+    cols = rng.choice(65534, size=4 * bricks - 2, replace=False) + 1
+    cols = np.concatenate([[0, 65535], cols])                   # the whole span of 2048 words
+    again = rng.choice(cols, size=3000, replace=False)          # columns of two rows
+    rows = rng.integers(0, 15, size=len(cols))
+    A = W.csr_from_coo(16, 65536, np.concatenate([rows, np.full(len(again), 15)]), np.concatenate([cols, again]),
+                       rng.uniform(-1, 1, len(cols) + len(again)).astype(np.float32))
+    plan = make_plan(gpu, A)
+    assert gpu.spmm_plan_sizes(plan)["n_bricks"] == bricks
+    assert_format_equal(gpu.spmm_plan_export(plan), oracle.build_bricks(A.M, A.rowptr, A.colind, A.vals))
