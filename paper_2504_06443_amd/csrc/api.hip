@@ -302,7 +302,7 @@ int build_host_list(spmm_plan_t* pl, int64_t N, const HostList** out) {
     const bool bf16 = pl->precision != SPMM_PRECISION_FP32 &&
                       bf16_path_shape(std::max<int64_t>(N, 1), pl->K);
     const int tile = bf16 ? mfma_tile_for(std::max<int64_t>(N, 1))
-                          : mfma_fp32_tile(std::max<int64_t>(N, 1), pl->K);
+                          : mfma_fp32_tile(std::max<int64_t>(N, 1), pl->K, pl->nnz);
     hl->info.n_tile = tile;
     hl->info.n_tiles = (int32_t)ceil_div(std::max<int64_t>(N, 1), tile);
     hl->info.num_cus = pl->num_cus;
@@ -949,7 +949,7 @@ bool uses_tm32(const spmm_plan_t* pl, const float* B, int64_t N, const float* C)
   if (pl->panel_height != 32 || !pl->tm32.arena) return false;
   if (pl->route != SPMM_ROUTE_AUTO && pl->route != SPMM_ROUTE_MFMA) return false;
   if (pl->precision != SPMM_PRECISION_FP32) return false;
-  if (pl->nnz + 64 >= (int64_t(1) << 30)) return false;   // the kernel's 32-bit value offsets
+  if (!mfma_32bit_values(pl->nnz)) return false;   // the kernel's 32-bit value offsets
   return mfma_fast_shape(N, pl->K) && ptr_is_aligned16(B) && ptr_is_aligned16(C);
 }
 

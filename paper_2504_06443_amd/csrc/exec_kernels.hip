@@ -721,12 +721,14 @@ bool mfma_fast_shape(int64_t N, int64_t K) {
   return N % V == 0 && mfma_32bit_shape(N, K);
 }
 
-// what the fast FP32 kernel serves: B rows reachable by 32-bit byte offsets
+// what the fast FP32 kernel serves: B rows reachable by 32-bit byte offsets, and the packed values
+// with their 64 spare floats
 bool mfma_32bit_shape(int64_t N, int64_t K) {
   return K > 0 && (double)K * (double)N * 4.0 < 4294967296.0;
 }
+bool mfma_32bit_values(int64_t nnz) { return nnz + 64 < (int64_t(1) << 30); }
 
-// Columns of C per wavefront of the FP32 kernel that serves (N, K).  The fast kernel takes as few
+// Columns of C per wavefront of the FP32 kernel that serves (N, K, nnz).  The fast kernel takes as few
 // tiles of at most 128 columns as N needs, all of the same width, in steps of 16 columns: N = 77
 // is one tile of 80 (five MFMAs a brick), not one of 128 (eight), and N = 144 two of 80, not two
 // of 128.  Measured on 131,072 rows of 3x3 blocks (322 k bricks), against tiles of 16, 32, 64 and
@@ -737,8 +739,8 @@ bool mfma_32bit_shape(int64_t N, int64_t K) {
 // tiles of 80 against 96 columns at N = 160: 384 / 328 us; of 112 against 128 at N = 224: 515 /
 // 458.  Other N have no such lines to keep, and there the narrower tile is ahead (N = 144 on the
 // blocks: 137 / 152).
-int mfma_fp32_tile(int64_t N, int64_t K) {
-  if (!mfma_32bit_shape(N, K)) return mfma_tile_for(N);
+int mfma_fp32_tile(int64_t N, int64_t K, int64_t nnz) {
+  if (!mfma_32bit_shape(N, K) || !mfma_32bit_values(nnz)) return mfma_tile_for(N);
   const int64_t tiles = std::max<int64_t>(1, (N + 127) / 128);
   const int t = (int)std::max<int64_t>(1, ((N + 15) / 16 + tiles - 1) / tiles);
   return 16 * (tiles > 1 && N % 32 == 0 ? (t + 1) / 2 * 2 : t);
@@ -772,9 +774,8 @@ hipError_t launch_spmm_mfma(const BrickFormat& f, const WorkItem* items, int64_t
                             const float* B, float* C, float* partial, int64_t M, int64_t N,
                             int64_t K, int64_t nnz, hipStream_t s) {
   if (n_items == 0 || N == 0) return hipSuccess;
-  // the fast kernel addresses the packed values (and their 64 spare floats) by 32-bit byte offsets
-  if (mfma_32bit_shape(N, K) && nnz + 64 < (int64_t(1) << 30)) {
-    const int tile = mfma_fp32_tile(N, K);
+  if (mfma_32bit_shape(N, K) && mfma_32bit_values(nnz)) {
+    const int tile = mfma_fp32_tile(N, K, nnz);
     unsigned gx = (unsigned)((n_items + kWavesPerBlock - 1) / kWavesPerBlock);
     gx = (gx + kXcds - 1) / kXcds * kXcds;  // whole rounds over the XCDs
     const dim3 grid(gx, (unsigned)((N + tile - 1) / tile)), block(64 * kWavesPerBlock);

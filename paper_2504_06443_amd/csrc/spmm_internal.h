@@ -160,9 +160,10 @@ hipError_t launch_restore_csr(const BrickFormat& f, const uint32_t* src, int64_t
                               float* csr_vals, hipStream_t s);
 
 int mfma_tile_for(int64_t N);   // power-of-two tiles: 16, 32, 64 or 128 columns per wavefront
-int mfma_fp32_tile(int64_t N, int64_t K);   // columns per wavefront of the FP32 kernel
+int mfma_fp32_tile(int64_t N, int64_t K, int64_t nnz);   // columns per wavefront of the FP32 kernel
 int mfma_resident_waves_per_cu(int64_t N, int64_t K);
-bool mfma_32bit_shape(int64_t N, int64_t K);   // B below 4 GiB: the fast FP32 kernel
+bool mfma_32bit_shape(int64_t N, int64_t K);   // B below 4 GiB: the fast FP32 kernel,
+bool mfma_32bit_values(int64_t nnz);           // where the packed values are too
 // shapes of the 32-row kernel when B and C are 16-byte aligned: N a multiple of the vector
 // width, B below 4 GiB
 bool mfma_fast_shape(int64_t N, int64_t K);

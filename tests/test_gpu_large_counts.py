@@ -1,5 +1,5 @@
 """Plans whose counts are at the upper end of what is accepted, where a launch of a wavefront a brick
-or a panel would hold 2^32 threads.  The matrices are regular or nearly empty, so that C and the
+or a panel would hold 2^32 threads, or 32-bit byte offsets end.  The matrices are regular or nearly empty, so that C and the
 format follow from the construction."""
 import numpy as np
 import pytest
@@ -62,3 +62,20 @@ def test_plan_of_2_to_30_rows(gpu):  # noqa: F811
     bricks = np.diff(got["panel_ptr"])
     assert np.array_equal(bricks[panels], np.diff(ref["panel_ptr"]))
     assert int(bricks.sum()) == len(ref["brick_mask"]) and got["panel_ptr"][0] == 0
+
+
+def test_tile_reported_where_values_are_beyond_32bit_offsets(gpu):  # noqa: F811
+    """2^30 stored entries: the general kernel runs, on tiles of a power of two columns, and the work
+    list says so."""
+    import torch
+    M = K = 1 << 15
+    rowptr = torch.arange(M + 1, dtype=torch.int64, device="cuda").mul_(K).to(torch.int32)
+    colind = torch.arange(K, dtype=torch.int32, device="cuda").repeat(M)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    vals = torch.randint(-1, 2, (M, K), generator=gen, device="cuda", dtype=torch.int8).to(torch.float32)
+    plan = gpu.spmm_plan(M, K, rowptr, colind, vals.flatten())
+    del rowptr, colind
+    print(f"planned {M} x {K}, every entry stored", flush=True)
+    B = torch.randint(-3, 4, (K, 48), generator=gen, device="cuda").to(torch.float32)
+    assert torch.equal(gpu.spmm_exec(plan, B), vals @ B)      # whole numbers below 2^24
+    assert gpu.spmm_plan_worklist(plan, 48)["n_tile"] == 64
