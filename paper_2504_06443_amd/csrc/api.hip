@@ -275,13 +275,14 @@ bool splits_nothing(const spmm_plan_t* pl, int64_t waves) {
 // The host's copy of panel_ptr.  spmm_plan fetches it where the default policy may split a panel,
 // the setters (which wait for the device anyway) wherever a list may be built after them; so no
 // call that only enqueues has to.
-int need_panel_ptr(spmm_plan_t* pl) {
+int need_panel_ptr(spmm_plan_t* pl, hipStream_t s = nullptr) {
   int status = SPMM_OK;
   if (!pl->h_panel_ptr.empty()) return SPMM_OK;
   try { pl->h_panel_ptr.resize((size_t)pl->P + 1); }
   catch (const std::bad_alloc&) { return fail(SPMM_ENOMEM, "host allocation failed"); }
-  HIP_TRY(hipMemcpy(pl->h_panel_ptr.data(), pl->panel_ptr, (size_t)(pl->P + 1) * sizeof(uint32_t),
-                    hipMemcpyDeviceToHost));
+  HIP_TRY(hipMemcpyAsync(pl->h_panel_ptr.data(), pl->panel_ptr, (size_t)(pl->P + 1) * sizeof(uint32_t),
+                         hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipStreamSynchronize(s));
 done:
   if (status != SPMM_OK) pl->h_panel_ptr.clear();
   return status;
@@ -481,6 +482,35 @@ class OnDevice {
   int before_ = 0;
   bool ok_, moved_ = false;
 };
+
+// While it lives, this thread's calls are allowed, and leave captures valid, whatever stream is being
+// captured: for entry points that have nothing to do with a capture that the caller may be in.
+class BesideCaptures {
+ public:
+  BesideCaptures() : ok_(hipThreadExchangeStreamCaptureMode(&mode_) == hipSuccess) {}
+  ~BesideCaptures() { if (ok_) (void)hipThreadExchangeStreamCaptureMode(&mode_); }
+  BesideCaptures(const BesideCaptures&) = delete;
+  BesideCaptures& operator=(const BesideCaptures&) = delete;
+
+ private:
+  hipStreamCaptureMode mode_ = hipStreamCaptureModeRelaxed;   // then the thread's own
+  bool ok_;
+};
+
+// need_panel_ptr on a stream of its own: the null stream would join a capture
+int need_panel_ptr_beside_captures(spmm_plan_t* pl) {
+  if (!pl->h_panel_ptr.empty()) return SPMM_OK;
+  int status = SPMM_OK;
+  hipStream_t s = nullptr;
+  const BesideCaptures beside;
+  const OnDevice here(pl->device);
+  if (!here.ok()) return fail(SPMM_EHIP, "device %d cannot be made current", pl->device);
+  HIP_TRY(hipStreamCreateWithFlags(&s, hipStreamNonBlocking));
+  status = need_panel_ptr(pl, s);
+done:
+  if (s) (void)hipStreamDestroy(s);
+  return status;
+}
 
 // What the CSR kernels read besides rowptr, from the brick format (the caller's CSR arrays may be
 // gone).  The default route sends no panel to them, so a plan is made without: 8 B/nnz of memory,
@@ -1239,7 +1269,7 @@ int spmm_plan_worklist(spmm_plan_t* pl, int64_t N, spmm_worklist_info_t* info,
   if (status != SPMM_OK) return status;
   *info = hl->info;
   if (items && hl->direct && pl->P > 0) {
-    if (const int st = need_panel_ptr(pl)) return st;
+    if (const int st = need_panel_ptr_beside_captures(pl)) return st;
     for (int64_t p = 0; p < pl->P; ++p)
       items[p] = spmm_work_item_t{(uint32_t)p, pl->h_panel_ptr[p], pl->h_panel_ptr[p + 1], 0, 1};
   }

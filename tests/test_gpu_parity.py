@@ -711,3 +711,25 @@ def test_captured_csr_products_see_every_later_update(gpu, route):
         vals.copy_(torch.from_numpy(v))
         update.replay()
         expect(v)
+
+
+def test_work_list_while_a_stream_is_capturing(gpu):
+    """spmm_plan_worklist answers also between a capture's begin and end, and leaves it valid."""
+    import torch
+    A = W.clustered_blocks(3000, 6, 90, seed=61)
+    B = W.dense_b(A.K, 48, 8)
+    plan = make_plan(gpu, A)                     # no panel of it is split: the plan keeps no list
+    Bd = torch.from_numpy(B).cuda()
+    Cd = torch.empty((A.M, 48), device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        gpu.spmm_exec(plan, Bd, Cd)
+        inside = gpu.spmm_plan_worklist(plan, 48)
+    ptr = gpu.spmm_plan_export(plan)["panel_ptr"]
+    assert inside["items"] == [(p, int(ptr[p]), int(ptr[p + 1]), 0, 1) for p in range(len(ptr) - 1)]
+    Cref, S = oracle.spmm_f64(A.rowptr, A.colind, A.vals, B)
+    for _ in range(2):
+        Cd.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        check_c(Cd.cpu().numpy(), Cref, S)
