@@ -1293,6 +1293,7 @@ int spmm_plan_worklist(spmm_plan_t* pl, int64_t N, spmm_worklist_info_t* info,
 
 void spmm_plan_destroy(spmm_plan_t* pl) {
   if (!pl) {
+    const BesideCaptures beside;   // (with nothing to destroy the call is allowed anywhere)
     DeviceKeep::instance().give_back(-1);
     return;
   }

@@ -74,3 +74,23 @@ def test_plans_of_several_threads_and_streams(gpu):  # noqa: F811
         Cg = Cd.cpu().numpy()
         assert not np.isnan(Cg).any()
         check_c(Cg, cases[i][3], cases[i][4])
+
+
+def test_giving_back_leaves_a_capture_valid(gpu):  # noqa: F811
+    import torch
+    A = W.clustered_blocks(20_000, 8, 200, seed=6)
+    B = W.dense_b(A.K, 40, 9)
+    make_plan(gpu, W.clustered_blocks(60_000, 10, 256, seed=5)).destroy()
+    plan, Bd, Cd = make_plan(gpu, A), torch.from_numpy(B).cuda(), torch.empty((A.M, 40), device="cuda")
+    before = free_bytes()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        gpu.spmm_exec(plan, Bd, Cd)
+        gpu._lib.spmm_plan_destroy(None)
+    assert free_bytes() - before >= 8 << 20
+    Cref, S = oracle.spmm_f64(A.rowptr, A.colind, A.vals, B)
+    for _ in range(2):
+        Cd.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        check_c(Cd.cpu().numpy(), Cref, S)
