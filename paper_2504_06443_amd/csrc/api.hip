@@ -983,6 +983,12 @@ bool uses_tm32(const spmm_plan_t* pl, const float* B, int64_t N, const float* C)
   return mfma_fast_shape(N, pl->K) && ptr_is_aligned16(B) && ptr_is_aligned16(C);
 }
 
+// The kernel in which the wavefronts of a workgroup share a panel's bricks serves the product where the
+// operands are 16-byte aligned and no other mode comes first.
+bool shares_tiles(const spmm_plan_t* pl, int64_t N) {
+  return pl->tile_sharing == SPMM_SHARE_WORKGROUP && mfma_wide_waves(N, pl->K) > 0;
+}
+
 // the three launches of one product; every pointer is a device pointer
 int launch_product(const spmm_plan_t* pl, const HostList* hl, const WorkItem* d_items,
                    const uint32_t* d_valu_panels, const MergeItem* d_merge, float* d_partial,
@@ -1003,7 +1009,7 @@ int launch_product(const spmm_plan_t* pl, const HostList* hl, const WorkItem* d_
     if (pl->precision != SPMM_PRECISION_FP32 && aligned && bf16_path_shape(N, pl->K))
       HIP_TRY(launch_spmm_bf16(f, d_items, hl->info.n_mfma_items, B, C, d_partial, pl->M, N, pl->K,
                                pl->precision == SPMM_PRECISION_BF16X3 ? 2 : 3, pl->nnz, s));
-    else if (pl->tile_sharing == SPMM_SHARE_WORKGROUP && aligned && mfma_wide_waves(N, pl->K) > 0)
+    else if (shares_tiles(pl, N) && aligned)
       HIP_TRY(launch_spmm_mfma_wide(f, d_items, hl->info.n_mfma_items, B, C, d_partial, pl->M, N,
                                     pl->K, s));
     else
@@ -1268,6 +1274,9 @@ int spmm_plan_worklist(spmm_plan_t* pl, int64_t N, spmm_worklist_info_t* info,
   const int status = build_host_list(pl, N, &hl);
   if (status != SPMM_OK) return status;
   *info = hl->info;
+  // 32-row panels and shared tiles keep tiles of a power of two columns (as many of them); lists are
+  // not dropped when these modes change, so the tile is looked up here.  Operands count as aligned.
+  if (uses_tm32(pl, nullptr, N, nullptr) || shares_tiles(pl, N)) info->n_tile = mfma_tile_for(N);
   if (items && hl->direct && pl->P > 0) {
     if (const int st = need_panel_ptr_beside_captures(pl)) return st;
     for (int64_t p = 0; p < pl->P; ++p)

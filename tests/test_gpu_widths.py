@@ -51,3 +51,27 @@ def test_narrow_tiles_do_not_split_more(gpu, N, as_wide_as):  # noqa: F811
     if N <= as_wide_as:   # the same number of tiles, hence the same list
         assert mine["n_mfma_items"] == wide["n_mfma_items"]
         assert mine["num_waves"] == wide["num_waves"]
+
+
+def test_tile_reported_under_32_row_panels_and_tile_sharing(gpu):  # noqa: F811
+    """Both modes run tiles of a power of two columns; the reported tile follows them, set and unset,
+    though the list of that width was made before.  Widths that a mode does not serve keep theirs."""
+    A = W.paired_panels(1000, cols_per_group=60, half_width=200, seed=73)
+    plan = make_plan(gpu, A)
+    widths = {44: 48, 48: 48, 77: 80, 388: 112, 389: 112, 260: 96}
+
+    def reported():
+        lists = {N: gpu.spmm_plan_worklist(plan, N) for N in widths}
+        for N, wl in lists.items():
+            assert wl["n_tiles"] == -(-N // wl["n_tile"]) == -(-N // 128)
+        return {N: wl["n_tile"] for N, wl in lists.items()}
+
+    assert reported() == widths
+    gpu.spmm_plan_set_tile_sharing(plan, gpu.SHARE_WORKGROUP)    # 388: four tiles; 260: three; 389 is odd
+    assert reported() == widths | {388: 128}
+    gpu.spmm_plan_set_tile_sharing(plan, gpu.SHARE_NONE)
+    assert reported() == widths
+    gpu.spmm_plan_set_panel_height(plan, 32)                     # N a multiple of four
+    assert reported() == widths | {44: 64, 48: 64, 388: 128, 260: 128}
+    gpu.spmm_plan_set_panel_height(plan, 16)
+    assert reported() == widths
