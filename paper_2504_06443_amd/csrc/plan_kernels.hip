@@ -668,13 +668,13 @@ __device__ inline void panel_bitmap(const int32_t* __restrict__ colind, const Pa
   __syncthreads();
 }
 
-// a1/a2 (counting half): active columns of each panel; validates colind.  Dynamic LDS: the bitmap.
+// a1/a2 (counting half): active columns of each panel; validates colind.  Requires a valid rowptr (the
+// host has seen k_rows' verdict).  Dynamic LDS: the bitmap.
 __global__ __launch_bounds__(kPanelThreads) void k_panel_census(
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind, int64_t M, int64_t K,
     int64_t P, uint32_t words_cap, uint32_t* err, uint32_t* __restrict__ ncols_p) {
   extern __shared__ uint32_t lds[];
   __shared__ int32_t rp[kPanel + 1];
-  if (*err & (kErrRowptrEnds | kErrRowptrOrder)) return;   // uniform: nothing below is safe
   const int64_t p = blockIdx.x;
   const PanelExtent x = panel_extent(rowptr, colind, M, p, rp);
   if (x.e0 >= x.e1 || x.cmax < x.cmin) {
@@ -909,17 +909,16 @@ __device__ inline uint32_t group_census(const int32_t* __restrict__ colind, cons
   return total;
 }
 
-// Census of the panels of at most kSortMid entries.  Those above kSortSmall, which are listed, take
-// the first mid_blocks workgroups, one each (the host does not know their count yet); a wavefront
-// takes each of the others.  One launch: the few hundred listed panels of a graph are a chain of
-// latencies that hides among the many small ones (20,360 panels, 159 of them listed: 24 + 16 us as
-// two launches, 27 so).
+// Census of the panels of at most kSortMid entries; rowptr is valid, as above.  Those above kSortSmall,
+// which are listed, take the first mid_blocks workgroups, one each (the host does not know their count
+// yet); a wavefront takes each of the others.  One launch: the few hundred listed panels of a graph are
+// a chain of latencies that hides among the many small ones (20,360 panels, 159 of them listed: 24 + 16
+// us as two launches, 27 so).
 template <typename KT, int B, bool MID>
 __global__ __launch_bounds__(kMidThreads) void k_panel_sort_census(
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind, int64_t M, int64_t K,
     int64_t P, const uint32_t* __restrict__ mid_list, const uint32_t* __restrict__ n_mid,
     uint32_t mid_blocks, uint32_t* err, uint32_t* __restrict__ ncols_p, uint32_t* __restrict__ order) {
-  if (*err & (kErrRowptrEnds | kErrRowptrOrder)) return;   // uniform: nothing below is safe
   if constexpr (MID) {
     if (blockIdx.x < mid_blocks) {
       __shared__ KT lds[kSortMid];
@@ -958,7 +957,6 @@ __global__ __launch_bounds__(kBigThreads) void k_panel_sort_census_big(
   __shared__ KT lds[kSortBig];
   __shared__ uint32_t sums[kBigThreads / 64];
   if (blockIdx.x >= *listed) return;   // (the host does not know the count yet)
-  if (*err & (kErrRowptrEnds | kErrRowptrOrder)) return;
   const int64_t p = list[blockIdx.x];
   const PanelRows x(rowptr, M, p);
   uint32_t cols = 0;
