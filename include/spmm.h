@@ -79,8 +79,8 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t *rowptr, const in
 /* ---------------------------------------------------------------------------
  * spmm_plan_update_values -- new values for the same sparsity pattern (the use
  * cases of Section 6, "Pre-processing Overheads": many products with one pattern,
- * e.g. a matrix re-assembled every time step).  One gather/scatter kernel instead
- * of a new plan.
+ * e.g. a matrix re-assembled every time step).  One gather kernel instead of
+ * a new plan.
  *
  *   vals    dev float[nnz], in the order of the colind array the plan was built
  *           from; read by a kernel enqueued on `stream`, so it must stay valid
@@ -123,9 +123,10 @@ int spmm_exec(spmm_plan_t *plan, const float *B, int64_t N, float *C, void *stre
  * static device array of 32 MiB per GPU (held until the process ends) instead of
  * plan-owned allocations.
  *
- *   - Work list plus partial tiles (16 x N floats per part of a split panel) must fit
- *     the 32 MiB; otherwise SPMM_ELIMIT with the sizes in spmm_last_error(), and
- *     nothing is enqueued.
+ *   - Work list (16 bytes per work item of the MFMA kernel, counted also where no panel
+ *     is split and no list is kept) plus partial tiles (16 x N floats per part of a split
+ *     panel) must fit the 32 MiB; otherwise SPMM_ELIMIT with the sizes in
+ *     spmm_last_error(), and nothing is enqueued.
  *   - The array keeps the work list of the last (plan, N) that used it on this GPU;
  *     a call with another plan or N first copies its list in with hipMemcpyAsync on
  *     `stream` (from host memory the plan owns), a repeat call copies nothing and

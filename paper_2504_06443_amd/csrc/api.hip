@@ -134,7 +134,7 @@ struct spmm_plan {
   uint32_t* brick_cols = nullptr;
   uint64_t* brick_mask = nullptr;
   uint32_t* brick_valptr = nullptr;
-  float* vals = nullptr;          // nnz + 1
+  float* vals = nullptr;          // nnz + 64
   uint32_t* src = nullptr;        // CSR entry of each packed value (value-only updates)
   // what the vector-ALU CSR kernels read (device): rowptr is kept from the start, the rest is made
   // when a route first sends panels there, and every update keeps it up to date from then on
@@ -1047,7 +1047,8 @@ int spmm_exec_noalloc(spmm_plan_t* pl, const float* B, int64_t N, float* C, void
   status = build_host_list(pl, N, &hl);   // host arithmetic only; cached per N
   if (status != SPMM_OK) return status;
 
-  // (what a list takes, also where none is needed: the same sizes are refused either way)
+  // what a list takes, also where none is kept (hl->direct): which sizes are refused does not depend on
+  // how the kernels get their items
   const size_t items_b = pad256((size_t)hl->info.n_mfma_items * sizeof(WorkItem));
   const size_t valu_b = pad256(hl->valu_panels.size() * sizeof(uint32_t));
   const size_t merge_b = pad256(hl->merges.size() * sizeof(MergeItem));

@@ -1437,9 +1437,10 @@ constexpr uint32_t kSortBuildRound = 256;   // a workgroup per CU
 template <int T>
 static hipError_t sort_build(const int32_t* rowptr, const int32_t* colind, const float* vals,
                              int64_t M, const uint32_t* list, const uint32_t* rest,
-                             uint32_t n_first, int64_t n_panels, uint32_t n_cap, uint32_t nb_cap, const uint32_t* panel_ptr, uint32_t* brick_cols,
-                             uint64_t* brick_mask, uint32_t* brick_valptr, float* packed,
-                             uint32_t* src, uint8_t* col_seen, hipStream_t s) {
+                             uint32_t n_first, int64_t n_panels, uint32_t n_cap, uint32_t nb_cap,
+                             const uint32_t* panel_ptr, uint32_t* brick_cols, uint64_t* brick_mask,
+                             uint32_t* brick_valptr, float* packed, uint32_t* src,
+                             uint8_t* col_seen, hipStream_t s) {
   if (n_panels == 0) return hipSuccess;
   n_cap = (n_cap + 1) & ~1u;
   // All bricks of a panel but the last have four columns, so four entries at least.  With room for a

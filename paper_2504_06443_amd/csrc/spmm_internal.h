@@ -98,7 +98,6 @@ hipError_t launch_plan_stats(const uint32_t* panel_ptr, const uint32_t* panel_nn
 hipError_t launch_find_long_rows(const int32_t* rowptr, int64_t M, int threshold,
                                  uint32_t* list, unsigned long long* counter, hipStream_t s);
 
-// per-panel path (LDS bitmap over the panel's column span)
 // per-panel path by sorting (any column span, panels of limited size)
 struct PanelLists {         // panels above 512 and above 2048 entries
   const uint32_t *mid, *big;
@@ -119,7 +118,8 @@ hipError_t launch_panel_sort_build(const int32_t* rowptr, const int32_t* colind,
                                    uint32_t* brick_cols, uint64_t* brick_mask,
                                    uint32_t* brick_valptr, float* packed, uint32_t* src,
                                    uint8_t* col_seen, hipStream_t s);
-uint32_t panel_bitmap_words(uint32_t span, int64_t P);   // 0: beyond the per-panel path
+// per-panel path by an LDS bitmap over the panel's column span
+uint32_t panel_bitmap_words(uint32_t span, int64_t P);   // 0: beyond this path
 hipError_t launch_panel_census(const int32_t* rowptr, const int32_t* colind, int64_t M, int64_t K,
                                int64_t P, uint32_t words_cap, uint32_t* err, uint32_t* ncols_p,
                                hipStream_t s);
@@ -141,7 +141,6 @@ hipError_t launch_scan_nonzero64(const uint64_t* in, int64_t n, uint32_t* out, u
                                  hipStream_t s);
 
 // ---- exec (a6..a8) -------------------------------------------------------
-// `items` may be null: one item per panel, n_items panels.
 // Device arrays of the brick format.  Each carries spare entries past its end
 // (kFormatPad bricks' worth: zero columns and patterns, value offsets equal to
 // nnz, zero values) so that kernels may fetch metadata a few bricks past a work
@@ -167,6 +166,8 @@ bool mfma_32bit_values(int64_t nnz);           // where the packed values are to
 // shapes of the 32-row kernel when B and C are 16-byte aligned: N a multiple of the vector
 // width, B below 4 GiB
 bool mfma_fast_shape(int64_t N, int64_t K);
+// In this and the launches of the other brick kernels of 16-row panels `items` may be null: one item per
+// panel, n_items panels.
 hipError_t launch_spmm_mfma(const BrickFormat& f, const WorkItem* items, int64_t n_items,
                             const float* B, float* C, float* partial, int64_t M, int64_t N,
                             int64_t K, int64_t nnz, hipStream_t s);

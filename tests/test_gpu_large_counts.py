@@ -1,6 +1,6 @@
 """Plans whose counts are at the upper end of what is accepted, where a launch of a wavefront a brick
-or a panel would hold 2^32 threads, or 32-bit byte offsets end.  The matrices are regular or nearly empty, so that C and the
-format follow from the construction."""
+or a panel would hold 2^32 threads, or 32-bit byte offsets end.  The matrices are regular or nearly
+empty, so that C and the format follow from the construction."""
 import numpy as np
 import pytest
 
