@@ -73,7 +73,7 @@ __device__ inline void raise_to(uint32_t* p, uint32_t v) {
 // and inside [0, nnz].  A panel with entries and an inverted span (the last column of every row
 // below the first column of some row) is not sorted or has a negative column.
 // Bound by the latency of two dependent loads, hence a thread per row; one block maximum per 1024
-// rows in flight keeps the atomics on one address few.  262,144 rows: 33 us as a thread per panel
+// rows in flight keeps the atomics on one address few.  262,144 rows: 29 us as a thread per panel
 // and a separate check, 12 us so.
 constexpr int kRowThreads = 1024;
 constexpr int kRowBlocks = 256;
@@ -267,7 +267,7 @@ __global__ void k_pack_values(const float* __restrict__ vals,
 // entry.  Gathering by packed position keeps the stores whole (the entries of a panel are 2 KB or
 // so, and their reads hit a cache); four positions per thread.  CSR: the plan also keeps the values
 // in CSR order, for the vector-ALU kernels.  7.86 M entries: scattering by entry and always writing
-// the CSR copy 28.9 us; this way about 15, 94 MB at 6.3 TB/s.
+// the CSR copy 27.3 us; this way 16.3, 94 MB at 5.8 TB/s.
 template <bool CSR>
 __global__ __launch_bounds__(kThreads) void k_update_values(
     const float* __restrict__ vals, const uint32_t* __restrict__ src, int64_t nnz,
@@ -709,7 +709,7 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_census(
 // compare-exchange inside a lane is a min and a max, across lanes one cross-lane read a key, and only
 // steps across wavefronts go through LDS (a sort all through LDS moved four words a pair and step).
 // The census leaves the sorted entries, rank << 16 | index inside the panel, for the build.
-// 20,360 panels of 46 entries, the largest 3000: the search-based kernels 195 us, these 81 (keys of 32 bits
+// 20,360 panels of 46 entries, the largest 3000: the search-based kernels 167 us, these 84 (keys of 32 bits
 // for the 48 panels above 2048: 30 -> 19 us).
 // 18,750 panels of 430: a sort through LDS by one wavefront 163 + 101 us (census, build), now 84 + 67.
 constexpr uint32_t kSortSmall = 512, kSortMid = 2048, kSortBig = 8192;
@@ -1054,7 +1054,7 @@ __global__ __launch_bounds__(T) void k_panel_sort_build(
 // in flight, and an entry's row and rank are worked out once and kept in LDS; the packed values and
 // their sources leave in order, whole lines at a time.  Panels above stage_cap go through the same
 // steps without the staging: they read the columns again and scatter their values.
-// 7.86 M entries in 16,384 panels: 92 us unstaged and walking groups of bitmap words, 50 us so;
+// 7.86 M entries in 16,384 panels: 71 us unstaged and walking groups of bitmap words, 51 us so;
 // 41 M entries in 57,696 panels 434 -> 250 us (0.76 GB).
 template <int G>
 __global__ __launch_bounds__(kPanelThreads) void k_panel_build(
