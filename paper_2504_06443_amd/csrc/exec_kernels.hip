@@ -642,11 +642,14 @@ __global__ __launch_bounds__(64 * kLongWaves) void k_spmm_valu_long(
 
 // ------------------------------------------------------------------ merge (a8)
 // Sum the partial 16 x N tiles of a split panel in part order and store to C.
-// A thread owns four floats and reads kMergeAhead parts at a time: the sum runs in part order, the
-// loads do not wait for it.  The workgroups of a panel share its 16 * N floats.  Bound by latency (a
-// few hundred panels of some tens of parts); 325,760-row graph, N = 128: one workgroup a panel and
-// one load at a time 10.1 us, now 6.7.
-constexpr int kMergeAhead = 8, kMergeThreads = 256;
+// A thread owns four floats and reads kMergeAhead parts at a time.  The sum runs in part order; the parts
+// of a round are added by selects, not behind a branch each, which would make the compiler load them one
+// after the other.  The workgroups of a panel share its 16 * N floats.  Bound by the latency of the rounds
+// (a part was written through another L2).  One load at a time, eight and sixteen in flight, us: 3750
+// panels of which one has 151 parts, N = 1 39.6 / 12.9 / 10.5, N = 128 65.9 / 17.3 / 17.0; 6250 panels, up
+// to 47 parts, N = 16 21.0 / 6.1 / 4.5, N = 128 12.9 / 6.0 / 6.8.  Thirty-two are behind at narrow widths
+// (N = 16 6.3).
+constexpr int kMergeAhead = 16, kMergeThreads = 256;
 
 __global__ __launch_bounds__(kMergeThreads) void k_merge(const MergeItem* __restrict__ items,
                                                          const float* __restrict__ partial,
@@ -668,9 +671,9 @@ __global__ __launch_bounds__(kMergeThreads) void k_merge(const MergeItem* __rest
         load_any<V>(reinterpret_cast<const char*>(src + (int64_t)min(q + k, it.nparts - 1) * tile + x), t[k]);
 #pragma unroll
       for (int k = 0; k < kMergeAhead; ++k) {
-        if (q + k >= it.nparts) break;   // uniform
+        const bool is = q + k < it.nparts;
 #pragma unroll
-        for (int w = 0; w < V; ++w) s[w] += t[k][w];
+        for (int w = 0; w < V; ++w) s[w] = is ? s[w] + t[k][w] : s[w];
       }
     }
     store_any_nt<V>(dst + x, s);

@@ -191,6 +191,32 @@ def test_split_panels_merge(gpu, split, N):
     assert np.array_equal(C1, C2)
 
 
+@pytest.mark.parametrize("N", [1, 3, 20, 77])
+@pytest.mark.parametrize("parts", [2, 16, 17, 18, 33, 34])
+def test_merge_of_many_parts(gpu, parts, N):
+    """Panels of exactly `parts` parts, around the numbers that one and two rounds of the merge kernel take
+    (the first part and sixteen more), and a last panel of seven rows."""
+    import torch
+    rng = np.random.default_rng(100 * parts + N)
+    M, K = 16 * 5 + 7, 16 * parts                 # a block of four bricks has sixteen columns
+    keep = rng.random((M, K)) < 0.4
+    keep[np.arange(K) % 16 % 7 + 80, np.arange(K)] = True            # every column in the last panel
+    keep[3:80:16] = True                                            # and in every other
+    rows, cols = np.nonzero(keep)
+    A = W.csr_from_coo(M, K, rows, cols, rng.uniform(-1, 1, len(rows)).astype(np.float32))
+    B = W.dense_b(K, N, 8)
+    plan = make_plan(gpu, A)
+    gpu.spmm_plan_set_split(plan, parts)
+    assert {i[4] for i in gpu.spmm_plan_worklist(plan, N)["items"]} == {parts}
+    Bd = torch.from_numpy(B).cuda()
+    Cref, S = oracle.spmm_f64(A.rowptr, A.colind, A.vals, B)
+    for product in (gpu.spmm_exec, gpu.spmm_exec_noalloc):
+        Cd = torch.full((M, N), float("nan"), device="cuda")
+        product(plan, Bd, Cd)
+        torch.cuda.synchronize()
+        check_c(Cd.cpu().numpy(), Cref, S)
+
+
 @pytest.mark.parametrize("policy", ["from2", "nearest"])
 @pytest.mark.parametrize("M,N", [(4000, 128), (120000, 32), (120000, 512)])
 def test_auto_split_matches_oracle_partition(gpu, policy, M, N):
