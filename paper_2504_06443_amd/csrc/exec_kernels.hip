@@ -356,7 +356,7 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void k_spmm_mfma_fast(
     // turned into row offsets in the chunk's last step, so that nothing waits for that load
     // while the ring's loads are younger than it
     uint32_t ro_following = 0;
-    auto step = [&](auto steady, int i, uint32_t g, const Meta& m, uint32_t ro_this,
+    auto step = [&](auto steady, auto ordered, int i, uint32_t g, const Meta& m, uint32_t ro_this,
                     uint32_t col_following) {
       constexpr bool kSteady = decltype(steady)::value;
       if constexpr (kSteady) {
@@ -379,8 +379,8 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void k_spmm_mfma_fast(
       const bool live = kSteady || g < nbricks;   // uniform: scalar selects
       issue(live ? m.mask[i] : 0ull, live ? m.off[i] : off_last, ro, i % R);
       // without the branches of the checked variant the steps of a chunk are one basic block;
-      // keep the scheduler from sinking a step's loads down to their use R steps later
-      if constexpr (kSteady) __builtin_amdgcn_sched_barrier(0);
+      // `ordered` keeps the scheduler from sinking a step's loads down to their use R steps later
+      if constexpr (decltype(ordered)::value) __builtin_amdgcn_sched_barrier(0);
     };
     // Whole chunks run in loops whose only exit is at their top; the last, partial chunk is
     // straight-line code after them.  With an exit in the middle of a loop body the compiler
@@ -392,26 +392,31 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void k_spmm_mfma_fast(
     // end.  Every chunk issues the same loads in the same order, so the count of loads in
     // flight is the same on every path into a loop head.
     uint32_t c = 0;
-    auto chunk = [&](auto steady) {
+    auto chunk = [&](auto steady, auto ordered) {
       const Meta nxt = load_meta(b_begin + c + CH);
       const uint32_t col_nxt = load_col(b_begin + c + CH);
 #pragma unroll
-      for (int i = 0; i < CH; ++i) step(steady, i, c + i, cur, ro_cur, col_nxt);
+      for (int i = 0; i < CH; ++i) step(steady, ordered, i, c + i, cur, ro_cur, col_nxt);
       cur = nxt;
       ro_cur = ro_following;
     };
+    // (ordered in the narrowest tile, whose steps hold so little else that their loads changed places: the
+    // check-free loop behind then began with a wait for younger ones.  512 panels of 160 scattered bricks,
+    // N = 16: 21.6 us, in order 20.3; panels of 39 the same.  In order in every chunk the kernel takes more
+    // scalar registers: 28 wavefronts a CU instead of 32, and Eq. 7 splits differently.)
     if (c + CH <= total) {
-      chunk(std::false_type{});
+      chunk(std::false_type{}, std::bool_constant<T == 1>{});
       c += CH;
     }
     if (c + CH <= nbricks) a_ahead = operand(0);   // c is a multiple of CH, so stage 0 is next
-    for (; c + CH <= nbricks; c += CH) chunk(std::true_type{});
-    for (; c + CH <= total; c += CH) chunk(std::false_type{});
+    for (; c + CH <= nbricks; c += CH) chunk(std::true_type{}, std::true_type{});
+    for (; c + CH <= total; c += CH) chunk(std::false_type{}, std::false_type{});
     if (c < total) {
 #pragma unroll
       for (int i = 0; i < CH; ++i) {
         if (i % R == 0 && i > 0 && c + i >= total) break;
-        step(std::false_type{}, i, c + i, cur, ro_cur, 0u);   // its last step fetches nothing real
+        // (its last step fetches nothing real)
+        step(std::false_type{}, std::false_type{}, i, c + i, cur, ro_cur, 0u);
       }
     }
   }

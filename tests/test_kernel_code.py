@@ -34,3 +34,17 @@ def test_merge_loads_a_round_of_parts_at_a_time(product_kernels):
         elif i.startswith(("s_cbranch", "s_branch", ".LBB")) or re.match(r"s_waitcnt.*vmcnt\(0\)", i):
             run = 0
     assert longest >= 16
+
+
+def test_narrow_tile_enters_its_loop_with_the_ring_full(product_kernels):
+    """Four steps of two loads are in flight at the head of the check-free loop, and the loop begins with
+    three more: the first operand waits for none of the eight youngest."""
+    code = instructions(product_kernels, "k_spmm_mfma_fastILi1ELb0E")
+    heads = {i[:-1]: n for n, i in enumerate(code) if i.startswith(".LBB")}
+    loops = [code[heads[i.split()[1]]:n] for n, i in enumerate(code)
+             if i.startswith("s_cbranch") and heads.get(i.split()[1], n) < n]
+    steady = [body for body in loops if sum(i.startswith("v_mfma") for i in body) == 8
+              and not any(i.startswith("s_cbranch") for i in body)]
+    assert len(steady) == 1
+    waits = [int(m[1]) for m in (re.search(r"vmcnt\((\d+)\)", i) for i in steady[0]) if m]
+    assert waits[0] >= 8
