@@ -99,9 +99,10 @@ struct HostList {
   uint64_t id = 0;                          // unique per list (tags the contents of the static scratch)
   int64_t N = 0;
   spmm_worklist_info_t info{};
-  // Every panel to the brick kernel, whole and in order: item i is panel i, the lists below are
-  // empty and the kernels read panel_ptr instead.
+  // Every panel to the brick kernel, in order: item i is panel i and the kernels read panel_ptr.  The
+  // lists below then hold the exceptions only, the parts of panels of split_bricks bricks and more.
   bool direct = false;
+  uint32_t split_bricks = kNoSplit;
   std::vector<WorkItem> items;
   std::vector<MergeItem> merges;
   std::vector<uint32_t> valu_panels;
@@ -111,14 +112,12 @@ struct HostList {
 // Device half: plan-owned copies of a HostList plus the partial-tile workspace.
 struct WorkList {
   const HostList* host = nullptr;
+  char* arena = nullptr;                    // everything below, one allocation
   WorkItem* d_items = nullptr;
   uint32_t* d_valu_panels = nullptr;
   MergeItem* d_merge = nullptr;
   float* d_partial = nullptr;               // n_slots tiles of 16 x N
-  void release(bool idle) {
-    for (void* p : {(void*)d_items, (void*)d_valu_panels, (void*)d_merge, (void*)d_partial})
-      keep_put(p, idle);
-  }
+  void release(bool idle) { keep_put(arena, idle); }
 };
 
 std::atomic<uint64_t> g_next_list_id{1};
@@ -218,11 +217,6 @@ struct Arena {
   }
 };
 
-template <typename T>
-hipError_t dev_alloc(T** p, int64_t n) {
-  return DeviceKeep::instance().get((void**)p, (size_t)std::max<int64_t>(n, 1) * sizeof(T));
-}
-
 int classify(int64_t nnz, int64_t nb) {
   if (nb == 0) return SPMM_NONE;
   if (nnz < 8 * nb) return SPMM_LOW;
@@ -317,10 +311,10 @@ int build_host_list(spmm_plan_t* pl, int64_t N, const HostList** out) {
     if ((pl->route == SPMM_ROUTE_AUTO || pl->route == SPMM_ROUTE_MFMA) && pl->order == SPMM_ORDER_PANEL) {
       const bool eq7 = pl->split == SPMM_SPLIT_EQ7_FROM2 || pl->split == SPMM_SPLIT_EQ7_NEAREST;
       const int64_t waves = eq7 && pl->P > 0 ? waves_of(pl->P * hl->info.n_tiles, (int64_t)pl->num_cus * resident) : 1;
+      hl->direct = true;
+      hl->info.num_waves = waves;
+      hl->info.n_mfma_items = pl->P;
       if (splits_nothing(pl, waves)) {
-        hl->direct = true;
-        hl->info.num_waves = waves;
-        hl->info.n_mfma_items = pl->P;
         pl->host_lists[N] = hl;
         *out = hl;
         return SPMM_OK;
@@ -346,12 +340,17 @@ int build_host_list(spmm_plan_t* pl, int64_t N, const HostList** out) {
       return pl->h_panel_class[p] != SPMM_LOW && pl->h_panel_class[p] != 255;
     };
     int64_t nm = 0, total = 0;   // panels of the MFMA kernel and their blocks
-    for (int64_t p = 0; p < pl->P; ++p) {
-      if (to_mfma(p)) {
-        ++nm;
-        total += ceil_div(ptr[p + 1] - ptr[p], kBrickK);
-      } else {
-        hl->valu_panels.push_back((uint32_t)p);
+    if (hl->direct) {
+      nm = pl->P;
+      total = pl->n_blocks;
+    } else {
+      for (int64_t p = 0; p < pl->P; ++p) {
+        if (to_mfma(p)) {
+          ++nm;
+          total += ceil_div(ptr[p + 1] - ptr[p], kBrickK);
+        } else {
+          hl->valu_panels.push_back((uint32_t)p);
+        }
       }
     }
 
@@ -369,13 +368,23 @@ int build_host_list(spmm_plan_t* pl, int64_t N, const HostList** out) {
       return pl->split > 1 && blocks >= pl->split ? pl->split : 1;
     };
     hl->info.num_waves = waves;
+    if (hl->direct) {
+      // the smallest panel that is split: the number of parts never falls with the number of blocks
+      int64_t whole = 0, split = ceil_div(pl->max_bricks, kBrickK);
+      while (split - whole > 1) {
+        const int64_t mid = (whole + split) / 2;
+        (parts_of(mid) > 1 ? split : whole) = mid;
+      }
+      if (parts_of(split) > 1) hl->split_bricks = (uint32_t)((split - 1) * kBrickK + 1);
+    } else {
+      hl->items.reserve((size_t)nm);
+    }
 
     int64_t slots = 0;
-    hl->items.reserve((size_t)nm);
     for (int64_t p = 0; p < pl->P; ++p) {
-      if (!to_mfma(p)) continue;
       const uint32_t b0 = ptr[p];
       const int64_t nbp = ptr[p + 1] - b0;
+      if (hl->direct ? nbp < (int64_t)hl->split_bricks : !to_mfma(p)) continue;
       const int64_t blocks = ceil_div(nbp, kBrickK);
       const int64_t want = parts_of(blocks);
       if (want <= 1) {   // also an empty panel: one work item without bricks
@@ -400,7 +409,8 @@ int build_host_list(spmm_plan_t* pl, int64_t N, const HostList** out) {
         return l.brick_end - l.brick_begin > r.brick_end - r.brick_begin;
       });
     }
-    hl->info.n_mfma_items = (int64_t)hl->items.size();
+    hl->info.n_mfma_items = (int64_t)hl->items.size() +
+                            (hl->direct ? pl->P - (int64_t)hl->merges.size() : 0);
     hl->info.n_valu_panels = (int64_t)hl->valu_panels.size();
     hl->info.n_split_panels = (int64_t)hl->merges.size();
     hl->n_slots = slots;
@@ -427,28 +437,31 @@ int build_worklist(spmm_plan_t* pl, int64_t N, hipStream_t stream, WorkList** ou
   WorkList* wl = new (std::nothrow) WorkList();
   if (!wl) return fail(SPMM_ENOMEM, "host allocation failed");
   wl->host = hl;
-  if (!hl->direct) HIP_TRY(dev_alloc(&wl->d_items, (int64_t)hl->items.size()));
-  if (!hl->valu_panels.empty()) HIP_TRY(dev_alloc(&wl->d_valu_panels, (int64_t)hl->valu_panels.size()));
-  if (!hl->merges.empty()) HIP_TRY(dev_alloc(&wl->d_merge, (int64_t)hl->merges.size()));
-  if (hl->n_slots > 0)
-    HIP_TRY(dev_alloc(&wl->d_partial, hl->n_slots * kPanel * std::max<int64_t>(N, 1)));
-  if (!hl->direct) {
+  if (!hl->items.empty() || !hl->valu_panels.empty()) {
+    // the lists and the partial tiles in one allocation; the lists come up in one copy
+    const size_t items_b = Arena::pad(hl->items.size() * sizeof(WorkItem));
+    const size_t valu_b = Arena::pad(hl->valu_panels.size() * sizeof(uint32_t));
+    const size_t merge_b = Arena::pad(hl->merges.size() * sizeof(MergeItem));
+    const size_t lists_b = items_b + valu_b + merge_b;
+    HIP_TRY(keep_get(&wl->arena, lists_b + (size_t)hl->n_slots * kPanel * (size_t)std::max<int64_t>(N, 1) * sizeof(float)));
+    wl->d_items = reinterpret_cast<WorkItem*>(wl->arena);
+    wl->d_valu_panels = reinterpret_cast<uint32_t*>(wl->arena + items_b);
+    wl->d_merge = reinterpret_cast<MergeItem*>(wl->arena + items_b + valu_b);
+    if (hl->n_slots > 0) wl->d_partial = reinterpret_cast<float*>(wl->arena + lists_b);
     stage.emplace();
-    size_t used = 0;
-    auto upload = [&](void* dst, const void* from, size_t bytes) {
-      if (stage->get() && used + bytes <= kStageBytes) {
-        memcpy(stage->get() + used, from, bytes);
-        from = stage->get() + used;
-        used += (bytes + 63) & ~size_t(63);
+    const bool staged = stage->get() && lists_b <= kStageBytes;
+    auto upload = [&](size_t at, const void* from, size_t bytes) {
+      if (bytes == 0) return hipSuccess;
+      if (staged) {
+        memcpy(stage->get() + at, from, bytes);
+        return hipSuccess;
       }
-      return hipMemcpyAsync(dst, from, bytes, hipMemcpyHostToDevice, stream);
+      return hipMemcpyAsync(wl->arena + at, from, bytes, hipMemcpyHostToDevice, stream);
     };
-    if (!hl->items.empty())
-      HIP_TRY(upload(wl->d_items, hl->items.data(), hl->items.size() * sizeof(WorkItem)));
-    if (!hl->valu_panels.empty())
-      HIP_TRY(upload(wl->d_valu_panels, hl->valu_panels.data(), hl->valu_panels.size() * sizeof(uint32_t)));
-    if (!hl->merges.empty())
-      HIP_TRY(upload(wl->d_merge, hl->merges.data(), hl->merges.size() * sizeof(MergeItem)));
+    HIP_TRY(upload(0, hl->items.data(), hl->items.size() * sizeof(WorkItem)));
+    HIP_TRY(upload(items_b, hl->valu_panels.data(), hl->valu_panels.size() * sizeof(uint32_t)));
+    HIP_TRY(upload(items_b + valu_b, hl->merges.data(), hl->merges.size() * sizeof(MergeItem)));
+    if (staged) HIP_TRY(hipMemcpyAsync(wl->arena, stage->get(), lists_b, hipMemcpyHostToDevice, stream));
     HIP_TRY(hipStreamSynchronize(stream));
   }
   try {
@@ -995,6 +1008,9 @@ int launch_product(const spmm_plan_t* pl, const HostList* hl, const WorkItem* d_
                    const float* B, int64_t N, float* C, hipStream_t s) {
   int status = SPMM_OK;
   const BrickFormat f{pl->panel_ptr, pl->brick_cols, pl->brick_mask, pl->brick_valptr, pl->vals};
+  const uint32_t n_listed = (uint32_t)hl->items.size();
+  const WorkSource work = hl->direct ? WorkSource{nullptr, d_items, (uint32_t)pl->P, n_listed, hl->split_bricks}
+                                     : WorkSource{d_items, nullptr, n_listed, 0, kNoSplit};
   if (uses_tm32(pl, B, N, C)) {
     // 32-row panels: one wavefront per super-panel and column tile, no work list
     HIP_TRY(launch_spmm_tm32(pl->tm32.sp_ptr, pl->tm32.bc_cols, pl->tm32.meta, pl->tm32.vals,
@@ -1007,13 +1023,13 @@ int launch_product(const spmm_plan_t* pl, const HostList* hl, const WorkItem* d_
     const bool aligned = N % V == 0 && ptr_is_aligned16(B) && ptr_is_aligned16(C) &&
                          (d_partial == nullptr || ptr_is_aligned16(d_partial));
     if (pl->precision != SPMM_PRECISION_FP32 && aligned && bf16_path_shape(N, pl->K))
-      HIP_TRY(launch_spmm_bf16(f, d_items, hl->info.n_mfma_items, B, C, d_partial, pl->M, N, pl->K,
+      HIP_TRY(launch_spmm_bf16(f, work, B, C, d_partial, pl->M, N, pl->K,
                                pl->precision == SPMM_PRECISION_BF16X3 ? 2 : 3, pl->nnz, s));
     else if (shares_tiles(pl, N) && aligned)
-      HIP_TRY(launch_spmm_mfma_wide(f, d_items, hl->info.n_mfma_items, B, C, d_partial, pl->M, N,
+      HIP_TRY(launch_spmm_mfma_wide(f, work, B, C, d_partial, pl->M, N,
                                     pl->K, s));
     else
-      HIP_TRY(launch_spmm_mfma(f, d_items, hl->info.n_mfma_items, B, C, d_partial, pl->M, N, pl->K,
+      HIP_TRY(launch_spmm_mfma(f, work, B, C, d_partial, pl->M, N, pl->K,
                                pl->nnz, s));
   }
   if (pl->csr_may_lag && hl->info.n_valu_panels > 0)
@@ -1047,7 +1063,7 @@ int spmm_exec_noalloc(spmm_plan_t* pl, const float* B, int64_t N, float* C, void
   status = build_host_list(pl, N, &hl);   // host arithmetic only; cached per N
   if (status != SPMM_OK) return status;
 
-  // what a list takes, also where none is kept (hl->direct): which sizes are refused does not depend on
+  // what a whole list takes, also where none or the exceptions only are kept (hl->direct): which sizes are refused does not depend on
   // how the kernels get their items
   const size_t items_b = pad256((size_t)hl->info.n_mfma_items * sizeof(WorkItem));
   const size_t valu_b = pad256(hl->valu_panels.size() * sizeof(uint32_t));
@@ -1059,7 +1075,7 @@ int spmm_exec_noalloc(spmm_plan_t* pl, const float* B, int64_t N, float* C, void
                 "exceed the static scratch of %zu B; use spmm_exec",
                 items_b + valu_b + merge_b, partial_b, kScratchBytes);
 
-  if (hl->direct)   // nothing to keep in the scratch
+  if (hl->direct && hl->items.empty())   // nothing to keep in the scratch
     return launch_product(pl, hl, nullptr, nullptr, nullptr, nullptr, B, N, C, s);
   {
     std::lock_guard<std::mutex> lock(g_scratch_mutex);
@@ -1278,23 +1294,27 @@ int spmm_plan_worklist(spmm_plan_t* pl, int64_t N, spmm_worklist_info_t* info,
   // 32-row panels and shared tiles keep tiles of a power of two columns (as many of them); lists are
   // not dropped when these modes change, so the tile is looked up here.  Operands count as aligned.
   if (uses_tm32(pl, nullptr, N, nullptr) || shares_tiles(pl, N)) info->n_tile = mfma_tile_for(N);
-  if (items && hl->direct && pl->P > 0) {
-    if (const int st = need_panel_ptr_beside_captures(pl)) return st;
-    for (int64_t p = 0; p < pl->P; ++p)
-      items[p] = spmm_work_item_t{(uint32_t)p, pl->h_panel_ptr[p], pl->h_panel_ptr[p + 1], 0, 1};
-  }
-  if (items && !hl->direct) {
-    for (size_t i = 0; i < hl->items.size(); ++i) {
-      const WorkItem& it = hl->items[i];
-      uint32_t part = 0, nparts = 1;
-      if (it.slot != kNoSlot) {   // merges are in the order of their slots
-        const auto m = std::upper_bound(hl->merges.begin(), hl->merges.end(), it.slot,
-                                        [](uint32_t slot, const MergeItem& x) { return slot < x.slot_begin; }) - 1;
-        part = it.slot - m->slot_begin;
-        nparts = m->nparts;
-      }
-      items[i] = spmm_work_item_t{it.panel, it.brick_begin, it.brick_end, part, nparts};
+  auto listed = [&](size_t i) {
+    const WorkItem& it = hl->items[i];
+    uint32_t part = 0, nparts = 1;
+    if (it.slot != kNoSlot) {   // merges are in the order of their slots
+      const auto m = std::upper_bound(hl->merges.begin(), hl->merges.end(), it.slot,
+                                      [](uint32_t slot, const MergeItem& x) { return slot < x.slot_begin; }) - 1;
+      part = it.slot - m->slot_begin;
+      nparts = m->nparts;
     }
+    return spmm_work_item_t{it.panel, it.brick_begin, it.brick_end, part, nparts};
+  };
+  if (items && hl->direct && pl->P > 0) {   // panels in order, a split one as its parts
+    if (const int st = need_panel_ptr_beside_captures(pl)) return st;
+    size_t next = 0;
+    for (int64_t p = 0; p < pl->P; ++p) {
+      if (next == hl->items.size() || hl->items[next].panel != (uint32_t)p)
+        *items++ = spmm_work_item_t{(uint32_t)p, pl->h_panel_ptr[p], pl->h_panel_ptr[p + 1], 0, 1};
+      for (; next < hl->items.size() && hl->items[next].panel == (uint32_t)p; ++next) *items++ = listed(next);
+    }
+  } else if (items) {
+    for (size_t i = 0; i < hl->items.size(); ++i) items[i] = listed(i);
   }
   if (valu_panels && !hl->valu_panels.empty())
     memcpy(valu_panels, hl->valu_panels.data(), hl->valu_panels.size() * sizeof(uint32_t));

@@ -70,10 +70,10 @@ __device__ inline void split_pair(float x0, float x1, uint32_t (&planes)[NP]) {
 
 template <int T, int NP>
 __global__ __launch_bounds__(64 * kWavesPerBlock) __attribute__((amdgpu_waves_per_eu(2))) void k_spmm_bf16(
-    const uint32_t* __restrict__ panel_ptr, const uint32_t* __restrict__ brick_cols,
+    SPMM_ITEM_PARAMS, const uint32_t* __restrict__ panel_ptr, const uint32_t* __restrict__ brick_cols,
     const uint64_t* __restrict__ brick_mask, const uint32_t* __restrict__ brick_valptr,
-    const float* __restrict__ vals, const WorkItem* __restrict__ items, int64_t n_items, const float* __restrict__ B,
-    float* __restrict__ C, float* __restrict__ partial, int64_t M, int64_t N, uint32_t k_last,
+    const float* __restrict__ vals, const float* __restrict__ B, float* __restrict__ C,
+    float* __restrict__ partial, int64_t M, int64_t N, uint32_t k_last,
     uint32_t /* reserved */) {
   constexpr int V = T < 4 ? T : 4;
   constexpr int NV = T / V;
@@ -83,10 +83,9 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) __attribute__((amdgpu_waves_pe
 
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
-  const uint32_t vblock = xcd_contiguous_block();
-  const int64_t item_id = (int64_t)vblock * kWavesPerBlock + wave;
-  if (item_id >= n_items) return;  // whole wavefront leaves together
-  const WorkItem it = work_item(items, panel_ptr, item_id);
+  WorkItem it;
+  if (!work_item<kWavesPerBlock>(SPMM_ITEM_MAP, panel_ptr, wave, &it))
+    return;  // whole wavefront leaves together
   const uint32_t panel = __builtin_amdgcn_readfirstlane(it.panel);
   const uint32_t b_begin = __builtin_amdgcn_readfirstlane(it.brick_begin);
   const uint32_t b_end = __builtin_amdgcn_readfirstlane(it.brick_end);
@@ -332,19 +331,18 @@ int bf16_resident_waves_per_cu(int64_t N, int planes) {
   }
 }
 
-hipError_t launch_spmm_bf16(const BrickFormat& f, const WorkItem* items, int64_t n_items,
-                            const float* B, float* C, float* partial, int64_t M, int64_t N,
-                            int64_t K, int planes, int64_t nnz, hipStream_t s) {
-  if (n_items == 0 || N == 0) return hipSuccess;
+hipError_t launch_spmm_bf16(const BrickFormat& f, const WorkSource& w, const float* B, float* C,
+                            float* partial, int64_t M, int64_t N, int64_t K, int planes, int64_t nnz, hipStream_t s) {
+  if (w.n_items == 0 || N == 0) return hipSuccess;
   const uint32_t zero_idx = (uint32_t)nnz;   // vals[nnz .. nnz+63] are zeros
   const int tile = mfma_tile_for(N);
-  unsigned gx = (unsigned)((n_items + kWavesPerBlock - 1) / kWavesPerBlock);
-  gx = (gx + kXcds - 1) / kXcds * kXcds;  // whole rounds over the XCDs
+  const unsigned gx = item_blocks<kWavesPerBlock>(w);
   const dim3 grid(gx, (unsigned)((N + tile - 1) / tile)), block(64 * kWavesPerBlock);
   const uint32_t k_last = (uint32_t)(K - 1);
 #define SPMM_LAUNCH_BF16(TT, PP)                                                            \
-  hipLaunchKernelGGL((k_spmm_bf16<TT, PP>), grid, block, 0, s, f.panel_ptr, f.brick_cols,   \
-                     f.brick_mask, f.brick_valptr, f.vals, items, n_items, B, C, partial, M, N, k_last, zero_idx)
+  hipLaunchKernelGGL((k_spmm_bf16<TT, PP>), grid, block, 0, s,                              \
+                     SPMM_ITEM_ARGS(kWavesPerBlock, w), f.panel_ptr, f.brick_cols,          \
+                     f.brick_mask, f.brick_valptr, f.vals, B, C, partial, M, N, k_last, zero_idx)
   if (planes == 2) {
     switch (tile) {
       case 16: SPMM_LAUNCH_BF16(1, 2); break;

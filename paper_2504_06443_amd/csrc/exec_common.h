@@ -76,17 +76,6 @@ __device__ inline void store_any_nt(float* __restrict__ p, const float* in) {
   }
 }
 
-// Work item `id` of a list, or, without one (every panel whole, in order), panel `id` itself: its
-// bricks come from panel_ptr, 8 bytes instead of 16, and no list has to be built, copied and kept.
-// With a list and without, 262,144 rows: plan, product (N = 128) and destruction 351 and 284 us, the
-// first product of a new width (N = 124) 203 and 151; a 4096-row band, N = 32, without allocation 11.5
-// and 8.4.
-__device__ inline WorkItem work_item(const WorkItem* __restrict__ items,
-                                     const uint32_t* __restrict__ panel_ptr, int64_t id) {
-  if (items) return items[id];
-  return WorkItem{(uint32_t)id, panel_ptr[id], panel_ptr[id + 1], kNoSlot};
-}
-
 // Workgroups are handed to the 8 XCDs round-robin, and each XCD has its own L2.  This maps a
 // workgroup to a "virtual" index such that each XCD works through a contiguous range of work
 // items: neighbouring panels -- which share most of their B rows in banded matrices -- then
@@ -94,6 +83,58 @@ __device__ inline WorkItem work_item(const WorkItem* __restrict__ items,
 __device__ inline uint32_t xcd_contiguous_block() {
   const uint32_t per_xcd = gridDim.x / kXcds;
   return (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
+}
+
+// A WorkSource as the kernels take it.  The items are mapped to the XCDs as xcd_contiguous_block does; the
+// parts of split panels come behind them, dealt to the XCDs in turn: they fill the time in which the last
+// panels end (a graph of 20,360 panels of which 184 are split, N = 128: parts in their panels' places
+// 117.2 us, in front 118.1, behind 115.6).
+struct ItemMap {
+  uint32_t n_items, per_xcd;        // items, and their workgroups on each XCD
+  uint32_t n_parts, split_bricks;
+  const WorkItem *items, *parts;
+};
+
+template <int kPer>
+inline uint32_t xcd_rounds(uint32_t n) { return ((n + kPer - 1) / kPer + kXcds - 1) / kXcds; }
+
+template <int kPer>
+inline unsigned item_blocks(const WorkSource& w) {
+  return (xcd_rounds<kPer>(w.n_items) + xcd_rounds<kPer>(w.n_parts)) * kXcds;
+}
+
+// As kernel parameters: scalars and not the struct, and in front, because a wavefront waits for these first
+// and the build has the leading ones in registers when it starts (-amdgpu-kernarg-preload-count).  Read
+// from memory they are a round trip before panel_ptr: 6250 panels of 40 bricks 31.2 -> 31.5 us.
+#define SPMM_ITEM_PARAMS                                                                        \
+  uint32_t n_items, uint32_t per_xcd, uint32_t n_parts, uint32_t split_bricks,                  \
+      const WorkItem *__restrict__ items, const WorkItem *__restrict__ parts
+#define SPMM_ITEM_MAP \
+  ItemMap { n_items, per_xcd, n_parts, split_bricks, items, parts }
+#define SPMM_ITEM_ARGS(PER, w) \
+  (w).n_items, xcd_rounds<PER>((w).n_items), (w).n_parts, (w).split_bricks, (w).items, (w).parts
+
+// The item of wavefront (or workgroup, kPer = 1) `wave` of this workgroup; false: none.  Without a list
+// a panel's bricks come from panel_ptr, 8 bytes instead of 16, and no list has to be built, copied and
+// kept (262,144 rows: plan, product at N = 128 and destruction 351 us with a list, 284 without; a graph
+// of 20,360 panels of which 184 are split 332 with a list of all items, 286 with one of the parts).
+template <int kPer>
+__device__ inline bool work_item(const ItemMap& m, const uint32_t* panel_ptr, uint32_t wave, WorkItem* it) {
+  const uint32_t whole = m.per_xcd * kXcds;
+  if (__builtin_expect(blockIdx.x < whole, 1)) {
+    const uint32_t id = ((blockIdx.x % kXcds) * m.per_xcd + blockIdx.x / kXcds) * kPer + wave;
+    if (id >= m.n_items) return false;
+    if (__builtin_expect(m.items != nullptr, 0)) {
+      *it = m.items[id];
+      return true;
+    }
+    *it = WorkItem{id, panel_ptr[id], panel_ptr[id + 1], kNoSlot};
+    return it->brick_end - it->brick_begin < m.split_bricks;
+  }
+  const uint32_t id = (blockIdx.x - whole) * kPer + wave;
+  if (id >= m.n_parts) return false;
+  *it = m.parts[id];
+  return true;
 }
 
 inline bool ptr_aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }

@@ -72,16 +72,14 @@ __device__ inline void load_b(const float* __restrict__ brow, int64_t N, int64_t
 
 template <int T, bool ALIGNED>
 __global__ __launch_bounds__(64 * kWavesPerBlock) void k_spmm_mfma(
-    BrickFormat f, const WorkItem* __restrict__ items, int64_t n_items,
-    const float* __restrict__ B, float* __restrict__ C, float* __restrict__ partial, int64_t M,
+    SPMM_ITEM_PARAMS, BrickFormat f, const float* __restrict__ B, float* __restrict__ C, float* __restrict__ partial, int64_t M,
     int64_t N) {
   constexpr int V = T < 4 ? T : 4;
   constexpr int NV = T / V;
   const int lane = threadIdx.x & 63;
-  const uint32_t vblock = xcd_contiguous_block();   // contiguous range of work items per XCD
-  const int64_t item_id = (int64_t)vblock * kWavesPerBlock + (threadIdx.x >> 6);
-  if (item_id >= n_items) return;  // whole wavefront leaves together
-  const WorkItem it = work_item(items, f.panel_ptr, item_id);
+  WorkItem it;
+  if (!work_item<kWavesPerBlock>(SPMM_ITEM_MAP, f.panel_ptr, threadIdx.x >> 6, &it))
+    return;  // whole wavefront leaves together
   const uint32_t panel = __builtin_amdgcn_readfirstlane(it.panel);
   const uint32_t b_begin = __builtin_amdgcn_readfirstlane(it.brick_begin);
   const uint32_t b_end = __builtin_amdgcn_readfirstlane(it.brick_end);
@@ -229,9 +227,9 @@ constexpr int kFastChunk = 8;
 
 template <int T, bool FULL>
 __global__ __launch_bounds__(64 * kWavesPerBlock) void k_spmm_mfma_fast(
-    const uint32_t* __restrict__ panel_ptr, const uint32_t* __restrict__ brick_cols,
+    SPMM_ITEM_PARAMS, const uint32_t* __restrict__ panel_ptr, const uint32_t* __restrict__ brick_cols,
     const uint64_t* __restrict__ brick_mask, const uint32_t* __restrict__ brick_valptr,
-    const float* __restrict__ vals, const WorkItem* __restrict__ items, int64_t n_items,
+    const float* __restrict__ vals,
     const float* __restrict__ B, float* __restrict__ C, float* __restrict__ partial, int64_t M,
     int64_t N, uint32_t k_last) {
   // (the format arrays are separate __restrict__ parameters, not a struct, so that
@@ -242,13 +240,12 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void k_spmm_mfma_fast(
   static_assert(CH % R == 0 && CH * kBrickK <= 64, "stage and lane mapping assume this");
 
   const int lane = threadIdx.x & 63;
-  const uint32_t vblock = xcd_contiguous_block();   // contiguous range of work items per XCD
   // the wavefront's index as a scalar, so that its work item comes through the scalar cache
   // (one round trip less through the vector-memory path before the first brick)
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t item_id = (int64_t)vblock * kWavesPerBlock + wave;
-  if (item_id >= n_items) return;  // whole wavefront leaves together
-  const WorkItem it = work_item(items, panel_ptr, item_id);
+  WorkItem it;
+  if (!work_item<kWavesPerBlock>(SPMM_ITEM_MAP, panel_ptr, wave, &it))
+    return;  // whole wavefront leaves together
   const uint32_t panel = it.panel;
   const uint32_t b_begin = it.brick_begin;
   const uint32_t b_end = it.brick_end;
@@ -691,14 +688,12 @@ __global__ __launch_bounds__(kMergeThreads) void k_merge(const MergeItem* __rest
 }
 
 template <int T, bool ALIGNED>
-hipError_t launch_mfma_t(const BrickFormat& f, const WorkItem* items, int64_t n_items,
-                         const float* B, float* C, float* partial, int64_t M, int64_t N,
-                         hipStream_t s) {
-  unsigned gx = (unsigned)((n_items + kWavesPerBlock - 1) / kWavesPerBlock);
-  gx = (gx + kXcds - 1) / kXcds * kXcds;  // whole rounds over the XCDs
+hipError_t launch_mfma_t(const BrickFormat& f, const WorkSource& w, const float* B, float* C,
+                         float* partial, int64_t M, int64_t N, hipStream_t s) {
+  const unsigned gx = item_blocks<kWavesPerBlock>(w);
   const unsigned gy = (unsigned)((N + 16 * T - 1) / (16 * T));
-  hipLaunchKernelGGL((k_spmm_mfma<T, ALIGNED>), dim3(gx, gy), dim3(64 * kWavesPerBlock), 0, s, f,
-                     items, n_items, B, C, partial, M, N);
+  hipLaunchKernelGGL((k_spmm_mfma<T, ALIGNED>), dim3(gx, gy), dim3(64 * kWavesPerBlock), 0, s, SPMM_ITEM_ARGS(kWavesPerBlock, w), f,
+                     B, C, partial, M, N);
   return hipGetLastError();
 }
 
@@ -778,20 +773,18 @@ int mfma_resident_waves_per_cu(int64_t N, int64_t K) {
   }
 }
 
-hipError_t launch_spmm_mfma(const BrickFormat& f, const WorkItem* items, int64_t n_items,
-                            const float* B, float* C, float* partial, int64_t M, int64_t N,
-                            int64_t K, int64_t nnz, hipStream_t s) {
-  if (n_items == 0 || N == 0) return hipSuccess;
+hipError_t launch_spmm_mfma(const BrickFormat& f, const WorkSource& w, const float* B, float* C,
+                            float* partial, int64_t M, int64_t N, int64_t K, int64_t nnz, hipStream_t s) {
+  if (w.n_items == 0 || N == 0) return hipSuccess;
   if (mfma_32bit_shape(N, K) && mfma_32bit_values(nnz)) {
     const int tile = mfma_fp32_tile(N, K, nnz);
-    unsigned gx = (unsigned)((n_items + kWavesPerBlock - 1) / kWavesPerBlock);
-    gx = (gx + kXcds - 1) / kXcds * kXcds;  // whole rounds over the XCDs
+    const unsigned gx = item_blocks<kWavesPerBlock>(w);
     const dim3 grid(gx, (unsigned)((N + tile - 1) / tile)), block(64 * kWavesPerBlock);
     const uint32_t k_last = (uint32_t)(K - 1);
 #define SPMM_LAUNCH_FAST(TT, FF)                                                                \
-  hipLaunchKernelGGL((k_spmm_mfma_fast<TT, FF>), grid, block, 0, s, f.panel_ptr, f.brick_cols,  \
-                     f.brick_mask, f.brick_valptr, f.vals, items, n_items, B, C, partial, M, N, \
-                     k_last)
+  hipLaunchKernelGGL((k_spmm_mfma_fast<TT, FF>), grid, block, 0, s,                             \
+                     SPMM_ITEM_ARGS(kWavesPerBlock, w), f.panel_ptr, f.brick_cols,              \
+                     f.brick_mask, f.brick_valptr, f.vals, B, C, partial, M, N, k_last)
     switch (tile / 16) {
       case 1: SPMM_LAUNCH_FAST(1, false); break;
       case 2: SPMM_LAUNCH_FAST(2, false); break;
@@ -812,13 +805,13 @@ hipError_t launch_spmm_mfma(const BrickFormat& f, const WorkItem* items, int64_t
   const bool al = (N % V == 0) && ptr_aligned16(B) && ptr_aligned16(C) &&
                   (partial == nullptr || ptr_aligned16(partial));
   switch (tile) {
-    case 16: return launch_mfma_t<1, true>(f, items, n_items, B, C, partial, M, N, s);
-    case 32: return al ? launch_mfma_t<2, true>(f, items, n_items, B, C, partial, M, N, s)
-                       : launch_mfma_t<2, false>(f, items, n_items, B, C, partial, M, N, s);
-    case 64: return al ? launch_mfma_t<4, true>(f, items, n_items, B, C, partial, M, N, s)
-                       : launch_mfma_t<4, false>(f, items, n_items, B, C, partial, M, N, s);
-    default: return al ? launch_mfma_t<8, true>(f, items, n_items, B, C, partial, M, N, s)
-                       : launch_mfma_t<8, false>(f, items, n_items, B, C, partial, M, N, s);
+    case 16: return launch_mfma_t<1, true>(f, w, B, C, partial, M, N, s);
+    case 32: return al ? launch_mfma_t<2, true>(f, w, B, C, partial, M, N, s)
+                       : launch_mfma_t<2, false>(f, w, B, C, partial, M, N, s);
+    case 64: return al ? launch_mfma_t<4, true>(f, w, B, C, partial, M, N, s)
+                       : launch_mfma_t<4, false>(f, w, B, C, partial, M, N, s);
+    default: return al ? launch_mfma_t<8, true>(f, w, B, C, partial, M, N, s)
+                       : launch_mfma_t<8, false>(f, w, B, C, partial, M, N, s);
   }
 }
 

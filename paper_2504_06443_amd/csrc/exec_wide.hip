@@ -21,11 +21,10 @@ constexpr int kChunk = 8;    // bricks per decode chunk
 
 template <int W>
 __global__ __launch_bounds__(64 * W) void k_spmm_mfma_wide(
-    const uint32_t* __restrict__ panel_ptr, const uint32_t* __restrict__ brick_cols,
+    SPMM_ITEM_PARAMS, const uint32_t* __restrict__ panel_ptr, const uint32_t* __restrict__ brick_cols,
     const uint64_t* __restrict__ brick_mask, const uint32_t* __restrict__ brick_valptr,
-    const float* __restrict__ vals, const WorkItem* __restrict__ items, int64_t n_items,
-    const float* __restrict__ B, float* __restrict__ C, float* __restrict__ partial, int64_t M,
-    int64_t N, uint32_t k_last) {
+    const float* __restrict__ vals, const float* __restrict__ B, float* __restrict__ C,
+    float* __restrict__ partial, int64_t M, int64_t N, uint32_t k_last) {
   constexpr int T = 8, V = 4, NV = 2;
   constexpr int R = kStages;
   constexpr int CH = kChunk;
@@ -36,9 +35,9 @@ __global__ __launch_bounds__(64 * W) void k_spmm_mfma_wide(
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t item_id = xcd_contiguous_block();   // one work item per workgroup
-  if (item_id >= n_items) return;                   // the whole workgroup leaves together
-  const WorkItem it = work_item(items, panel_ptr, item_id);   // uniform index: through the scalar cache
+  WorkItem it;                                      // one work item per workgroup
+  if (!work_item<1>(SPMM_ITEM_MAP, panel_ptr, 0, &it))
+    return;                                         // the whole workgroup leaves together
   const uint32_t panel = it.panel;
   const uint32_t b_begin = it.brick_begin;
   const uint32_t b_end = it.brick_end;
@@ -192,24 +191,23 @@ int mfma_wide_waves(int64_t N, int64_t K) {
   return 0;
 }
 
-hipError_t launch_spmm_mfma_wide(const BrickFormat& f, const WorkItem* items, int64_t n_items,
-                                 const float* B, float* C, float* partial, int64_t M, int64_t N,
-                                 int64_t K, hipStream_t s) {
-  if (n_items == 0 || N == 0) return hipSuccess;
+hipError_t launch_spmm_mfma_wide(const BrickFormat& f, const WorkSource& w, const float* B, float* C,
+                                 float* partial, int64_t M, int64_t N, int64_t K, hipStream_t s) {
+  if (w.n_items == 0 || N == 0) return hipSuccess;
   const int W = mfma_wide_waves(N, K);
   if (W == 0 || !ptr_aligned16(B) || !ptr_aligned16(C) ||
       (partial != nullptr && !ptr_aligned16(partial)))
     return hipErrorInvalidValue;
   const int64_t tiles = (N + 127) / 128;
-  const unsigned gx = (unsigned)((n_items + kXcds - 1) / kXcds * kXcds);
+  const unsigned gx = item_blocks<1>(w);
   const dim3 grid(gx, (unsigned)(tiles / W));
   const uint32_t k_last = (uint32_t)(K - 1);
   if (W == 4)
-    hipLaunchKernelGGL(k_spmm_mfma_wide<4>, grid, dim3(256), 0, s, f.panel_ptr, f.brick_cols,
-                       f.brick_mask, f.brick_valptr, f.vals, items, n_items, B, C, partial, M, N, k_last);
+    hipLaunchKernelGGL(k_spmm_mfma_wide<4>, grid, dim3(256), 0, s,
+                       SPMM_ITEM_ARGS(1, w), f.panel_ptr, f.brick_cols, f.brick_mask, f.brick_valptr, f.vals, B, C, partial, M, N, k_last);
   else
-    hipLaunchKernelGGL(k_spmm_mfma_wide<2>, grid, dim3(128), 0, s, f.panel_ptr, f.brick_cols,
-                       f.brick_mask, f.brick_valptr, f.vals, items, n_items, B, C, partial, M, N, k_last);
+    hipLaunchKernelGGL(k_spmm_mfma_wide<2>, grid, dim3(128), 0, s,
+                       SPMM_ITEM_ARGS(1, w), f.panel_ptr, f.brick_cols, f.brick_mask, f.brick_valptr, f.vals, B, C, partial, M, N, k_last);
   return hipGetLastError();
 }
 

@@ -50,6 +50,18 @@ struct WorkItem {           // one wavefront's share of the MFMA kernel
 };
 constexpr uint32_t kNoSlot = 0xFFFFFFFFu;
 
+// What the wavefronts of a brick kernel take.  Either a list names every item, or the panels do, whole
+// and in order, with panel_ptr in the list's place; panels of split_bricks bricks and more are left to
+// `parts`, which lists their parts.
+struct WorkSource {
+  const WorkItem* items;    // null: item i is panel i
+  const WorkItem* parts;    // items null: parts of split panels
+  uint32_t n_items;         // of the list, or panels
+  uint32_t n_parts;
+  uint32_t split_bricks;    // kNoSplit where no panel is split
+};
+constexpr uint32_t kNoSplit = 0xFFFFFFFFu;
+
 struct MergeItem {          // one split panel
   uint32_t panel;
   uint32_t slot_begin;      // its partial tiles are slot_begin .. slot_begin+nparts-1
@@ -166,22 +178,20 @@ bool mfma_32bit_values(int64_t nnz);           // where the packed values are to
 // shapes of the 32-row kernel when B and C are 16-byte aligned: N a multiple of the vector
 // width, B below 4 GiB
 bool mfma_fast_shape(int64_t N, int64_t K);
-// In this and the launches of the other brick kernels of 16-row panels `items` may be null: one item per
-// panel, n_items panels.
-hipError_t launch_spmm_mfma(const BrickFormat& f, const WorkItem* items, int64_t n_items,
+hipError_t launch_spmm_mfma(const BrickFormat& f, const WorkSource& work,
                             const float* B, float* C, float* partial, int64_t M, int64_t N,
                             int64_t K, int64_t nnz, hipStream_t s);
 // wide-N variant (exec_wide.hip): one workgroup per work item whose wavefronts take different
 // 128-column tiles and share the decoded bricks through LDS.  mfma_wide_waves: wavefronts per
 // workgroup it would use for (N, K), 0 when the shape is not served
 int mfma_wide_waves(int64_t N, int64_t K);
-hipError_t launch_spmm_mfma_wide(const BrickFormat& f, const WorkItem* items, int64_t n_items,
+hipError_t launch_spmm_mfma_wide(const BrickFormat& f, const WorkSource& work,
                                  const float* B, float* C, float* partial, int64_t M, int64_t N,
                                  int64_t K, hipStream_t s);
 // split-bf16 variant (exec_bf16.hip): planes = 2 or 3 bf16 terms per FP32 input
 bool bf16_path_shape(int64_t N, int64_t K);
 int bf16_resident_waves_per_cu(int64_t N, int planes);
-hipError_t launch_spmm_bf16(const BrickFormat& f, const WorkItem* items, int64_t n_items,
+hipError_t launch_spmm_bf16(const BrickFormat& f, const WorkSource& work,
                             const float* B, float* C, float* partial, int64_t M, int64_t N,
                             int64_t K, int planes, int64_t nnz, hipStream_t s);
 // `panels` is sorted ascending; `long_rows` lists the rows of the whole matrix with more than
