@@ -120,20 +120,27 @@ inline unsigned item_blocks(const WorkSource& w) {
 // of 20,360 panels of which 184 are split 332 with a list of all items, 286 with one of the parts).
 template <int kPer>
 __device__ inline bool work_item(const ItemMap& m, const uint32_t* panel_ptr, uint32_t wave, WorkItem* it) {
-  const uint32_t whole = m.per_xcd * kXcds;
-  if (__builtin_expect(blockIdx.x < whole, 1)) {
-    const uint32_t id = ((blockIdx.x % kXcds) * m.per_xcd + blockIdx.x / kXcds) * kPer + wave;
-    if (id >= m.n_items) return false;
-    if (__builtin_expect(m.items != nullptr, 0)) {
-      *it = m.items[id];
-      return true;
-    }
-    *it = WorkItem{id, panel_ptr[id], panel_ptr[id + 1], kNoSlot};
-    return it->brick_end - it->brick_begin < m.split_bricks;
+  const uint32_t whole = m.per_xcd * kXcds;   // workgroups of the items
+  const bool part = blockIdx.x >= whole;
+  const uint32_t block = part ? blockIdx.x - whole : (blockIdx.x % kXcds) * m.per_xcd + blockIdx.x / kXcds;
+  const uint32_t id = block * kPer + wave;
+  if (__builtin_expect(id >= (part ? m.n_parts : m.n_items), 0)) return false;
+  const WorkItem* list = part ? m.parts : m.items;
+  // (the loads of begin and end stand behind the branch, and the test for a split panel is no branch, so
+  // that nothing which follows waits for them: a split panel has nothing to multiply and, as a panel behind
+  // the last row, nothing to store)
+  const uint32_t *begin = panel_ptr + id, *end = begin + 1;
+  uint32_t panel = id, slot = kNoSlot, split = m.split_bricks;
+  if (list) {
+    begin = &list[id].brick_begin;
+    end = &list[id].brick_end;
+    panel = list[id].panel;
+    slot = list[id].slot;
+    split = kNoSplit;
   }
-  const uint32_t id = (blockIdx.x - whole) * kPer + wave;
-  if (id >= m.n_parts) return false;
-  *it = m.parts[id];
+  const uint32_t b = *begin, e = *end;
+  const bool is_whole = e - b < split;
+  *it = WorkItem{is_whole ? panel : kNoPanel, b, is_whole ? e : b, slot};
   return true;
 }
 

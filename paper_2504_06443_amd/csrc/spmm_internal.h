@@ -49,6 +49,7 @@ struct WorkItem {           // one wavefront's share of the MFMA kernel
   uint32_t slot;            // kNoSlot: store to C; else index of a 16 x N partial tile
 };
 constexpr uint32_t kNoSlot = 0xFFFFFFFFu;
+constexpr uint32_t kNoPanel = 0xFFFFFFFFu;   // its rows lie behind every matrix's last
 
 // What the wavefronts of a brick kernel take.  Either a list names every item, or the panels do, whole
 // and in order, with panel_ptr in the list's place; panels of split_bricks bricks and more are left to
