@@ -11,6 +11,7 @@
 #include <cstdio>
 #include <cstring>
 #include <atomic>
+#include <chrono>
 #include <map>
 #include <mutex>
 #include <new>
@@ -66,7 +67,7 @@ class HostStage {
       }
     }
     void* p = nullptr;
-    if (hipHostMalloc(&p, kStageBytes, hipHostMallocPortable) == hipSuccess) p_ = static_cast<char*>(p);
+    if (hipHostMalloc(&p, kStageBytes, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess) p_ = static_cast<char*>(p);
     else (void)hipGetLastError();
   }
   // (the owner has waited for the copies by now)
@@ -93,6 +94,21 @@ class HostStage {
   }
   char* p_ = nullptr;
 };
+
+// Waits until the device has set `flag` (pinned memory): by looking for a short while, which is as long as
+// the kernels of most plans take and sees the flag some microseconds before the runtime would report the
+// stream idle, then by waiting for the stream.
+hipError_t wait_for_flag(const uint32_t* flag, hipStream_t s) {
+  auto is_set = [&] { return __atomic_load_n(flag, __ATOMIC_ACQUIRE) != 0; };
+  const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(200);
+  while (!is_set()) {
+    for (int i = 0; i < 32; ++i) __builtin_ia32_pause();
+    if (std::chrono::steady_clock::now() < until) continue;
+    const hipError_t e = hipStreamSynchronize(s);
+    return e != hipSuccess ? e : is_set() ? hipSuccess : hipErrorUnknown;
+  }
+  return hipSuccess;
+}
 
 // Host half of a work list: what the routing and Eq. 6-7 decide for one N.
 struct HostList {
@@ -746,7 +762,7 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
   uint32_t *scan_tmp, *ncols_p, *mid_list, *big_list;
   enum { kPathSearch, kPathBitmap, kPathSort } path = kPathSearch;
   uint32_t h_maxnb = 0, words_cap = 0;
-  bool sort_fits = false;
+  bool sort_fits = false, counted = false;
   uint8_t* col_seen;
   const int64_t scan_elems =
       std::max((int64_t)scan_tmp_elems(nnz), (int64_t)panel_scan_tmp_elems());  // bricks <= nnz
@@ -802,17 +818,31 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
   pl->rowptr = fixed.take<int32_t>(M + 1);
   pl->src = fixed.take<uint32_t>(nnz);
 
-  // ---- rowptr validation and the widest panel span (device), before anything trusts rowptr
+  // ---- rowptr validation, the widest panel span and, where the spans are short, the census (device),
+  // before anything trusts rowptr
   HIP_TRY(hipMemsetAsync(work.base, 0, (size_t)(reinterpret_cast<char*>(scan_tmp) - work.base), s));
-  HIP_TRY(launch_rows(rowptr, colind, M, P, nnz, pl->rowptr, pl->panel_nnzptr, ctl, s));
-  HIP_TRY(read_ctl());
+  if (stage.get()) {
+    PlanControl* pinned = reinterpret_cast<PlanControl*>(stage.get());
+    uint32_t* flag = reinterpret_cast<uint32_t*>(stage.get() + Arena::pad(sizeof(PlanControl)));
+    __atomic_store_n(flag, 0u, __ATOMIC_RELAXED);
+    HIP_TRY(launch_rows_census(rowptr, colind, M, K, P, nnz, pl->rowptr, pl->panel_nnzptr, ncols_p,
+                               pl->panel_ptr, scan_tmp, ctl, pinned, flag, s));
+    HIP_TRY(wait_for_flag(flag, s));
+    memcpy(&h_ctl, pinned, sizeof(PlanControl));
+  } else {
+    HIP_TRY(launch_rows_census(rowptr, colind, M, K, P, nnz, pl->rowptr, pl->panel_nnzptr, ncols_p,
+                               pl->panel_ptr, scan_tmp, ctl, nullptr, nullptr, s));
+    HIP_TRY(read_ctl());
+  }
   if (h_ctl.err & (kErrRowptrEnds | kErrRowptrOrder)) {
     status = fail(SPMM_EFORMAT, "invalid rowptr (%s)",
                   (h_ctl.err & kErrRowptrEnds) ? "rowptr[0] != 0 or rowptr[M] != nnz" : "not monotone");
     goto done;
   }
-  if (h_ctl.err & (kErrColRange | kErrColOrder)) {   // a panel whose column span is inverted
-    status = fail(SPMM_EFORMAT, "invalid colind (columns of a row not strictly ascending)");
+  if (h_ctl.err) {   // a panel whose column span is inverted, or what the census found where it ran
+    status = fail(SPMM_EFORMAT, "invalid colind (%s)",
+                  (h_ctl.err & kErrColRange) ? "column out of range"
+                                             : "columns of a row not strictly ascending");
     goto done;
   }
   words_cap = panel_bitmap_words(h_ctl.span, P);
@@ -828,7 +858,10 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
   sort_fits = panel_sort_fits(P, nnz, h_ctl.max_nnz);
   if (words_cap != 0 && (int64_t)words_cap * P <= (sort_fits ? 2 : 8) * nnz) path = kPathBitmap;
   else if (sort_fits) path = kPathSort;
-  if (path == kPathBitmap) {
+  counted = h_ctl.counted;   // then panel_ptr is there, whichever path takes it
+  if (counted && path == kPathBitmap) {
+    // (and nothing is left of the census)
+  } else if (path == kPathBitmap) {
     // ---- a1/a2: census (also validates colind) -> bricks per panel
     HIP_TRY(launch_panel_census(rowptr, colind, M, K, P, words_cap, &ctl->err, ncols_p, s));
   } else if (path == kPathSort) {
@@ -841,8 +874,8 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
     status = wide_a1();
     if (status != SPMM_OK) goto done;
   }
-  HIP_TRY(launch_panel_scan(ncols_p, P, pl->panel_ptr, scan_tmp, ctl, s));
-  HIP_TRY(read_ctl());
+  if (!counted) HIP_TRY(launch_panel_scan(ncols_p, P, pl->panel_ptr, scan_tmp, ctl, s));
+  if (!counted || path != kPathBitmap) HIP_TRY(read_ctl());
   if (h_ctl.err) {
     status = fail(SPMM_EFORMAT, "invalid colind (%s)",
                   (h_ctl.err & kErrColRange) ? "column out of range"
@@ -872,7 +905,6 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
   pl->brick_mask = bricks.take<uint64_t>(pl->nb + kFormatPad);
   pl->brick_valptr = bricks.take<uint32_t>(pl->nb + 1 + kFormatPad);
   pl->vals = bricks.take<float>(nnz + 64);
-  HIP_TRY(launch_format_pad(pl->brick_cols, pl->brick_mask, pl->brick_valptr, pl->vals, pl->nb, nnz, s));
 
   if (path == kPathSort) {
     HIP_TRY(launch_panel_sort_build(rowptr, colind, vals, M, P,
@@ -908,9 +940,9 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
     HIP_TRY(launch_pack_values(vals, ent_brick, ent_bit, pl->brick_mask, pl->brick_valptr, nnz,
                                pl->vals, pl->src, s));
   }
-  // ---- a5: per-panel classes and the synergy counts
-  HIP_TRY(launch_plan_stats(pl->panel_ptr, pl->panel_nnzptr, P, pl->brick_mask, pl->nb, col_seen, K,
-                            ctl->counters, s));
+  // ---- the spare entries behind the brick arrays, and a5: per-panel classes and the synergy counts
+  HIP_TRY(launch_plan_stats(pl->panel_ptr, pl->panel_nnzptr, P, pl->brick_cols, pl->brick_mask,
+                            pl->brick_valptr, pl->vals, pl->nb, nnz, col_seen, K, ctl->counters, s));
 
   // ---- host copies for the work-list builder and the model
   pl->max_bricks = h_maxnb;

@@ -65,72 +65,6 @@ __device__ inline void raise_to(uint32_t* p, uint32_t v) {
   if (v > __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(p, v);
 }
 
-// ---------------------------------------------------------------- rows
-// One pass over the rows, a thread each, sixteen neighbouring lanes a panel: checks rowptr, copies
-// it into the plan, writes the entry offset of each panel, and finds the widest column span and the
-// largest entry count of a panel, from which the plan chooses how to build.  A row's columns are
-// bounded by its first and last entry; they are read only where the row's own offsets are in order
-// and inside [0, nnz].  A panel with entries and an inverted span (the last column of every row
-// below the first column of some row) is not sorted or has a negative column.
-// Bound by the latency of two dependent loads, hence a thread per row; one block maximum per 1024
-// rows in flight keeps the atomics on one address few.  262,144 rows: 29 us as a thread per panel
-// and a separate check, 12 us so.
-constexpr int kRowThreads = 1024;
-constexpr int kRowBlocks = 256;
-
-__global__ __launch_bounds__(kRowThreads) void k_rows(
-    const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind, int64_t M, int64_t P,
-    int64_t nnz, int32_t* __restrict__ rowptr_copy, uint32_t* __restrict__ panel_nnzptr,
-    PlanControl* ctl) {
-  __shared__ uint32_t s_err, s_span, s_nnz;
-  if (threadIdx.x == 0) { s_err = 0; s_span = 0; s_nnz = 0; }
-  __syncthreads();
-  uint32_t err = 0, span = 0, most = 0;
-  const int64_t stride = (int64_t)gridDim.x * kRowThreads;
-  for (int64_t base = (int64_t)blockIdx.x * kRowThreads; base <= M; base += stride) {
-    const int64_t i = base + threadIdx.x;
-    int32_t lo = 0x7FFFFFFF, hi = -1;
-    uint32_t cnt = 0;
-    if (i <= M) {
-      const int32_t a = rowptr[i], b = i < M ? rowptr[i + 1] : a;
-      rowptr_copy[i] = a;
-      if (i % kPanel == 0) panel_nnzptr[i / kPanel] = (uint32_t)a;
-      else if (i == M) panel_nnzptr[P] = (uint32_t)a;
-      if (i == 0 && a != 0) err |= kErrRowptrEnds;
-      if (i == M && a != nnz) err |= kErrRowptrEnds;
-      if (a < 0 || a > nnz || b < a) err |= kErrRowptrOrder;
-      else if (a < b && b <= nnz) {
-        lo = colind[a];
-        hi = colind[b - 1];
-        cnt = (uint32_t)(b - a);
-      }
-    }
-#pragma unroll
-    for (int d = 8; d > 0; d >>= 1) {
-      lo = min(lo, __shfl_xor(lo, d, 64));
-      hi = max(hi, __shfl_xor(hi, d, 64));
-      cnt += __shfl_xor(cnt, d, 64);
-    }
-    if (hi >= lo) span = max(span, (uint32_t)((int64_t)hi - lo + 1));
-    else if (cnt) err |= kErrColOrder;
-    most = max(most, cnt);
-  }
-  err = wave_or(err);
-  span = wave_max(span);
-  most = wave_max(most);
-  if ((threadIdx.x & 63) == 0) {
-    if (err) atomicOr(&s_err, err);
-    atomicMax(&s_span, span);
-    atomicMax(&s_nnz, most);
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    if (s_err) atomicOr(&ctl->err, s_err);
-    raise_to(&ctl->span, s_span);
-    raise_to(&ctl->max_nnz, s_nnz);
-  }
-}
-
 // Requires a valid rowptr.  Also records the row of every entry.
 __global__ void k_validate_cols(const int32_t* __restrict__ rowptr,
                                 const int32_t* __restrict__ colind, int64_t M, int64_t K,
@@ -317,13 +251,23 @@ __global__ __launch_bounds__(kThreads) void k_restore_csr(
 // and same-address atomics of many workgroups were what the separate kernels for these three spent
 // their time on (630 k bricks of 16,384 panels: 55 us in three launches, 8 us in
 // this one).
+// The first workgroup also writes the spare entries behind the brick arrays (see BrickFormat).
 constexpr int kStatThreads = 1024;
 constexpr int kStatBlocks = 128;
 
 __global__ __launch_bounds__(kStatThreads) void k_plan_stats(
     const uint32_t* __restrict__ panel_ptr, const uint32_t* __restrict__ panel_nnzptr, int64_t P,
-    const uint64_t* __restrict__ brick_mask, int64_t nb, const uint8_t* __restrict__ col_seen,
-    int64_t K, unsigned long long* counters) {
+    uint32_t* __restrict__ brick_cols, uint64_t* __restrict__ brick_mask,
+    uint32_t* __restrict__ brick_valptr, float* __restrict__ vals, int64_t nb, int64_t nnz,
+    const uint8_t* __restrict__ col_seen, int64_t K, unsigned long long* counters) {
+  static_assert(kFormatPad * kBrickK <= kStatThreads && kFormatPad < 64, "one workgroup writes the pads");
+  if (blockIdx.x == 0) {
+    const int t = threadIdx.x;
+    if (t < kFormatPad * kBrickK) brick_cols[nb * kBrickK + t] = 0;
+    if (t < kFormatPad) brick_mask[nb + t] = 0;
+    if (t < kFormatPad + 1) brick_valptr[nb + t] = (uint32_t)nnz;
+    if (t < 64) vals[nnz + t] = 0.f;
+  }
   constexpr int kWaves = kStatThreads / 64;
   __shared__ uint32_t hist[kWaves][65];          // a histogram per wavefront: fewer collisions
   __shared__ unsigned long long acc[kCntPopHist];
@@ -390,17 +334,6 @@ __global__ __launch_bounds__(kStatThreads) void k_plan_stats(
     for (int w = 0; w < kWaves; ++w) h += hist[w][threadIdx.x];
     if (h) atomicAdd(&counters[kCntPopHist + threadIdx.x], h);
   }
-}
-
-// the spare entries behind the brick arrays (see BrickFormat); one workgroup of kThreads
-__global__ void k_format_pad(uint32_t* __restrict__ brick_cols, uint64_t* __restrict__ brick_mask,
-                             uint32_t* __restrict__ brick_valptr, float* __restrict__ vals,
-                             int64_t nb, int64_t nnz) {
-  const int t = threadIdx.x;
-  if (t < kFormatPad * kBrickK) brick_cols[nb * kBrickK + t] = 0;
-  if (t < kFormatPad) brick_mask[nb + t] = 0;
-  if (t < kFormatPad + 1) brick_valptr[nb + t] = (uint32_t)nnz;
-  if (t < 64) vals[nnz + t] = 0.f;
 }
 
 // Rows with more than `threshold` entries, compacted in any order (the CSR kernel gives each of
@@ -669,7 +602,7 @@ __device__ inline void panel_bitmap(const int32_t* __restrict__ colind, const Pa
 }
 
 // a1/a2 (counting half): active columns of each panel; validates colind.  Requires a valid rowptr (the
-// host has seen k_rows' verdict).  Dynamic LDS: the bitmap.
+// host has seen k_rows_census' verdict).  Dynamic LDS: the bitmap.
 __global__ __launch_bounds__(kPanelThreads) void k_panel_census(
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind, int64_t M, int64_t K,
     int64_t P, uint32_t words_cap, uint32_t* err, uint32_t* __restrict__ ncols_p) {
@@ -688,7 +621,7 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_census(
     return;
   }
   const uint32_t words = (uint32_t)(x.cmax - x.cmin) / 32u + 1u;
-  if (words > words_cap) {   // cannot happen for sorted rows (the cap comes from k_rows)
+  if (words > words_cap) {   // cannot happen for sorted rows (the cap comes from k_rows_census)
     if (threadIdx.x == 0) { atomicOr(err, (uint32_t)kErrColOrder); ncols_p[p] = 0; }
     return;
   }
@@ -698,6 +631,246 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_census(
   uint32_t total;
   wave_exclusive(cnt, &total);
   if (threadIdx.x == 0) ncols_p[p] = total;
+}
+
+// ---- rows and, for band-like matrices, the census in the same pass
+// The first launch of every plan.  A wavefront takes a panel: checks its rowptr, copies it into the plan,
+// writes the panel's entry offset, finds its column span and entry count (from which the plan chooses how to
+// build), and, where a bitmap over that span is short, counts the panel's active columns as k_panel_census
+// does.  A row's columns are bounded by its first and last entry; they are read only where the row's own
+// offsets are in order and inside [0, nnz].  A panel with entries and an inverted span (the last column of
+// every row below the first column of some row) is not sorted or has a negative column.
+// A workgroup takes a run of panels and leaves its totals in `totals`, so nothing is added to a common
+// counter and the scan that follows needs no pass of its own over the counts.  Entries are read four a lane,
+// neighbours, whose columns mostly share a bitmap word and then cost one LDS atomic; only an entry that does
+// not lie above the one before it looks up whether it begins a row.
+// Bound by the latency of three dependent loads a panel.  262,144 rows, 7.86 M entries: a pass over the rows,
+// a wait for their span and the census took 12 + 15 + 20 us, this takes 18.7; the rows of a graph of 20,360
+// panels 12.2 -> 9.6.
+constexpr int kFirstThreads = 512, kFirstWaves = kFirstThreads / 64;
+constexpr int kFirstBlocks = 768;                   // three a CU
+constexpr uint32_t kFirstWords = 512;               // bitmap words a wavefront: 16,384 columns
+
+struct PanelTotals {
+  uint32_t bricks, blocks, cols, max_cols;
+  uint32_t span, max_nnz, err, skipped;   // skipped: a panel without a count
+};
+
+typedef int32_t Int4Any __attribute__((ext_vector_type(4), aligned(4)));   // at any dword address
+
+__device__ inline void wave_lds_fence() {   // LDS writes of the wavefront's lanes, seen by its other lanes
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+__global__ __launch_bounds__(kFirstThreads, 6) void k_rows_census(
+    const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind, int64_t M, int64_t K,
+    int64_t P, int64_t nnz, int64_t run, int32_t* __restrict__ rowptr_copy,
+    uint32_t* __restrict__ panel_nnzptr, uint32_t* __restrict__ ncols_p,
+    PanelTotals* __restrict__ totals) {
+  __shared__ uint32_t s_bm[kFirstWaves][kFirstWords];
+  __shared__ int32_t s_rp[kFirstWaves][kPanel + 1];
+  __shared__ PanelTotals s_tot[kFirstWaves];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t* bm = s_bm[wave];
+  int32_t* rp = s_rp[wave];
+  PanelTotals t{};
+  const int64_t p_end = min((int64_t)(blockIdx.x + 1) * run, P);
+  for (int64_t p = (int64_t)blockIdx.x * run + wave; p < p_end; p += kFirstWaves) {
+    const int64_t i = p * kPanel + lane;
+    const int32_t a = rowptr[min(i, M)];
+    const int32_t b = __shfl_down(a, 1, 64);   // (row M's own offset past the last row)
+    int32_t lo = 0x7FFFFFFF, hi = -1;
+    uint32_t cnt = 0, err = 0;
+    if (lane <= kPanel) rp[lane] = a;
+    if (lane < kPanel && i < M) {
+      rowptr_copy[i] = a;
+      if (i == 0 && a != 0) err |= kErrRowptrEnds;
+      if (a < 0 || a > nnz || b < a) err |= kErrRowptrOrder;
+      else if (a < b && b <= nnz) {
+        lo = colind[a];
+        hi = colind[b - 1];
+        cnt = (uint32_t)(b - a);
+      }
+    }
+    if (i == M && lane <= kPanel) {            // the end of the last row
+      rowptr_copy[M] = a;
+      panel_nnzptr[P] = (uint32_t)a;
+      if (a != nnz) err |= kErrRowptrEnds;
+      if (a < 0 || a > nnz) err |= kErrRowptrOrder;
+    }
+    if (lane == 0) panel_nnzptr[p] = (uint32_t)a;
+    err = wave_or(err);
+#pragma unroll
+    for (int d = 8; d > 0; d >>= 1) {          // rows sit in lanes 0..15
+      lo = min(lo, __shfl_xor(lo, d, 64));
+      hi = max(hi, __shfl_xor(hi, d, 64));
+      cnt += __shfl_xor(cnt, d, 64);
+    }
+    const int32_t cmin = __builtin_amdgcn_readfirstlane(lo), cmax = __builtin_amdgcn_readfirstlane(hi);
+    const uint32_t n = __builtin_amdgcn_readfirstlane(cnt);
+    t.max_nnz = max(t.max_nnz, n);
+    if (cmax < cmin) {
+      t.err |= err | (n ? (uint32_t)kErrColOrder : 0u);
+      if (lane == 0) ncols_p[p] = 0;
+      continue;
+    }
+    const uint32_t span = (uint32_t)((int64_t)cmax - cmin + 1);
+    const uint32_t words = (span + 31) / 32;
+    t.span = max(t.span, span);
+    t.err |= err;
+    if (err || words > kFirstWords || words > 4 * n + 64) {
+      t.skipped = 1;
+      continue;
+    }
+
+    // census: the panel's rows are in order, so its entries are the n from the first row's offset on
+    for (uint32_t w = lane; w < words; w += 64) bm[w] = 0;
+    wave_lds_fence();
+    const int32_t* __restrict__ col = colind + rp[0];
+    uint32_t bad = 0;
+    int32_t last = -1;                         // the column before this round's first
+    for (uint32_t base = 0; base < n; base += 256) {
+      const uint32_t e = base + 4 * lane;
+      int32_t j[4];
+      if (e + 4 <= n) {
+        const Int4Any v = *reinterpret_cast<const Int4Any*>(col + e);
+        j[0] = v.x; j[1] = v.y; j[2] = v.z; j[3] = v.w;
+      } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) j[k] = col[min(e + k, n - 1)];
+      }
+      int32_t before = __shfl_up(j[3], 1, 64);
+      if (lane == 0) before = last;
+      last = __shfl(j[3], 63, 64);
+      uint32_t word = 0xFFFFFFFFu, bits = 0, unsure = 0;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if (e + k < n) {
+          if (j[k] < 0 || j[k] >= K) bad |= kErrColRange;
+          if ((k ? j[k > 0 ? k - 1 : 0] : before) >= j[k]) unsure |= 1u << k;
+          if (j[k] >= cmin && j[k] <= cmax) {
+            const uint32_t d = (uint32_t)(j[k] - cmin);
+            if (d / 32 != word) {
+              if (bits) atomicOr(&bm[word], bits);
+              word = d / 32;
+              bits = 0;
+            }
+            bits |= 1u << (d & 31);
+          } else {
+            bad |= kErrColOrder;   // outside the span its sorted row promised
+          }
+        }
+      }
+      if (bits) atomicOr(&bm[word], bits);
+      while (unsure) {             // above its predecessor, or the first of a row
+        const int64_t at = (int64_t)rp[0] + e + (uint32_t)__builtin_ctz(unsure);
+        if (at > rp[row_in_panel(rp, at)]) bad |= kErrColOrder;
+        unsure &= unsure - 1;
+      }
+    }
+    wave_lds_fence();
+    uint32_t cols = 0;
+    for (uint32_t w = lane; w < words; w += 64) cols += __popc(bm[w]);
+    cols = __builtin_amdgcn_readfirstlane(wave_sum(cols));
+    t.err |= wave_or(bad);
+    if (lane == 0) ncols_p[p] = cols;
+    const uint32_t bricks = (cols + kBrickK - 1) / kBrickK;
+    t.bricks += bricks;
+    t.blocks += (bricks + kBrickK - 1) / kBrickK;
+    t.cols += cols;
+    t.max_cols = max(t.max_cols, cols);
+    wave_lds_fence();              // (bm and rp are the next panel's from here on)
+  }
+  if (P == 0 && threadIdx.x == 0) {
+    const int32_t a = rowptr[0];
+    rowptr_copy[0] = a;
+    panel_nnzptr[0] = (uint32_t)a;
+    if (a != 0 || a != nnz) t.err |= kErrRowptrEnds;
+    if (a < 0 || a > nnz) t.err |= kErrRowptrOrder;
+  }
+  if (lane == 0) s_tot[wave] = t;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < kFirstWaves; ++w) {
+      const PanelTotals o = s_tot[w];
+      t.bricks += o.bricks; t.blocks += o.blocks; t.cols += o.cols;
+      t.max_cols = max(t.max_cols, o.max_cols);
+      t.span = max(t.span, o.span); t.max_nnz = max(t.max_nnz, o.max_nnz);
+      t.err |= o.err; t.skipped |= o.skipped;
+    }
+    totals[blockIdx.x] = t;
+  }
+}
+
+// panel_ptr from the counts and totals of k_rows_census (n_totals workgroups of `run` panels each); a
+// workgroup here takes `group` of those runs.  Without every panel's count there is nothing to scan.  The
+// first workgroup puts the matrix's totals into the control block and, for the host that waits for them,
+// into pinned memory, flag last (a copy behind the kernels takes 4 us, and the wait for the stream more).
+__global__ __launch_bounds__(kScanThreads) void k_census_scan(
+    const uint32_t* __restrict__ ncols_p, int64_t P, int64_t run, const PanelTotals* __restrict__ totals,
+    uint32_t n_totals, uint32_t group, uint32_t* __restrict__ panel_ptr, PlanControl* ctl,
+    PlanControl* pinned, uint32_t* flag) {
+  __shared__ PanelTotals s_tot[kScanThreads / 64];
+  __shared__ uint32_t s_before[kScanThreads / 64];
+  PanelTotals t{};
+  uint32_t before = 0;
+  for (uint32_t b = threadIdx.x; b < n_totals; b += kScanThreads) {
+    const PanelTotals o = totals[b];
+    if (b < blockIdx.x * group) before += o.bricks;
+    t.bricks += o.bricks; t.blocks += o.blocks; t.cols += o.cols;
+    t.max_cols = max(t.max_cols, o.max_cols);
+    t.span = max(t.span, o.span); t.max_nnz = max(t.max_nnz, o.max_nnz);
+    t.err |= o.err; t.skipped |= o.skipped;
+  }
+  t = PanelTotals{wave_sum(t.bricks), wave_sum(t.blocks), wave_sum(t.cols), wave_max(t.max_cols),
+                  wave_max(t.span), wave_max(t.max_nnz), wave_or(t.err), wave_or(t.skipped)};
+  before = wave_sum(before);
+  if ((threadIdx.x & 63) == 0) { s_tot[threadIdx.x >> 6] = t; s_before[threadIdx.x >> 6] = before; }
+  __syncthreads();
+  t = s_tot[0];
+  uint32_t at = s_before[0];
+#pragma unroll
+  for (int w = 1; w < kScanThreads / 64; ++w) {
+    const PanelTotals o = s_tot[w];
+    t.bricks += o.bricks; t.blocks += o.blocks; t.cols += o.cols;
+    t.max_cols = max(t.max_cols, o.max_cols);
+    t.span = max(t.span, o.span); t.max_nnz = max(t.max_nnz, o.max_nnz);
+    t.err |= o.err; t.skipped |= o.skipped;
+    at += s_before[w];
+  }
+  const bool counted = !t.skipped && !t.err;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    PlanControl c;                 // (its counters stay as they are)
+    c.err = t.err; c.span = t.span; c.max_nnz = t.max_nnz; c.counted = counted;
+    c.max_cols = counted ? t.max_cols : 0;
+    c.nb = counted ? t.bricks : 0;
+    c.n_active = counted ? t.cols : 0;
+    c.n_blocks = counted ? t.blocks : 0;
+    for (PlanControl* to : {ctl, pinned}) {
+      if (!to) continue;
+      to->err = c.err; to->span = c.span; to->max_nnz = c.max_nnz; to->counted = c.counted;
+      to->max_cols = c.max_cols; to->nb = c.nb; to->n_active = c.n_active; to->n_blocks = c.n_blocks;
+    }
+    if (counted) panel_ptr[P] = t.bricks;
+    if (flag) __hip_atomic_store(flag, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+  if (!counted) return;
+  const int64_t p_end = min((int64_t)(blockIdx.x + 1) * group * run, P);
+  for (int64_t p0 = (int64_t)blockIdx.x * group * run; p0 < p_end; p0 += 4 * kScanThreads) {
+    const int64_t p = p0 + 4 * threadIdx.x;
+    uint32_t nb[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) nb[k] = p + k < p_end ? (ncols_p[p + k] + kBrickK - 1) / kBrickK : 0u;
+    uint32_t total;
+    uint32_t to = at + block_exclusive(nb[0] + nb[1] + nb[2] + nb[3], &total);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (p + k < p_end) panel_ptr[p + k] = to;
+      to += nb[k];
+    }
+    at += total;
+  }
 }
 
 // ---- per-panel path for scattered matrices: sort instead of a bitmap
@@ -1245,16 +1418,26 @@ hipError_t launch_scan_nonzero64(const uint64_t* in, int64_t n, uint32_t* out, u
   return scan_impl(LoadNonZero{in}, n, out, tmp, s);
 }
 
-hipError_t launch_rows(const int32_t* rowptr, const int32_t* colind, int64_t M, int64_t P, int64_t nnz,
-                       int32_t* rowptr_copy, uint32_t* panel_nnzptr, PlanControl* ctl,
-                       hipStream_t s) {
-  const unsigned g = (unsigned)std::min<int64_t>(grid_for(M + 1, kRowThreads), kRowBlocks);
-  hipLaunchKernelGGL(k_rows, dim3(g), dim3(kRowThreads), 0, s, rowptr, colind, M, P, nnz,
-                     rowptr_copy, panel_nnzptr, ctl);
+hipError_t launch_rows_census(const int32_t* rowptr, const int32_t* colind, int64_t M, int64_t K,
+                              int64_t P, int64_t nnz, int32_t* rowptr_copy, uint32_t* panel_nnzptr,
+                              uint32_t* ncols_p, uint32_t* panel_ptr, uint32_t* tmp, PlanControl* ctl,
+                              PlanControl* pinned, uint32_t* flag, hipStream_t s) {
+  static_assert(sizeof(PanelTotals) == 32, "eight words of `tmp` each");
+  PanelTotals* totals = reinterpret_cast<PanelTotals*>(tmp);
+  const int64_t want = std::max<int64_t>(1, std::min<int64_t>((P + kFirstWaves - 1) / kFirstWaves, kFirstBlocks));
+  const int64_t run = std::max<int64_t>(1, (P + want - 1) / want);
+  const unsigned n = (unsigned)std::max<int64_t>(1, (P + run - 1) / run);
+  hipLaunchKernelGGL(k_rows_census, dim3(n), dim3(kFirstThreads), 0, s, rowptr, colind, M, K, P, nnz, run,
+                     rowptr_copy, panel_nnzptr, ncols_p, totals);
+  const unsigned group = (unsigned)std::max<int64_t>(1, 4 * kScanThreads / run);
+  hipLaunchKernelGGL(k_census_scan, dim3((n + group - 1) / group), dim3(kScanThreads), 0, s, ncols_p, P, run,
+                     totals, n, group, panel_ptr, ctl, pinned, flag);
   return hipGetLastError();
 }
 
-size_t panel_scan_tmp_elems() { return kPanelScanBlocks; }
+size_t panel_scan_tmp_elems() {
+  return std::max<size_t>(kPanelScanBlocks, kFirstBlocks * sizeof(PanelTotals) / sizeof(uint32_t));
+}
 
 hipError_t launch_panel_scan(const uint32_t* ncols_p, int64_t P, uint32_t* panel_ptr, uint32_t* tmp,
                              PlanControl* ctl, hipStream_t s) {
@@ -1262,14 +1445,6 @@ hipError_t launch_panel_scan(const uint32_t* ncols_p, int64_t P, uint32_t* panel
   const dim3 grid(grid_for((P + run - 1) / run, kScanThreads)), block(kScanThreads);
   hipLaunchKernelGGL(k_panel_sums, grid, block, 0, s, ncols_p, P, run, tmp, ctl);
   hipLaunchKernelGGL(k_panel_scan, grid, block, 0, s, ncols_p, P, run, tmp, panel_ptr, ctl);
-  return hipGetLastError();
-}
-
-hipError_t launch_format_pad(uint32_t* brick_cols, uint64_t* brick_mask, uint32_t* brick_valptr,
-                             float* vals, int64_t nb, int64_t nnz, hipStream_t s) {
-  static_assert(kFormatPad * kBrickK <= kThreads && kFormatPad < 64, "one workgroup writes the pads");
-  hipLaunchKernelGGL(k_format_pad, dim3(1), dim3(kThreads), 0, s, brick_cols, brick_mask,
-                     brick_valptr, vals, nb, nnz);
   return hipGetLastError();
 }
 
@@ -1368,13 +1543,15 @@ hipError_t launch_restore_csr(const BrickFormat& f, const uint32_t* src, int64_t
 }
 
 hipError_t launch_plan_stats(const uint32_t* panel_ptr, const uint32_t* panel_nnzptr, int64_t P,
-                             const uint64_t* brick_mask, int64_t nb, const uint8_t* col_seen,
-                             int64_t K, unsigned long long* counters, hipStream_t s) {
-  if (nb == 0) return hipSuccess;   // no brick: every count is zero
+                             uint32_t* brick_cols, uint64_t* brick_mask, uint32_t* brick_valptr,
+                             float* vals, int64_t nb, int64_t nnz, const uint8_t* col_seen, int64_t K,
+                             unsigned long long* counters, hipStream_t s) {
   const int64_t most = std::max(std::max(nb, P), K / 16 + 16);
-  const unsigned g = (unsigned)std::min<int64_t>(grid_for(most, kStatThreads), kStatBlocks);
-  hipLaunchKernelGGL(k_plan_stats, dim3(g), dim3(kStatThreads), 0, s, panel_ptr, panel_nnzptr, P,
-                     brick_mask, nb, col_seen, K, counters);
+  const unsigned g = nb == 0 ? 1u   // no brick: every count is zero
+                             : (unsigned)std::min<int64_t>(grid_for(most, kStatThreads), kStatBlocks);
+  hipLaunchKernelGGL(k_plan_stats, dim3(g), dim3(kStatThreads), 0, s, panel_ptr, panel_nnzptr,
+                     nb == 0 ? 0 : P, brick_cols, brick_mask, brick_valptr, vals, nb, nnz, col_seen,
+                     nb == 0 ? 0 : K, counters);
   return hipGetLastError();
 }
 

@@ -36,7 +36,7 @@ struct PlanControl {        // device, zeroed when a plan begins; read back at i
   uint32_t max_cols;        // most active columns of a panel
   uint32_t nb;              // bricks
   uint32_t n_mid, n_big;    // panels in the lists of the sort-based path
-  uint32_t pad;
+  uint32_t counted;         // every panel's columns were counted in the first pass
   unsigned long long n_active;   // active columns, summed over the panels
   unsigned long long n_blocks;   // blocks of four bricks, every panel rounded up
   unsigned long long counters[kNumCounters];
@@ -70,15 +70,16 @@ struct MergeItem {          // one split panel
 };
 
 // ---- plan (a1..a5) -------------------------------------------------------
-hipError_t launch_rows(const int32_t* rowptr, const int32_t* colind, int64_t M, int64_t P, int64_t nnz,
-                       int32_t* rowptr_copy, uint32_t* panel_nnzptr, PlanControl* ctl,
-                       hipStream_t s);
+// checks rowptr, copies it, panel_nnzptr, ctl->err / span / max_nnz / counted; where ctl->counted, also what
+// launch_panel_census and launch_panel_scan do.  `pinned` (or null) gets what ctl does, then `flag` 1.
+hipError_t launch_rows_census(const int32_t* rowptr, const int32_t* colind, int64_t M, int64_t K,
+                              int64_t P, int64_t nnz, int32_t* rowptr_copy, uint32_t* panel_nnzptr,
+                              uint32_t* ncols_p, uint32_t* panel_ptr, uint32_t* tmp, PlanControl* ctl,
+                              PlanControl* pinned, uint32_t* flag, hipStream_t s);
 // ncols_p -> panel_ptr[P+1] (bricks, scanned), ctl->nb, ctl->n_active, ctl->max_cols
 size_t panel_scan_tmp_elems();
 hipError_t launch_panel_scan(const uint32_t* ncols_p, int64_t P, uint32_t* panel_ptr, uint32_t* tmp,
                              PlanControl* ctl, hipStream_t s);
-hipError_t launch_format_pad(uint32_t* brick_cols, uint64_t* brick_mask, uint32_t* brick_valptr,
-                             float* vals, int64_t nb, int64_t nnz, hipStream_t s);
 hipError_t launch_validate_cols(const int32_t* rowptr, const int32_t* colind, int64_t M, int64_t K,
                                 int64_t nnz, uint32_t* ent_row, uint32_t* err, hipStream_t s);
 hipError_t launch_first_in_panel(const int32_t* rowptr, const int32_t* colind,
@@ -105,8 +106,9 @@ hipError_t launch_pack_values(const float* vals, const uint32_t* ent_brick, cons
 hipError_t launch_update_values(const float* vals, const uint32_t* src, int64_t nnz, float* packed,
                                 float* csr_vals, hipStream_t s);
 hipError_t launch_plan_stats(const uint32_t* panel_ptr, const uint32_t* panel_nnzptr, int64_t P,
-                             const uint64_t* brick_mask, int64_t nb, const uint8_t* col_seen,
-                             int64_t K, unsigned long long* counters, hipStream_t s);
+                             uint32_t* brick_cols, uint64_t* brick_mask, uint32_t* brick_valptr,
+                             float* vals, int64_t nb, int64_t nnz, const uint8_t* col_seen, int64_t K,
+                             unsigned long long* counters, hipStream_t s);
 // rows with more than `threshold` entries -> list (any order), count added to *counter
 hipError_t launch_find_long_rows(const int32_t* rowptr, int64_t M, int threshold,
                                  uint32_t* list, unsigned long long* counter, hipStream_t s);
