@@ -224,6 +224,7 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void k_spmm_mfma(
 // bricks, say) four steps of the next panel's rows would otherwise add 40 % to
 // the traffic from memory.
 constexpr int kFastChunk = 8;
+constexpr int64_t kNarrowLargeB = int64_t(64) << 20;
 
 template <int T, bool FULL>
 __global__ __launch_bounds__(64 * kWavesPerBlock) void k_spmm_mfma_fast(
@@ -777,6 +778,14 @@ hipError_t launch_spmm_mfma(const BrickFormat& f, const WorkSource& w, const flo
                             float* partial, int64_t M, int64_t N, int64_t K, int64_t nnz, hipStream_t s) {
   if (w.n_items == 0 || N == 0) return hipSuccess;
   if (mfma_32bit_shape(N, K) && mfma_32bit_values(nnz)) {
+    // Tiles of 16 and 32 columns in 16-byte loads (exec_narrow.hip).  Not where panels are split, as in
+    // power-law graphs, and B is not large: short panels of scattered rows, each a miss, gain nothing from fewer
+    // accesses and lose 1 to 3 % to the larger chunk (graphs of 283 k and 450 k rows, us: N = 14 26.7 / 27.5 and 40.1 /
+    // 41.5, N = 32 28.4 / 28.8 and 41.8 / 42.6; 600 k and 900 k rows, B of 77 and 115 MB: 63.6 / 60.5 and
+    // 95.7 / 82.6; N = 8 at 283 k 22.5 / 21.3).  Without split panels, N = 14 to 32, bands, cells and blocks of
+    // 25 k to 400 k rows: 2 to 12 % ahead or the same.
+    if (N >= 4 && N <= 32 && (w.n_parts == 0 || N <= 8 || K * N * 4 >= kNarrowLargeB))
+      return launch_spmm_mfma_narrow(f, w, B, C, partial, M, N, K, s);
     const int tile = mfma_fp32_tile(N, K, nnz);
     const unsigned gx = item_blocks<kWavesPerBlock>(w);
     const dim3 grid(gx, (unsigned)((N + tile - 1) / tile)), block(64 * kWavesPerBlock);
