@@ -54,6 +54,7 @@ void keep_put(void* p, bool idle) { DeviceKeep::instance().put(p, idle); }
 // pageable memory is staged by the runtime, 25 to 150 us a call): buffers of kStageBytes, one per
 // call that needs one, at most kStages kept.  Without one (null) the copy goes the pageable way.
 constexpr size_t kStageBytes = size_t(1) << 20, kStages = 4;
+constexpr size_t kWorkKept = size_t(16) << 20;   // working memory that may stay with its plan (about K + 4 P + nnz / 100 bytes)
 
 class HostStage {
  public:
@@ -209,11 +210,13 @@ struct spmm_plan {
   // the arrays above are carved out of two device allocations
   char* fixed_arena = nullptr;   // panel_ptr, rowptr, panel_nnzptr, src
   char* brick_arena = nullptr;   // brick_cols, brick_mask, brick_valptr, vals
+  char* work_arena = nullptr;    // what the plan was made with, where it could not be let go
   bool idle = false;             // set before the end: as in drop_lists
   ~spmm_plan() {
     drop_lists(idle);
     keep_put(fixed_arena, idle);
     keep_put(brick_arena, idle);
+    keep_put(work_arena, idle);
     keep_put(csr_arena, idle);
     if (tm32.arena) (void)hipFree(tm32.arena);
   }
@@ -940,34 +943,50 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
     HIP_TRY(launch_pack_values(vals, ent_brick, ent_bit, pl->brick_mask, pl->brick_valptr, nnz,
                                pl->vals, pl->src, s));
   }
-  // ---- the spare entries behind the brick arrays, and a5: per-panel classes and the synergy counts
-  HIP_TRY(launch_plan_stats(pl->panel_ptr, pl->panel_nnzptr, P, pl->brick_cols, pl->brick_mask,
-                            pl->brick_valptr, pl->vals, pl->nb, nnz, col_seen, K, ctl->counters, s));
-
-  // ---- host copies for the work-list builder and the model
+  // ---- the spare entries behind the brick arrays, a5: per-panel classes and the synergy counts, and
+  // host copies for the work-list builder and the model
   pl->max_bricks = h_maxnb;
   pl->n_blocks = (int64_t)h_ctl.n_blocks;
-  if (!splits_nothing(pl, 1)) {   // for some N the default policy may split a panel
-    try {
-      pl->h_panel_ptr.resize((size_t)P + 1);
-    } catch (const std::bad_alloc&) {
-      status = fail(SPMM_ENOMEM, "host allocation failed");
-      goto done;
+  {
+    const bool want_ptr = !splits_nothing(pl, 1);   // for some N the default policy may split a panel
+    const size_t ptr_b = (size_t)(P + 1) * sizeof(uint32_t), ctl_b = Arena::pad(sizeof(PlanControl));
+    if (want_ptr) {
+      try {
+        pl->h_panel_ptr.resize((size_t)P + 1);
+      } catch (const std::bad_alloc&) {
+        status = fail(SPMM_ENOMEM, "host allocation failed");
+        goto done;
+      }
     }
-    const size_t bytes = (size_t)(P + 1) * sizeof(uint32_t);
-    const bool staged = stage.get() && sizeof(PlanControl) + bytes <= kStageBytes;
-    void* to = staged ? (void*)(stage.get() + sizeof(PlanControl)) : (void*)pl->h_panel_ptr.data();
-    HIP_TRY(hipMemcpyAsync(to, pl->panel_ptr, bytes, hipMemcpyDeviceToHost, s));
-    HIP_TRY(read_ctl());
-    if (staged) memcpy(pl->h_panel_ptr.data(), to, bytes);
-  } else {
-    HIP_TRY(read_ctl());
+    const bool pinned = stage.get() && (!want_ptr || 2 * ctl_b + ptr_b <= kStageBytes);
+    uint32_t* flag = reinterpret_cast<uint32_t*>(stage.get() + ctl_b);
+    uint32_t* ptr = reinterpret_cast<uint32_t*>(stage.get() + 2 * ctl_b);
+    if (pinned) __atomic_store_n(flag, 0u, __ATOMIC_RELAXED);
+    HIP_TRY(launch_plan_stats(pl->panel_ptr, pl->panel_nnzptr, P, pl->brick_cols, pl->brick_mask,
+                              pl->brick_valptr, pl->vals, pl->nb, nnz, col_seen, K, ctl,
+                              pinned ? reinterpret_cast<PlanControl*>(stage.get()) : nullptr,
+                              pinned && want_ptr ? ptr : nullptr, pinned ? flag : nullptr, s));
+    if (pinned) {
+      HIP_TRY(wait_for_flag(flag, s));
+      memcpy(&h_ctl, stage.get(), sizeof(PlanControl));
+      if (want_ptr) memcpy(pl->h_panel_ptr.data(), ptr, ptr_b);
+      // the flag comes some microseconds before the runtime sees the kernels' end, and memory that another
+      // stream may write next has to wait for that: a small block stays with the plan instead
+      if (work.cap <= kWorkKept) {
+        pl->work_arena = work.base;
+        work.base = nullptr;
+      }
+    } else {
+      if (want_ptr)
+        HIP_TRY(hipMemcpyAsync(pl->h_panel_ptr.data(), pl->panel_ptr, ptr_b, hipMemcpyDeviceToHost, s));
+      HIP_TRY(read_ctl());
+    }
   }
   memcpy(pl->h_counters, h_ctl.counters, sizeof(pl->h_counters));
 
 done:
-  // (a call that succeeds ends with a wait for `s`, the only stream that used these)
-  const bool idle = status == SPMM_OK || hipStreamSynchronize(s) == hipSuccess;
+  // (`s` is the only stream that used these)
+  const bool idle = (status == SPMM_OK && !work.base && !wide.base) || hipStreamSynchronize(s) == hipSuccess;
   keep_put(work.base, idle);
   keep_put(wide.base, idle);
   if (status != SPMM_OK) {

@@ -251,7 +251,10 @@ __global__ __launch_bounds__(kThreads) void k_restore_csr(
 // and same-address atomics of many workgroups were what the separate kernels for these three spent
 // their time on (630 k bricks of 16,384 panels: 55 us in three launches, 8 us in
 // this one).
-// The first workgroup also writes the spare entries behind the brick arrays (see BrickFormat).
+// The first workgroup also writes the spare entries behind the brick arrays (see BrickFormat).  The last one to
+// end puts the counters into pinned memory, flag last, for the host that looks for it, and all copy panel_ptr there
+// where the host wants it: two copies and the wait for the stream took 10 to 20 us more.  Everything a
+// workgroup has written is visible to the device and the host before it counts itself as ended.
 constexpr int kStatThreads = 1024;
 constexpr int kStatBlocks = 128;
 
@@ -259,7 +262,9 @@ __global__ __launch_bounds__(kStatThreads) void k_plan_stats(
     const uint32_t* __restrict__ panel_ptr, const uint32_t* __restrict__ panel_nnzptr, int64_t P,
     uint32_t* __restrict__ brick_cols, uint64_t* __restrict__ brick_mask,
     uint32_t* __restrict__ brick_valptr, float* __restrict__ vals, int64_t nb, int64_t nnz,
-    const uint8_t* __restrict__ col_seen, int64_t K, unsigned long long* counters) {
+    const uint8_t* __restrict__ col_seen, int64_t K, PlanControl* ctl, PlanControl* pinned,
+    uint32_t* pinned_ptr, int64_t n_ptr, uint32_t* flag) {
+  unsigned long long* counters = ctl->counters;
   static_assert(kFormatPad * kBrickK <= kStatThreads && kFormatPad < 64, "one workgroup writes the pads");
   if (blockIdx.x == 0) {
     const int t = threadIdx.x;
@@ -334,6 +339,23 @@ __global__ __launch_bounds__(kStatThreads) void k_plan_stats(
     for (int w = 0; w < kWaves; ++w) h += hist[w][threadIdx.x];
     if (h) atomicAdd(&counters[kCntPopHist + threadIdx.x], h);
   }
+  if (!pinned) return;
+  if (pinned_ptr)
+    for (int64_t p = first; p < n_ptr; p += stride)
+      __hip_atomic_store(&pinned_ptr[p], panel_ptr[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  // (one release a workgroup, by the thread that counts it: one by every wavefront took 25 us)
+  __shared__ uint32_t s_last;
+  __syncthreads();
+  if (threadIdx.x == 0)
+    s_last = __hip_atomic_fetch_add(&ctl->ended, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+  __syncthreads();
+  if (!s_last) return;
+  if (threadIdx.x < kNumCounters)
+    __hip_atomic_store(&pinned->counters[threadIdx.x],
+                       __hip_atomic_load(&counters[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  __syncthreads();
+  if (threadIdx.x == 0) __hip_atomic_store(flag, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Rows with more than `threshold` entries, compacted in any order (the CSR kernel gives each of
@@ -1545,13 +1567,14 @@ hipError_t launch_restore_csr(const BrickFormat& f, const uint32_t* src, int64_t
 hipError_t launch_plan_stats(const uint32_t* panel_ptr, const uint32_t* panel_nnzptr, int64_t P,
                              uint32_t* brick_cols, uint64_t* brick_mask, uint32_t* brick_valptr,
                              float* vals, int64_t nb, int64_t nnz, const uint8_t* col_seen, int64_t K,
-                             unsigned long long* counters, hipStream_t s) {
+                             PlanControl* ctl, PlanControl* pinned, uint32_t* pinned_ptr,
+                             uint32_t* flag, hipStream_t s) {
   const int64_t most = std::max(std::max(nb, P), K / 16 + 16);
   const unsigned g = nb == 0 ? 1u   // no brick: every count is zero
                              : (unsigned)std::min<int64_t>(grid_for(most, kStatThreads), kStatBlocks);
   hipLaunchKernelGGL(k_plan_stats, dim3(g), dim3(kStatThreads), 0, s, panel_ptr, panel_nnzptr,
                      nb == 0 ? 0 : P, brick_cols, brick_mask, brick_valptr, vals, nb, nnz, col_seen,
-                     nb == 0 ? 0 : K, counters);
+                     nb == 0 ? 0 : K, ctl, pinned, pinned_ptr, P + 1, flag);
   return hipGetLastError();
 }
 

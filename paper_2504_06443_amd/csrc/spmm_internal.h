@@ -37,6 +37,8 @@ struct PlanControl {        // device, zeroed when a plan begins; read back at i
   uint32_t nb;              // bricks
   uint32_t n_mid, n_big;    // panels in the lists of the sort-based path
   uint32_t counted;         // every panel's columns were counted in the first pass
+  uint32_t ended;           // workgroups of k_plan_stats that have ended
+  uint32_t pad;
   unsigned long long n_active;   // active columns, summed over the panels
   unsigned long long n_blocks;   // blocks of four bricks, every panel rounded up
   unsigned long long counters[kNumCounters];
@@ -108,7 +110,9 @@ hipError_t launch_update_values(const float* vals, const uint32_t* src, int64_t 
 hipError_t launch_plan_stats(const uint32_t* panel_ptr, const uint32_t* panel_nnzptr, int64_t P,
                              uint32_t* brick_cols, uint64_t* brick_mask, uint32_t* brick_valptr,
                              float* vals, int64_t nb, int64_t nnz, const uint8_t* col_seen, int64_t K,
-                             unsigned long long* counters, hipStream_t s);
+                             PlanControl* ctl, PlanControl* pinned, uint32_t* pinned_ptr,
+                             uint32_t* flag, hipStream_t s);
+// (pinned, or null: gets the counters, pinned_ptr, or null: panel_ptr, then `flag` 1)
 // rows with more than `threshold` entries -> list (any order), count added to *counter
 hipError_t launch_find_long_rows(const int32_t* rowptr, int64_t M, int threshold,
                                  uint32_t* list, unsigned long long* counter, hipStream_t s);
