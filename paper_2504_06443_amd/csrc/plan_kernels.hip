@@ -1249,8 +1249,9 @@ __global__ __launch_bounds__(T) void k_panel_sort_build(
 // in flight, and an entry's row and rank are worked out once and kept in LDS; the packed values and
 // their sources leave in order, whole lines at a time.  Panels above stage_cap go through the same
 // steps without the staging: they read the columns again and scatter their values.
-// 7.86 M entries in 16,384 panels: 71 us unstaged and walking groups of bitmap words, 51 us so;
-// 41 M entries in 57,696 panels 434 -> 250 us (0.76 GB).
+// 7.86 M entries in 16,384 panels: 71 us unstaged and walking groups of bitmap words, 49 us staged, 46.6 with
+// four neighbouring columns a lane (one LDS atomic a bitmap word) and an entry's row from bit counts (18.5 M -> 14.3 M
+// vector instructions); 41 M entries in 57,696 panels 434 -> 250 us staged (0.76 GB).
 template <int G>
 __global__ __launch_bounds__(kPanelThreads) void k_panel_build(
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind,
@@ -1260,6 +1261,11 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_build(
     float* __restrict__ packed, uint32_t* __restrict__ src, uint8_t* __restrict__ col_seen) {
   extern __shared__ unsigned long long lds64[];
   __shared__ int32_t rp[kPanel + 1];
+  // staged panels: bit i of `starts` is set where a row with entries begins at entry i + 1, and rows[k] is the
+  // k-th such row: an entry's row from two bit counts and a look into the table, not from a comparison with every
+  // row's start
+  __shared__ unsigned long long starts[kPanelStageMax / 64];
+  __shared__ uint32_t rows[kPanel];
   unsigned long long* pat = lds64;                                   // [nb_cap]
   uint32_t* bm = reinterpret_cast<uint32_t*>(lds64 + nb_cap);        // [words_cap]
   uint32_t* pre = bm + words_cap;     // [words_cap / G + 1]; pre[g] = set bits in words [0, G*g)
@@ -1289,18 +1295,42 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_build(
 
   for (uint32_t k = threadIdx.x; k < nb; k += kPanelThreads) pat[k] = 0;
   for (uint32_t w = threadIdx.x; w < words; w += kPanelThreads) bm[w] = 0;
+  static_assert(kPanelStageMax / 64 <= kPanelThreads, "a lane clears a word");
+  if (threadIdx.x < kPanelStageMax / 64) starts[threadIdx.x] = 0;
   __syncthreads();
-  for (uint32_t i0 = threadIdx.x; i0 < n; i0 += 4 * kPanelThreads) {
+  if (staged) {
+    const uint32_t r = min(threadIdx.x, (uint32_t)kPanel - 1);
+    const uint32_t begin = (uint32_t)(rp[r] - rp[0]), end = (uint32_t)(rp[r + 1] - rp[0]);
+    const bool has = threadIdx.x < kPanel && begin < end;
+    const uint64_t which = __ballot(has);
+    if (has) {
+      rows[__popcll(which & ((1ull << threadIdx.x) - 1ull))] = r;
+      if (begin > 0) atomicOr(&starts[(begin - 1) / 64], 1ull << ((begin - 1) % 64));
+    }
+  }
+  for (uint32_t i0 = 4 * threadIdx.x; i0 < n; i0 += 4 * kPanelThreads) {
     uint32_t d[4];
+    if (i0 + 4 <= n) {
+      const Int4Any v = *reinterpret_cast<const Int4Any*>(colind + x.e0 + i0);
+      d[0] = (uint32_t)(v.x - x.cmin); d[1] = (uint32_t)(v.y - x.cmin);
+      d[2] = (uint32_t)(v.z - x.cmin); d[3] = (uint32_t)(v.w - x.cmin);
+    } else {
 #pragma unroll
-    for (int u = 0; u < 4; ++u)   // past the end: the last entry again
-      d[u] = (uint32_t)(colind[x.e0 + min(i0 + u * kPanelThreads, n - 1)] - x.cmin);
+      for (int u = 0; u < 4; ++u)   // past the end: the last entry again
+        d[u] = (uint32_t)(colind[x.e0 + min(i0 + u, n - 1)] - x.cmin);
+    }
+    uint32_t word = d[0] >> 5, bits = 0;
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const uint32_t i = i0 + u * kPanelThreads;
-      if (i < n && d[u] / 32u < words) atomicOr(&bm[d[u] >> 5], 1u << (d[u] & 31));
-      if (i < n && staged) key[i] = d[u];
+      if (d[u] >> 5 != word) {
+        if (word < words) atomicOr(&bm[word], bits);
+        word = d[u] >> 5;
+        bits = 0;
+      }
+      bits |= 1u << (d[u] & 31);
+      if (i0 + u < n && staged) key[i0 + u] = d[u];
     }
+    if (word < words) atomicOr(&bm[word], bits);
   }
   __syncthreads();
 
@@ -1348,18 +1378,31 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_build(
     brick_cols[(int64_t)pp * kBrickK + k] = kPadCol;
 
   // a3: pattern bits, accumulated in LDS; a staged entry keeps rank and row, 16 * rank + row
-  auto entry_key = [&](uint32_t i, uint32_t d) {
-    return min(rank_of(d), nb * kBrickK - 1) * kPanel + row_of(i);
-  };
+  auto entry_key = [&](uint32_t row, uint32_t d) { return min(rank_of(d), nb * kBrickK - 1) * kPanel + row; };
   auto unstaged_key = [&](uint32_t i) {
-    return entry_key(i, (uint32_t)(colind[x.e0 + i] - x.cmin));
+    return entry_key(row_of(i), (uint32_t)(colind[x.e0 + i] - x.cmin));
   };
   auto brick_of = [](uint32_t k) { return k / (kPanel * kBrickK); };
   auto bit_of = [](uint32_t k) { return k % kPanel * kBrickK + k / kPanel % kBrickK; };
-  for (uint32_t i = threadIdx.x; i < n; i += kPanelThreads) {
-    const uint32_t k = staged ? entry_key(i, key[i]) : unstaged_key(i);
-    if (staged) key[i] = k;
-    atomicOr(&pat[brick_of(k)], 1ull << bit_of(k));
+  if (staged) {
+    uint32_t before = 0;   // rows that begin in the entries before these 64, the first not counted
+    for (uint32_t i0 = 0; i0 < n; i0 += kPanelThreads) {
+      const unsigned long long m = starts[i0 / 64];
+      const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)m), hi = __builtin_amdgcn_readfirstlane((uint32_t)(m >> 32));
+      const uint32_t i = i0 + threadIdx.x;
+      if (i < n) {
+        const uint32_t nth = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, before));
+        const uint32_t k = entry_key(rows[min(nth, (uint32_t)kPanel - 1)], key[i]);
+        key[i] = k;
+        atomicOr(&pat[brick_of(k)], 1ull << bit_of(k));
+      }
+      before += __popc(lo) + __popc(hi);
+    }
+  } else {
+    for (uint32_t i = threadIdx.x; i < n; i += kPanelThreads) {
+      const uint32_t k = unstaged_key(i);
+      atomicOr(&pat[brick_of(k)], 1ull << bit_of(k));
+    }
   }
   __syncthreads();
 

@@ -63,6 +63,19 @@ def test_last_columns_of_the_matrix(gpu):  # noqa: F811
     check(gpu, band(400, 7, (30, 7, 0), (7, 7, 7), seed=4))
 
 
+@pytest.mark.parametrize("lengths", [(64,) * 16, (0, 64, 0, 0, 128, 1, 63, 0), (0,) * 15 + (65,), (1,) * 16,
+                                     (63, 1, 0, 0, 64, 0, 65), (128,) * 16, (128,) * 15 + (129,), (200,) * 16,
+                                     (3, 0, 61, 0, 0, 0, 0, 192)])
+def test_rows_that_begin_around_blocks_of_entries(gpu, lengths):  # noqa: F811
+    """Rows that begin at, before and behind multiples of 64 entries, empty ones between, and panels of 2048
+    entries, of one more and of many more, which are not staged; a panel of one row follows."""
+    rng = np.random.default_rng(sum(lengths))
+    r = np.repeat(np.arange(len(lengths)), lengths)
+    c = np.concatenate([np.sort(rng.choice(330, n, replace=False)) for n in lengths])
+    r, c = np.concatenate([r, np.full(7, 16)]), np.concatenate([c, np.arange(7) * 2])
+    check(gpu, W.csr_from_coo(17, 400, r, c, rng.uniform(-1, 1, len(r)).astype(np.float32)))
+
+
 @pytest.mark.parametrize("at", [0, 1, 3, 4, 7, 8, 255, 256, 257, 300])
 @pytest.mark.parametrize("fault", ["swapped", "duplicate", "beyond", "negative", "rowptr"])
 def test_faults_inside_a_counted_panel(gpu, at, fault):  # noqa: F811
