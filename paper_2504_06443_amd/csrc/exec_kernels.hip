@@ -201,7 +201,8 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void k_spmm_mfma(
 
 // ------------------------------------------------------------------ MFMA, fast path
 // Same lane mapping as above for B smaller than 4 GiB (32-bit byte offsets), any N and any
-// dword-aligned B and C, on tiles of 16*T columns, T = 1..8.  A lane owns one vector of W0 =
+// dword-aligned B and C, on tiles of 16*T columns, T = 1..8 (T = 1 and 2 where launch_spmm_mfma does not
+// choose exec_narrow.hip).  A lane owns one vector of W0 =
 // min(T, 4) columns and, for T > 4, a second one of W1 = T - 4.  Loads and stores need no more
 // than dword alignment, so rows of an odd N are read with the same vectors as rows of a whole
 // one.  A vector that reaches past column N is moved back to end at N, for the load and for the

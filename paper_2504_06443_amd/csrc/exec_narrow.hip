@@ -7,8 +7,8 @@
 // lanes hold a row of the tile, so one load holds the rows of G = 4/T bricks, and lane groups and registers then
 // change places (T = 2: eight lanes; T = 1: eight, then four) until register (brick, column) holds the four rows
 // of one brick in the MFMA's layout.  Column u of lane l's MFMA is then column 4*j + T*s + u of the tile, where
-// l % 16 = 4T*s + j.  923,136 rows of blocks, N = 32: accesses to L1 85 M -> 52 M, 213.7 -> 180.4 us; the
-// lines in flight between L1 and L2 (53 a CU on average) bind it now.  Fetching half a chunk at an item's end
+// l % 16 = 4T*s + j.  923,136 rows of blocks, N = 32: accesses to L1 85 M -> 52 M, 213.7 -> 180.4 us; L1 now takes
+// accesses for 0.47 of the time and waits for lines from L2 for 0.48.  Fetching half a chunk at an item's end
 // (more code, spilled scalars) 181.8; registers for 8 wavefronts a SIMD (75 spilled scalars) 184.9; at most 5
 // wavefronts 185.9.
 //
