@@ -60,8 +60,9 @@ enum spmm_class { SPMM_NONE = -1, SPMM_LOW = 0, SPMM_MEDIUM = 1, SPMM_HIGH = 2 }
  *   out      receives the plan; destroy with spmm_plan_destroy
  *
  * The CSR arrays are only read during the call (the plan keeps its own copies of
- * what it needs later) and may be freed after it returns.  The call synchronises
- * `stream` several times (it reads back sizes to allocate).  The input is
+ * what it needs later) and may be freed after it returns.  The call waits for
+ * what it enqueued several times (it reads back sizes to allocate); when it returns,
+ * the plan may be used on any stream.  The input is
  * validated on the device first; an invalid CSR gives SPMM_EFORMAT and no plan.
  *
  * Format (panel p = rows 16p..16p+15; P = ceil(M/16) panels; nb bricks):
