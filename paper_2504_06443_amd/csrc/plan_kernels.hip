@@ -246,6 +246,10 @@ __global__ __launch_bounds__(kThreads) void k_restore_csr(
   }
 }
 
+__device__ inline void wave_stores_done() {   // the wavefront's own stores and atomics have arrived
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
 // a5: per-panel class (Table 1, integer compare) and class totals, histogram of bricks by stored
 // elements, columns that occur.  Few, large workgroups: each adds its totals to the counters once,
 // and same-address atomics of many workgroups were what the separate kernels for these three spent
@@ -254,7 +258,9 @@ __global__ __launch_bounds__(kThreads) void k_restore_csr(
 // The first workgroup also writes the spare entries behind the brick arrays (see BrickFormat).  The last one to
 // end puts the counters into pinned memory, flag last, for the host that looks for it, and all copy panel_ptr there
 // where the host wants it: two copies and the wait for the stream took 10 to 20 us more.  Everything a
-// workgroup has written is visible to the device and the host before it counts itself as ended.
+// workgroup has written is visible to the device and the host before it counts itself as ended: every
+// wavefront waits for its own stores and atomics (a barrier does not, and a release only for those of the
+// wavefront that makes it) before the thread that counts the workgroup releases.
 constexpr int kStatThreads = 1024;
 constexpr int kStatBlocks = 128;
 
@@ -345,6 +351,7 @@ __global__ __launch_bounds__(kStatThreads) void k_plan_stats(
       __hip_atomic_store(&pinned_ptr[p], panel_ptr[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   // (one release a workgroup, by the thread that counts it: one by every wavefront took 25 us)
   __shared__ uint32_t s_last;
+  wave_stores_done();
   __syncthreads();
   if (threadIdx.x == 0)
     s_last = __hip_atomic_fetch_add(&ctl->ended, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
@@ -354,6 +361,7 @@ __global__ __launch_bounds__(kStatThreads) void k_plan_stats(
     __hip_atomic_store(&pinned->counters[threadIdx.x],
                        __hip_atomic_load(&counters[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  wave_stores_done();
   __syncthreads();
   if (threadIdx.x == 0) __hip_atomic_store(flag, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }

@@ -1,5 +1,6 @@
-"""Loads that a kernel's design keeps in flight, in the code that hipcc makes for gfx950: the compiler may
-sink a load down to its use, which no result shows."""
+"""What no result shows, in the code that hipcc makes for gfx950: loads that a kernel's design keeps in flight
+(the compiler may sink a load down to its use), and waits between what a kernel writes and the signal that it
+has."""
 import os
 import re
 import subprocess
@@ -9,19 +10,28 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-@pytest.fixture(scope="module")
-def product_kernels(tmp_path_factory):
+def compiled(source, directory):
     from paper_2504_06443_amd import build
-    out = str(tmp_path_factory.mktemp("asm") / "exec_kernels.s")
+    out = str(directory / (source + ".s"))
     flags = [f for f in build.FLAGS if f not in ("-shared", "-fPIC")]
     subprocess.check_call([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *flags, "-S", "--offload-device-only", "-o", out,
-                           os.path.join(build.CSRC, "exec_kernels.hip")], stderr=subprocess.DEVNULL)
+                           os.path.join(build.CSRC, source)], stderr=subprocess.DEVNULL)
     with open(out) as f:
         return f.read()
 
 
+@pytest.fixture(scope="module")
+def product_kernels(tmp_path_factory):
+    return compiled("exec_kernels.hip", tmp_path_factory.mktemp("asm"))
+
+
+@pytest.fixture(scope="module")
+def plan_kernels(tmp_path_factory):
+    return compiled("plan_kernels.hip", tmp_path_factory.mktemp("asm"))
+
+
 def instructions(code, kernel):
-    body = re.search(r"^_ZN4spmm\S*%s\S*:.*?s_endpgm" % kernel, code, re.M | re.S)[0]
+    body = re.search(r"^_ZN4spmm\S*%s\S*:.*?^\.Lfunc_end" % kernel, code, re.M | re.S)[0]
     return [line.split(";")[0].strip() for line in body.splitlines()]
 
 
@@ -48,3 +58,26 @@ def test_narrow_tile_enters_its_loop_with_the_ring_full(product_kernels):
     assert len(steady) == 1
     waits = [int(m[1]) for m in (re.search(r"vmcnt\((\d+)\)", i) for i in steady[0]) if m]
     assert waits[0] >= 8
+
+
+def test_plan_stats_signals_behind_what_every_wavefront_wrote(plan_kernels):
+    """The thread that counts its workgroup as ended (an atomic that returns the count) and the one that sets
+    the host's flag (the last store) do so behind a barrier; each wavefront comes to that barrier with nothing
+    of its own under way: the wait stands in the barrier's own basic block, so no branch leads past it."""
+    code = instructions(plan_kernels, "k_plan_stats")
+    counted = max(n for n, i in enumerate(code) if i.startswith("global_atomic_add") and i.endswith("sc0"))
+    flagged = max(n for n, i in enumerate(code) if i.startswith(("global_store", "flat_store")))
+    assert counted < flagged
+    barriers = []
+    for signal in (counted, flagged):
+        at = max(n for n in range(signal) if code[n] == "s_barrier")
+        barriers.append(at)
+        waited = False
+        for i in reversed(code[:at]):
+            if re.match(r"s_waitcnt.*vmcnt\(0\)", i):
+                waited = True
+                break
+            if i.startswith((".LBB", "s_cbranch", "s_branch", "global_", "flat_", "buffer_")):
+                break
+        assert waited, "the barrier before %r" % code[signal]
+    assert barriers[0] < counted < barriers[1]
