@@ -745,6 +745,7 @@ __global__ __launch_bounds__(kFirstThreads, 6) void k_rows_census(
       if (lane == 0) ncols_p[p] = 0;
       continue;
     }
+    if (cmin < 0 || cmax >= K) err |= kErrColRange;   // (the span of such a panel may not fit 32 bits)
     const uint32_t span = (uint32_t)((int64_t)cmax - cmin + 1);
     const uint32_t words = (span + 31) / 32;
     t.span = max(t.span, span);

@@ -102,3 +102,25 @@ def test_faults_inside_a_counted_panel(gpu, at, fault):  # noqa: F811
                       torch.from_numpy(A.vals).cuda())
     assert err.value.code == gpu.SPMM_EFORMAT
     check(gpu, A)                                             # and the next plan is as ever
+
+
+@pytest.mark.parametrize("ends", [(-2**31, 2**31 - 1), (-2**31 + 5, 2**31 - 1), (-2**31, 2**31 - 32), (-1, 2**31 - 1),
+                                  (-2**31, 5), (0, 2**31 - 1), (-2, 900)])
+def test_columns_far_outside_the_matrix(gpu, ends):  # noqa: F811
+    """Spans that wrap around in 32 bits, or come to few bitmap words so, beside panels that are counted at the
+    same time: refused, and no column is taken for a place in a bitmap."""
+    import torch
+    M, lo, hi = 16 * 24, *ends
+    inner = np.unique(np.clip(lo + 32 * np.arange(1, 9000, 7, dtype=np.int64), lo + 1, hi - 1))[:1200]
+    r = np.concatenate([np.repeat(np.arange(M), 6), np.full(len(inner), 37)])
+    c = np.concatenate([np.tile(np.arange(6) * 5, M), 100 + np.arange(len(inner))])
+    A = W.csr_from_coo(M, 2000, r, c, np.ones(len(r), np.float32))
+    ci = A.colind.copy()
+    b, e = int(A.rowptr[37]), int(A.rowptr[38])
+    ci[b:e] = np.resize(inner, e - b)
+    ci[b], ci[e - 1] = lo, hi
+    with pytest.raises(gpu.SpmmError) as err:
+        gpu.spmm_plan(A.M, A.K, torch.from_numpy(A.rowptr).cuda(), torch.from_numpy(ci).cuda(),
+                      torch.from_numpy(A.vals).cuda())
+    assert err.value.code == gpu.SPMM_EFORMAT
+    check(gpu, A)
