@@ -145,7 +145,8 @@ __global__ __launch_bounds__(64 * kWavesPerBlock, T == 2 ? 4 : 1) void k_spmm_mf
             for (int s = 0; s < G; ++s) {
               const float now = a;
               if (G * q + s + 1 < CH) a = operand(G * q + s + 1);
-              multiply(now, q, s);
+              // (zeros times the rows that stand in for no brick are NaN where those are infinite)
+              if (!kPartial || (uint32_t)(G * q + s) < live) multiply(now, q, s);
             }
           }
         }

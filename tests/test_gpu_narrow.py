@@ -45,3 +45,24 @@ def test_split_panels_on_either_side_of_the_rule(gpu, N):  # noqa: F811
     C = gpu.spmm_exec(plan, torch.from_numpy(B).cuda())
     torch.cuda.synchronize()
     check_c(C.cpu().numpy(), Cref, S)
+
+
+@pytest.mark.parametrize("N", [8, 16, 20, 32, 48])
+def test_infinities_stay_where_the_other_tiles_have_them(gpu, N):  # noqa: F811
+    """A panel's rows with an entry in the column of an infinity are infinite, its other rows NaN (0 * inf), and
+    no other panel has either, whatever place the column's brick has in a load or chunk (N = 48: the wider tiles)."""
+    import torch
+    A = panels_of(BRICKS)
+    plan = make_plan(gpu, A)
+    gpu.spmm_plan_set_split(plan, gpu.SPLIT_NEVER)
+    dense = np.zeros((A.M, A.K), np.float32)
+    dense[np.repeat(np.arange(A.M), np.diff(A.rowptr)), A.colind] = A.vals
+    bricks = np.repeat(BRICKS, 16)[:A.M]
+    for n in BRICKS[1:]:
+        B = W.dense_b(A.K, N, 7)
+        B[4 * n - 1] = np.inf                              # the last column of panels of n bricks
+        C = gpu.spmm_exec(plan, torch.from_numpy(B).cuda()).cpu().numpy()
+        entry = dense[:, 4 * n - 1]
+        expect = np.where(bricks < n, 0.0, np.where(entry != 0, np.copysign(np.inf, entry), np.nan))
+        got = np.where(np.isfinite(C), 0.0, C)
+        np.testing.assert_array_equal(got, np.repeat(expect[:, None], N, 1).astype(np.float32))
