@@ -1060,8 +1060,10 @@ int launch_product(const spmm_plan_t* pl, const HostList* hl, const WorkItem* d_
   int status = SPMM_OK;
   const BrickFormat f{pl->panel_ptr, pl->brick_cols, pl->brick_mask, pl->brick_valptr, pl->vals};
   const uint32_t n_listed = (uint32_t)hl->items.size();
-  const WorkSource work = hl->direct ? WorkSource{nullptr, d_items, (uint32_t)pl->P, n_listed, hl->split_bricks}
-                                     : WorkSource{d_items, nullptr, n_listed, 0, kNoSplit};
+  const bool any_split = !hl->merges.empty();
+  const WorkSource work = hl->direct
+                              ? WorkSource{nullptr, d_items, (uint32_t)pl->P, n_listed, hl->split_bricks, any_split}
+                              : WorkSource{d_items, nullptr, n_listed, 0, kNoSplit, any_split};
   if (uses_tm32(pl, B, N, C)) {
     // 32-row panels: one wavefront per super-panel and column tile, no work list
     HIP_TRY(launch_spmm_tm32(pl->tm32.sp_ptr, pl->tm32.bc_cols, pl->tm32.meta, pl->tm32.vals,

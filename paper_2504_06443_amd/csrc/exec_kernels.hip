@@ -785,7 +785,7 @@ hipError_t launch_spmm_mfma(const BrickFormat& f, const WorkSource& w, const flo
     // 41.5, N = 32 28.4 / 28.8 and 41.8 / 42.6; 600 k and 900 k rows, B of 77 and 115 MB: 63.6 / 60.5 and
     // 95.7 / 82.6; N = 8 at 283 k 22.5 / 21.3).  Without split panels, N = 14 to 32, bands, cells and blocks of
     // 25 k to 400 k rows: 2 to 12 % ahead or the same.
-    if (N >= 4 && N <= 32 && (w.n_parts == 0 || N <= 8 || K * N * 4 >= kNarrowLargeB))
+    if (N >= 4 && N <= 32 && (!w.any_split || N <= 8 || K * N * 4 >= kNarrowLargeB))
       return launch_spmm_mfma_narrow(f, w, B, C, partial, M, N, K, s);
     const int tile = mfma_fp32_tile(N, K, nnz);
     const unsigned gx = item_blocks<kWavesPerBlock>(w);

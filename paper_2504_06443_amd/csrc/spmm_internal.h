@@ -61,7 +61,8 @@ struct WorkSource {
   const WorkItem* parts;    // items null: parts of split panels
   uint32_t n_items;         // of the list, or panels
   uint32_t n_parts;
-  uint32_t split_bricks;    // kNoSplit where no panel is split
+  uint32_t split_bricks;    // kNoSplit where `parts` is empty
+  bool any_split;           // of the items and parts, some are parts
 };
 constexpr uint32_t kNoSplit = 0xFFFFFFFFu;
 

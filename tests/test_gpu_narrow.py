@@ -33,6 +33,36 @@ def test_chunks_and_widths(gpu, N, offset):  # noqa: F811
     assert bool((whole[:offset] == 7.0).all()) and bool((whole[offset + A.M * N:] == 7.0).all())
 
 
+def kernels_of(call):
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CUDA], acc_events=True) as seen:
+        call()
+        torch.cuda.synchronize()
+    return " ".join(e.key for e in seen.key_averages())
+
+
+@pytest.mark.parametrize("listed", ["exceptions", "heavy first", "class route"])
+def test_the_rule_sees_split_panels_in_every_list(gpu, listed):  # noqa: F811
+    """B is small: split panels take this kernel up to N = 8, whole ones up to 32, however the work is listed."""
+    import torch
+    A = panels_of(BRICKS)
+    plan = make_plan(gpu, A)
+    if listed == "heavy first":
+        gpu.spmm_plan_set_order(plan, gpu.ORDER_HEAVY_FIRST)
+    if listed == "class route":
+        gpu.spmm_plan_set_route(plan, gpu.ROUTE_CLASS)
+    for parts in (3, gpu.SPLIT_NEVER):
+        gpu.spmm_plan_set_split(plan, parts)
+        for N in (8, 16, 32, 33):
+            B = torch.from_numpy(W.dense_b(A.K, N, 7)).cuda()
+            gpu.spmm_exec(plan, B)                            # (the first product uploads its list)
+            names = kernels_of(lambda: gpu.spmm_exec(plan, B))
+            assert ("k_merge" in names) == (parts == 3), names
+            narrow = N <= (8 if parts == 3 else 32)
+            assert ("k_spmm_mfma_narrow" in names, "k_spmm_mfma_fast" in names) == (narrow, not narrow), names
+
+
 @pytest.mark.parametrize("N", [8, 16, 32])
 def test_split_panels_on_either_side_of_the_rule(gpu, N):  # noqa: F811
     """Split panels take this kernel at N = 8 and the other at 16 and 32 (B is small)."""
