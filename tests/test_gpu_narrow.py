@@ -96,3 +96,31 @@ def test_infinities_stay_where_the_other_tiles_have_them(gpu, N):  # noqa: F811
         expect = np.where(bricks < n, 0.0, np.where(entry != 0, np.copysign(np.inf, entry), np.nan))
         got = np.where(np.isfinite(C), 0.0, C)
         np.testing.assert_array_equal(got, np.repeat(expect[:, None], N, 1).astype(np.float32))
+
+
+@pytest.mark.parametrize("N, log2_k", [(9, 21), (13, 21), (16, 21), (17, 20), (22, 20), (31, 20), (32, 20)])
+@pytest.mark.parametrize("heavy_first", [False, True])
+def test_partial_tiles_where_b_is_large(gpu, N, log2_k, heavy_first):  # noqa: F811
+    """Split panels beyond N = 8 take this kernel where B has 64 MiB and more: the columns of a small matrix,
+    far apart."""
+    import torch
+    A = panels_of(BRICKS)
+    K = 1 << log2_k
+    at = (np.arange(A.K) * (K // A.K) + N).astype(np.int32)
+    assert at[-1] < K and K * N * 4 >= 64 << 20
+    plan = gpu.spmm_plan(A.M, K, torch.from_numpy(A.rowptr).cuda(), torch.from_numpy(at[A.colind]).cuda(),
+                         torch.from_numpy(A.vals).cuda())
+    gpu.spmm_plan_set_split(plan, 3)
+    if heavy_first:
+        gpu.spmm_plan_set_order(plan, gpu.ORDER_HEAVY_FIRST)
+    B = W.dense_b(A.K, N, 7)
+    Cref, S = oracle.spmm_f64(A.rowptr, A.colind, A.vals, B)
+    Bd = torch.zeros((K, N), device="cuda")
+    Bd[torch.from_numpy(at).long().cuda()] = torch.from_numpy(B).cuda()
+    names = kernels_of(lambda: gpu.spmm_exec(plan, Bd))
+    assert "k_spmm_mfma_narrow" in names and "k_merge" in names, names
+    for product in (gpu.spmm_exec, gpu.spmm_exec_noalloc):
+        Cd = torch.full((A.M, N), float("nan"), device="cuda")
+        product(plan, Bd, Cd)
+        torch.cuda.synchronize()
+        check_c(Cd.cpu().numpy(), Cref, S)
