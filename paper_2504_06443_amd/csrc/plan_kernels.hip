@@ -366,6 +366,14 @@ __global__ __launch_bounds__(kStatThreads) void k_plan_stats(
   if (threadIdx.x == 0) __hip_atomic_store(flag, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// the control block into pinned memory, flag last; one wavefront, whose release covers every lane's stores
+__global__ __launch_bounds__(64) void k_publish(const uint32_t* __restrict__ ctl, uint32_t n_words,
+                                                uint32_t* pinned, uint32_t* flag) {
+  for (uint32_t i = threadIdx.x; i < n_words; i += 64)
+    __hip_atomic_store(&pinned[i], ctl[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  if (threadIdx.x == 0) __hip_atomic_store(flag, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Rows with more than `threshold` entries, compacted in any order (the CSR kernel gives each of
 // them a workgroup of its own).  The list has room for nnz / threshold + 1 rows.
 __global__ void k_find_long_rows(const int32_t* __restrict__ rowptr, int64_t M, int threshold,
@@ -1613,6 +1621,12 @@ hipError_t launch_restore_csr(const BrickFormat& f, const uint32_t* src, int64_t
   const unsigned g = (unsigned)std::min<int64_t>(grid_for(nb, kThreads / 64), kRestoreBlocks);
   hipLaunchKernelGGL(k_restore_csr, dim3(g), dim3(kThreads), 0, s, f.brick_cols, f.brick_mask,
                      f.brick_valptr, f.vals, src, nb, colind, csr_vals);
+  return hipGetLastError();
+}
+
+hipError_t launch_publish(const PlanControl* ctl, PlanControl* pinned, uint32_t* flag, hipStream_t s) {
+  hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, s, reinterpret_cast<const uint32_t*>(ctl),
+                     (uint32_t)(sizeof(PlanControl) / sizeof(uint32_t)), reinterpret_cast<uint32_t*>(pinned), flag);
   return hipGetLastError();
 }
 

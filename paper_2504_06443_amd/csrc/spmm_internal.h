@@ -108,6 +108,8 @@ hipError_t launch_pack_values(const float* vals, const uint32_t* ent_brick, cons
 // csr_vals: null where the plan keeps no values in CSR order
 hipError_t launch_update_values(const float* vals, const uint32_t* src, int64_t nnz, float* packed,
                                 float* csr_vals, hipStream_t s);
+// `pinned` gets what ctl holds, then `flag` 1
+hipError_t launch_publish(const PlanControl* ctl, PlanControl* pinned, uint32_t* flag, hipStream_t s);
 hipError_t launch_plan_stats(const uint32_t* panel_ptr, const uint32_t* panel_nnzptr, int64_t P,
                              uint32_t* brick_cols, uint64_t* brick_mask, uint32_t* brick_valptr,
                              float* vals, int64_t nb, int64_t nnz, const uint8_t* col_seen, int64_t K,
