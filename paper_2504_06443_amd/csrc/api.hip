@@ -54,7 +54,10 @@ void keep_put(void* p, bool idle) { DeviceKeep::instance().put(p, idle); }
 // pageable memory is staged by the runtime, 25 to 150 us a call): buffers of kStageBytes, one per
 // call that needs one, at most kStages kept.  Without one (null) the copy goes the pageable way.
 constexpr size_t kStageBytes = size_t(1) << 20, kStages = 4;
-constexpr size_t kWorkKept = size_t(16) << 20;   // working memory that may stay with its plan (about K + 4 P + nnz / 100 bytes)
+// Working memory (about K + 4 P + nnz / 100 bytes) that may stay with its plan, so that spmm_plan need not wait for
+// the end of its last kernel, 5 to 6 us behind that kernel's flag (262,144 rows of blocks: 98 us, waiting
+// 104.6).  Plans of millions of columns take more memory, and wait.
+constexpr size_t kWorkKept = size_t(2) << 20;
 
 class HostStage {
  public:

@@ -35,6 +35,22 @@ def test_kept_memory_is_bounded_and_given_back(gpu):  # noqa: F811
     assert base - free_bytes() <= 4 << 20
 
 
+def test_plans_do_not_hold_what_they_were_made_with(gpu):  # noqa: F811
+    """Working memory has a byte a column: small matrices of many columns, on each of the three paths."""
+    K = 6_000_000
+    band = W.csr_from_coo(2000, K, np.repeat(np.arange(2000), 5), np.tile(np.arange(5), 2000) + np.repeat(np.arange(2000), 5))
+    for A in (band, W.csr_from_coo(2000, K, np.repeat(np.arange(2000), 5), np.arange(10000) * 599),
+              W.csr_from_coo(32, K, np.repeat([3, 20], 9000), np.tile(np.arange(9000) * 666, 2))):
+        dev = to_dev(A)
+        gpu._lib.spmm_plan_destroy(None)
+        base = free_bytes()
+        plans = [gpu.spmm_plan(A.M, A.K, *dev) for _ in range(16)]
+        gpu._lib.spmm_plan_destroy(None)
+        assert base - free_bytes() <= 16 * (2 << 20)
+        for p in plans:
+            p.destroy()
+
+
 def test_plans_of_several_threads_and_streams(gpu):  # noqa: F811
     import torch
     mats = [W.clustered_blocks(20_000, 8, 200, seed=1), W.power_law(M=30_000, target_nnz=None, cap=900, seed=2),
