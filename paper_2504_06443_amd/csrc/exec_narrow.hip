@@ -7,10 +7,12 @@
 // lanes hold a row of the tile, so one load holds the rows of G = 4/T bricks, and lane groups and registers then
 // change places (T = 2: eight lanes; T = 1: eight, then four) until register (brick, column) holds the four rows
 // of one brick in the MFMA's layout.  Column u of lane l's MFMA is then column 4*j + T*s + u of the tile, where
-// l % 16 = 4T*s + j.  923,136 rows of blocks, N = 32: accesses to L1 85 M -> 52 M, 213.7 -> 180.4 us; L1 now takes
-// accesses for 0.47 of the time and waits for lines from L2 for 0.48.  Fetching half a chunk at an item's end
-// (more code, spilled scalars) 181.8; registers for 8 wavefronts a SIMD (75 spilled scalars) 184.9; at most 5
-// wavefronts 185.9.
+// l % 16 = 4T*s + j.  923,136 rows of blocks, N = 32, products one after another: accesses to L1 85 M -> 52 M,
+// 213.7 -> 180.4 us (the first hundred after an idle time take 195 to 290, so traces of short runs show more); L1
+// now takes accesses for 0.47 of the time and waits for lines from L2 for 0.48.  There is room for 8 wavefronts a
+// SIMD (50 vector, 98 scalar registers); a launch bound that asks for 8 makes the compiler keep to 80 scalar
+// registers and spill as many again: 184.9.  At most 5 wavefronts 185.9; fetching half a chunk at an item's end
+// (more code, spilled scalars) 181.8.
 //
 // A chunk of eight bricks is in flight while it is multiplied load by load, and each load's registers take
 // the next chunk's.  The last chunk is fetched behind tests for what is left, so that items of ten bricks do not
