@@ -64,8 +64,9 @@ enum spmm_class { SPMM_NONE = -1, SPMM_LOW = 0, SPMM_MEDIUM = 1, SPMM_HIGH = 2 }
  * what it enqueued several times (it reads back sizes to allocate); when it returns,
  * the plan may be used on any stream.  The input is
  * validated on the device first; an invalid CSR gives SPMM_EFORMAT and no plan.
- * Beside its own arrays a plan may hold up to 2 MiB of the memory it was made with,
- * until it is destroyed; more than that is let go before the call returns.
+ * Beside its own arrays a plan may hold up to 2 MiB of the memory it was made with
+ * (in a block of up to 3 MiB, where one of an earlier plan serves), until it is
+ * destroyed; more than that is let go before the call returns.
  *
  * Format (panel p = rows 16p..16p+15; P = ceil(M/16) panels; nb bricks):
  *   panel_ptr    u32[P+1]  first brick of each panel
