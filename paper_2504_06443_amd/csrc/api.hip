@@ -99,6 +99,10 @@ class HostStage {
   char* p_ = nullptr;
 };
 
+// A matrix is scattered where the widest span of a panel's columns is more than this many times the mean of
+// a panel's active columns.
+constexpr int64_t kScatteredSpan = 64;
+
 // Waits until the device has set `flag` (pinned memory): by looking for a short while, which is as long as
 // the kernels of most plans take and sees the flag some microseconds before the runtime would report the
 // stream idle, then by waiting for the stream.
@@ -170,6 +174,7 @@ struct spmm_plan {
   // host copies used by the work-list builder and the synergy model
   std::vector<uint32_t> h_panel_ptr;      // empty until a list needs it (need_panel_ptr)
   int64_t max_bricks = 0, n_blocks = 0;   // of a panel; of the matrix (Eq. 6-7's unit)
+  bool scattered = false;                 // a panel's columns lie far apart (kScatteredSpan)
   std::vector<uint8_t> h_panel_class;     // filled with the CSR arrays, for the routes that ask
   unsigned long long h_counters[kNumCounters] = {};
   int64_t n_active_cols = 0;
@@ -912,6 +917,7 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
     goto done;
   }
 
+  pl->scattered = (int64_t)h_ctl.span * P > kScatteredSpan * pl->n_active_cols;
   h_maxnb = (h_ctl.max_cols + kBrickK - 1) / kBrickK;
   if (path == kPathBitmap && !panel_build_fits(words_cap, std::max<uint32_t>(h_maxnb, 1))) {
     path = kPathSearch;   // a panel with more bricks than fit in LDS: finish on the search-based path
@@ -1081,9 +1087,10 @@ int launch_product(const spmm_plan_t* pl, const HostList* hl, const WorkItem* d_
   const BrickFormat f{pl->panel_ptr, pl->brick_cols, pl->brick_mask, pl->brick_valptr, pl->vals};
   const uint32_t n_listed = (uint32_t)hl->items.size();
   const bool any_split = !hl->merges.empty();
-  const WorkSource work = hl->direct
-                              ? WorkSource{nullptr, d_items, (uint32_t)pl->P, n_listed, hl->split_bricks, any_split}
-                              : WorkSource{d_items, nullptr, n_listed, 0, kNoSplit, any_split};
+  const int32_t simds = 4 * pl->num_cus;
+  const WorkSource work =
+      hl->direct ? WorkSource{nullptr, d_items, (uint32_t)pl->P, n_listed, hl->split_bricks, any_split, simds, pl->scattered}
+                 : WorkSource{d_items, nullptr, n_listed, 0, kNoSplit, any_split, simds, pl->scattered};
   if (uses_tm32(pl, B, N, C)) {
     // 32-row panels: one wavefront per super-panel and column tile, no work list
     HIP_TRY(launch_spmm_tm32(pl->tm32.sp_ptr, pl->tm32.bc_cols, pl->tm32.meta, pl->tm32.vals,

@@ -751,6 +751,38 @@ int mfma_fp32_tile(int64_t N, int64_t K, int64_t nnz) {
   return 16 * (tiles > 1 && N % 32 == 0 ? (t + 1) / 2 * 2 : t);
 }
 
+// Columns per wavefront that run.  Few panels on the tiles above leave SIMDs idle, or one with twice the
+// wavefronts of another, and a single wavefront is a chain of latencies; on tiles of half the width they are
+// twice as many.  Times in us, wide / narrower, of 3x3 blocks (ten a block row) and of cells of fill 0.1:
+//   128 -> 64 columns at up to 2.5 wavefronts a SIMD: 640 panels, N = 128 10.5 / 9.7 and 14.7 / 12.5; 2500 panels
+//     21.1 / 19.3 and 31.9 / 27.8; at 2.9 a SIMD blocks lose (21.6 / 24.0).  Scattered panels, bound by memory and
+//     not by MFMAs, gain beyond that, too, as long as B stays in the Infinity Cache (graph of 4096 panels 30.3 /
+//     26.6, cells of 8192 112.5 / 107.1; a graph of 12,288 panels, B of 100 MB, 73.6 / 75.1).
+//   64 -> 32 and 32 -> 16 where the wider one gives at most 1.25 a SIMD, in 16-byte loads (exec_narrow.hip): 256
+//     panels, N = 64 6.8 / 5.3 / 4.7 and 8.5 / 6.5 / 5.6; 1250 panels, N = 64 10.0 / 9.0 / 9.2; 1024 panels, N = 128
+//     10.4 / 11.0 / 13.4.
+// Not where the narrower tiles multiply many columns more than there are: N = 80 as two of 48, 930 panels, 9.1 / 9.7.
+// Work lists and Eq. 7 go by the wide tiles, so which panels are split does not depend on this.
+int mfma_run_tile(const WorkSource& w, int64_t N, int64_t K, int64_t nnz) {
+  const int whole = mfma_fp32_tile(N, K, nnz);
+  if (!mfma_32bit_shape(N, K) || !mfma_32bit_values(nnz) || N < 20 || (N > 32 && N < 48)) return whole;
+  const int64_t items = (int64_t)w.n_items + w.n_parts;
+  auto tiles = [&](int64_t width) { return (N + width - 1) / width; };
+  int tile = whole;
+  for (int width = 64; width >= 16; width /= 2) {
+    const int64_t k = tiles(width), t = ((N + 15) / 16 + k - 1) / k;
+    const int64_t narrower = 16 * (t > 1 && N % 32 == 0 ? (t + 1) / 2 * 2 : t);
+    const int64_t columns = k * narrower, least = tiles(whole) * whole;   // multiplied, with those behind N
+    const int64_t waves = items * tiles(2 * width);
+    if (narrower >= tile) continue;
+    if (width == 64 ? 10 * columns <= 11 * least &&
+                          (2 * waves <= 5 * w.simds || (w.scattered && N % 32 == 0 && K * N * 4 <= kNarrowLargeB))
+                    : 4 * columns < 5 * least && 4 * waves <= 5 * w.simds)
+      tile = (int)narrower;
+  }
+  return tile;
+}
+
 // The "thread blocks per SM" of Eq. 7: wavefronts of the MFMA kernel that fit on one CU at a time,
 // taken at the power-of-two tile of N (the fast kernel's where N is a multiple of its vector width,
 // else the general kernel's), not at the narrower tile that runs.  The narrower tiles hold up to
@@ -784,10 +816,11 @@ hipError_t launch_spmm_mfma(const BrickFormat& f, const WorkSource& w, const flo
     // accesses and lose 1 to 3 % to the larger chunk (graphs of 283 k and 450 k rows, us: N = 14 26.7 / 27.5 and 40.1 /
     // 41.5, N = 32 28.4 / 28.8 and 41.8 / 42.6; 600 k and 900 k rows, B of 77 and 115 MB: 63.6 / 60.5 and
     // 95.7 / 82.6; N = 8 at 283 k 22.5 / 21.3).  Without split panels, N = 14 to 32, bands, cells and blocks of
-    // 25 k to 400 k rows: 2 to 12 % ahead or the same.
-    if (N >= 4 && N <= 32 && (!w.any_split || N <= 8 || K * N * 4 >= kNarrowLargeB))
-      return launch_spmm_mfma_narrow(f, w, B, C, partial, M, N, K, s);
-    const int tile = mfma_fp32_tile(N, K, nnz);
+    // 25 k to 400 k rows: 2 to 12 % ahead or the same.  The tiles of few panels at wider N are ahead or the same, split
+    // or not (graph of 640 panels, N = 64 9.7 / 9.2).
+    const int tile = mfma_run_tile(w, N, K, nnz);
+    if (N >= 4 && tile <= 32 && (N > 32 || !w.any_split || N <= 8 || K * N * 4 >= kNarrowLargeB))
+      return launch_spmm_mfma_narrow(f, w, tile, B, C, partial, M, N, K, s);
     const unsigned gx = item_blocks<kWavesPerBlock>(w);
     const dim3 grid(gx, (unsigned)((N + tile - 1) / tile)), block(64 * kWavesPerBlock);
     const uint32_t k_last = (uint32_t)(K - 1);

@@ -14,6 +14,8 @@
 // registers and spill as many again: 184.9.  At most 5 wavefronts 185.9; fetching half a chunk at an item's end
 // (more code, spilled scalars) 181.8.
 //
+// Wider C of few panels takes several such tiles (mfma_run_tile).
+//
 // A chunk of eight bricks is in flight while it is multiplied load by load, and each load's registers take
 // the next chunk's.  The last chunk is fetched behind tests for what is left, so that items of ten bricks do not
 // read eight more.
@@ -61,7 +63,8 @@ __global__ __launch_bounds__(64 * kWavesPerBlock, T == 2 ? 4 : 1) void k_spmm_mf
   const uint32_t perm_transpose = 4u * (uint32_t)(4 * (lane & 15) + kq);
   const uint32_t perm_base = 4u * (4u * in_load + kq);
   const uint32_t row_bytes = (uint32_t)N * 4u;
-  const uint32_t at = min(4u * j, (uint32_t)N - 4u);
+  const uint32_t col0 = blockIdx.y * (16u * T) + 4u * j;
+  const uint32_t at = min(col0, (uint32_t)N - 4u);
   const uint32_t lane_off = at * 4u;
 
   float4_t acc[T];
@@ -214,7 +217,7 @@ __global__ __launch_bounds__(64 * kWavesPerBlock, T == 2 ? 4 : 1) void k_spmm_mf
     out = partial + ((int64_t)slot * kPanel + 4 * kq) * N;
     rows_left = 4;
   }
-  if (4u * j < (uint32_t)N) {
+  if (col0 < (uint32_t)N) {
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       if (v < rows_left) {
@@ -229,15 +232,15 @@ __global__ __launch_bounds__(64 * kWavesPerBlock, T == 2 ? 4 : 1) void k_spmm_mf
 
 }  // namespace
 
-hipError_t launch_spmm_mfma_narrow(const BrickFormat& f, const WorkSource& w, const float* B, float* C,
+hipError_t launch_spmm_mfma_narrow(const BrickFormat& f, const WorkSource& w, int tile, const float* B, float* C,
                                    float* partial, int64_t M, int64_t N, int64_t K, hipStream_t s) {
-  const dim3 grid(item_blocks<kWavesPerBlock>(w)), block(64 * kWavesPerBlock);
+  const dim3 grid(item_blocks<kWavesPerBlock>(w), (unsigned)((N + tile - 1) / tile)), block(64 * kWavesPerBlock);
   const uint32_t k_last = (uint32_t)(K - 1);
 #define SPMM_LAUNCH_NARROW(TT)                                                                  \
   hipLaunchKernelGGL(k_spmm_mfma_narrow<TT>, grid, block, 0, s,                                 \
                      SPMM_ITEM_ARGS(kWavesPerBlock, w), f.panel_ptr, f.brick_cols,              \
                      f.brick_mask, f.brick_valptr, f.vals, B, C, partial, M, N, k_last)
-  if (N <= 16) SPMM_LAUNCH_NARROW(1); else SPMM_LAUNCH_NARROW(2);
+  if (tile == 16) SPMM_LAUNCH_NARROW(1); else SPMM_LAUNCH_NARROW(2);
 #undef SPMM_LAUNCH_NARROW
   return hipGetLastError();
 }

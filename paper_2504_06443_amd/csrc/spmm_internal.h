@@ -63,6 +63,8 @@ struct WorkSource {
   uint32_t n_parts;
   uint32_t split_bricks;    // kNoSplit where `parts` is empty
   bool any_split;           // of the items and parts, some are parts
+  int32_t simds;            // of the device
+  bool scattered;           // columns of a panel lie far apart: its B rows are its own
 };
 constexpr uint32_t kNoSplit = 0xFFFFFFFFu;
 
@@ -181,7 +183,9 @@ hipError_t launch_restore_csr(const BrickFormat& f, const uint32_t* src, int64_t
                               float* csr_vals, hipStream_t s);
 
 int mfma_tile_for(int64_t N);   // power-of-two tiles: 16, 32, 64 or 128 columns per wavefront
-int mfma_fp32_tile(int64_t N, int64_t K, int64_t nnz);   // columns per wavefront of the FP32 kernel
+int mfma_fp32_tile(int64_t N, int64_t K, int64_t nnz);   // columns per wavefront of the FP32 kernel,
+// and where `work` is too little to fill the device (or scattered) with those
+int mfma_run_tile(const WorkSource& work, int64_t N, int64_t K, int64_t nnz);
 int mfma_resident_waves_per_cu(int64_t N, int64_t K);
 bool mfma_32bit_shape(int64_t N, int64_t K);   // B below 4 GiB: the fast FP32 kernel,
 bool mfma_32bit_values(int64_t nnz);           // where the packed values are too
@@ -191,8 +195,8 @@ bool mfma_fast_shape(int64_t N, int64_t K);
 hipError_t launch_spmm_mfma(const BrickFormat& f, const WorkSource& work,
                             const float* B, float* C, float* partial, int64_t M, int64_t N,
                             int64_t K, int64_t nnz, hipStream_t s);
-// tiles of 16 and 32 columns (exec_narrow.hip): 4 <= N <= 32
-hipError_t launch_spmm_mfma_narrow(const BrickFormat& f, const WorkSource& work, const float* B, float* C,
+// tiles of 16 and 32 columns (exec_narrow.hip): N >= 4
+hipError_t launch_spmm_mfma_narrow(const BrickFormat& f, const WorkSource& work, int tile, const float* B, float* C,
                                    float* partial, int64_t M, int64_t N, int64_t K, hipStream_t s);
 // wide-N variant (exec_wide.hip): one workgroup per work item whose wavefronts take different
 // 128-column tiles and share the decoded bricks through LDS.  mfma_wide_waves: wavefronts per

@@ -1,0 +1,85 @@
+"""Few panels are multiplied on narrower tiles than many: widths around every tile, ragged and whole, on either
+side of the counts where the tile changes, with and without split panels."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2504_06443_amd import workloads as W
+from test_gpu_narrow import kernels_of
+from test_gpu_parity import check_c, gpu, make_plan  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+WIDTHS = (20, 31, 32, 47, 48, 50, 64, 65, 77, 80, 96, 97, 112, 113, 127, 128, 129, 144, 160, 191, 192, 200, 223, 255,
+          256, 257, 300)
+
+
+def simds():
+    import torch
+    return 4 * torch.cuda.get_device_properties(0).multi_processor_count
+
+
+@pytest.mark.parametrize("per_simd", [0.02, 0.6, 1.25, 2.5, 2.6])
+@pytest.mark.parametrize("split", [0, 2])
+@pytest.mark.parametrize("scattered", [False, True])
+def test_every_width_on_either_side_of_the_rule(gpu, per_simd, split, scattered):  # noqa: F811
+    import torch
+    panels = int(per_simd * simds()) + (per_simd == 2.5)
+    rows = 16 * panels - 11                                 # a ragged last panel
+    A = W.uniform_random(rows, rows, 0.02, 3) if scattered and panels < 100 else \
+        W.brick_sweep(0.1, M=16 * panels, target_nnz=100 * panels, seed=5) if scattered else \
+        W.clustered_blocks(rows, 2, 40, seed=7)
+    plan = make_plan(gpu, A)
+    gpu.spmm_plan_set_split(plan, split)
+    Ball = W.dense_b(A.K, max(WIDTHS), 11)
+    Call, S = oracle.spmm_f64(A.rowptr, A.colind, A.vals, Ball)
+    for N in WIDTHS:
+        print(f"{panels} panels, N={N} split={split} scattered={scattered}", flush=True)
+        offset = N % 4                                      # operands at every dword alignment
+        Bd = torch.empty(A.K * N + 4, device="cuda")[offset:offset + A.K * N].view(A.K, N)
+        Bd.copy_(torch.from_numpy(Ball[:, :N].copy()))
+        whole = torch.full((A.M * N + 8,), 7.0, device="cuda")
+        Cd = whole[offset:offset + A.M * N].view(A.M, N)
+        Cd.fill_(float("nan"))
+        gpu.spmm_exec(plan, Bd, Cd)
+        torch.cuda.synchronize()
+        check_c(Cd.cpu().numpy(), Call[:, :N], S[:, :N])
+        assert bool((whole[:offset] == 7.0).all()) and bool((whole[offset + A.M * N:] == 7.0).all())
+
+
+@pytest.mark.parametrize("N", [48, 64, 128])
+def test_split_panels_and_lists_do_not_depend_on_the_tile(gpu, N):  # noqa: F811
+    """Eq. 7 goes by the wide tiles, and the few panels here run on narrow ones."""
+    import torch
+    A = W.power_law(M=4000, target_nnz=None, cap=2000, alpha=1.6, seed=41)
+    plan = make_plan(gpu, A)
+    wl = gpu.spmm_plan_worklist(plan, N)
+    assert wl["n_tile"] == min(N, 128) and wl["n_tiles"] == -(-N // 128) and wl["n_split_panels"] > 0
+    B = W.dense_b(A.K, N, 42)
+    Bd = torch.from_numpy(B).cuda()
+    C = gpu.spmm_exec(plan, Bd)
+    names = kernels_of(lambda: gpu.spmm_exec(plan, Bd))
+    assert "k_spmm_mfma_narrow" in names and "k_merge" in names, names
+    again = torch.full_like(C, float("nan"))
+    gpu.spmm_exec_noalloc(plan, Bd, again)
+    torch.cuda.synchronize()
+    assert torch.equal(C, again)
+    Cref, S = oracle.spmm_f64(A.rowptr, A.colind, A.vals, B)
+    check_c(C.cpu().numpy(), Cref, S)
+
+
+@pytest.mark.parametrize("N", [32, 64, 96, 200])
+def test_infinities_stay_in_their_panels(gpu, N):  # noqa: F811
+    """Tiles that read bricks in pairs or fours multiply none that is not there, in any column tile."""
+    import torch
+    from test_gpu_narrow import BRICKS
+    from test_gpu_split_exceptions import panels_of
+    A = panels_of(BRICKS)
+    plan = make_plan(gpu, A)
+    gpu.spmm_plan_set_split(plan, gpu.SPLIT_NEVER)
+    bricks = np.repeat(BRICKS, 16)[:A.M]
+    for n in BRICKS[1:]:
+        B = W.dense_b(A.K, N, 7)
+        B[4 * n - 1] = np.inf
+        C = gpu.spmm_exec(plan, torch.from_numpy(B).cuda()).cpu().numpy()
+        np.testing.assert_array_equal(np.isfinite(C), np.repeat((bricks < n)[:, None], N, 1))
