@@ -837,12 +837,12 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
     uint32_t* flag = reinterpret_cast<uint32_t*>(stage.get() + Arena::pad(sizeof(PlanControl)));
     __atomic_store_n(flag, 0u, __ATOMIC_RELAXED);
     HIP_TRY(launch_rows_census(rowptr, colind, M, K, P, nnz, pl->rowptr, pl->panel_nnzptr, ncols_p,
-                               pl->panel_ptr, scan_tmp, ctl, pinned, flag, s));
+                               pl->panel_ptr, scan_tmp, ctl, pinned, flag, mid_list, big_list, s));
     HIP_TRY(wait_for_flag(flag, s));
     memcpy(&h_ctl, pinned, sizeof(PlanControl));
   } else {
     HIP_TRY(launch_rows_census(rowptr, colind, M, K, P, nnz, pl->rowptr, pl->panel_nnzptr, ncols_p,
-                               pl->panel_ptr, scan_tmp, ctl, nullptr, nullptr, s));
+                               pl->panel_ptr, scan_tmp, ctl, nullptr, nullptr, mid_list, big_list, s));
     HIP_TRY(read_ctl());
   }
   if (h_ctl.err & (kErrRowptrEnds | kErrRowptrOrder)) {
@@ -867,7 +867,7 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
   //   120 / 123, 4.2 (cells, 2 M, fill 0.05) 239 / 140, 4.2 (fill 0.8) 163 / 143.
   // Bitmap against search at 4: 0.6 / 1.0 ms.
   sort_fits = panel_sort_fits(P, nnz, h_ctl.max_nnz);
-  if (words_cap != 0 && (int64_t)words_cap * P <= (sort_fits ? 2 : 8) * nnz) path = kPathBitmap;
+  if (words_cap != 0 && (int64_t)words_cap * P <= (sort_fits ? kBandWords : 8) * nnz) path = kPathBitmap;
   else if (sort_fits) path = kPathSort;
   counted = h_ctl.counted;   // then panel_ptr is there, whichever path takes it
   if (counted && path == kPathBitmap) {
@@ -877,7 +877,7 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
     HIP_TRY(launch_panel_census(rowptr, colind, M, K, P, words_cap, &ctl->err, ncols_p, s));
   } else if (path == kPathSort) {
     HIP_TRY(launch_panel_sort_census(rowptr, colind, M, K, P, nnz, h_ctl.max_nnz,
-                                     pl->panel_nnzptr, mid_list, big_list, ctl, ncols_p, pl->src, s));
+                                     mid_list, big_list, ctl, ncols_p, pl->src, s));
   } else {
     // ---- search-based path for every other matrix.  Its a1
     // kernels only compare columns, so they may run before the host has seen the verdict of
@@ -938,7 +938,7 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
   if (path == kPathSort) {
     HIP_TRY(launch_panel_sort_build(rowptr, colind, vals, M, P,
                                     PanelLists{mid_list, big_list, h_ctl.n_mid, h_ctl.n_big},
-                                    h_ctl.max_nnz, std::max<uint32_t>(h_maxnb, 1), pl->panel_ptr, pl->brick_cols,
+                                    h_ctl.max_nnz, std::max<uint32_t>(h_maxnb, 1), pl->panel_ptr, ncols_p, pl->brick_cols,
                                     pl->brick_mask, pl->brick_valptr, pl->vals, pl->src, col_seen,
                                     s));
   } else if (path == kPathBitmap) {

@@ -27,7 +27,6 @@ namespace spmm {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int64_t kMaxLaunchThreads = int64_t(1) << 32;   // a launch has fewer than this
 
 inline unsigned grid_for(int64_t n, int threads = kThreads) {
   int64_t g = (n + threads - 1) / threads;
@@ -554,6 +553,78 @@ __global__ __launch_bounds__(kScanThreads) void k_panel_scan(const uint32_t* __r
   }
 }
 
+// The same in one launch, for as many panels as a workgroup adds up while it could wait for another launch:
+// each adds up the bricks of all panels before its own, the last one everything.  20,360 panels: 5.0 + 5.0 us and the
+// gap between -> 7.6; 62,500: 6.0 + 5.0 -> 10.6.
+constexpr int kOneScanThreads = 1024;
+constexpr int64_t kOneScanPanels = 1 << 16;
+
+__global__ __launch_bounds__(kOneScanThreads) void k_panel_scan_one(const uint32_t* __restrict__ ncols_p, int64_t P,
+                                                                    uint32_t* __restrict__ panel_ptr, PlanControl* ctl) {
+  constexpr int kWaves = kOneScanThreads / 64, kOwn = 4;
+  struct Sums { uint32_t bricks, blocks, most; unsigned long long cols; };
+  __shared__ Sums s_before[kWaves], s_own[kWaves];
+  auto add = [](Sums& t, uint32_t n) {
+    const uint32_t b = (n + kBrickK - 1) / kBrickK;
+    t.bricks += b;
+    t.blocks += (b + kBrickK - 1) / kBrickK;
+    t.most = max(t.most, n);
+    t.cols += n;
+  };
+  auto over_wave = [](Sums t) {
+    return Sums{wave_sum(t.bricks), wave_sum(t.blocks), wave_max(t.most), wave_sum(t.cols)};
+  };
+  const int64_t first = (int64_t)blockIdx.x * kOneScanThreads * kOwn;
+  Sums before{};
+  for (int64_t p = 4 * threadIdx.x; p < first; p += 4 * kOneScanThreads) {   // (first is a multiple of the step)
+    const uint4 n = *reinterpret_cast<const uint4*>(ncols_p + p);
+    add(before, n.x); add(before, n.y); add(before, n.z); add(before, n.w);
+  }
+  const int64_t p0 = first + kOwn * threadIdx.x;
+  uint32_t nb[kOwn];
+  Sums own{};
+#pragma unroll
+  for (int k = 0; k < kOwn; ++k) {
+    const uint32_t n = p0 + k < P ? ncols_p[p0 + k] : 0u;
+    nb[k] = (n + kBrickK - 1) / kBrickK;
+    add(own, n);
+  }
+  const int wave = threadIdx.x >> 6;
+  const uint32_t mine = own.bricks;
+  uint32_t in_wave = mine;   // exclusive scan across the wavefront
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t up = __shfl_up(in_wave, d, 64);
+    if ((int)(threadIdx.x & 63) >= d) in_wave += up;
+  }
+  in_wave -= mine;
+  before = over_wave(before);
+  own = over_wave(own);
+  if ((threadIdx.x & 63) == 0) { s_before[wave] = before; s_own[wave] = own; }
+  __syncthreads();
+  uint32_t at = in_wave;
+  for (int w = 0; w < kWaves; ++w) at += s_before[w].bricks + (w < wave ? s_own[w].bricks : 0u);
+#pragma unroll
+  for (int k = 0; k < kOwn; ++k) {
+    if (p0 + k < P) panel_ptr[p0 + k] = at;
+    at += nb[k];
+  }
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+    Sums t{};
+    for (int w = 0; w < kWaves; ++w) {
+      t.bricks += s_before[w].bricks + s_own[w].bricks;
+      t.blocks += s_before[w].blocks + s_own[w].blocks;
+      t.most = max(t.most, max(s_before[w].most, s_own[w].most));
+      t.cols += s_before[w].cols + s_own[w].cols;
+    }
+    panel_ptr[P] = t.bricks;
+    ctl->nb = t.bricks;
+    ctl->n_active = t.cols;
+    ctl->n_blocks = t.blocks;
+    ctl->max_cols = t.most;
+  }
+}
+
 // ---------------------------------------------------------------- per-panel path
 // One wavefront (a 64-thread workgroup) per panel, the panel's active columns as a bitmap in
 // LDS over the panel's column span [cmin, cmax]: setting a bit per entry is the census (a1),
@@ -562,8 +633,6 @@ __global__ __launch_bounds__(kScanThreads) void k_panel_scan(const uint32_t* __r
 // panel's pattern popcounts, the value positions (a4; a panel's values are contiguous, so
 // brick_valptr needs no scan across panels).  Used when the widest panel span and the largest
 // brick count of a panel fit in LDS; other matrices take the search-based kernels above.
-constexpr int kPanelThreads = 64;
-constexpr uint32_t kPanelMaxWords = 32768;          // 1 Mi columns of span
 
 struct PanelExtent {
   int64_t e0, e1;        // entries of the panel
@@ -688,6 +757,8 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_census(
 constexpr int kFirstThreads = 512, kFirstWaves = kFirstThreads / 64;
 constexpr int kFirstBlocks = 768;                   // three a CU
 constexpr uint32_t kFirstWords = 512;               // bitmap words a wavefront: 16,384 columns
+
+constexpr uint32_t kSortSmall = 512, kSortMid = 2048, kSortBig = 8192;   // entries; see the path that sorts
 
 struct PanelTotals {
   uint32_t bricks, blocks, cols, max_cols;
@@ -846,10 +917,13 @@ __global__ __launch_bounds__(kFirstThreads, 6) void k_rows_census(
 // workgroup here takes `group` of those runs.  Without every panel's count there is nothing to scan.  The
 // first workgroup puts the matrix's totals into the control block and, for the host that waits for them,
 // into pinned memory, flag last (a copy behind the kernels takes 4 us, and the wait for the stream more).
+// Where the panels will be sorted, those of more than kSortSmall and of more than kSortMid entries are listed, in any
+// order (a launch of its own: 2.9 us and the gap before it).
 __global__ __launch_bounds__(kScanThreads) void k_census_scan(
     const uint32_t* __restrict__ ncols_p, int64_t P, int64_t run, const PanelTotals* __restrict__ totals,
     uint32_t n_totals, uint32_t group, uint32_t* __restrict__ panel_ptr, PlanControl* ctl,
-    PlanControl* pinned, uint32_t* flag) {
+    PlanControl* pinned, uint32_t* flag, int64_t nnz, const uint32_t* __restrict__ panel_nnzptr,
+    uint32_t* __restrict__ mid_list, uint32_t* __restrict__ big_list) {
   __shared__ PanelTotals s_tot[kScanThreads / 64];
   __shared__ uint32_t s_before[kScanThreads / 64];
   PanelTotals t{};
@@ -894,8 +968,28 @@ __global__ __launch_bounds__(kScanThreads) void k_census_scan(
     if (counted) panel_ptr[P] = t.bricks;
     if (flag) __hip_atomic_store(flag, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
   }
-  if (!counted) return;
   const int64_t p_end = min((int64_t)(blockIdx.x + 1) * group * run, P);
+  const uint32_t words = panel_bitmap_words(t.span, P);
+  const bool band = words != 0 && (int64_t)words * P <= kBandWords * nnz;   // (as the host chooses)
+  if (!t.err && !band && t.max_nnz > kSortSmall) {   // (rowptr is in order: the lists have room)
+    __shared__ uint32_t s_count[2], s_base[2];
+    for (int64_t p0 = (int64_t)blockIdx.x * group * run; p0 < p_end; p0 += kScanThreads) {
+      __syncthreads();
+      if (threadIdx.x < 2) s_count[threadIdx.x] = 0;
+      __syncthreads();
+      const int64_t p = p0 + threadIdx.x;
+      const uint32_t n = p < p_end ? panel_nnzptr[p + 1] - panel_nnzptr[p] : 0;
+      const int which = n > kSortMid ? 1 : (n > kSortSmall ? 0 : -1);
+      uint32_t in_block = 0;
+      if (which >= 0) in_block = atomicAdd(&s_count[which], 1u);
+      __syncthreads();
+      if (threadIdx.x < 2 && s_count[threadIdx.x])
+        s_base[threadIdx.x] = atomicAdd(threadIdx.x ? &ctl->n_big : &ctl->n_mid, s_count[threadIdx.x]);
+      __syncthreads();
+      if (which >= 0) (which ? big_list : mid_list)[s_base[which] + in_block] = (uint32_t)p;
+    }
+  }
+  if (!counted) return;
   for (int64_t p0 = (int64_t)blockIdx.x * group * run; p0 < p_end; p0 += 4 * kScanThreads) {
     const int64_t p = p0 + 4 * threadIdx.x;
     uint32_t nb[4];
@@ -920,33 +1014,14 @@ __global__ __launch_bounds__(kScanThreads) void k_census_scan(
 // workgroup of 256, up to 8192 one of 1024.  All sort in registers, up to eight keys a lane: a
 // compare-exchange inside a lane is a min and a max, across lanes one cross-lane read a key, and only
 // steps across wavefronts go through LDS (a sort all through LDS moved four words a pair and step).
-// The census leaves the sorted entries, rank << 16 | index inside the panel, for the build.
-// 20,360 panels of 46 entries, the largest 3000: the search-based kernels 167 us, these 84 (keys of 32 bits
-// for the 48 panels above 2048: 30 -> 19 us).
+// Where the two upper classes are the few heavy panels of many light ones, as in graphs, their columns are ranked by
+// a bitmap of all columns instead (k_panel_bitmap_census).
+// The census leaves the entries, rank << 16 | index inside the panel, for the build, sorted or as they are stored.
+// 20,360 panels of 46 entries, the largest 3000: the search-based kernels 167 us, sorting all classes 84 (keys of 32
+// bits for the 48 panels above 2048: 30 -> 19 us).
 // 18,750 panels of 430: a sort through LDS by one wavefront 163 + 101 us (census, build), now 84 + 67.
-constexpr uint32_t kSortSmall = 512, kSortMid = 2048, kSortBig = 8192;
 constexpr int kMidThreads = 256, kBigThreads = 1024;
 static_assert(kMidThreads * 8 == kSortMid && kBigThreads * 8 == kSortBig, "eight keys a lane");
-
-// the panels of more than kSortSmall and of more than kSortMid entries, listed in any order
-__global__ __launch_bounds__(1024) void k_panel_lists(const uint32_t* __restrict__ panel_nnzptr,
-                                                      int64_t P, uint32_t* __restrict__ mid_list,
-                                                      uint32_t* __restrict__ big_list,
-                                                      PlanControl* ctl) {
-  __shared__ uint32_t count[2], base[2];
-  if (threadIdx.x < 2) count[threadIdx.x] = 0;
-  __syncthreads();
-  const int64_t p = (int64_t)blockIdx.x * 1024 + threadIdx.x;
-  const uint32_t n = p < P ? panel_nnzptr[p + 1] - panel_nnzptr[p] : 0;
-  const int which = n > kSortMid ? 1 : (n > kSortSmall ? 0 : -1);
-  uint32_t at = 0;
-  if (which >= 0) at = atomicAdd(&count[which], 1u);
-  __syncthreads();
-  if (threadIdx.x < 2 && count[threadIdx.x])
-    base[threadIdx.x] = atomicAdd(threadIdx.x ? &ctl->n_big : &ctl->n_mid, count[threadIdx.x]);
-  __syncthreads();
-  if (which >= 0) (which ? big_list : mid_list)[base[which] + at] = (uint32_t)p;
-}
 
 // A key is column << B | index.  In 32 bits, half the moves of a 64-bit one: B = 11 for panels of up to
 // kSortMid entries and fewer than 2^21 columns, B = 13 for up to kSortBig and fewer than 2^19 (fewer,
@@ -1177,10 +1252,80 @@ __global__ __launch_bounds__(kBigThreads) void k_panel_sort_census_big(
   if (threadIdx.x == 0) ncols_p[p] = cols;
 }
 
+// Census of the listed panels by a bitmap of all columns, a workgroup each: no order, so no sort, and a rank from a
+// table of the bits set before every eighth word.  `order` keeps the entries as they are stored.
+// Bound by latency, so all loads of a thread are in flight at once.  207 listed panels of 20,360, 325,760 columns:
+// their share of the sorting launches 27 + 19 -> 11 us beside 23 for the small ones (spmm_plan 159 -> 138); 30,000
+// rows 117 -> 93.  Bitmaps of a million columns leave a CU one workgroup: 640 listed panels 65 us, sorted 40.
+constexpr int kListedThreads = 1024;
+constexpr uint32_t kListedMaxWords = 16384;          // 512 Ki columns: 72 KiB of LDS with the table
+
+__global__ __launch_bounds__(kListedThreads) void k_panel_bitmap_census(
+    const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind, int64_t M, int64_t K,
+    const uint32_t* __restrict__ mid_list, const uint32_t* __restrict__ big_list, const PlanControl* ctl,
+    uint32_t words, uint32_t* err, uint32_t* __restrict__ ncols_p, uint32_t* __restrict__ order) {
+  extern __shared__ uint32_t lds[];
+  __shared__ uint32_t sums[kListedThreads / 64];
+  uint32_t *bm = lds, *pre = lds + words;   // [words], [words / kGroupWords, rounded up]
+  const uint32_t n_big = ctl->n_big, n_mid = ctl->n_mid;   // (the host does not know them yet)
+  if (blockIdx.x >= n_big + n_mid) return;
+  const int64_t p = blockIdx.x < n_big ? big_list[blockIdx.x] : mid_list[blockIdx.x - n_big];
+  const PanelRows x(rowptr, M, p);
+  constexpr int R = kSortBig / kListedThreads;
+  int32_t j[R], before[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const uint32_t i = r * kListedThreads + threadIdx.x;
+    j[r] = i < x.n ? colind[x.e0 + i] : -1;
+    before[r] = i < x.n && i > 0 ? colind[x.e0 + i - 1] : -1;
+  }
+  for (uint32_t w = threadIdx.x; w < words; w += kListedThreads) bm[w] = 0;
+  __syncthreads();
+  uint32_t bad = 0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const uint32_t i = r * kListedThreads + threadIdx.x;
+    if (i < x.n) {
+      if (before[r] >= j[r] && !x.starts_row(i)) bad |= kErrColOrder;
+      if (j[r] < 0 || j[r] >= K) bad |= kErrColRange;
+      else atomicOr(&bm[(uint32_t)j[r] >> 5], 1u << (j[r] & 31));
+    }
+  }
+  if (bad) atomicOr(err, bad);
+  __syncthreads();
+  const uint32_t groups = (words + kGroupWords - 1) / kGroupWords;
+  const uint32_t per = (groups + kListedThreads - 1) / kListedThreads;
+  const uint32_t g0 = min(threadIdx.x * per, groups), g1 = min(g0 + per, groups);
+  uint32_t mine = 0;
+  for (uint32_t g = g0; g < g1; ++g) {
+    uint32_t c = 0;
+    for (uint32_t w = g * kGroupWords; w < min((g + 1) * kGroupWords, words); ++w) c += __popc(bm[w]);
+    pre[g] = c;
+    mine += c;
+  }
+  uint32_t total;
+  uint32_t run = group_exclusive<kListedThreads>(mine, &total, sums);
+  for (uint32_t g = g0; g < g1; ++g) {
+    const uint32_t c = pre[g];
+    pre[g] = run;
+    run += c;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const uint32_t i = r * kListedThreads + threadIdx.x;
+    if (i >= x.n || j[r] < 0 || j[r] >= K) continue;   // (with the latter the plan is refused)
+    const uint32_t w = (uint32_t)j[r] >> 5;
+    uint32_t rank = pre[w / kGroupWords] + __popc(bm[w] & ((1u << (j[r] & 31)) - 1u));
+    for (uint32_t v = w & ~(kGroupWords - 1); v < w; ++v) rank += __popc(bm[v]);
+    order[x.e0 + i] = rank << 16 | i;
+  }
+  if (threadIdx.x == 0) ncols_p[p] = total;
+}
+
 // a2 (placing half), a3 and a4 of the listed panels (n_first of `list`, then those of `rest`; no list:
-// of all) of at most n_cap entries, from the
-// sorted entries that the census left in `src` (which this kernel then overwrites with the entry of
-// each packed value).  T threads a panel.  Dynamic LDS: patterns (nb_cap x u64), the sorted entries
+// of all) of at most n_cap entries, from what the census left in `src` (which this kernel then overwrites with
+// the entry of each packed value).  T threads a panel.  Dynamic LDS: patterns (nb_cap x u64), ranks and indexes
 // (n_cap words), value offsets (nb_cap words), the order of the packed values (n_cap x two bytes),
 // through which they leave in order, whole lines at a time.
 template <int T>
@@ -1188,13 +1333,13 @@ __global__ __launch_bounds__(T) void k_panel_sort_build(
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind,
     const float* __restrict__ vals, int64_t M, const uint32_t* __restrict__ list,
     const uint32_t* __restrict__ rest, uint32_t n_first, uint32_t n_cap, uint32_t nb_cap,
-    const uint32_t* __restrict__ panel_ptr, uint32_t* __restrict__ brick_cols,
+    const uint32_t* __restrict__ panel_ptr, const uint32_t* __restrict__ ncols_p, uint32_t* __restrict__ brick_cols,
     uint64_t* __restrict__ brick_mask, uint32_t* __restrict__ brick_valptr,
     float* __restrict__ packed, uint32_t* src, uint8_t* __restrict__ col_seen) {
   extern __shared__ unsigned long long lds64[];
   __shared__ uint32_t sums[T / 64];
   unsigned long long* pat = lds64;                                   // [nb_cap]
-  uint32_t* ent = reinterpret_cast<uint32_t*>(pat + nb_cap);         // [n_cap] rank << 16 | index
+  uint32_t* ent = reinterpret_cast<uint32_t*>(pat + nb_cap);         // [n_cap]: rank << 16 | index
   uint32_t* vptr = ent + n_cap;                                      // [nb_cap]
   uint16_t* at = reinterpret_cast<uint16_t*>(vptr + nb_cap);         // [n_cap]
   const int64_t p = !list ? blockIdx.x : blockIdx.x < n_first ? list[blockIdx.x] : rest[blockIdx.x - n_first];
@@ -1208,8 +1353,9 @@ __global__ __launch_bounds__(T) void k_panel_sort_build(
   for (uint32_t i = threadIdx.x; i < n; i += T) ent[i] = src[x.e0 + i];
   __syncthreads();
 
-  // columns, from the first entry of each; the tail of the last brick padded.  Pattern bits.
-  const uint32_t ncols = (ent[n - 1] >> 16) + 1u;
+  // columns, from the first entry of each (entries that are not sorted may write one several times, all the same); the
+  // tail of the last brick padded.  Pattern bits.
+  const uint32_t ncols = ncols_p[p];
   auto rank_of = [&](uint32_t w) { return min(w >> 16, nb * kBrickK - 1); };
   auto index_of = [&](uint32_t w) { return min(w & 0xFFFFu, n - 1); };
   auto bit_of = [&](uint32_t w) { return x.row_of(index_of(w)) * kBrickK + rank_of(w) % kBrickK; };
@@ -1503,7 +1649,8 @@ hipError_t launch_scan_nonzero64(const uint64_t* in, int64_t n, uint32_t* out, u
 hipError_t launch_rows_census(const int32_t* rowptr, const int32_t* colind, int64_t M, int64_t K,
                               int64_t P, int64_t nnz, int32_t* rowptr_copy, uint32_t* panel_nnzptr,
                               uint32_t* ncols_p, uint32_t* panel_ptr, uint32_t* tmp, PlanControl* ctl,
-                              PlanControl* pinned, uint32_t* flag, hipStream_t s) {
+                              PlanControl* pinned, uint32_t* flag, uint32_t* mid_list, uint32_t* big_list,
+                              hipStream_t s) {
   static_assert(sizeof(PanelTotals) == 32, "eight words of `tmp` each");
   PanelTotals* totals = reinterpret_cast<PanelTotals*>(tmp);
   const int64_t want = std::max<int64_t>(1, std::min<int64_t>((P + kFirstWaves - 1) / kFirstWaves, kFirstBlocks));
@@ -1513,7 +1660,7 @@ hipError_t launch_rows_census(const int32_t* rowptr, const int32_t* colind, int6
                      rowptr_copy, panel_nnzptr, ncols_p, totals);
   const unsigned group = (unsigned)std::max<int64_t>(1, 4 * kScanThreads / run);
   hipLaunchKernelGGL(k_census_scan, dim3((n + group - 1) / group), dim3(kScanThreads), 0, s, ncols_p, P, run,
-                     totals, n, group, panel_ptr, ctl, pinned, flag);
+                     totals, n, group, panel_ptr, ctl, pinned, flag, nnz, panel_nnzptr, mid_list, big_list);
   return hipGetLastError();
 }
 
@@ -1523,6 +1670,11 @@ size_t panel_scan_tmp_elems() {
 
 hipError_t launch_panel_scan(const uint32_t* ncols_p, int64_t P, uint32_t* panel_ptr, uint32_t* tmp,
                              PlanControl* ctl, hipStream_t s) {
+  if (P <= kOneScanPanels) {
+    hipLaunchKernelGGL(k_panel_scan_one, dim3(grid_for(P, 4 * kOneScanThreads)), dim3(kOneScanThreads), 0, s,
+                       ncols_p, P, panel_ptr, ctl);
+    return hipGetLastError();
+  }
   const int64_t run = panel_scan_run(P);
   const dim3 grid(grid_for((P + run - 1) / run, kScanThreads)), block(kScanThreads);
   hipLaunchKernelGGL(k_panel_sums, grid, block, 0, s, ncols_p, P, run, tmp, ctl);
@@ -1662,18 +1814,31 @@ bool panel_sort_fits(int64_t P, int64_t nnz, uint32_t max_nnz) {
 int64_t panel_mid_list_elems(int64_t nnz) { return nnz / kSortSmall; }
 int64_t panel_big_list_elems(int64_t nnz) { return nnz / kSortMid; }
 
+// The listed panels go through a bitmap of all columns where they are the few heavy ones of many: at most 128
+// entries a panel in the mean, so at most a quarter of the panels is listed.
+constexpr int64_t kFewListedMean = 128;
+
 hipError_t launch_panel_sort_census(const int32_t* rowptr, const int32_t* colind, int64_t M,
                                     int64_t K, int64_t P, int64_t nnz, uint32_t max_nnz,
-                                    const uint32_t* panel_nnzptr, uint32_t* mid_list,
-                                    uint32_t* big_list, PlanControl* ctl, uint32_t* ncols_p,
-                                    uint32_t* order, hipStream_t s) {
+                                    const uint32_t* mid_list, const uint32_t* big_list, PlanControl* ctl,
+                                    uint32_t* ncols_p, uint32_t* order, hipStream_t s) {
   if (P == 0) return hipSuccess;
   const bool narrow = K < (int64_t(1) << (32 - kMidBits)), narrow_big = K < (int64_t(1) << (32 - kBigBits));
-  const bool mid = max_nnz > kSortSmall;
+  const int64_t words = (K + 31) / 32;
+  const bool listed = max_nnz > kSortSmall, bitmap = listed && nnz <= kFewListedMean * P && words <= kListedMaxWords;
+  if (bitmap) {
+    const size_t lds = (size_t)(words + (words + kGroupWords - 1) / kGroupWords) * 4;
+    if (lds > 48 * 1024) {
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_panel_bitmap_census),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(k_panel_bitmap_census, dim3((unsigned)std::min(P, panel_mid_list_elems(nnz))),
+                       dim3(kListedThreads), lds, s, rowptr, colind, M, K, mid_list, big_list, ctl, (uint32_t)words,
+                       &ctl->err, ncols_p, order);
+  }
+  const bool mid = listed && !bitmap;
   const unsigned mid_blocks = mid ? (unsigned)std::min(P, panel_mid_list_elems(nnz)) : 0u;
-  if (mid)
-    hipLaunchKernelGGL(k_panel_lists, dim3(grid_for(P, 1024)), dim3(1024), 0, s, panel_nnzptr, P,
-                       mid_list, big_list, ctl);
   const dim3 grid(mid_blocks + grid_for(P, kMidThreads / 64)), block(kMidThreads);
 #define SPMM_LAUNCH_CENSUS(KT, BITS, MID)                                                         \
   hipLaunchKernelGGL((k_panel_sort_census<KT, BITS, MID>), grid, block, 0, s, rowptr, colind, M, K, \
@@ -1686,7 +1851,7 @@ hipError_t launch_panel_sort_census(const int32_t* rowptr, const int32_t* colind
     else SPMM_LAUNCH_CENSUS(unsigned long long, 32, false);
   }
 #undef SPMM_LAUNCH_CENSUS
-  if (max_nnz > kSortMid) {
+  if (max_nnz > kSortMid && !bitmap) {
     const dim3 at_most((unsigned)std::min(P, panel_big_list_elems(nnz))), big(kBigThreads);
     if (narrow_big)
       hipLaunchKernelGGL((k_panel_sort_census_big<uint32_t, kBigBits>), at_most, big, 0, s, rowptr,
@@ -1704,8 +1869,8 @@ template <int T>
 static hipError_t sort_build(const int32_t* rowptr, const int32_t* colind, const float* vals,
                              int64_t M, const uint32_t* list, const uint32_t* rest,
                              uint32_t n_first, int64_t n_panels, uint32_t n_cap, uint32_t nb_cap,
-                             const uint32_t* panel_ptr, uint32_t* brick_cols, uint64_t* brick_mask,
-                             uint32_t* brick_valptr, float* packed, uint32_t* src,
+                             const uint32_t* panel_ptr, const uint32_t* ncols_p, uint32_t* brick_cols,
+                             uint64_t* brick_mask, uint32_t* brick_valptr, float* packed, uint32_t* src,
                              uint8_t* col_seen, hipStream_t s) {
   if (n_panels == 0) return hipSuccess;
   n_cap = (n_cap + 1) & ~1u;
@@ -1719,43 +1884,34 @@ static hipError_t sort_build(const int32_t* rowptr, const int32_t* colind, const
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(k_panel_sort_build<T>, dim3((unsigned)n_panels), dim3(T), lds, s, rowptr, colind,
-                     vals, M, list, rest, n_first, n_cap, nb_cap, panel_ptr, brick_cols, brick_mask,
-                     brick_valptr, packed, src, col_seen);
+  hipLaunchKernelGGL(k_panel_sort_build<T>, dim3((unsigned)n_panels), dim3(T), lds, s, rowptr, colind, vals, M, list,
+                     rest, n_first, n_cap, nb_cap, panel_ptr, ncols_p, brick_cols,
+                     brick_mask, brick_valptr, packed, src, col_seen);
   return hipGetLastError();
 }
 
 hipError_t launch_panel_sort_build(const int32_t* rowptr, const int32_t* colind, const float* vals,
                                    int64_t M, int64_t P, const PanelLists& l, uint32_t max_nnz,
-                                   uint32_t max_bricks, const uint32_t* panel_ptr,
+                                   uint32_t max_bricks, const uint32_t* panel_ptr, const uint32_t* ncols_p,
                                    uint32_t* brick_cols, uint64_t* brick_mask,
                                    uint32_t* brick_valptr, float* packed, uint32_t* src,
                                    uint8_t* col_seen, hipStream_t s) {
   hipError_t e = sort_build<64>(rowptr, colind, vals, M, nullptr, nullptr, 0, P, std::min(max_nnz, kSortSmall),
-                                max_bricks, panel_ptr, brick_cols, brick_mask, brick_valptr, packed,
-                                src, col_seen, s);
+                                   max_bricks, panel_ptr, ncols_p, brick_cols, brick_mask, brick_valptr, packed,
+                                   src, col_seen, s);
   // Few listed panels are one round of workgroups: together, in the time of the largest (48 panels
   // above 2048 entries and 159 above 512: 15 + 10 us as two launches, 10 as one).  Many are
   // ahead with the smaller workgroups and the LDS that the smaller ones need.
   const bool together = l.n_big > 0 && l.n_big + l.n_mid <= kSortBuildRound;
   if (e == hipSuccess && !together)
     e = sort_build<kMidThreads>(rowptr, colind, vals, M, l.mid, nullptr, l.n_mid, l.n_mid,
-                                std::min(max_nnz, kSortMid), max_bricks, panel_ptr, brick_cols,
-                                brick_mask, brick_valptr, packed, src, col_seen, s);
+                                   std::min(max_nnz, kSortMid), max_bricks, panel_ptr, ncols_p, brick_cols,
+                                   brick_mask, brick_valptr, packed, src, col_seen, s);
   if (e == hipSuccess)
     e = sort_build<kBigThreads>(rowptr, colind, vals, M, l.big, l.mid, l.n_big,
-                                together ? l.n_big + l.n_mid : l.n_big, max_nnz, max_bricks, panel_ptr,
-                                brick_cols, brick_mask, brick_valptr, packed, src, col_seen, s);
+                                   together ? l.n_big + l.n_mid : l.n_big, max_nnz, max_bricks, panel_ptr, ncols_p,
+                                   brick_cols, brick_mask, brick_valptr, packed, src, col_seen, s);
   return e;
-}
-
-// bitmap words (a power of two, at least 64) for a widest panel span of `span` columns, or 0 if
-// that does not fit the LDS bitmap, or a workgroup a panel does not fit a launch
-uint32_t panel_bitmap_words(uint32_t span, int64_t P) {
-  if (P * kPanelThreads >= kMaxLaunchThreads) return 0;
-  uint32_t words = 64;
-  while ((uint64_t)words * 32 < span && words < kPanelMaxWords) words *= 2;
-  return (uint64_t)words * 32 >= span ? words : 0;
 }
 
 bool panel_build_fits(uint32_t words_cap, uint32_t nb_cap) {

@@ -75,12 +75,28 @@ struct MergeItem {          // one split panel
 };
 
 // ---- plan (a1..a5) -------------------------------------------------------
+constexpr int64_t kMaxLaunchThreads = int64_t(1) << 32;   // a launch has fewer than this
+constexpr int kPanelThreads = 64;                         // a workgroup a panel in the kernels with a bitmap
+constexpr uint32_t kPanelMaxWords = 32768;                // 1 Mi columns of span
+constexpr int64_t kBandWords = 2;   // bitmap words x panels an entry, up to which bitmaps go before sorting
+
+// bitmap words (a power of two, at least 64) for a widest panel span of `span` columns, or 0 if
+// that does not fit the LDS bitmap, or a workgroup a panel does not fit a launch
+__host__ __device__ inline uint32_t panel_bitmap_words(uint32_t span, int64_t P) {
+  if (P * kPanelThreads >= kMaxLaunchThreads) return 0;
+  uint32_t words = 64;
+  while ((uint64_t)words * 32 < span && words < kPanelMaxWords) words *= 2;
+  return (uint64_t)words * 32 >= span ? words : 0;
+}
+
 // checks rowptr, copies it, panel_nnzptr, ctl->err / span / max_nnz / counted; where ctl->counted, also what
-// launch_panel_census and launch_panel_scan do.  `pinned` (or null) gets what ctl does, then `flag` 1.
+// launch_panel_census and launch_panel_scan do, else the lists of launch_panel_sort_census.  `pinned` (or null)
+// gets what ctl does, then `flag` 1.
 hipError_t launch_rows_census(const int32_t* rowptr, const int32_t* colind, int64_t M, int64_t K,
                               int64_t P, int64_t nnz, int32_t* rowptr_copy, uint32_t* panel_nnzptr,
                               uint32_t* ncols_p, uint32_t* panel_ptr, uint32_t* tmp, PlanControl* ctl,
-                              PlanControl* pinned, uint32_t* flag, hipStream_t s);
+                              PlanControl* pinned, uint32_t* flag, uint32_t* mid_list, uint32_t* big_list,
+                              hipStream_t s);
 // ncols_p -> panel_ptr[P+1] (bricks, scanned), ctl->nb, ctl->n_active, ctl->max_cols
 size_t panel_scan_tmp_elems();
 hipError_t launch_panel_scan(const uint32_t* ncols_p, int64_t P, uint32_t* panel_ptr, uint32_t* tmp,
@@ -132,18 +148,17 @@ int64_t panel_big_list_elems(int64_t nnz);
 bool panel_sort_fits(int64_t P, int64_t nnz, uint32_t max_nnz);
 hipError_t launch_panel_sort_census(const int32_t* rowptr, const int32_t* colind, int64_t M,
                                     int64_t K, int64_t P, int64_t nnz, uint32_t max_nnz,
-                                    const uint32_t* panel_nnzptr, uint32_t* mid_list,
-                                    uint32_t* big_list, PlanControl* ctl, uint32_t* ncols_p,
+                                    const uint32_t* mid_list, const uint32_t* big_list,
+                                    PlanControl* ctl, uint32_t* ncols_p,
                                     uint32_t* order /* [nnz]; read back by the build from src */,
                                     hipStream_t s);
 hipError_t launch_panel_sort_build(const int32_t* rowptr, const int32_t* colind, const float* vals,
                                    int64_t M, int64_t P, const PanelLists& l, uint32_t max_nnz,
-                                   uint32_t max_bricks, const uint32_t* panel_ptr,
+                                   uint32_t max_bricks, const uint32_t* panel_ptr, const uint32_t* ncols_p,
                                    uint32_t* brick_cols, uint64_t* brick_mask,
                                    uint32_t* brick_valptr, float* packed, uint32_t* src,
                                    uint8_t* col_seen, hipStream_t s);
 // per-panel path by an LDS bitmap over the panel's column span
-uint32_t panel_bitmap_words(uint32_t span, int64_t P);   // 0: beyond this path
 hipError_t launch_panel_census(const int32_t* rowptr, const int32_t* colind, int64_t M, int64_t K,
                                int64_t P, uint32_t words_cap, uint32_t* err, uint32_t* ncols_p,
                                hipStream_t s);
