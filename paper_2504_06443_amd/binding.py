@@ -1,6 +1,8 @@
 """ctypes binding of libspmm_brick.so: same names as the C ABI in include/spmm.h.
 
 Argument marshalling only -- every step of the path runs in the HIP library.
+What a program calls per product or per matrix goes through the module _native
+where its arguments are plain tensors, everything else through ctypes.
 Device arrays are torch tensors (PyTorch is used for device memory and
 streams); results of host-side queries come back as plain Python / numpy.
 Importing this module raises if the library has not been built: there is no
@@ -23,6 +25,15 @@ if not os.path.exists(LIB_PATH):
         "(or __graft_entry__.build()); there is no CPU fallback")
 
 _lib = C.CDLL(LIB_PATH)
+
+# (a product of 4096 rows, N = 32, one behind another: 8.5 us through ctypes, 3.7 so, as when replayed from a graph)
+try:
+    from . import _native
+except ImportError as e:
+    raise ImportError(f"{_HERE}/_native.so not found or not loadable ({e}): build it with "
+                      "`python -m paper_2504_06443_amd.build` (or __graft_entry__.build())") from e
+_native.bind(*(C.cast(f, C.c_void_p).value for f in
+               (_lib.spmm_exec, _lib.spmm_exec_noalloc, _lib.spmm_plan_update_values, _lib.spmm_plan)))
 
 SPMM_OK, SPMM_EINVAL, SPMM_EFORMAT, SPMM_ENOMEM, SPMM_EHIP, SPMM_ELIMIT = 0, -1, -2, -3, -4, -5
 ROUTE_AUTO, ROUTE_MFMA, ROUTE_VALU, ROUTE_CLASS = 0, 1, 2, 3
@@ -136,12 +147,14 @@ class Plan:
 
     def __init__(self, handle, M, K, nnz):
         self._h = handle
+        self._addr = handle.value         # for _native; None once destroyed
         self.M, self.K, self.nnz = M, K, nnz
 
     def __del__(self):
         self.destroy()
 
     def destroy(self):
+        self._addr = None
         if getattr(self, "_h", None):
             if _lib is not None:          # (None while the interpreter shuts down)
                 _lib.spmm_plan_destroy(self._h)
@@ -150,6 +163,10 @@ class Plan:
 
 def spmm_plan(M: int, K: int, rowptr, colind, vals, stream=None) -> Plan:
     """CSR (device int32/int32/float32 tensors) -> plan holding the brick format."""
+    made = _native.plan(M, K, rowptr, colind, vals) if stream is None else None
+    if made is not None:
+        _check(made[0])
+        return Plan(_vp(made[1]), M, K, int(colind.numel()))
     nnz = int(colind.numel())
     if int(rowptr.numel()) != M + 1:
         raise ValueError("rowptr must have M + 1 entries")
@@ -165,6 +182,9 @@ def spmm_plan(M: int, K: int, rowptr, colind, vals, stream=None) -> Plan:
 
 def spmm_plan_update_values(plan: Plan, vals, stream=None):
     """New values (device float32 [nnz], CSR order) for the plan's unchanged pattern."""
+    status = _native.update(plan._addr, plan.nnz, vals) if stream is None else None
+    if status is not None:
+        return _check(status)
     if int(vals.numel()) != plan.nnz:
         raise ValueError("vals has the wrong length")
     _check(_lib.spmm_plan_update_values(plan._h, _dev(vals, torch.float32) if plan.nnz else None,
@@ -173,6 +193,12 @@ def spmm_plan_update_values(plan: Plan, vals, stream=None):
 
 def spmm_exec(plan: Plan, B, C_out=None, stream=None, _entry=None):
     """C = A . B on the current (or given) stream.  B: device float32 [K, N]."""
+    if stream is None and C_out is not None:
+        status = _native.product(_entry is not None, plan._addr, plan.M, plan.K, B, C_out)
+        if status is not None:
+            if status:
+                _check(status)
+            return C_out
     N = int(B.shape[1])
     if B.shape[0] != plan.K:
         raise ValueError("B has the wrong number of rows")

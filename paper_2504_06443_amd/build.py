@@ -1,12 +1,15 @@
-"""Compile libspmm_brick.so for gfx950 with hipcc (in-tree, next to the sources)."""
+"""Compile libspmm_brick.so for gfx950 with hipcc and the module _native that calls it from Python (in-tree,
+next to the sources)."""
 from __future__ import annotations
 
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libspmm_brick.so")
+NATIVE = os.path.join(HERE, "_native.so")
 SOURCES = ("api.hip", "plan_kernels.hip", "exec_kernels.hip", "exec_narrow.hip", "exec_wide.hip", "exec_bf16.hip",
            "tm32_kernels.hip", "calibrate.hip")
 
@@ -29,5 +32,23 @@ def build_library(verbose: bool = False) -> str:
     return LIB
 
 
+def build_native(verbose: bool = False) -> str:
+    """Host code only, against the headers of the installed torch."""
+    import torch
+    from torch.utils import cpp_extension
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *[f for p in cpp_extension.include_paths("cuda") for f in ("-isystem", p)],
+           "-isystem", sysconfig.get_paths()["include"],
+           "-o", NATIVE, os.path.join(CSRC, "native.cpp"),
+           "-L" + lib, "-Wl,-rpath," + lib, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    return NATIVE
+
+
 if __name__ == "__main__":
     print(build_library(verbose=True))
+    print(build_native(verbose=True))
