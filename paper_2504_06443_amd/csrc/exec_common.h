@@ -76,6 +76,18 @@ __device__ inline void store_any_nt(float* __restrict__ p, const float* in) {
   }
 }
 
+// One of the floats behind `base`, at `index` (per lane) behind byte `at` (uniform): a buffer load of stride four,
+// which scales the index itself.  With a global load the shift is a vector instruction a brick, which costs tiles of up
+// to 64 columns, whose loop has few others: 4096 panels of cells of fill 0.1, N = 64 30.2 -> 28.8 us, N = 48 23.4 -> 22.6,
+// 16,384 of blocks, N = 64 69.1 -> 67.7.  The wider tiles gain nothing, and a graph at N = 128 lost 8 %.
+typedef int int4_t __attribute__((ext_vector_type(4)));
+extern "C" __device__ float spmm_load_indexed(int4_t buffer, int index, int offset, int at, int aux) __asm(
+    "llvm.amdgcn.struct.buffer.load.f32");
+__device__ inline int4_t float_buffer(const float* base) {
+  const uint64_t a = (uint64_t)base;
+  return int4_t{(int)(uint32_t)a, (int)((uint32_t)(a >> 32) | 4u << 16), -1 /* indexes */, 0x00027000};
+}
+
 // Workgroups are handed to the 8 XCDs round-robin, and each XCD has its own L2.  This maps a
 // workgroup to a "virtual" index such that each XCD works through a contiguous range of work
 // items: neighbouring panels -- which share most of their B rows in banded matrices -- then
@@ -142,6 +154,16 @@ __device__ inline bool work_item(const ItemMap& m, const uint32_t* panel_ptr, ui
   const bool is_whole = e - b < split;
   *it = WorkItem{is_whole ? panel : kNoPanel, b, is_whole ? e : b, slot};
   return true;
+}
+
+constexpr int64_t kNarrowLargeB = int64_t(64) << 20;
+
+// Workgroups of one wavefront, where panels are split and B is large: a graph's panels differ so much that the slots
+// of a workgroup's first wavefronts stay empty until the last one ends.  Graphs of 326 k and 800 k rows, N = 64 60.2 -> 58.8
+// and 145 -> 140 us, N = 128 115.9 -> 111.2 and 276 -> 267, N = 256 221 -> 214; 100 k rows 36.7 / 37.6.  Matrices of even panels
+// keep four: 400 k rows of blocks, N = 128 181 / 184, cells 0 to 2 % either way.
+inline bool single_waves(const WorkSource& w, int64_t N, int64_t K) {
+  return w.any_split && K * N * 4 >= kNarrowLargeB;
 }
 
 inline bool ptr_aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }

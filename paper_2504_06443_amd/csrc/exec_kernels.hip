@@ -225,10 +225,9 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void k_spmm_mfma(
 // bricks, say) four steps of the next panel's rows would otherwise add 40 % to
 // the traffic from memory.
 constexpr int kFastChunk = 8;
-constexpr int64_t kNarrowLargeB = int64_t(64) << 20;
 
-template <int T, bool FULL>
-__global__ __launch_bounds__(64 * kWavesPerBlock) void k_spmm_mfma_fast(
+template <int T, bool FULL, int WPB>
+__global__ __launch_bounds__(64 * WPB) void k_spmm_mfma_fast(
     SPMM_ITEM_PARAMS, const uint32_t* __restrict__ panel_ptr, const uint32_t* __restrict__ brick_cols,
     const uint64_t* __restrict__ brick_mask, const uint32_t* __restrict__ brick_valptr,
     const float* __restrict__ vals,
@@ -246,7 +245,7 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void k_spmm_mfma_fast(
   // (one round trip less through the vector-memory path before the first brick)
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   WorkItem it;
-  if (!work_item<kWavesPerBlock>(SPMM_ITEM_MAP, panel_ptr, wave, &it))
+  if (!work_item<WPB>(SPMM_ITEM_MAP, panel_ptr, wave, &it))
     return;  // whole wavefront leaves together
   const uint32_t panel = it.panel;
   const uint32_t b_begin = it.brick_begin;
@@ -272,6 +271,7 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void k_spmm_mfma_fast(
   if (b_begin < b_end) {
     const uint32_t nbricks = b_end - b_begin;
     const char* Bbytes = reinterpret_cast<const char*>(B);
+    [[maybe_unused]] const int4_t vals_at = float_buffer(vals);
 
     struct Meta { uint64_t mask[CH]; uint32_t off[CH]; };
     auto load_meta = [&](uint32_t base) {   // uniform addresses: scalar loads
@@ -311,8 +311,9 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void k_spmm_mfma_fast(
       const uint32_t cnt = __builtin_amdgcn_mbcnt_hi(
           (uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
       // scalar base + 32-bit byte offset (the launcher checks that the values fit 4 GiB)
-      st_a[s] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(vals) +
-                                                (off * 4u + cnt * 4u));
+      if constexpr (T <= 4) st_a[s] = spmm_load_indexed(vals_at, (int)cnt, 0, (int)(off * 4u), 0);
+      else
+        st_a[s] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(vals) + (off * 4u + cnt * 4u));
       const char* brow = Bbytes + (ro + lane_off0);
       load_any<W0>(brow, &st_b[s][0]);
       // whole 128-column tiles: the second vector lies a constant distance behind the first
@@ -711,7 +712,7 @@ int occupancy_t() {
 template <int T>
 int occupancy_fast_t() {
   int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_spmm_mfma_fast<T, false>, 64 * kWavesPerBlock,
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_spmm_mfma_fast<T, false, kWavesPerBlock>, 64 * kWavesPerBlock,
                                                    0) != hipSuccess || nb < 1)
     nb = 1;
   return nb * kWavesPerBlock;
@@ -821,13 +822,17 @@ hipError_t launch_spmm_mfma(const BrickFormat& f, const WorkSource& w, const flo
     const int tile = mfma_run_tile(w, N, K, nnz);
     if (N >= 4 && tile <= 32 && (N > 32 || !w.any_split || N <= 8 || K * N * 4 >= kNarrowLargeB))
       return launch_spmm_mfma_narrow(f, w, tile, B, C, partial, M, N, K, s);
-    const unsigned gx = item_blocks<kWavesPerBlock>(w);
-    const dim3 grid(gx, (unsigned)((N + tile - 1) / tile)), block(64 * kWavesPerBlock);
+    const unsigned gy = (unsigned)((N + tile - 1) / tile);
     const uint32_t k_last = (uint32_t)(K - 1);
-#define SPMM_LAUNCH_FAST(TT, FF)                                                                \
-  hipLaunchKernelGGL((k_spmm_mfma_fast<TT, FF>), grid, block, 0, s,                             \
-                     SPMM_ITEM_ARGS(kWavesPerBlock, w), f.panel_ptr, f.brick_cols,              \
+    const bool single = single_waves(w, N, K);
+#define SPMM_LAUNCH_WAVES(TT, FF, W)                                                            \
+  hipLaunchKernelGGL((k_spmm_mfma_fast<TT, FF, W>), dim3(item_blocks<W>(w), gy), dim3(64 * W), 0, s, \
+                     SPMM_ITEM_ARGS(W, w), f.panel_ptr, f.brick_cols,                           \
                      f.brick_mask, f.brick_valptr, f.vals, B, C, partial, M, N, k_last)
+#define SPMM_LAUNCH_FAST(TT, FF)                                                                \
+  do {                                                                                          \
+    if (single) SPMM_LAUNCH_WAVES(TT, FF, 1); else SPMM_LAUNCH_WAVES(TT, FF, kWavesPerBlock);   \
+  } while (0)
     switch (tile / 16) {
       case 1: SPMM_LAUNCH_FAST(1, false); break;
       case 2: SPMM_LAUNCH_FAST(2, false); break;
@@ -840,6 +845,7 @@ hipError_t launch_spmm_mfma(const BrickFormat& f, const WorkSource& w, const flo
         if (N % 128 == 0) SPMM_LAUNCH_FAST(8, true); else SPMM_LAUNCH_FAST(8, false);
         break;
     }
+#undef SPMM_LAUNCH_WAVES
 #undef SPMM_LAUNCH_FAST
     return hipGetLastError();
   }

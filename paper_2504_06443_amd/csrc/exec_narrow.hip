@@ -41,8 +41,8 @@ __device__ inline void swap_fours(float& a, float& c) {
   c = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(y, x, 0x104 /* row_shl:4 */, 0xF, 0x5, false));
 }
 
-template <int T>
-__global__ __launch_bounds__(64 * kWavesPerBlock, T == 2 ? 4 : 1) void k_spmm_mfma_narrow(
+template <int T, int WPB>
+__global__ __launch_bounds__(64 * WPB, T == 2 ? 4 : 1) void k_spmm_mfma_narrow(
     SPMM_ITEM_PARAMS, const uint32_t* __restrict__ panel_ptr, const uint32_t* __restrict__ brick_cols,
     const uint64_t* __restrict__ brick_mask, const uint32_t* __restrict__ brick_valptr,
     const float* __restrict__ vals, const float* __restrict__ B, float* __restrict__ C,
@@ -53,7 +53,7 @@ __global__ __launch_bounds__(64 * kWavesPerBlock, T == 2 ? 4 : 1) void k_spmm_mf
   const int lane = threadIdx.x & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   WorkItem it;
-  if (!work_item<kWavesPerBlock>(SPMM_ITEM_MAP, panel_ptr, wave, &it))
+  if (!work_item<WPB>(SPMM_ITEM_MAP, panel_ptr, wave, &it))
     return;  // whole wavefront leaves together
   const uint32_t panel = it.panel, b_begin = it.brick_begin, b_end = it.brick_end, slot = it.slot;
 
@@ -74,6 +74,7 @@ __global__ __launch_bounds__(64 * kWavesPerBlock, T == 2 ? 4 : 1) void k_spmm_mf
   if (b_begin < b_end) {
     const uint32_t nbricks = b_end - b_begin;
     const char* Bbytes = reinterpret_cast<const char*>(B);
+    const int4_t vals_at = float_buffer(vals);
     struct Meta { uint64_t mask[CH]; uint32_t off[CH]; };
     auto load_meta = [&](uint32_t base) {
       const uint64_t* __restrict__ mp = brick_mask + base;
@@ -97,8 +98,7 @@ __global__ __launch_bounds__(64 * kWavesPerBlock, T == 2 ? 4 : 1) void k_spmm_mf
       st_mask[i] = mask;
       const uint32_t cnt = __builtin_amdgcn_mbcnt_hi(
           (uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-      st_a[i] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(vals) +
-                                                (off * 4u + cnt * 4u));
+      st_a[i] = spmm_load_indexed(vals_at, (int)cnt, 0, (int)(off * 4u), 0);
     };
     auto rows_of = [&](uint32_t ro, int q) {
       return (uint32_t)__builtin_amdgcn_ds_bpermute(perm_base + 16u * G * q, ro);
@@ -234,13 +234,17 @@ __global__ __launch_bounds__(64 * kWavesPerBlock, T == 2 ? 4 : 1) void k_spmm_mf
 
 hipError_t launch_spmm_mfma_narrow(const BrickFormat& f, const WorkSource& w, int tile, const float* B, float* C,
                                    float* partial, int64_t M, int64_t N, int64_t K, hipStream_t s) {
-  const dim3 grid(item_blocks<kWavesPerBlock>(w), (unsigned)((N + tile - 1) / tile)), block(64 * kWavesPerBlock);
+  const unsigned gy = (unsigned)((N + tile - 1) / tile);
   const uint32_t k_last = (uint32_t)(K - 1);
-#define SPMM_LAUNCH_NARROW(TT)                                                                  \
-  hipLaunchKernelGGL(k_spmm_mfma_narrow<TT>, grid, block, 0, s,                                 \
-                     SPMM_ITEM_ARGS(kWavesPerBlock, w), f.panel_ptr, f.brick_cols,              \
+#define SPMM_LAUNCH_NARROW(TT, W)                                                               \
+  hipLaunchKernelGGL((k_spmm_mfma_narrow<TT, W>), dim3(item_blocks<W>(w), gy), dim3(64 * W), 0, s, \
+                     SPMM_ITEM_ARGS(W, w), f.panel_ptr, f.brick_cols,                           \
                      f.brick_mask, f.brick_valptr, f.vals, B, C, partial, M, N, k_last)
-  if (tile == 16) SPMM_LAUNCH_NARROW(1); else SPMM_LAUNCH_NARROW(2);
+  if (single_waves(w, N, K)) {
+    if (tile == 16) SPMM_LAUNCH_NARROW(1, 1); else SPMM_LAUNCH_NARROW(2, 1);
+  } else {
+    if (tile == 16) SPMM_LAUNCH_NARROW(1, kWavesPerBlock); else SPMM_LAUNCH_NARROW(2, kWavesPerBlock);
+  }
 #undef SPMM_LAUNCH_NARROW
   return hipGetLastError();
 }

@@ -1,0 +1,52 @@
+"""Values read by index from a uniform byte offset (tiles of up to 64 columns), and workgroups of one wavefront."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2504_06443_amd import workloads as W
+from test_gpu_narrow import kernels_of
+from test_gpu_parity import check_c, gpu, make_plan  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def test_values_beyond_two_gib(gpu):  # noqa: F811
+    """671 M stored entries: byte offsets of values with the top bit of 32 set."""
+    import torch
+    M, K = 20480, 1 << 15
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    rowptr = torch.arange(M + 1, dtype=torch.int64, device="cuda").mul_(K).to(torch.int32)
+    colind = torch.arange(K, dtype=torch.int32, device="cuda").repeat(M)
+    vals = torch.randint(-1, 2, (M, K), generator=gen, device="cuda", dtype=torch.int8).to(torch.float32)
+    plan = gpu.spmm_plan(M, K, rowptr, colind, vals.flatten())
+    del rowptr, colind
+    print(f"planned {M} x {K}, every entry stored", flush=True)
+    for N in (16, 32, 48, 64):
+        B = torch.randint(-3, 4, (K, N), generator=gen, device="cuda").to(torch.float32)
+        got = gpu.spmm_exec(plan, B)
+        print(f"N={N}", flush=True)
+        assert torch.equal(got, vals @ B)                     # whole numbers below 2^24
+
+
+@pytest.mark.parametrize("N", [17, 32, 64, 100, 128, 256])
+@pytest.mark.parametrize("large", [False, True])
+def test_split_panels_over_a_large_b(gpu, N, large):  # noqa: F811
+    """Split panels over a B of 64 MiB and more run in workgroups of one wavefront; a number of items that is no
+    multiple of four or of the XCDs, and parts behind whole panels."""
+    import torch
+    A = W.power_law(M=16 * 1003 - 5, target_nnz=None, cap=1500, alpha=1.7, seed=N)
+    K = -(-(64 << 20) // (4 * N)) if large else A.K
+    col = (A.colind.astype(np.int64) * (K // A.K) + K % A.K).astype(np.int32)   # the last column is reached
+    plan = gpu.spmm_plan(A.M, K, torch.from_numpy(A.rowptr).cuda(), torch.from_numpy(col).cuda(),
+                         torch.from_numpy(A.vals).cuda())
+    B = W.dense_b(A.K, N, 7)
+    Cref, S = oracle.spmm_f64(A.rowptr, A.colind, A.vals, B)
+    Bd = torch.zeros((K, N), device="cuda")
+    Bd[torch.arange(A.K, device="cuda") * (K // A.K) + K % A.K] = torch.from_numpy(B).cuda()
+    names = kernels_of(lambda: gpu.spmm_exec(plan, Bd))
+    assert "k_merge" in names and (", 1>" in names) == large, names
+    for product in (gpu.spmm_exec, gpu.spmm_exec_noalloc):
+        Cd = torch.full((A.M, N), float("nan"), device="cuda")
+        product(plan, Bd, Cd)
+        torch.cuda.synchronize()
+        check_c(Cd.cpu().numpy(), Cref, S)
