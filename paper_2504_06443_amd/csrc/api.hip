@@ -158,7 +158,7 @@ struct spmm_plan {
   uint64_t* brick_mask = nullptr;
   uint32_t* brick_valptr = nullptr;
   float* vals = nullptr;          // nnz + 64
-  uint32_t* src = nullptr;        // CSR entry of each packed value (value-only updates)
+  ValueSources src{};             // CSR entry of each packed value (value-only updates)
   // what the vector-ALU CSR kernels read (device): rowptr is kept from the start, the rest is made
   // when a route first sends panels there, and every update keeps it up to date from then on
   // (csr_on), whatever the route: a product captured under that route may be replayed at any time
@@ -827,7 +827,7 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
   pl->panel_ptr = fixed.take<uint32_t>(P + 1);
   pl->panel_nnzptr = fixed.take<uint32_t>(P + 1);
   pl->rowptr = fixed.take<int32_t>(M + 1);
-  pl->src = fixed.take<uint32_t>(nnz);
+  pl->src.entries = fixed.take<uint32_t>(nnz);   // (as steps, once it is known that they fit, or the sorted path's work)
 
   // ---- rowptr validation, the widest panel span and, where the spans are short, the census (device),
   // before anything trusts rowptr
@@ -877,7 +877,7 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
     HIP_TRY(launch_panel_census(rowptr, colind, M, K, P, words_cap, &ctl->err, ncols_p, s));
   } else if (path == kPathSort) {
     HIP_TRY(launch_panel_sort_census(rowptr, colind, M, K, P, nnz, h_ctl.max_nnz,
-                                     mid_list, big_list, ctl, ncols_p, pl->src, s));
+                                     mid_list, big_list, ctl, ncols_p, pl->src.entries, s));
   } else {
     // ---- search-based path for every other matrix.  Its a1
     // kernels only compare columns, so they may run before the host has seen the verdict of
@@ -939,10 +939,12 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
     HIP_TRY(launch_panel_sort_build(rowptr, colind, vals, M, P,
                                     PanelLists{mid_list, big_list, h_ctl.n_mid, h_ctl.n_big},
                                     h_ctl.max_nnz, std::max<uint32_t>(h_maxnb, 1), pl->panel_ptr, ncols_p, pl->brick_cols,
-                                    pl->brick_mask, pl->brick_valptr, pl->vals, pl->src, col_seen,
+                                    pl->brick_mask, pl->brick_valptr, pl->vals, pl->src.entries, col_seen,
                                     s));
   } else if (path == kPathBitmap) {
     // ---- a2 (placing), a3, a4, one wavefront per panel
+    if (h_ctl.max_nnz <= kStepEntries)
+      pl->src = ValueSources{nullptr, reinterpret_cast<int16_t*>(pl->src.entries)};
     HIP_TRY(launch_panel_build(rowptr, colind, vals, M, K, P, words_cap,
                                std::max<uint32_t>(h_maxnb, 1), h_ctl.max_nnz, pl->panel_ptr,
                                pl->brick_cols, pl->brick_mask, pl->brick_valptr, pl->vals,
@@ -967,7 +969,7 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
                                 pl->brick_mask, ent_brick, ent_bit, col_seen, s));
     HIP_TRY(launch_scan_popc64(pl->brick_mask, pl->nb, pl->brick_valptr, scan_tmp, s));
     HIP_TRY(launch_pack_values(vals, ent_brick, ent_bit, pl->brick_mask, pl->brick_valptr, nnz,
-                               pl->vals, pl->src, s));
+                               pl->vals, pl->src.entries, s));
   }
   // ---- the spare entries behind the brick arrays, a5: per-panel classes and the synergy counts, and
   // host copies for the work-list builder and the model

@@ -28,7 +28,7 @@ namespace {
 
 constexpr int kThreads = 256;
 
-inline unsigned grid_for(int64_t n, int threads = kThreads) {
+inline unsigned grid_for(int64_t n, int64_t threads = kThreads) {
   int64_t g = (n + threads - 1) / threads;
   return (unsigned)(g > 0 ? g : 1);
 }
@@ -195,30 +195,56 @@ __global__ void k_pack_values(const float* __restrict__ vals,
   src[pos] = (uint32_t)e;
 }
 
-// New values for an unchanged pattern: packed position p takes the CSR entry src[p] recorded when
-// the plan was built.  Bound by memory: 4 bytes each of values, positions and packed values per
-// entry.  Gathering by packed position keeps the stores whole (the entries of a panel are 2 KB or
-// so, and their reads hit a cache); four positions per thread.  CSR: the plan also keeps the values
-// in CSR order, for the vector-ALU kernels.  7.86 M entries: scattering by entry and always writing
-// the CSR copy 27.3 us; this way 16.3, 94 MB at 5.8 TB/s.
-template <bool CSR>
+// entries(p): the CSR entry of packed value p; of four consecutive ones from a multiple of four
+struct EntrySource {
+  const uint32_t* p;
+  __device__ uint32_t operator()(int64_t i) const { return p[i]; }
+  __device__ uint4 four(int64_t i) const { return *reinterpret_cast<const uint4*>(p + i); }
+};
+struct StepSource {
+  const int16_t* p;
+  __device__ uint32_t operator()(int64_t i) const { return (uint32_t)(i + p[i]); }
+  __device__ uint4 four(int64_t i) const {
+    const short4 d = *reinterpret_cast<const short4*>(p + i);
+    return uint4{(uint32_t)(i + d.x), (uint32_t)(i + 1 + d.y), (uint32_t)(i + 2 + d.z), (uint32_t)(i + 3 + d.w)};
+  }
+};
+
+// New values for an unchanged pattern: packed position p takes the CSR entry that was recorded when
+// the plan was built.  Bound by memory: 4 bytes each of values and packed values per entry, and 4 or 2 of
+// where it comes from.  Gathering by packed position keeps the stores whole (the entries of a panel are 2 KB or
+// so, and their reads hit a cache); two times four positions per thread.  CSR: the plan also keeps the values
+// in CSR order, for the vector-ALU kernels.  7.86 M entries, one update behind another: from the entries, four positions a
+// thread 17.3 us, 94 MB; from steps 14.3, 79 MB; and eight positions a thread 13.5, as sixteen.
+constexpr int kUpdateFours = 2;
+constexpr int64_t kUpdateBlock = (int64_t)kThreads * 4 * kUpdateFours;   // positions a workgroup
+
+template <typename Source, bool CSR>
 __global__ __launch_bounds__(kThreads) void k_update_values(
-    const float* __restrict__ vals, const uint32_t* __restrict__ src, int64_t nnz,
+    const float* __restrict__ vals, Source src, int64_t nnz,
     float* __restrict__ packed, float* __restrict__ csr_vals) {
-  const int64_t p = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * 4;
-  if (p + 4 <= nnz) {
-    const uint4 e = *reinterpret_cast<const uint4*>(src + p);
-    float4 v;
-    v.x = vals[e.x]; v.y = vals[e.y]; v.z = vals[e.z]; v.w = vals[e.w];
-    *reinterpret_cast<float4*>(packed + p) = v;
+  const int64_t first = blockIdx.x * kUpdateBlock + 4 * threadIdx.x;
+  if ((blockIdx.x + 1) * kUpdateBlock <= nnz) {
+    uint4 e[kUpdateFours];
+    float4 v[kUpdateFours];
+#pragma unroll
+    for (int q = 0; q < kUpdateFours; ++q) e[q] = src.four(first + q * 4 * kThreads);
+#pragma unroll
+    for (int q = 0; q < kUpdateFours; ++q) {
+      v[q].x = vals[e[q].x]; v[q].y = vals[e[q].y]; v[q].z = vals[e[q].z]; v[q].w = vals[e[q].w];
+    }
+#pragma unroll
+    for (int q = 0; q < kUpdateFours; ++q) *reinterpret_cast<float4*>(packed + first + q * 4 * kThreads) = v[q];
     if constexpr (CSR) {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) csr_vals[p + k] = vals[p + k];
+      for (int q = 0; q < kUpdateFours; ++q)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) csr_vals[first + q * 4 * kThreads + k] = vals[first + q * 4 * kThreads + k];
     }
   } else {
-    for (int64_t q = p; q < nnz; ++q) {
-      packed[q] = vals[src[q]];
-      if constexpr (CSR) csr_vals[q] = vals[q];
+    for (int64_t p = blockIdx.x * kUpdateBlock + threadIdx.x; p < nnz; p += kThreads) {
+      packed[p] = vals[src(p)];
+      if constexpr (CSR) csr_vals[p] = vals[p];
     }
   }
 }
@@ -228,10 +254,11 @@ __global__ __launch_bounds__(kThreads) void k_update_values(
 // 2^30 of them, a launch fewer than kMaxLaunchThreads threads.
 constexpr int kRestoreBlocks = 1 << 16;
 
+template <typename Source>
 __global__ __launch_bounds__(kThreads) void k_restore_csr(
     const uint32_t* __restrict__ brick_cols, const uint64_t* __restrict__ brick_mask,
     const uint32_t* __restrict__ brick_valptr, const float* __restrict__ packed,
-    const uint32_t* __restrict__ src, int64_t nb, int32_t* __restrict__ colind,
+    Source src, int64_t nb, int32_t* __restrict__ colind,
     float* __restrict__ csr_vals) {
   const int lane = threadIdx.x & 63;
   const int64_t stride = (int64_t)gridDim.x * (kThreads / 64);
@@ -239,7 +266,7 @@ __global__ __launch_bounds__(kThreads) void k_restore_csr(
     const uint64_t mask = brick_mask[b];
     if (!((mask >> lane) & 1ull)) continue;
     const uint32_t pos = brick_valptr[b] + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
-    const uint32_t e = src[pos];
+    const uint32_t e = src(pos);
     colind[e] = (int32_t)brick_cols[b * kBrickK + (lane & (kBrickK - 1))];
     csr_vals[e] = packed[pos];
   }
@@ -1414,14 +1441,14 @@ __global__ __launch_bounds__(T) void k_panel_sort_build(
 // steps without the staging: they read the columns again and scatter their values.
 // 7.86 M entries in 16,384 panels: 71 us unstaged and walking groups of bitmap words, 49 us staged, 46.6 with
 // four neighbouring columns a lane (one LDS atomic a bitmap word) and an entry's row from bit counts (18.5 M -> 14.3 M
-// vector instructions); 41 M entries in 57,696 panels 434 -> 250 us staged (0.76 GB).
+// vector instructions), 44.3 with 16-bit steps for sources; 41 M entries in 57,696 panels 434 -> 250 us staged (0.76 GB).
 template <int G>
 __global__ __launch_bounds__(kPanelThreads) void k_panel_build(
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind,
     const float* __restrict__ vals, int64_t M, int64_t K, uint32_t words_cap, uint32_t nb_cap,
     uint32_t stage_cap, const uint32_t* __restrict__ panel_ptr, uint32_t* __restrict__ brick_cols,
     uint64_t* __restrict__ brick_mask, uint32_t* __restrict__ brick_valptr,
-    float* __restrict__ packed, uint32_t* __restrict__ src, uint8_t* __restrict__ col_seen) {
+    float* __restrict__ packed, ValueSources src, uint8_t* __restrict__ col_seen) {
   extern __shared__ unsigned long long lds64[];
   __shared__ int32_t rp[kPanel + 1];
   // staged panels: bit i of `starts` is set where a row with entries begins at entry i + 1, and rows[k] is the
@@ -1588,6 +1615,10 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_build(
     carry += total;
   }
   __syncthreads();
+  auto put_source = [&](uint32_t to, uint32_t from) {   // inside the panel
+    if (src.steps) src.steps[x.e0 + to] = (int16_t)((int32_t)from - (int32_t)to);
+    else src.entries[x.e0 + to] = (uint32_t)x.e0 + from;
+  };
   auto place_of = [&](uint32_t k) {   // inside the panel's values
     return vptr[brick_of(k)] + (uint32_t)__popcll(pat[brick_of(k)] & ((1ull << bit_of(k)) - 1ull));
   };
@@ -1610,7 +1641,7 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_build(
         const uint32_t i = i0 + u * kPanelThreads;
         if (i < n) {
           packed[x.e0 + i] = v[u];
-          src[x.e0 + i] = (uint32_t)x.e0 + from[u];
+          put_source(i, from[u]);
         }
       }
     }
@@ -1619,7 +1650,7 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_build(
       const uint32_t pos = place_of(unstaged_key(i));
       if (pos < n) {
         packed[x.e0 + pos] = vals[x.e0 + i];
-        src[x.e0 + pos] = (uint32_t)x.e0 + i;
+        put_source(pos, i);
       }
     }
   }
@@ -1756,24 +1787,38 @@ hipError_t launch_pack_values(const float* vals, const uint32_t* ent_brick, cons
   return hipGetLastError();
 }
 
-hipError_t launch_update_values(const float* vals, const uint32_t* src, int64_t nnz, float* packed,
-                                float* csr_vals, hipStream_t s) {
-  if (nnz == 0) return hipSuccess;
-  const dim3 grid(grid_for((nnz + 3) / 4)), block(kThreads);
+template <typename Source>
+static hipError_t update_values(const float* vals, Source src, int64_t nnz, float* packed, float* csr_vals,
+                                hipStream_t s) {
+  const dim3 grid(grid_for(nnz, kUpdateBlock)), block(kThreads);
   if (csr_vals)
-    hipLaunchKernelGGL(k_update_values<true>, grid, block, 0, s, vals, src, nnz, packed, csr_vals);
+    hipLaunchKernelGGL((k_update_values<Source, true>), grid, block, 0, s, vals, src, nnz, packed, csr_vals);
   else
-    hipLaunchKernelGGL(k_update_values<false>, grid, block, 0, s, vals, src, nnz, packed, csr_vals);
+    hipLaunchKernelGGL((k_update_values<Source, false>), grid, block, 0, s, vals, src, nnz, packed, csr_vals);
   return hipGetLastError();
 }
 
-hipError_t launch_restore_csr(const BrickFormat& f, const uint32_t* src, int64_t nb, int32_t* colind,
-                              float* csr_vals, hipStream_t s) {
-  if (nb == 0) return hipSuccess;
+hipError_t launch_update_values(const float* vals, const ValueSources& src, int64_t nnz, float* packed,
+                                float* csr_vals, hipStream_t s) {
+  if (nnz == 0) return hipSuccess;
+  return src.steps ? update_values(vals, StepSource{src.steps}, nnz, packed, csr_vals, s)
+                   : update_values(vals, EntrySource{src.entries}, nnz, packed, csr_vals, s);
+}
+
+template <typename Source>
+static hipError_t restore_csr(const BrickFormat& f, Source src, int64_t nb, int32_t* colind, float* csr_vals,
+                              hipStream_t s) {
   const unsigned g = (unsigned)std::min<int64_t>(grid_for(nb, kThreads / 64), kRestoreBlocks);
-  hipLaunchKernelGGL(k_restore_csr, dim3(g), dim3(kThreads), 0, s, f.brick_cols, f.brick_mask,
+  hipLaunchKernelGGL(k_restore_csr<Source>, dim3(g), dim3(kThreads), 0, s, f.brick_cols, f.brick_mask,
                      f.brick_valptr, f.vals, src, nb, colind, csr_vals);
   return hipGetLastError();
+}
+
+hipError_t launch_restore_csr(const BrickFormat& f, const ValueSources& src, int64_t nb, int32_t* colind,
+                              float* csr_vals, hipStream_t s) {
+  if (nb == 0) return hipSuccess;
+  return src.steps ? restore_csr(f, StepSource{src.steps}, nb, colind, csr_vals, s)
+                   : restore_csr(f, EntrySource{src.entries}, nb, colind, csr_vals, s);
 }
 
 hipError_t launch_publish(const PlanControl* ctl, PlanControl* pinned, uint32_t* flag, hipStream_t s) {
@@ -1937,7 +1982,7 @@ hipError_t launch_panel_build(const int32_t* rowptr, const int32_t* colind, cons
                               int64_t M, int64_t K, int64_t P, uint32_t words_cap, uint32_t nb_cap,
                               uint32_t max_nnz, const uint32_t* panel_ptr, uint32_t* brick_cols,
                               uint64_t* brick_mask, uint32_t* brick_valptr, float* packed,
-                              uint32_t* src, uint8_t* col_seen, hipStream_t s) {
+                              const ValueSources& src, uint8_t* col_seen, hipStream_t s) {
   if (P == 0) return hipSuccess;
   const PanelBuildLayout layout = panel_build_layout(words_cap, nb_cap, max_nnz);
   if (layout.bytes == 0) return hipErrorInvalidValue;   // (the caller asked panel_build_fits)

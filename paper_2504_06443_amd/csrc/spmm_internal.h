@@ -123,8 +123,15 @@ hipError_t launch_scatter_bits(const int32_t* colind, const uint32_t* ent_row, c
 hipError_t launch_pack_values(const float* vals, const uint32_t* ent_brick, const uint8_t* ent_bit,
                               const uint64_t* brick_mask, const uint32_t* brick_valptr,
                               int64_t nnz, float* packed, uint32_t* src, hipStream_t s);
+// The CSR entry of each packed value: the entries themselves, or how far each lies from the value's own position, which
+// 16 bits hold where no panel has more than kStepEntries entries (a panel's values are its entries in another order).
+constexpr uint32_t kStepEntries = 1u << 15;
+struct ValueSources {
+  uint32_t* entries;   // one of the two
+  int16_t* steps;
+};
 // csr_vals: null where the plan keeps no values in CSR order
-hipError_t launch_update_values(const float* vals, const uint32_t* src, int64_t nnz, float* packed,
+hipError_t launch_update_values(const float* vals, const ValueSources& src, int64_t nnz, float* packed,
                                 float* csr_vals, hipStream_t s);
 // `pinned` gets what ctl holds, then `flag` 1
 hipError_t launch_publish(const PlanControl* ctl, PlanControl* pinned, uint32_t* flag, hipStream_t s);
@@ -167,7 +174,7 @@ hipError_t launch_panel_build(const int32_t* rowptr, const int32_t* colind, cons
                               int64_t M, int64_t K, int64_t P, uint32_t words_cap, uint32_t nb_cap,
                               uint32_t max_nnz, const uint32_t* panel_ptr, uint32_t* brick_cols,
                               uint64_t* brick_mask, uint32_t* brick_valptr, float* packed,
-                              uint32_t* src, uint8_t* col_seen, hipStream_t s);
+                              const ValueSources& src, uint8_t* col_seen, hipStream_t s);
 
 // exclusive scans; out has n+1 entries (out[n] = total); tmp holds block sums
 size_t scan_tmp_elems(int64_t n);
@@ -193,8 +200,8 @@ struct BrickFormat {
   const float* vals;             // nnz + 64
 };
 
-// colind and values in CSR order from the brick format; src[p] = CSR entry of packed value p
-hipError_t launch_restore_csr(const BrickFormat& f, const uint32_t* src, int64_t nb, int32_t* colind,
+// colind and values in CSR order from the brick format
+hipError_t launch_restore_csr(const BrickFormat& f, const ValueSources& src, int64_t nb, int32_t* colind,
                               float* csr_vals, hipStream_t s);
 
 int mfma_tile_for(int64_t N);   // power-of-two tiles: 16, 32, 64 or 128 columns per wavefront
