@@ -771,6 +771,7 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
     return e;
   };
   uint32_t *scan_tmp, *ncols_p, *mid_list, *big_list;
+  size_t clear_b = 0;
   enum { kPathSearch, kPathBitmap, kPathSort } path = kPathSearch;
   uint32_t h_maxnb = 0, words_cap = 0;
   bool sort_fits = false, counted = false;
@@ -831,18 +832,18 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
 
   // ---- rowptr validation, the widest panel span and, where the spans are short, the census (device),
   // before anything trusts rowptr
-  HIP_TRY(hipMemsetAsync(work.base, 0, (size_t)(reinterpret_cast<char*>(scan_tmp) - work.base), s));
+  clear_b = (size_t)(reinterpret_cast<char*>(scan_tmp) - work.base);   // ctl and col_seen
   if (stage.get()) {
     PlanControl* pinned = reinterpret_cast<PlanControl*>(stage.get());
     uint32_t* flag = reinterpret_cast<uint32_t*>(stage.get() + Arena::pad(sizeof(PlanControl)));
     __atomic_store_n(flag, 0u, __ATOMIC_RELAXED);
     HIP_TRY(launch_rows_census(rowptr, colind, M, K, P, nnz, pl->rowptr, pl->panel_nnzptr, ncols_p,
-                               pl->panel_ptr, scan_tmp, ctl, pinned, flag, mid_list, big_list, s));
+                               pl->panel_ptr, scan_tmp, ctl, pinned, flag, mid_list, big_list, work.base, clear_b, s));
     HIP_TRY(wait_for_flag(flag, s));
     memcpy(&h_ctl, pinned, sizeof(PlanControl));
   } else {
     HIP_TRY(launch_rows_census(rowptr, colind, M, K, P, nnz, pl->rowptr, pl->panel_nnzptr, ncols_p,
-                               pl->panel_ptr, scan_tmp, ctl, nullptr, nullptr, mid_list, big_list, s));
+                               pl->panel_ptr, scan_tmp, ctl, nullptr, nullptr, mid_list, big_list, work.base, clear_b, s));
     HIP_TRY(read_ctl());
   }
   if (h_ctl.err & (kErrRowptrEnds | kErrRowptrOrder)) {

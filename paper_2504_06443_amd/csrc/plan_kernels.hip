@@ -778,12 +778,15 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_census(
 // counter and the scan that follows needs no pass of its own over the counts.  Entries are read four a lane,
 // neighbours, whose columns mostly share a bitmap word and then cost one LDS atomic; only an entry that does
 // not lie above the one before it looks up whether it begins a row.
-// Bound by the latency of three dependent loads a panel.  262,144 rows, 7.86 M entries: a pass over the rows,
-// a wait for their span and the census took 12 + 15 + 20 us, this takes 18.7; the rows of a graph of 20,360
-// panels 12.2 -> 9.6.
+// Bound by the latency of dependent loads, so the next panel's rows and the first rounds of entries are on their way
+// early; it also clears the control block and the flags of columns, which takes a launch before it and its gap
+// (2 us; 4096 rows: plan, product and destruction 54.6 -> 52.5 us).  262,144 rows, 7.86 M entries: a pass over the rows,
+// a wait for their span and the census took 12 + 15 + 20 us, one pass 18.7, three workgroups a CU so 18.4, four 17.1; the
+// rows of a graph of 20,360 panels 12.2 -> 9.6.
 constexpr int kFirstThreads = 512, kFirstWaves = kFirstThreads / 64;
-constexpr int kFirstBlocks = 768;                   // three a CU
+constexpr int kFirstBlocks = 1024;                  // four a CU
 constexpr uint32_t kFirstWords = 512;               // bitmap words a wavefront: 16,384 columns
+constexpr size_t kClearEach = 8;                    // vectors a thread clears at most
 
 constexpr uint32_t kSortSmall = 512, kSortMid = 2048, kSortBig = 8192;   // entries; see the path that sorts
 
@@ -799,11 +802,11 @@ __device__ inline void wave_lds_fence() {   // LDS writes of the wavefront's lan
   __builtin_amdgcn_wave_barrier();
 }
 
-__global__ __launch_bounds__(kFirstThreads, 6) void k_rows_census(
+__global__ __launch_bounds__(kFirstThreads, 8) void k_rows_census(
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind, int64_t M, int64_t K,
     int64_t P, int64_t nnz, int64_t run, int32_t* __restrict__ rowptr_copy,
     uint32_t* __restrict__ panel_nnzptr, uint32_t* __restrict__ ncols_p,
-    PanelTotals* __restrict__ totals) {
+    PanelTotals* __restrict__ totals, uint4* __restrict__ clear, uint32_t n_clear) {
   __shared__ uint32_t s_bm[kFirstWaves][kFirstWords];
   __shared__ int32_t s_rp[kFirstWaves][kPanel + 1];
   __shared__ PanelTotals s_tot[kFirstWaves];
@@ -811,23 +814,26 @@ __global__ __launch_bounds__(kFirstThreads, 6) void k_rows_census(
   uint32_t* bm = s_bm[wave];
   int32_t* rp = s_rp[wave];
   PanelTotals t{};
-  const int64_t p_end = min((int64_t)(blockIdx.x + 1) * run, P);
-  for (int64_t p = (int64_t)blockIdx.x * run + wave; p < p_end; p += kFirstWaves) {
+  const int64_t p_end = min((int64_t)(blockIdx.x + 1) * run, P), p_first = (int64_t)blockIdx.x * run + wave;
+  int32_t a_next = rowptr[min(p_first * kPanel + lane, M)];
+  for (uint32_t i = blockIdx.x * kFirstThreads + threadIdx.x; i < n_clear; i += gridDim.x * kFirstThreads)
+    clear[i] = uint4{0, 0, 0, 0};
+  for (int64_t p = p_first; p < p_end; p += kFirstWaves) {
     const int64_t i = p * kPanel + lane;
-    const int32_t a = rowptr[min(i, M)];
+    const int32_t a = a_next;
+    a_next = rowptr[min(i + kFirstWaves * kPanel, M)];
     const int32_t b = __shfl_down(a, 1, 64);   // (row M's own offset past the last row)
     int32_t lo = 0x7FFFFFFF, hi = -1;
     uint32_t cnt = 0, err = 0;
     if (lane <= kPanel) rp[lane] = a;
-    if (lane < kPanel && i < M) {
+    const bool row = lane < kPanel && i < M;
+    const bool in_order = row && a >= 0 && a <= nnz && b >= a;
+    const bool has = in_order && a < b && b <= nnz;
+    if (row) {
       rowptr_copy[i] = a;
       if (i == 0 && a != 0) err |= kErrRowptrEnds;
-      if (a < 0 || a > nnz || b < a) err |= kErrRowptrOrder;
-      else if (a < b && b <= nnz) {
-        lo = colind[a];
-        hi = colind[b - 1];
-        cnt = (uint32_t)(b - a);
-      }
+      if (!in_order) err |= kErrRowptrOrder;
+      if (has) cnt = (uint32_t)(b - a);
     }
     if (i == M && lane <= kPanel) {            // the end of the last row
       rowptr_copy[M] = a;
@@ -838,13 +844,35 @@ __global__ __launch_bounds__(kFirstThreads, 6) void k_rows_census(
     if (lane == 0) panel_nnzptr[p] = (uint32_t)a;
     err = wave_or(err);
 #pragma unroll
-    for (int d = 8; d > 0; d >>= 1) {          // rows sit in lanes 0..15
+    for (int d = 8; d > 0; d >>= 1) cnt += __shfl_xor(cnt, d, 64);   // rows sit in lanes 0..15
+    const uint32_t n = __builtin_amdgcn_readfirstlane(cnt);
+    // The first two rounds of entries come with the rows' ends: with the rows in order, as they are without `err`
+    // (but for the matrix's very end, which is another panel's), they are the n from the first row's offset on.
+    const int32_t* __restrict__ col = colind + __builtin_amdgcn_readfirstlane(a);
+    auto four = [&](uint32_t e, int32_t (&j)[4]) {
+      if (e + 4 <= n) {
+        const Int4Any v = *reinterpret_cast<const Int4Any*>(col + e);
+        j[0] = v.x; j[1] = v.y; j[2] = v.z; j[3] = v.w;
+      } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) j[k] = col[min(e + k, n - 1)];
+      }
+    };
+    int32_t ahead[2][4] = {};
+    if (has) {
+      lo = colind[a];
+      hi = colind[b - 1];
+    }
+    if (n && !err) {
+      four(4 * lane, ahead[0]);
+      if (n > 256) four(256 + 4 * lane, ahead[1]);
+    }
+#pragma unroll
+    for (int d = 8; d > 0; d >>= 1) {
       lo = min(lo, __shfl_xor(lo, d, 64));
       hi = max(hi, __shfl_xor(hi, d, 64));
-      cnt += __shfl_xor(cnt, d, 64);
     }
     const int32_t cmin = __builtin_amdgcn_readfirstlane(lo), cmax = __builtin_amdgcn_readfirstlane(hi);
-    const uint32_t n = __builtin_amdgcn_readfirstlane(cnt);
     t.max_nnz = max(t.max_nnz, n);
     if (cmax < cmin) {
       t.err |= err | (n ? (uint32_t)kErrColOrder : 0u);
@@ -861,22 +889,17 @@ __global__ __launch_bounds__(kFirstThreads, 6) void k_rows_census(
       continue;
     }
 
-    // census: the panel's rows are in order, so its entries are the n from the first row's offset on
+    // census
     for (uint32_t w = lane; w < words; w += 64) bm[w] = 0;
     wave_lds_fence();
-    const int32_t* __restrict__ col = colind + rp[0];
     uint32_t bad = 0;
     int32_t last = -1;                         // the column before this round's first
     for (uint32_t base = 0; base < n; base += 256) {
       const uint32_t e = base + 4 * lane;
       int32_t j[4];
-      if (e + 4 <= n) {
-        const Int4Any v = *reinterpret_cast<const Int4Any*>(col + e);
-        j[0] = v.x; j[1] = v.y; j[2] = v.z; j[3] = v.w;
-      } else {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) j[k] = col[min(e + k, n - 1)];
-      }
+      for (int k = 0; k < 4; ++k) { j[k] = ahead[0][k]; ahead[0][k] = ahead[1][k]; }
+      if (base + 512 < n) four(e + 512, ahead[1]);
       int32_t before = __shfl_up(j[3], 1, 64);
       if (lane == 0) before = last;
       last = __shfl(j[3], 63, 64);
@@ -1681,14 +1704,21 @@ hipError_t launch_rows_census(const int32_t* rowptr, const int32_t* colind, int6
                               int64_t P, int64_t nnz, int32_t* rowptr_copy, uint32_t* panel_nnzptr,
                               uint32_t* ncols_p, uint32_t* panel_ptr, uint32_t* tmp, PlanControl* ctl,
                               PlanControl* pinned, uint32_t* flag, uint32_t* mid_list, uint32_t* big_list,
-                              hipStream_t s) {
+                              void* clear, size_t clear_bytes, hipStream_t s) {
   static_assert(sizeof(PanelTotals) == 32, "eight words of `tmp` each");
   PanelTotals* totals = reinterpret_cast<PanelTotals*>(tmp);
   const int64_t want = std::max<int64_t>(1, std::min<int64_t>((P + kFirstWaves - 1) / kFirstWaves, kFirstBlocks));
   const int64_t run = std::max<int64_t>(1, (P + want - 1) / want);
   const unsigned n = (unsigned)std::max<int64_t>(1, (P + run - 1) / run);
+  // Few panels and many columns: more to clear than these workgroups should
+  uint32_t n_clear = (uint32_t)(clear_bytes / sizeof(uint4));
+  if (clear_bytes / sizeof(uint4) > kClearEach * kFirstThreads * n) {
+    const hipError_t e = hipMemsetAsync(clear, 0, clear_bytes, s);
+    if (e != hipSuccess) return e;
+    n_clear = 0;
+  }
   hipLaunchKernelGGL(k_rows_census, dim3(n), dim3(kFirstThreads), 0, s, rowptr, colind, M, K, P, nnz, run,
-                     rowptr_copy, panel_nnzptr, ncols_p, totals);
+                     rowptr_copy, panel_nnzptr, ncols_p, totals, static_cast<uint4*>(clear), n_clear);
   const unsigned group = (unsigned)std::max<int64_t>(1, 4 * kScanThreads / run);
   hipLaunchKernelGGL(k_census_scan, dim3((n + group - 1) / group), dim3(kScanThreads), 0, s, ncols_p, P, run,
                      totals, n, group, panel_ptr, ctl, pinned, flag, nnz, panel_nnzptr, mid_list, big_list);

@@ -91,12 +91,12 @@ __host__ __device__ inline uint32_t panel_bitmap_words(uint32_t span, int64_t P)
 
 // checks rowptr, copies it, panel_nnzptr, ctl->err / span / max_nnz / counted; where ctl->counted, also what
 // launch_panel_census and launch_panel_scan do, else the lists of launch_panel_sort_census.  `pinned` (or null)
-// gets what ctl does, then `flag` 1.
+// gets what ctl does, then `flag` 1.  `clear` (256-byte aligned, ctl in it) is cleared on the way.
 hipError_t launch_rows_census(const int32_t* rowptr, const int32_t* colind, int64_t M, int64_t K,
                               int64_t P, int64_t nnz, int32_t* rowptr_copy, uint32_t* panel_nnzptr,
                               uint32_t* ncols_p, uint32_t* panel_ptr, uint32_t* tmp, PlanControl* ctl,
                               PlanControl* pinned, uint32_t* flag, uint32_t* mid_list, uint32_t* big_list,
-                              hipStream_t s);
+                              void* clear, size_t clear_bytes, hipStream_t s);
 // ncols_p -> panel_ptr[P+1] (bricks, scanned), ctl->nb, ctl->n_active, ctl->max_cols
 size_t panel_scan_tmp_elems();
 hipError_t launch_panel_scan(const uint32_t* ncols_p, int64_t P, uint32_t* panel_ptr, uint32_t* tmp,
