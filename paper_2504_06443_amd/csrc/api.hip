@@ -1091,9 +1091,11 @@ int launch_product(const spmm_plan_t* pl, const HostList* hl, const WorkItem* d_
   const uint32_t n_listed = (uint32_t)hl->items.size();
   const bool any_split = !hl->merges.empty();
   const int32_t simds = 4 * pl->num_cus;
+  const int64_t mean_bricks = pl->nb / std::max<int64_t>(pl->P, 1);
   const WorkSource work =
-      hl->direct ? WorkSource{nullptr, d_items, (uint32_t)pl->P, n_listed, hl->split_bricks, any_split, simds, pl->scattered}
-                 : WorkSource{d_items, nullptr, n_listed, 0, kNoSplit, any_split, simds, pl->scattered};
+      hl->direct ? WorkSource{nullptr, d_items, (uint32_t)pl->P, n_listed, hl->split_bricks, any_split, simds,
+                              pl->scattered, mean_bricks}
+                 : WorkSource{d_items, nullptr, n_listed, 0, kNoSplit, any_split, simds, pl->scattered, mean_bricks};
   if (uses_tm32(pl, B, N, C)) {
     // 32-row panels: one wavefront per super-panel and column tile, no work list
     HIP_TRY(launch_spmm_tm32(pl->tm32.sp_ptr, pl->tm32.bc_cols, pl->tm32.meta, pl->tm32.vals,

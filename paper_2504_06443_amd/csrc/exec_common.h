@@ -78,8 +78,8 @@ __device__ inline void store_any_nt(float* __restrict__ p, const float* in) {
 
 // One of the floats behind `base`, at `index` (per lane) behind byte `at` (uniform): a buffer load of stride four,
 // which scales the index itself.  With a global load the shift is a vector instruction a brick, which costs tiles of up
-// to 64 columns, whose loop has few others: 4096 panels of cells of fill 0.1, N = 64 30.2 -> 28.8 us, N = 48 23.4 -> 22.6,
-// 16,384 of blocks, N = 64 69.1 -> 67.7.  The wider tiles gain nothing, and a graph at N = 128 lost 8 %.
+// to 64 columns, whose loop has few others (see values_by_index).  The wider tiles gain nothing, and a graph at N = 128
+// lost 8 %.
 typedef int int4_t __attribute__((ext_vector_type(4)));
 extern "C" __device__ float spmm_load_indexed(int4_t buffer, int index, int offset, int at, int aux) __asm(
     "llvm.amdgcn.struct.buffer.load.f32");
@@ -154,6 +154,18 @@ __device__ inline bool work_item(const ItemMap& m, const uint32_t* panel_ptr, ui
   const bool is_whole = e - b < split;
   *it = WorkItem{is_whole ? panel : kNoPanel, b, is_whole ? e : b, slot};
   return true;
+}
+
+// Whether values are loaded by index (spmm_load_indexed).  It saves an instruction a brick, but a wavefront's first
+// bricks arrive later, so panels have to have as many bricks as each width wants.  us, shift / index:
+//   16 columns, N = 16: bands of 3 a row (10 bricks a panel) 10.8 / 11.1, of 6 (18) 14.0 / 14.2, of 14 (46) 25.9 / 25.8,
+//     of 20 (60) 31.8 / 31.5; cells of fill 0.06 (42) 11.4 / 11.5, of 0.1 (50) 15.05 / 14.9, (100) 24.05 / 23.2
+//   32 columns, N = 32: bands 14.6 / 14.9, 18.5 / 18.4, 37.2 / 36.3, 46.6 / 45.4; cells 16.1 / 16.1, 22.4 / 22.4, 37.8 / 37.3
+//   48 columns, N = 48: bands 19.3 / 20.5, 24.3 / 24.7, 54.5 / 54.3, 73.8 / 73.8; cells 23.3 / 23.7, 32.15 / 32.4, 54.5 / 52.3;
+//     4096 panels of 75 bricks 23.55 / 22.9
+//   64 columns, N = 64: cells 28.4 / 29.0, 40.05 / 41.6, 70.4 / 70.4; 4096 panels of 75 bricks 29.8 / 28.6
+inline bool values_by_index(const WorkSource& w, int tile) {
+  return w.mean_bricks >= (tile == 32 ? 20 : tile == 16 ? 44 : 64);
 }
 
 constexpr int64_t kNarrowLargeB = int64_t(64) << 20;

@@ -226,7 +226,7 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void k_spmm_mfma(
 // the traffic from memory.
 constexpr int kFastChunk = 8;
 
-template <int T, bool FULL, int WPB>
+template <int T, bool FULL, bool IDX, int WPB>
 __global__ __launch_bounds__(64 * WPB) void k_spmm_mfma_fast(
     SPMM_ITEM_PARAMS, const uint32_t* __restrict__ panel_ptr, const uint32_t* __restrict__ brick_cols,
     const uint64_t* __restrict__ brick_mask, const uint32_t* __restrict__ brick_valptr,
@@ -311,7 +311,7 @@ __global__ __launch_bounds__(64 * WPB) void k_spmm_mfma_fast(
       const uint32_t cnt = __builtin_amdgcn_mbcnt_hi(
           (uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
       // scalar base + 32-bit byte offset (the launcher checks that the values fit 4 GiB)
-      if constexpr (T <= 4) st_a[s] = spmm_load_indexed(vals_at, (int)cnt, 0, (int)(off * 4u), 0);
+      if constexpr (IDX) st_a[s] = spmm_load_indexed(vals_at, (int)cnt, 0, (int)(off * 4u), 0);
       else
         st_a[s] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(vals) + (off * 4u + cnt * 4u));
       const char* brow = Bbytes + (ro + lane_off0);
@@ -712,7 +712,7 @@ int occupancy_t() {
 template <int T>
 int occupancy_fast_t() {
   int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_spmm_mfma_fast<T, false, kWavesPerBlock>, 64 * kWavesPerBlock,
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_spmm_mfma_fast<T, false, false, kWavesPerBlock>, 64 * kWavesPerBlock,
                                                    0) != hipSuccess || nb < 1)
     nb = 1;
   return nb * kWavesPerBlock;
@@ -825,24 +825,24 @@ hipError_t launch_spmm_mfma(const BrickFormat& f, const WorkSource& w, const flo
     const unsigned gy = (unsigned)((N + tile - 1) / tile);
     const uint32_t k_last = (uint32_t)(K - 1);
     const bool single = single_waves(w, N, K);
-#define SPMM_LAUNCH_WAVES(TT, FF, W)                                                            \
-  hipLaunchKernelGGL((k_spmm_mfma_fast<TT, FF, W>), dim3(item_blocks<W>(w), gy), dim3(64 * W), 0, s, \
+#define SPMM_LAUNCH_WAVES(TT, FF, II, W)                                                        \
+  hipLaunchKernelGGL((k_spmm_mfma_fast<TT, FF, II, W>), dim3(item_blocks<W>(w), gy), dim3(64 * W), 0, s, \
                      SPMM_ITEM_ARGS(W, w), f.panel_ptr, f.brick_cols,                           \
                      f.brick_mask, f.brick_valptr, f.vals, B, C, partial, M, N, k_last)
-#define SPMM_LAUNCH_FAST(TT, FF)                                                                \
+#define SPMM_LAUNCH_FAST(TT, FF, II)                                                            \
   do {                                                                                          \
-    if (single) SPMM_LAUNCH_WAVES(TT, FF, 1); else SPMM_LAUNCH_WAVES(TT, FF, kWavesPerBlock);   \
+    if (single) SPMM_LAUNCH_WAVES(TT, FF, II, 1); else SPMM_LAUNCH_WAVES(TT, FF, II, kWavesPerBlock); \
   } while (0)
     switch (tile / 16) {
-      case 1: SPMM_LAUNCH_FAST(1, false); break;
-      case 2: SPMM_LAUNCH_FAST(2, false); break;
-      case 3: SPMM_LAUNCH_FAST(3, false); break;
-      case 4: SPMM_LAUNCH_FAST(4, false); break;
-      case 5: SPMM_LAUNCH_FAST(5, false); break;
-      case 6: SPMM_LAUNCH_FAST(6, false); break;
-      case 7: SPMM_LAUNCH_FAST(7, false); break;
+      case 1: SPMM_LAUNCH_FAST(1, false, false); break;   // (split panels: short ones mostly)
+      case 2: SPMM_LAUNCH_FAST(2, false, false); break;
+      case 3: if (values_by_index(w, tile)) SPMM_LAUNCH_FAST(3, false, true); else SPMM_LAUNCH_FAST(3, false, false); break;
+      case 4: if (values_by_index(w, tile)) SPMM_LAUNCH_FAST(4, false, true); else SPMM_LAUNCH_FAST(4, false, false); break;
+      case 5: SPMM_LAUNCH_FAST(5, false, false); break;
+      case 6: SPMM_LAUNCH_FAST(6, false, false); break;
+      case 7: SPMM_LAUNCH_FAST(7, false, false); break;
       default:   // whole 128-column tiles: the second vector of a B row at a constant offset
-        if (N % 128 == 0) SPMM_LAUNCH_FAST(8, true); else SPMM_LAUNCH_FAST(8, false);
+        if (N % 128 == 0) SPMM_LAUNCH_FAST(8, true, false); else SPMM_LAUNCH_FAST(8, false, false);
         break;
     }
 #undef SPMM_LAUNCH_WAVES

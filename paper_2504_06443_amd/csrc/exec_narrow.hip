@@ -41,7 +41,7 @@ __device__ inline void swap_fours(float& a, float& c) {
   c = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(y, x, 0x104 /* row_shl:4 */, 0xF, 0x5, false));
 }
 
-template <int T, int WPB>
+template <int T, bool IDX, int WPB>
 __global__ __launch_bounds__(64 * WPB, T == 2 ? 4 : 1) void k_spmm_mfma_narrow(
     SPMM_ITEM_PARAMS, const uint32_t* __restrict__ panel_ptr, const uint32_t* __restrict__ brick_cols,
     const uint64_t* __restrict__ brick_mask, const uint32_t* __restrict__ brick_valptr,
@@ -74,7 +74,7 @@ __global__ __launch_bounds__(64 * WPB, T == 2 ? 4 : 1) void k_spmm_mfma_narrow(
   if (b_begin < b_end) {
     const uint32_t nbricks = b_end - b_begin;
     const char* Bbytes = reinterpret_cast<const char*>(B);
-    const int4_t vals_at = float_buffer(vals);
+    [[maybe_unused]] const int4_t vals_at = float_buffer(vals);
     struct Meta { uint64_t mask[CH]; uint32_t off[CH]; };
     auto load_meta = [&](uint32_t base) {
       const uint64_t* __restrict__ mp = brick_mask + base;
@@ -98,7 +98,9 @@ __global__ __launch_bounds__(64 * WPB, T == 2 ? 4 : 1) void k_spmm_mfma_narrow(
       st_mask[i] = mask;
       const uint32_t cnt = __builtin_amdgcn_mbcnt_hi(
           (uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-      st_a[i] = spmm_load_indexed(vals_at, (int)cnt, 0, (int)(off * 4u), 0);
+      if constexpr (IDX) st_a[i] = spmm_load_indexed(vals_at, (int)cnt, 0, (int)(off * 4u), 0);
+      else
+        st_a[i] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(vals) + (off * 4u + cnt * 4u));
     };
     auto rows_of = [&](uint32_t ro, int q) {
       return (uint32_t)__builtin_amdgcn_ds_bpermute(perm_base + 16u * G * q, ro);
@@ -236,16 +238,21 @@ hipError_t launch_spmm_mfma_narrow(const BrickFormat& f, const WorkSource& w, in
                                    float* partial, int64_t M, int64_t N, int64_t K, hipStream_t s) {
   const unsigned gy = (unsigned)((N + tile - 1) / tile);
   const uint32_t k_last = (uint32_t)(K - 1);
-#define SPMM_LAUNCH_NARROW(TT, W)                                                               \
-  hipLaunchKernelGGL((k_spmm_mfma_narrow<TT, W>), dim3(item_blocks<W>(w), gy), dim3(64 * W), 0, s, \
+#define SPMM_LAUNCH_WAVES(TT, II, W)                                                            \
+  hipLaunchKernelGGL((k_spmm_mfma_narrow<TT, II, W>), dim3(item_blocks<W>(w), gy), dim3(64 * W), 0, s, \
                      SPMM_ITEM_ARGS(W, w), f.panel_ptr, f.brick_cols,                           \
                      f.brick_mask, f.brick_valptr, f.vals, B, C, partial, M, N, k_last)
-  if (single_waves(w, N, K)) {
-    if (tile == 16) SPMM_LAUNCH_NARROW(1, 1); else SPMM_LAUNCH_NARROW(2, 1);
+#define SPMM_LAUNCH_NARROW(TT, II)                                                              \
+  do {                                                                                          \
+    if (single_waves(w, N, K)) SPMM_LAUNCH_WAVES(TT, II, 1); else SPMM_LAUNCH_WAVES(TT, II, kWavesPerBlock); \
+  } while (0)
+  if (values_by_index(w, tile)) {
+    if (tile == 16) SPMM_LAUNCH_NARROW(1, true); else SPMM_LAUNCH_NARROW(2, true);
   } else {
-    if (tile == 16) SPMM_LAUNCH_NARROW(1, kWavesPerBlock); else SPMM_LAUNCH_NARROW(2, kWavesPerBlock);
+    if (tile == 16) SPMM_LAUNCH_NARROW(1, false); else SPMM_LAUNCH_NARROW(2, false);
   }
 #undef SPMM_LAUNCH_NARROW
+#undef SPMM_LAUNCH_WAVES
   return hipGetLastError();
 }
 

@@ -65,6 +65,7 @@ struct WorkSource {
   bool any_split;           // of the items and parts, some are parts
   int32_t simds;            // of the device
   bool scattered;           // columns of a panel lie far apart: its B rows are its own
+  int64_t mean_bricks;      // of a panel
 };
 constexpr uint32_t kNoSplit = 0xFFFFFFFFu;
 
