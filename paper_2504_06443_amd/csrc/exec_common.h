@@ -164,8 +164,12 @@ __device__ inline bool work_item(const ItemMap& m, const uint32_t* panel_ptr, ui
 //   48 columns, N = 48: bands 19.3 / 20.5, 24.3 / 24.7, 54.5 / 54.3, 73.8 / 73.8; cells 23.3 / 23.7, 32.15 / 32.4, 54.5 / 52.3;
 //     4096 panels of 75 bricks 23.55 / 22.9
 //   64 columns, N = 64: cells 28.4 / 29.0, 40.05 / 41.6, 70.4 / 70.4; 4096 panels of 75 bricks 29.8 / 28.6
-inline bool values_by_index(const WorkSource& w, int tile) {
-  return w.mean_bricks >= (tile == 32 ? 20 : tile == 16 ? 44 : 64);
+// And as many wavefronts that others hide it, 3.5 a SIMD (cells of 75 bricks, blocks of 30): 1000 panels, N = 16 9.06 / 9.34
+// and 5.90 / 6.07, N = 32 9.94 / 10.2 and 6.93 / 7.13, N = 64 in two tiles 12.3 / 12.7; 3000, N = 16 12.1 / 12.2 and
+// 9.34 / 9.45, N = 32 15.9 / 15.8 and 12.1 / 12.0, N = 64 22.5 / 23.0; 4000, N = 16 14.1 / 14.0, N = 64 29.4 / 28.3.
+inline bool values_by_index(const WorkSource& w, int tile, int64_t tiles) {
+  return w.mean_bricks >= (tile == 32 ? 20 : tile == 16 ? 44 : 64) &&
+         2 * tiles * ((int64_t)w.n_items + w.n_parts) >= 7 * (int64_t)w.simds;
 }
 
 constexpr int64_t kNarrowLargeB = int64_t(64) << 20;

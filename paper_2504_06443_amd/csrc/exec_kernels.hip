@@ -756,9 +756,15 @@ int mfma_fp32_tile(int64_t N, int64_t K, int64_t nnz) {
 // wavefronts of another, and a single wavefront is a chain of latencies; on tiles of half the width they are
 // twice as many.  Times in us, wide / narrower, of 3x3 blocks (ten a block row) and of cells of fill 0.1:
 //   128 -> 64 columns at up to 2.5 wavefronts a SIMD: 640 panels, N = 128 10.5 / 9.7 and 14.7 / 12.5; 2500 panels
-//     21.1 / 19.3 and 31.9 / 27.8; at 2.9 a SIMD blocks lose (21.6 / 24.0).  Scattered panels, bound by memory and
+//     21.1 / 19.3 and 31.9 / 27.8; at 2.9 a SIMD blocks lose (21.6 / 24.0).  Less far where the narrower are not twice
+//     as many (N = 300, 5 tiles for 3: at 3.6 a SIMD 21.3 / 18.3, at 4 a band 13.9 / 14.5), or rows of B are not
+//     aligned (N = 339, at 4.1 a SIMD 23.1 / 21.3, at 4.95 22.0 / 23.0).  Scattered panels, bound by memory and
 //     not by MFMAs, gain beyond that, too, as long as B stays in the Infinity Cache (graph of 4096 panels 30.3 /
-//     26.6, cells of 8192 112.5 / 107.1; a graph of 12,288 panels, B of 100 MB, 73.6 / 75.1).
+//     26.6, cells of 8192 112.5 / 107.1; a graph of 12,288 panels, B of 100 MB, 73.6 / 75.1): split ones, and whole ones
+//     of many bricks (cells, N = 128, 6000 panels of 25 bricks 46.7 / 44.1, of 6 21.2 / 21.8; 4000 of 25, 7.8 a SIMD,
+//     32.2 / 33.0; N = 256, 2800 of 25 44.5 / 41.8).
+//     Not where the SIMD with most has as many columns as before (blocks of 1977 panels, N = 128 20.7 / 21.0; 463, N = 160,
+//     three tiles for two 8.4 / 8.55).
 //   64 -> 32 and 32 -> 16 where the wider one gives at most 1.25 a SIMD, in 16-byte loads (exec_narrow.hip): 256
 //     panels, N = 64 6.8 / 5.3 / 4.7 and 8.5 / 6.5 / 5.6; 1250 panels, N = 64 10.0 / 9.0 / 9.2; 1024 panels, N = 128
 //     10.4 / 11.0 / 13.4.
@@ -769,6 +775,7 @@ int mfma_run_tile(const WorkSource& w, int64_t N, int64_t K, int64_t nnz) {
   if (!mfma_32bit_shape(N, K) || !mfma_32bit_values(nnz) || N < 20 || (N > 32 && N < 48)) return whole;
   const int64_t items = (int64_t)w.n_items + w.n_parts;
   auto tiles = [&](int64_t width) { return (N + width - 1) / width; };
+  const bool spread = w.scattered && N % 32 == 0 && K * N * 4 <= kNarrowLargeB;
   int tile = whole;
   for (int width = 64; width >= 16; width /= 2) {
     const int64_t k = tiles(width), t = ((N + 15) / 16 + k - 1) / k;
@@ -776,8 +783,13 @@ int mfma_run_tile(const WorkSource& w, int64_t N, int64_t K, int64_t nnz) {
     const int64_t columns = k * narrower, least = tiles(whole) * whole;   // multiplied, with those behind N
     const int64_t waves = items * tiles(2 * width);
     if (narrower >= tile) continue;
+    const int64_t most = k < 2 * tiles(whole) ? 8 : (N % 4 ? 9 : 10);   // narrower wavefronts for two SIMDs
+    // columns of the SIMD with most: no gain where that stays, but for wavefronts that were alone
+    const int64_t then = (items * k + w.simds - 1) / w.simds * narrower, wide = items * tiles(whole);
+    const bool less = then < (wide + w.simds - 1) / w.simds * whole + (wide <= w.simds ? 1 : 0);
     if (width == 64 ? 10 * columns <= 11 * least &&
-                          (2 * waves <= 5 * w.simds || (w.scattered && N % 32 == 0 && K * N * 4 <= kNarrowLargeB))
+                          ((less && 2 * items * k <= most * w.simds) ||
+                           (spread && (w.any_split || (w.mean_bricks >= 16 && items * k >= 10 * w.simds))))
                     : 4 * columns < 5 * least && 4 * waves <= 5 * w.simds)
       tile = (int)narrower;
   }
@@ -836,8 +848,8 @@ hipError_t launch_spmm_mfma(const BrickFormat& f, const WorkSource& w, const flo
     switch (tile / 16) {
       case 1: SPMM_LAUNCH_FAST(1, false, false); break;   // (split panels: short ones mostly)
       case 2: SPMM_LAUNCH_FAST(2, false, false); break;
-      case 3: if (values_by_index(w, tile)) SPMM_LAUNCH_FAST(3, false, true); else SPMM_LAUNCH_FAST(3, false, false); break;
-      case 4: if (values_by_index(w, tile)) SPMM_LAUNCH_FAST(4, false, true); else SPMM_LAUNCH_FAST(4, false, false); break;
+      case 3: if (values_by_index(w, tile, gy)) SPMM_LAUNCH_FAST(3, false, true); else SPMM_LAUNCH_FAST(3, false, false); break;
+      case 4: if (values_by_index(w, tile, gy)) SPMM_LAUNCH_FAST(4, false, true); else SPMM_LAUNCH_FAST(4, false, false); break;
       case 5: SPMM_LAUNCH_FAST(5, false, false); break;
       case 6: SPMM_LAUNCH_FAST(6, false, false); break;
       case 7: SPMM_LAUNCH_FAST(7, false, false); break;

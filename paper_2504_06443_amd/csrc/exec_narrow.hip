@@ -14,7 +14,8 @@
 // registers and spill as many again: 184.9.  At most 5 wavefronts 185.9; fetching half a chunk at an item's end
 // (more code, spilled scalars) 181.8.
 //
-// Wider C of few panels takes several such tiles (mfma_run_tile).
+// Wider C of few panels takes several such tiles (mfma_run_tile): MANY, as a first column that is not known cost short
+// panels of one tile 1 % (310,036 rows, 3 a row, N = 17 16.3 / 16.5 us).
 //
 // A chunk of eight bricks is in flight while it is multiplied load by load, and each load's registers take
 // the next chunk's.  The last chunk is fetched behind tests for what is left, so that items of ten bricks do not
@@ -41,7 +42,7 @@ __device__ inline void swap_fours(float& a, float& c) {
   c = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(y, x, 0x104 /* row_shl:4 */, 0xF, 0x5, false));
 }
 
-template <int T, bool IDX, int WPB>
+template <int T, bool IDX, bool MANY, int WPB>
 __global__ __launch_bounds__(64 * WPB, T == 2 ? 4 : 1) void k_spmm_mfma_narrow(
     SPMM_ITEM_PARAMS, const uint32_t* __restrict__ panel_ptr, const uint32_t* __restrict__ brick_cols,
     const uint64_t* __restrict__ brick_mask, const uint32_t* __restrict__ brick_valptr,
@@ -63,7 +64,7 @@ __global__ __launch_bounds__(64 * WPB, T == 2 ? 4 : 1) void k_spmm_mfma_narrow(
   const uint32_t perm_transpose = 4u * (uint32_t)(4 * (lane & 15) + kq);
   const uint32_t perm_base = 4u * (4u * in_load + kq);
   const uint32_t row_bytes = (uint32_t)N * 4u;
-  const uint32_t col0 = blockIdx.y * (16u * T) + 4u * j;
+  const uint32_t col0 = (MANY ? blockIdx.y * (16u * T) : 0u) + 4u * j;
   const uint32_t at = min(col0, (uint32_t)N - 4u);
   const uint32_t lane_off = at * 4u;
 
@@ -238,19 +239,20 @@ hipError_t launch_spmm_mfma_narrow(const BrickFormat& f, const WorkSource& w, in
                                    float* partial, int64_t M, int64_t N, int64_t K, hipStream_t s) {
   const unsigned gy = (unsigned)((N + tile - 1) / tile);
   const uint32_t k_last = (uint32_t)(K - 1);
-#define SPMM_LAUNCH_WAVES(TT, II, W)                                                            \
-  hipLaunchKernelGGL((k_spmm_mfma_narrow<TT, II, W>), dim3(item_blocks<W>(w), gy), dim3(64 * W), 0, s, \
+#define SPMM_LAUNCH_WAVES(TT, II, MM, W)                                                        \
+  hipLaunchKernelGGL((k_spmm_mfma_narrow<TT, II, MM, W>), dim3(item_blocks<W>(w), gy), dim3(64 * W), 0, s, \
                      SPMM_ITEM_ARGS(W, w), f.panel_ptr, f.brick_cols,                           \
                      f.brick_mask, f.brick_valptr, f.vals, B, C, partial, M, N, k_last)
-#define SPMM_LAUNCH_NARROW(TT, II)                                                              \
+#define SPMM_LAUNCH_NARROW(TT)                                                                  \
   do {                                                                                          \
-    if (single_waves(w, N, K)) SPMM_LAUNCH_WAVES(TT, II, 1); else SPMM_LAUNCH_WAVES(TT, II, kWavesPerBlock); \
+    if (gy > 1) SPMM_LAUNCH_WAVES(TT, false, true, kWavesPerBlock);   /* too few for an index */ \
+    else if (single_waves(w, N, K))                                                             \
+      { if (by_index) SPMM_LAUNCH_WAVES(TT, true, false, 1); else SPMM_LAUNCH_WAVES(TT, false, false, 1); } \
+    else if (by_index) SPMM_LAUNCH_WAVES(TT, true, false, kWavesPerBlock);                      \
+    else SPMM_LAUNCH_WAVES(TT, false, false, kWavesPerBlock);                                   \
   } while (0)
-  if (values_by_index(w, tile)) {
-    if (tile == 16) SPMM_LAUNCH_NARROW(1, true); else SPMM_LAUNCH_NARROW(2, true);
-  } else {
-    if (tile == 16) SPMM_LAUNCH_NARROW(1, false); else SPMM_LAUNCH_NARROW(2, false);
-  }
+  const bool by_index = values_by_index(w, tile, gy);
+  if (tile == 16) SPMM_LAUNCH_NARROW(1); else SPMM_LAUNCH_NARROW(2);
 #undef SPMM_LAUNCH_NARROW
 #undef SPMM_LAUNCH_WAVES
   return hipGetLastError();

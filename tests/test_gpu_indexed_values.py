@@ -53,23 +53,26 @@ def test_split_panels_over_a_large_b(gpu, N, large):  # noqa: F811
 
 
 @pytest.mark.parametrize("N, least", [(16, 44), (31, 20), (32, 20), (48, 64), (61, 64), (64, 64)])
-@pytest.mark.parametrize("short", [0, 1])
-def test_values_by_index_from_a_mean_of_bricks(gpu, N, least, short):  # noqa: F811
-    """1300 panels of 3, 2m - 3 and m bricks on average: m as each width wants it, and one less."""
+@pytest.mark.parametrize("too_few", ["", "bricks", "panels"])
+def test_values_by_index_from_a_mean_of_bricks(gpu, N, least, too_few):  # noqa: F811
+    """Panels of 3 and of 2m - 3 bricks: m on average as each width wants it, or one less; 3.5 panels a SIMD, or one
+    less."""
     import torch
-    P, rng = 1300, np.random.default_rng(N)
-    m = least - short
+    simds = 4 * torch.cuda.get_device_properties(0).multi_processor_count
+    P, rng = 7 * simds // 2 - (too_few == "panels"), np.random.default_rng(N)
+    m = least - (too_few == "bricks")
     bricks = np.where(np.arange(P) % 2, 3, 2 * m - 3)
-    cols = np.concatenate([rng.choice(4 * b + 9, size=4 * b, replace=False) for b in bricks])
+    K = 8 * least + 9
+    cols = np.concatenate([np.arange(4 * b) * 2 % K for b in bricks])   # (K is odd)
     panel = np.repeat(np.arange(P), 4 * bricks)
     rows = 16 * panel + rng.integers(0, 16, size=len(cols))
-    A = W.csr_from_coo(16 * P, 8 * least + 9, rows, cols, rng.uniform(-1, 1, len(cols)).astype(np.float32))
+    A = W.csr_from_coo(16 * P, K, rows, cols, rng.uniform(-1, 1, len(cols)).astype(np.float32))
     plan = make_plan(gpu, A)
-    assert gpu.spmm_plan_export(plan)["brick_mask"].shape[0] == P * m
+    assert gpu.spmm_plan_export(plan)["brick_mask"].shape[0] // P == m
     B = W.dense_b(A.K, N, 3)
     Cref, S = oracle.spmm_f64(A.rowptr, A.colind, A.vals, B)
     got = []
     names = kernels_of(lambda: got.append(gpu.spmm_exec(plan, torch.from_numpy(B).cuda())))
-    kernel = "narrow<%d, %s, 4>" if N <= 32 else "fast<%d, false, %s, 4>"
-    assert kernel % ((N + 15) // 16, "false" if short else "true") in names, names
+    kernel = "narrow<%d, %s, false, 4>" if N <= 32 else "fast<%d, false, %s, 4>"
+    assert kernel % ((N + 15) // 16, "false" if too_few else "true") in names, names
     check_c(got[0].cpu().numpy(), Cref, S)
