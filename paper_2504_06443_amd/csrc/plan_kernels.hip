@@ -213,11 +213,11 @@ struct StepSource {
 // New values for an unchanged pattern: packed position p takes the CSR entry that was recorded when
 // the plan was built.  Bound by memory: 4 bytes each of values and packed values per entry, and 4 or 2 of
 // where it comes from.  Gathering by packed position keeps the stores whole (the entries of a panel are 2 KB or
-// so, and their reads hit a cache); two times four positions per thread.  CSR: the plan also keeps the values
-// in CSR order, for the vector-ALU kernels.  7.86 M entries, one update behind another: from the entries, four positions a
-// thread 17.3 us, 94 MB; from steps 14.3, 79 MB; and eight positions a thread 13.5, as sixteen.
-constexpr int kUpdateFours = 2;
-constexpr int64_t kUpdateBlock = (int64_t)kThreads * 4 * kUpdateFours;   // positions a workgroup
+// so, and their reads hit a cache); four positions a thread.  CSR: the plan also keeps the values in CSR order, for the
+// vector-ALU kernels.  7.86 M entries, one update behind another: from the entries 17.3 us, 94 MB; from steps 14.3, 79 MB.
+// Eight positions a thread took 13.5 there, but longer where there are fewer (1.1 M entries, update and product at N =
+// 16 15.7 / 16.7 us; 3.75 M of cells 19.9 / 21.3).
+constexpr int64_t kUpdateBlock = (int64_t)kThreads * 4;   // positions a workgroup
 
 template <typename Source, bool CSR>
 __global__ __launch_bounds__(kThreads) void k_update_values(
@@ -225,21 +225,13 @@ __global__ __launch_bounds__(kThreads) void k_update_values(
     float* __restrict__ packed, float* __restrict__ csr_vals) {
   const int64_t first = blockIdx.x * kUpdateBlock + 4 * threadIdx.x;
   if ((blockIdx.x + 1) * kUpdateBlock <= nnz) {
-    uint4 e[kUpdateFours];
-    float4 v[kUpdateFours];
-#pragma unroll
-    for (int q = 0; q < kUpdateFours; ++q) e[q] = src.four(first + q * 4 * kThreads);
-#pragma unroll
-    for (int q = 0; q < kUpdateFours; ++q) {
-      v[q].x = vals[e[q].x]; v[q].y = vals[e[q].y]; v[q].z = vals[e[q].z]; v[q].w = vals[e[q].w];
-    }
-#pragma unroll
-    for (int q = 0; q < kUpdateFours; ++q) *reinterpret_cast<float4*>(packed + first + q * 4 * kThreads) = v[q];
+    const uint4 e = src.four(first);
+    float4 v;
+    v.x = vals[e.x]; v.y = vals[e.y]; v.z = vals[e.z]; v.w = vals[e.w];
+    *reinterpret_cast<float4*>(packed + first) = v;
     if constexpr (CSR) {
 #pragma unroll
-      for (int q = 0; q < kUpdateFours; ++q)
-#pragma unroll
-        for (int k = 0; k < 4; ++k) csr_vals[first + q * 4 * kThreads + k] = vals[first + q * 4 * kThreads + k];
+      for (int k = 0; k < 4; ++k) csr_vals[first + k] = vals[first + k];
     }
   } else {
     for (int64_t p = blockIdx.x * kUpdateBlock + threadIdx.x; p < nnz; p += kThreads) {
