@@ -765,9 +765,11 @@ int mfma_fp32_tile(int64_t N, int64_t K, int64_t nnz) {
 //     32.2 / 33.0; N = 256, 2800 of 25 44.5 / 41.8).
 //     Not where the SIMD with most has as many columns as before (blocks of 1977 panels, N = 128 20.7 / 21.0; 463, N = 160,
 //     three tiles for two 8.4 / 8.55).
-//   64 -> 32 and 32 -> 16 where the wider one gives at most 1.25 a SIMD, in 16-byte loads (exec_narrow.hip): 256
-//     panels, N = 64 6.8 / 5.3 / 4.7 and 8.5 / 6.5 / 5.6; 1250 panels, N = 64 10.0 / 9.0 / 9.2; 1024 panels, N = 128
-//     10.4 / 11.0 / 13.4.
+//   64 -> 32 and 32 -> 16 where the wider one gives at most 1.5 a SIMD, in 16-byte loads (exec_narrow.hip): 256
+//     panels, N = 64 6.8 / 5.3 / 4.7 and 8.5 / 6.5 / 5.6; 1250 panels, N = 64 10.0 / 9.0 / 9.2; 1530, N = 64 11.4 / 10.1 and
+//     18.3 / 15.4, N = 32 7.9 / 7.5 and 13.2 / 11.4; 1024 panels, N = 128 10.4 / 11.0 / 13.4. Cells of 3000 panels lose (22.5 /
+//     24.7); split panels gain further (graphs of 2500 panels, N = 64 14.9 / 14.2, N = 96 18.2 / 16.8; of 4000, N = 64 18.4 /
+//     17.9), up to twelve of the narrower a SIMD (of 10,000 31.5 / 31.9).
 // Not where the narrower tiles multiply many columns more than there are: N = 80 as two of 48, 930 panels, 9.1 / 9.7.
 // Work lists and Eq. 7 go by the wide tiles, so which panels are split does not depend on this.
 int mfma_run_tile(const WorkSource& w, int64_t N, int64_t K, int64_t nnz) {
@@ -775,7 +777,7 @@ int mfma_run_tile(const WorkSource& w, int64_t N, int64_t K, int64_t nnz) {
   if (!mfma_32bit_shape(N, K) || !mfma_32bit_values(nnz) || N < 20 || (N > 32 && N < 48)) return whole;
   const int64_t items = (int64_t)w.n_items + w.n_parts;
   auto tiles = [&](int64_t width) { return (N + width - 1) / width; };
-  const bool spread = w.scattered && N % 32 == 0 && K * N * 4 <= kNarrowLargeB;
+  const bool spread = w.scattered && N % 32 == 0 && K * N * 4 < kNarrowLargeB;
   int tile = whole;
   for (int width = 64; width >= 16; width /= 2) {
     const int64_t k = tiles(width), t = ((N + 15) / 16 + k - 1) / k;
@@ -790,7 +792,9 @@ int mfma_run_tile(const WorkSource& w, int64_t N, int64_t K, int64_t nnz) {
     if (width == 64 ? 10 * columns <= 11 * least &&
                           ((less && 2 * items * k <= most * w.simds) ||
                            (spread && (w.any_split || (w.mean_bricks >= 16 && items * k >= 10 * w.simds))))
-                    : 4 * columns < 5 * least && 4 * waves <= 5 * w.simds)
+                    : 4 * columns < 5 * least &&
+                          ((less && 2 * waves <= 3 * w.simds) ||
+                           (width == 32 && spread && w.any_split && items * k <= 12 * w.simds)))
       tile = (int)narrower;
   }
   return tile;

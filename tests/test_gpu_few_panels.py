@@ -19,7 +19,7 @@ def simds():
     return 4 * torch.cuda.get_device_properties(0).multi_processor_count
 
 
-@pytest.mark.parametrize("per_simd", [0.02, 0.6, 1.25, 2.5, 2.6])
+@pytest.mark.parametrize("per_simd", [0.02, 0.6, 1.5, 1.6, 2.5, 2.6])
 @pytest.mark.parametrize("split", [0, 2])
 @pytest.mark.parametrize("scattered", [False, True])
 def test_every_width_on_either_side_of_the_rule(gpu, per_simd, split, scattered):  # noqa: F811
