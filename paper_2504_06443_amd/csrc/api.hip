@@ -99,8 +99,8 @@ class HostStage {
   char* p_ = nullptr;
 };
 
-// A matrix is scattered where the widest span of a panel's columns is more than this many times the mean of
-// a panel's active columns.
+// A matrix is scattered where the spans of its panels' columns add up to more than this many times their active
+// columns (the widest span would make one of every band with a single long row).
 constexpr int64_t kScatteredSpan = 64;
 
 // Waits until the device has set `flag` (pinned memory): by looking for a short while, which is as long as
@@ -131,6 +131,7 @@ struct HostList {
   std::vector<MergeItem> merges;
   std::vector<uint32_t> valu_panels;
   int64_t n_slots = 0;                      // partial 16 x N tiles of split panels
+  int64_t part_bricks = 0;                  // bricks of split panels
 };
 
 // Device half: plan-owned copies of a HostList plus the partial-tile workspace.
@@ -174,7 +175,7 @@ struct spmm_plan {
   // host copies used by the work-list builder and the synergy model
   std::vector<uint32_t> h_panel_ptr;      // empty until a list needs it (need_panel_ptr)
   int64_t max_bricks = 0, n_blocks = 0;   // of a panel; of the matrix (Eq. 6-7's unit)
-  bool scattered = false;                 // a panel's columns lie far apart (kScatteredSpan)
+  bool scattered = false;                 // the columns of most panels lie far apart (kScatteredSpan)
   std::vector<uint8_t> h_panel_class;     // filled with the CSR arrays, for the routes that ask
   unsigned long long h_counters[kNumCounters] = {};
   int64_t n_active_cols = 0;
@@ -421,6 +422,7 @@ int build_host_list(spmm_plan_t* pl, int64_t N, const HostList** out) {
       const int64_t per = ceil_div(blocks, want);          // blocks per part
       const int64_t nparts = ceil_div(blocks, per);        // parts that are not empty
       hl->merges.push_back(MergeItem{(uint32_t)p, (uint32_t)slots, (uint32_t)nparts});
+      hl->part_bricks += nbp;
       for (int64_t q = 0; q < nparts; ++q) {
         const int64_t lo = std::min<int64_t>(nbp, q * per * kBrickK);
         const int64_t hi = std::min<int64_t>(nbp, (q + 1) * per * kBrickK);
@@ -918,7 +920,7 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
     goto done;
   }
 
-  pl->scattered = (int64_t)h_ctl.span * P > kScatteredSpan * pl->n_active_cols;
+  pl->scattered = (int64_t)h_ctl.spans > kScatteredSpan * pl->n_active_cols;
   h_maxnb = (h_ctl.max_cols + kBrickK - 1) / kBrickK;
   if (path == kPathBitmap && !panel_build_fits(words_cap, std::max<uint32_t>(h_maxnb, 1))) {
     path = kPathSearch;   // a panel with more bricks than fit in LDS: finish on the search-based path
@@ -1089,13 +1091,15 @@ int launch_product(const spmm_plan_t* pl, const HostList* hl, const WorkItem* d_
   int status = SPMM_OK;
   const BrickFormat f{pl->panel_ptr, pl->brick_cols, pl->brick_mask, pl->brick_valptr, pl->vals};
   const uint32_t n_listed = (uint32_t)hl->items.size();
-  const bool any_split = !hl->merges.empty();
-  const int32_t simds = 4 * pl->num_cus;
-  const int64_t mean_bricks = pl->nb / std::max<int64_t>(pl->P, 1);
-  const WorkSource work =
-      hl->direct ? WorkSource{nullptr, d_items, (uint32_t)pl->P, n_listed, hl->split_bricks, any_split, simds,
-                              pl->scattered, mean_bricks}
-                 : WorkSource{d_items, nullptr, n_listed, 0, kNoSplit, any_split, simds, pl->scattered, mean_bricks};
+  WorkSource work{d_items, nullptr, n_listed, 0, kNoSplit, 4 * pl->num_cus, pl->scattered, pl->P, pl->nb,
+                  (int64_t)hl->merges.size(), hl->part_bricks};
+  if (hl->direct) {
+    work.items = nullptr;
+    work.parts = d_items;
+    work.n_items = (uint32_t)pl->P;
+    work.n_parts = n_listed;
+    work.split_bricks = hl->split_bricks;
+  }
   if (uses_tm32(pl, B, N, C)) {
     // 32-row panels: one wavefront per super-panel and column tile, no work list
     HIP_TRY(launch_spmm_tm32(pl->tm32.sp_ptr, pl->tm32.bc_cols, pl->tm32.meta, pl->tm32.vals,

@@ -168,7 +168,7 @@ __device__ inline bool work_item(const ItemMap& m, const uint32_t* panel_ptr, ui
 // and 5.90 / 6.07, N = 32 9.94 / 10.2 and 6.93 / 7.13, N = 64 in two tiles 12.3 / 12.7; 3000, N = 16 12.1 / 12.2 and
 // 9.34 / 9.45, N = 32 15.9 / 15.8 and 12.1 / 12.0, N = 64 22.5 / 23.0; 4000, N = 16 14.1 / 14.0, N = 64 29.4 / 28.3.
 inline bool values_by_index(const WorkSource& w, int tile, int64_t tiles) {
-  return w.mean_bricks >= (tile == 32 ? 20 : tile == 16 ? 44 : 64) &&
+  return w.mean_bricks() >= (tile == 32 ? 20 : tile == 16 ? 44 : 64) &&
          2 * tiles * ((int64_t)w.n_items + w.n_parts) >= 7 * (int64_t)w.simds;
 }
 
@@ -179,7 +179,7 @@ constexpr int64_t kNarrowLargeB = int64_t(64) << 20;
 // and 145 -> 140 us, N = 128 115.9 -> 111.2 and 276 -> 267, N = 256 221 -> 214; 100 k rows 36.7 / 37.6.  Matrices of even panels
 // keep four: 400 k rows of blocks, N = 128 181 / 184, cells 0 to 2 % either way.
 inline bool single_waves(const WorkSource& w, int64_t N, int64_t K) {
-  return w.any_split && K * N * 4 >= kNarrowLargeB;
+  return w.n_split > 0 && K * N * 4 >= kNarrowLargeB;
 }
 
 inline bool ptr_aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }

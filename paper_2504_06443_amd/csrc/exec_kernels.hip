@@ -758,18 +758,26 @@ int mfma_fp32_tile(int64_t N, int64_t K, int64_t nnz) {
 //   128 -> 64 columns at up to 2.5 wavefronts a SIMD: 640 panels, N = 128 10.5 / 9.7 and 14.7 / 12.5; 2500 panels
 //     21.1 / 19.3 and 31.9 / 27.8; at 2.9 a SIMD blocks lose (21.6 / 24.0).  Less far where the narrower are not twice
 //     as many (N = 300, 5 tiles for 3: at 3.6 a SIMD 21.3 / 18.3, at 4 a band 13.9 / 14.5), or rows of B are not
-//     aligned (N = 339, at 4.1 a SIMD 23.1 / 21.3, at 4.95 22.0 / 23.0).  Scattered panels, bound by memory and
-//     not by MFMAs, gain beyond that, too, as long as B stays in the Infinity Cache (graph of 4096 panels 30.3 /
-//     26.6, cells of 8192 112.5 / 107.1; a graph of 12,288 panels, B of 100 MB, 73.6 / 75.1): split ones, and whole ones
-//     of many bricks (cells, N = 128, 6000 panels of 25 bricks 46.7 / 44.1, of 6 21.2 / 21.8; 4000 of 25, 7.8 a SIMD,
-//     32.2 / 33.0; N = 256, 2800 of 25 44.5 / 41.8).
+//     aligned (N = 339, at 4.1 a SIMD 23.1 / 21.3, at 4.95 22.0 / 23.0).  Beyond that, as long as B stays in the Infinity
+//     Cache (a graph of 12,288 panels, B of 100 MB, 73.6 / 75.1):
+//     - graphs: scattered panels, bound by memory and not by MFMAs, one in 40 and more of them split (4096 panels 30.3 /
+//       26.6);
+//     - scattered panels of many bricks (cells of 8192 panels 112.5 / 107.1; N = 128, 6000 panels of 25 bricks 46.7 / 44.1, of
+//       6 21.2 / 21.8; 4000 of 25, 7.8 a SIMD, 32.2 / 33.0; N = 256, 2800 of 25 44.5 / 41.8);
+//     - any matrix with split panels whose wide wavefronts are more than the device holds (4 a SIMD, 5 of 96 columns), where
+//       the long ones of a second round end alone: blocks and one row of 1000 entries, 3750 panels 29.6 / 32.9, 4100 39.1 /
+//       35.8, 4500 40.1 / 37.9, 5300 44.6 / 42.9, 6100 45.3 / 48.1, 7100 51.1 / 52.7; so beyond 11/8 rounds only scattered ones
+//       (cells and four long rows, 6100 46.3 / 44.7) and those with one brick in 128 in split panels (blocks and 30 rows of 2000
+//       entries, 6100 56.1 / 52.6, 7100 61.8 / 58.5; one full row, 6250 78.6 / 78.7), of several wide tiles up to 7/4 rounds
+//       (N = 256, 3300 panels and 30 rows 62.0 / 60.0, 3750 62.4 / 65.3).
 //     Not where the SIMD with most has as many columns as before (blocks of 1977 panels, N = 128 20.7 / 21.0; 463, N = 160,
 //     three tiles for two 8.4 / 8.55).
 //   64 -> 32 and 32 -> 16 where the wider one gives at most 1.5 a SIMD, in 16-byte loads (exec_narrow.hip): 256
 //     panels, N = 64 6.8 / 5.3 / 4.7 and 8.5 / 6.5 / 5.6; 1250 panels, N = 64 10.0 / 9.0 / 9.2; 1530, N = 64 11.4 / 10.1 and
 //     18.3 / 15.4, N = 32 7.9 / 7.5 and 13.2 / 11.4; 1024 panels, N = 128 10.4 / 11.0 / 13.4. Cells of 3000 panels lose (22.5 /
-//     24.7); split panels gain further (graphs of 2500 panels, N = 64 14.9 / 14.2, N = 96 18.2 / 16.8; of 4000, N = 64 18.4 /
-//     17.9), up to twelve of the narrower a SIMD (of 10,000 31.5 / 31.9).
+//     24.7); graphs gain further (of 2500 panels, N = 64 14.9 / 14.2, N = 96 18.2 / 16.8; of 4000, N = 64 18.4 /
+//     17.9), up to twelve of the narrower a SIMD (of 10,000 31.5 / 31.9), but no matrix with only a few long rows (blocks and
+//     one of 1000 entries, 3750 panels, N = 64 19.0 / 20.9; cells and one of 2000, 4000 panels 15.8 / 17.0).
 // Not where the narrower tiles multiply many columns more than there are: N = 80 as two of 48, 930 panels, 9.1 / 9.7.
 // Work lists and Eq. 7 go by the wide tiles, so which panels are split does not depend on this.
 int mfma_run_tile(const WorkSource& w, int64_t N, int64_t K, int64_t nnz) {
@@ -777,7 +785,13 @@ int mfma_run_tile(const WorkSource& w, int64_t N, int64_t K, int64_t nnz) {
   if (!mfma_32bit_shape(N, K) || !mfma_32bit_values(nnz) || N < 20 || (N > 32 && N < 48)) return whole;
   const int64_t items = (int64_t)w.n_items + w.n_parts;
   auto tiles = [&](int64_t width) { return (N + width - 1) / width; };
-  const bool spread = w.scattered && N % 32 == 0 && K * N * 4 < kNarrowLargeB;
+  const bool whole_lines = N % 32 == 0 && K * N * 4 < kNarrowLargeB;
+  const bool graph = w.scattered && 40 * w.n_split >= w.panels;
+  const int64_t wide = items * tiles(whole);
+  const int64_t round = (whole > 96 ? 4 : 5) * (int64_t)w.simds;
+  const bool second_round = w.n_split > 0 && wide > round &&
+                            (w.scattered || 8 * wide <= 11 * round ||
+                             (128 * w.part_bricks >= w.bricks && (tiles(whole) == 1 || 4 * wide <= 7 * round)));
   int tile = whole;
   for (int width = 64; width >= 16; width /= 2) {
     const int64_t k = tiles(width), t = ((N + 15) / 16 + k - 1) / k;
@@ -787,14 +801,15 @@ int mfma_run_tile(const WorkSource& w, int64_t N, int64_t K, int64_t nnz) {
     if (narrower >= tile) continue;
     const int64_t most = k < 2 * tiles(whole) ? 8 : (N % 4 ? 9 : 10);   // narrower wavefronts for two SIMDs
     // columns of the SIMD with most: no gain where that stays, but for wavefronts that were alone
-    const int64_t then = (items * k + w.simds - 1) / w.simds * narrower, wide = items * tiles(whole);
+    const int64_t then = (items * k + w.simds - 1) / w.simds * narrower;
     const bool less = then < (wide + w.simds - 1) / w.simds * whole + (wide <= w.simds ? 1 : 0);
     if (width == 64 ? 10 * columns <= 11 * least &&
                           ((less && 2 * items * k <= most * w.simds) ||
-                           (spread && (w.any_split || (w.mean_bricks >= 16 && items * k >= 10 * w.simds))))
+                           (whole_lines && (graph || second_round ||
+                                            (w.scattered && w.mean_bricks() >= 16 && items * k >= 10 * w.simds))))
                     : 4 * columns < 5 * least &&
                           ((less && 2 * waves <= 3 * w.simds) ||
-                           (width == 32 && spread && w.any_split && items * k <= 12 * w.simds)))
+                           (width == 32 && whole_lines && graph && items * k <= 12 * w.simds)))
       tile = (int)narrower;
   }
   return tile;
@@ -836,7 +851,7 @@ hipError_t launch_spmm_mfma(const BrickFormat& f, const WorkSource& w, const flo
     // 25 k to 400 k rows: 2 to 12 % ahead or the same.  The tiles of few panels at wider N are ahead or the same, split
     // or not (graph of 640 panels, N = 64 9.7 / 9.2).
     const int tile = mfma_run_tile(w, N, K, nnz);
-    if (N >= 4 && tile <= 32 && (N > 32 || !w.any_split || N <= 8 || K * N * 4 >= kNarrowLargeB))
+    if (N >= 4 && tile <= 32 && (N > 32 || w.n_split == 0 || N <= 8 || K * N * 4 >= kNarrowLargeB))
       return launch_spmm_mfma_narrow(f, w, tile, B, C, partial, M, N, K, s);
     const unsigned gy = (unsigned)((N + tile - 1) / tile);
     const uint32_t k_last = (uint32_t)(K - 1);

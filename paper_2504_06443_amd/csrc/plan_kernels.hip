@@ -785,6 +785,14 @@ constexpr uint32_t kSortSmall = 512, kSortMid = 2048, kSortBig = 8192;   // entr
 struct PanelTotals {
   uint32_t bricks, blocks, cols, max_cols;
   uint32_t span, max_nnz, err, skipped;   // skipped: a panel without a count
+  unsigned long long spans;               // the sum of the panels'
+  __device__ void add(const PanelTotals& o) {
+    bricks += o.bricks; blocks += o.blocks; cols += o.cols;
+    max_cols = max(max_cols, o.max_cols);
+    span = max(span, o.span); max_nnz = max(max_nnz, o.max_nnz);
+    err |= o.err; skipped |= o.skipped;
+    spans += o.spans;
+  }
 };
 
 typedef int32_t Int4Any __attribute__((ext_vector_type(4), aligned(4)));   // at any dword address
@@ -875,6 +883,7 @@ __global__ __launch_bounds__(kFirstThreads, 8) void k_rows_census(
     const uint32_t span = (uint32_t)((int64_t)cmax - cmin + 1);
     const uint32_t words = (span + 31) / 32;
     t.span = max(t.span, span);
+    t.spans += span;
     t.err |= err;
     if (err || words > kFirstWords || words > 4 * n + 64) {
       t.skipped = 1;
@@ -946,10 +955,7 @@ __global__ __launch_bounds__(kFirstThreads, 8) void k_rows_census(
   if (threadIdx.x == 0) {
     for (int w = 1; w < kFirstWaves; ++w) {
       const PanelTotals o = s_tot[w];
-      t.bricks += o.bricks; t.blocks += o.blocks; t.cols += o.cols;
-      t.max_cols = max(t.max_cols, o.max_cols);
-      t.span = max(t.span, o.span); t.max_nnz = max(t.max_nnz, o.max_nnz);
-      t.err |= o.err; t.skipped |= o.skipped;
+      t.add(o);
     }
     totals[blockIdx.x] = t;
   }
@@ -973,13 +979,10 @@ __global__ __launch_bounds__(kScanThreads) void k_census_scan(
   for (uint32_t b = threadIdx.x; b < n_totals; b += kScanThreads) {
     const PanelTotals o = totals[b];
     if (b < blockIdx.x * group) before += o.bricks;
-    t.bricks += o.bricks; t.blocks += o.blocks; t.cols += o.cols;
-    t.max_cols = max(t.max_cols, o.max_cols);
-    t.span = max(t.span, o.span); t.max_nnz = max(t.max_nnz, o.max_nnz);
-    t.err |= o.err; t.skipped |= o.skipped;
+    t.add(o);
   }
   t = PanelTotals{wave_sum(t.bricks), wave_sum(t.blocks), wave_sum(t.cols), wave_max(t.max_cols),
-                  wave_max(t.span), wave_max(t.max_nnz), wave_or(t.err), wave_or(t.skipped)};
+                  wave_max(t.span), wave_max(t.max_nnz), wave_or(t.err), wave_or(t.skipped), wave_sum(t.spans)};
   before = wave_sum(before);
   if ((threadIdx.x & 63) == 0) { s_tot[threadIdx.x >> 6] = t; s_before[threadIdx.x >> 6] = before; }
   __syncthreads();
@@ -988,23 +991,20 @@ __global__ __launch_bounds__(kScanThreads) void k_census_scan(
 #pragma unroll
   for (int w = 1; w < kScanThreads / 64; ++w) {
     const PanelTotals o = s_tot[w];
-    t.bricks += o.bricks; t.blocks += o.blocks; t.cols += o.cols;
-    t.max_cols = max(t.max_cols, o.max_cols);
-    t.span = max(t.span, o.span); t.max_nnz = max(t.max_nnz, o.max_nnz);
-    t.err |= o.err; t.skipped |= o.skipped;
+    t.add(o);
     at += s_before[w];
   }
   const bool counted = !t.skipped && !t.err;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     PlanControl c;                 // (its counters stay as they are)
-    c.err = t.err; c.span = t.span; c.max_nnz = t.max_nnz; c.counted = counted;
+    c.err = t.err; c.span = t.span; c.max_nnz = t.max_nnz; c.counted = counted; c.spans = t.spans;
     c.max_cols = counted ? t.max_cols : 0;
     c.nb = counted ? t.bricks : 0;
     c.n_active = counted ? t.cols : 0;
     c.n_blocks = counted ? t.blocks : 0;
     for (PlanControl* to : {ctl, pinned}) {
       if (!to) continue;
-      to->err = c.err; to->span = c.span; to->max_nnz = c.max_nnz; to->counted = c.counted;
+      to->err = c.err; to->span = c.span; to->max_nnz = c.max_nnz; to->counted = c.counted; to->spans = c.spans;
       to->max_cols = c.max_cols; to->nb = c.nb; to->n_active = c.n_active; to->n_blocks = c.n_blocks;
     }
     if (counted) panel_ptr[P] = t.bricks;
@@ -1697,7 +1697,7 @@ hipError_t launch_rows_census(const int32_t* rowptr, const int32_t* colind, int6
                               uint32_t* ncols_p, uint32_t* panel_ptr, uint32_t* tmp, PlanControl* ctl,
                               PlanControl* pinned, uint32_t* flag, uint32_t* mid_list, uint32_t* big_list,
                               void* clear, size_t clear_bytes, hipStream_t s) {
-  static_assert(sizeof(PanelTotals) == 32, "eight words of `tmp` each");
+  static_assert(sizeof(PanelTotals) == 40, "ten words of `tmp` each");
   PanelTotals* totals = reinterpret_cast<PanelTotals*>(tmp);
   const int64_t want = std::max<int64_t>(1, std::min<int64_t>((P + kFirstWaves - 1) / kFirstWaves, kFirstBlocks));
   const int64_t run = std::max<int64_t>(1, (P + want - 1) / want);

@@ -41,6 +41,7 @@ struct PlanControl {        // device, zeroed when a plan begins; read back at i
   uint32_t pad;
   unsigned long long n_active;   // active columns, summed over the panels
   unsigned long long n_blocks;   // blocks of four bricks, every panel rounded up
+  unsigned long long spans;      // column spans, summed over the panels
   unsigned long long counters[kNumCounters];
 };
 
@@ -62,10 +63,12 @@ struct WorkSource {
   uint32_t n_items;         // of the list, or panels
   uint32_t n_parts;
   uint32_t split_bricks;    // kNoSplit where `parts` is empty
-  bool any_split;           // of the items and parts, some are parts
   int32_t simds;            // of the device
-  bool scattered;           // columns of a panel lie far apart: its B rows are its own
-  int64_t mean_bricks;      // of a panel
+  bool scattered;           // the columns of most panels lie far apart: their B rows are their own
+  int64_t panels, bricks;   // of the matrix,
+  int64_t n_split;          // and of those the panels that are split
+  int64_t part_bricks;      // with their bricks
+  int64_t mean_bricks() const { return bricks / (panels > 1 ? panels : 1); }
 };
 constexpr uint32_t kNoSplit = 0xFFFFFFFFu;
 

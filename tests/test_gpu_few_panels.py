@@ -83,3 +83,39 @@ def test_infinities_stay_in_their_panels(gpu, N):  # noqa: F811
         B[4 * n - 1] = np.inf
         C = gpu.spmm_exec(plan, torch.from_numpy(B).cuda()).cpu().numpy()
         np.testing.assert_array_equal(np.isfinite(C), np.repeat((bricks < n)[:, None], N, 1))
+
+
+def with_long_rows(A, rows, entries):
+    """A with `rows` of its rows stored in `entries` columns spread over all of them."""
+    at = (np.arange(rows) + 1) * A.M // (rows + 1)
+    old = np.repeat(np.arange(A.M), np.diff(A.rowptr))
+    keep = ~np.isin(old, at)
+    row = np.concatenate([old[keep], np.repeat(at, entries)])
+    col = np.concatenate([A.colind[keep], np.tile(np.arange(entries) * A.K // entries, rows)])
+    return W.csr_from_coo(A.M, A.K, row, col, np.random.default_rng(rows).uniform(-1, 1, len(row)).astype(np.float32))
+
+
+@pytest.mark.parametrize("per_simd, rows, entries, tiles", [
+    (3.66, 0, 0, {64: 64, 128: 128}),            # even panels, more than narrow tiles are for,
+    (3.66, 1, 1000, {64: 64, 96: 96, 128: 128}),     # and the same with a long row: neither a graph
+    (4.4, 1, 1000, {64: 64, 128: 64}),           # but just over what the device holds
+    (6.1, 1, 1000, {64: 64, 128: 128}),
+    (6.1, 30, 2000, {64: 64, 128: 64}),          # or with much of the matrix in long rows
+    (2.0, "graph", 0, {64: 32, 96: 32, 128: 32}),
+    (6.1, "graph", 0, {64: 64, 96: 96, 128: 64})])
+def test_a_few_long_rows_do_not_make_a_graph(gpu, per_simd, rows, entries, tiles):  # noqa: F811
+    import torch
+    M = 16 * int(per_simd * simds())
+    A = W.power_law(M, target_nnz=int(2.854 * M), seed=3) if rows == "graph" else W.clustered_blocks(M, 4, 60, seed=7)
+    if rows != "graph" and rows:
+        A = with_long_rows(A, rows, entries)
+    plan = make_plan(gpu, A)
+    Ball = W.dense_b(A.K, max(tiles), 11)
+    Call, S = oracle.spmm_f64(A.rowptr, A.colind, A.vals, Ball)
+    for N, tile in tiles.items():
+        assert (gpu.spmm_plan_worklist(plan, N)["n_split_panels"] > 0) == (rows != 0)
+        B = torch.from_numpy(Ball[:, :N].copy()).cuda()
+        C = gpu.spmm_exec(plan, B)
+        names = kernels_of(lambda: gpu.spmm_exec(plan, B))
+        assert "fast<%d," % (tile // 16) in names or "narrow<%d," % (tile // 16) in names, (N, names)
+        check_c(C.cpu().numpy(), Call[:, :N], S[:, :N])
