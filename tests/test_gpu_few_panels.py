@@ -119,3 +119,27 @@ def test_a_few_long_rows_do_not_make_a_graph(gpu, per_simd, rows, entries, tiles
         names = kernels_of(lambda: gpu.spmm_exec(plan, B))
         assert "fast<%d," % (tile // 16) in names or "narrow<%d," % (tile // 16) in names, (N, names)
         check_c(C.cpu().numpy(), Call[:, :N], S[:, :N])
+
+
+@pytest.mark.parametrize("N", [32, 64, 128])
+@pytest.mark.parametrize("rows, waves", [(1, 4), (9, 4), ("graph", 1)])
+def test_long_rows_over_a_large_b(gpu, N, rows, waves):  # noqa: F811
+    """Workgroups of one wavefront are for graphs, not for a band with a few long rows."""
+    import torch
+    M = 16 * 4133 - 3
+    A = W.power_law(M, target_nnz=int(2.854 * M), seed=3) if rows == "graph" else \
+        with_long_rows(W.clustered_blocks(M, 3, 40, seed=7), rows, 3000)
+    step = -(-(64 << 20) // (4 * N * A.K))
+    K = step * A.K + 5                                      # 64 MiB of B
+    col = (A.colind.astype(np.int64) * step + 5).astype(np.int32)
+    plan = gpu.spmm_plan(A.M, K, torch.from_numpy(A.rowptr).cuda(), torch.from_numpy(col).cuda(),
+                         torch.from_numpy(A.vals).cuda())
+    assert gpu.spmm_plan_worklist(plan, N)["n_split_panels"] > 0
+    B = W.dense_b(A.K, N, 11)
+    Bd = torch.zeros((K, N), device="cuda")
+    Bd[torch.arange(A.K, device="cuda") * step + 5] = torch.from_numpy(B).cuda()
+    C = gpu.spmm_exec(plan, Bd)
+    names = kernels_of(lambda: gpu.spmm_exec(plan, Bd))
+    assert ", %d>" % waves in names, names
+    Cref, S = oracle.spmm_f64(A.rowptr, A.colind, A.vals, B)
+    check_c(C.cpu().numpy(), Cref, S)
