@@ -879,7 +879,7 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
     // ---- a1/a2: census (also validates colind) -> bricks per panel
     HIP_TRY(launch_panel_census(rowptr, colind, M, K, P, words_cap, &ctl->err, ncols_p, s));
   } else if (path == kPathSort) {
-    HIP_TRY(launch_panel_sort_census(rowptr, colind, M, K, P, nnz, h_ctl.max_nnz,
+    HIP_TRY(launch_panel_sort_census(rowptr, colind, M, K, P, nnz, h_ctl.max_nnz, h_ctl.n_listed,
                                      mid_list, big_list, ctl, ncols_p, pl->src.entries, s));
   } else {
     // ---- search-based path for every other matrix.  Its a1

@@ -786,12 +786,13 @@ struct PanelTotals {
   uint32_t bricks, blocks, cols, max_cols;
   uint32_t span, max_nnz, err, skipped;   // skipped: a panel without a count
   unsigned long long spans;               // the sum of the panels'
+  uint32_t listed, unused;                // panels of more than kSortSmall entries
   __device__ void add(const PanelTotals& o) {
     bricks += o.bricks; blocks += o.blocks; cols += o.cols;
     max_cols = max(max_cols, o.max_cols);
     span = max(span, o.span); max_nnz = max(max_nnz, o.max_nnz);
     err |= o.err; skipped |= o.skipped;
-    spans += o.spans;
+    spans += o.spans; listed += o.listed;
   }
 };
 
@@ -874,6 +875,7 @@ __global__ __launch_bounds__(kFirstThreads, 8) void k_rows_census(
     }
     const int32_t cmin = __builtin_amdgcn_readfirstlane(lo), cmax = __builtin_amdgcn_readfirstlane(hi);
     t.max_nnz = max(t.max_nnz, n);
+    t.listed += n > kSortSmall ? 1u : 0u;
     if (cmax < cmin) {
       t.err |= err | (n ? (uint32_t)kErrColOrder : 0u);
       if (lane == 0) ncols_p[p] = 0;
@@ -982,7 +984,8 @@ __global__ __launch_bounds__(kScanThreads) void k_census_scan(
     t.add(o);
   }
   t = PanelTotals{wave_sum(t.bricks), wave_sum(t.blocks), wave_sum(t.cols), wave_max(t.max_cols),
-                  wave_max(t.span), wave_max(t.max_nnz), wave_or(t.err), wave_or(t.skipped), wave_sum(t.spans)};
+                  wave_max(t.span), wave_max(t.max_nnz), wave_or(t.err), wave_or(t.skipped), wave_sum(t.spans),
+                  wave_sum(t.listed), 0};
   before = wave_sum(before);
   if ((threadIdx.x & 63) == 0) { s_tot[threadIdx.x >> 6] = t; s_before[threadIdx.x >> 6] = before; }
   __syncthreads();
@@ -998,6 +1001,7 @@ __global__ __launch_bounds__(kScanThreads) void k_census_scan(
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     PlanControl c;                 // (its counters stay as they are)
     c.err = t.err; c.span = t.span; c.max_nnz = t.max_nnz; c.counted = counted; c.spans = t.spans;
+    c.n_listed = t.listed;
     c.max_cols = counted ? t.max_cols : 0;
     c.nb = counted ? t.bricks : 0;
     c.n_active = counted ? t.cols : 0;
@@ -1005,6 +1009,7 @@ __global__ __launch_bounds__(kScanThreads) void k_census_scan(
     for (PlanControl* to : {ctl, pinned}) {
       if (!to) continue;
       to->err = c.err; to->span = c.span; to->max_nnz = c.max_nnz; to->counted = c.counted; to->spans = c.spans;
+      to->n_listed = c.n_listed;
       to->max_cols = c.max_cols; to->nb = c.nb; to->n_active = c.n_active; to->n_blocks = c.n_blocks;
     }
     if (counted) panel_ptr[P] = t.bricks;
@@ -1056,20 +1061,18 @@ __global__ __launch_bounds__(kScanThreads) void k_census_scan(
 // workgroup of 256, up to 8192 one of 1024.  All sort in registers, up to eight keys a lane: a
 // compare-exchange inside a lane is a min and a max, across lanes one cross-lane read a key, and only
 // steps across wavefronts go through LDS (a sort all through LDS moved four words a pair and step).
-// Where the two upper classes are the few heavy panels of many light ones, as in graphs, their columns are ranked by
-// a bitmap of all columns instead (k_panel_bitmap_census).
+// The columns of the largest class, and of few panels of the middle one beside it, are ranked by a bitmap of all columns
+// instead, where that fits (k_panel_bitmap_census).
 // The census leaves the entries, rank << 16 | index inside the panel, for the build, sorted or as they are stored.
-// 20,360 panels of 46 entries, the largest 3000: the search-based kernels 167 us, sorting all classes 84 (keys of 32
-// bits for the 48 panels above 2048: 30 -> 19 us).
+// 20,360 panels of 46 entries, the largest 3000: the search-based kernels 167 us, sorting all classes 84.
 // 18,750 panels of 430: a sort through LDS by one wavefront 163 + 101 us (census, build), now 84 + 67.
 constexpr int kMidThreads = 256, kBigThreads = 1024;
 static_assert(kMidThreads * 8 == kSortMid && kBigThreads * 8 == kSortBig, "eight keys a lane");
 
 // A key is column << B | index.  In 32 bits, half the moves of a 64-bit one: B = 11 for panels of up to
-// kSortMid entries and fewer than 2^21 columns, B = 13 for up to kSortBig and fewer than 2^19 (fewer,
-// so that no key is all ones, which pads).  In 64 bits: B = 32.
-constexpr int kMidBits = 11, kBigBits = 13;
-static_assert(kSortMid <= 1u << kMidBits && kSortBig <= 1u << kBigBits, "indexes fit");
+// kSortMid entries and fewer than 2^21 columns (fewer, so that no key is all ones, which pads).  In 64 bits: B = 32.
+constexpr int kMidBits = 11;
+static_assert(kSortMid <= 1u << kMidBits, "indexes fit");
 template <typename KT, int B> struct SortKey {
   static __device__ KT make(uint32_t col, uint32_t idx) { return ((KT)col << B) | idx; }
   static __device__ uint32_t col(KT k) { return (uint32_t)(k >> B); }
@@ -1277,39 +1280,52 @@ __global__ __launch_bounds__(kMidThreads) void k_panel_sort_census(
   if ((threadIdx.x & 63) == 0) ncols_p[p] = cols;
 }
 
-// census of the listed panels of at most kSortBig entries, a workgroup each
-template <typename KT, int B>
+// census of the listed panels of at most kSortBig entries, a workgroup each (columns beyond the bitmaps, so keys of 64
+// bits)
 __global__ __launch_bounds__(kBigThreads) void k_panel_sort_census_big(
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind, int64_t M, int64_t K,
     const uint32_t* __restrict__ list, const uint32_t* __restrict__ listed, uint32_t* err,
     uint32_t* __restrict__ ncols_p, uint32_t* __restrict__ order) {
-  __shared__ KT lds[kSortBig];
+  __shared__ unsigned long long lds[kSortBig];
   __shared__ uint32_t sums[kBigThreads / 64];
   if (blockIdx.x >= *listed) return;   // (the host does not know the count yet)
   const int64_t p = list[blockIdx.x];
   const PanelRows x(rowptr, M, p);
   uint32_t cols = 0;
-  if (x.n <= kBigThreads * 4) cols = group_census<kBigThreads, 4, B, KT>(colind, x, K, err, order, lds, sums);
-  else if (x.n <= kSortBig) cols = group_census<kBigThreads, 8, B, KT>(colind, x, K, err, order, lds, sums);
+  if (x.n <= kBigThreads * 4)
+    cols = group_census<kBigThreads, 4, 32, unsigned long long>(colind, x, K, err, order, lds, sums);
+  else if (x.n <= kSortBig)
+    cols = group_census<kBigThreads, 8, 32, unsigned long long>(colind, x, K, err, order, lds, sums);
   if (threadIdx.x == 0) ncols_p[p] = cols;
 }
 
-// Census of the listed panels by a bitmap of all columns, a workgroup each: no order, so no sort, and a rank from a
+// Census of listed panels by a bitmap of all columns, a workgroup each: no order, so no sort, and a rank from a
 // table of the bits set before every eighth word.  `order` keeps the entries as they are stored.
-// Bound by latency, so all loads of a thread are in flight at once.  207 listed panels of 20,360, 325,760 columns:
-// their share of the sorting launches 27 + 19 -> 11 us beside 23 for the small ones (spmm_plan 159 -> 138); 30,000
-// rows 117 -> 93.  Bitmaps of a million columns leave a CU one workgroup: 640 listed panels 65 us, sorted 40.
+// Bound by latency, so all loads of a thread are in flight at once.  A workgroup clears and counts the whole bitmap,
+// however few entries it has, so which panels come here goes by how many they are.  us, census of all classes, sorted
+// / the largest class by bitmap / the middle one, too (in brackets: panels of the largest, of the middle class):
+//   graphs of 30,000 rows (4, 11) 32.0 / 20.8 / 15.8; of 326,000 (32, 156) 44.3 / 34.6 / 32.6; of 460,000 (53, 219) 50.7 / 43.0 / 44.3
+//   65,536 columns, 4000 and 600 entries, (1, 450) 29.3 / 19.2 / 15.1; 8000 entries, (16, 1000) 50.9 / 24.8 / 23.5
+//   262,144 columns, 4000 and 600 entries, (1, 0) 33.0 / 23.8; (16, 450) 37.9 / 28.4 / 26.2; (16, 1000) 41.7 / 32.9 / 33.4; (64, 3000)
+//     56.7 / 47.1 / 59.3; (700, 450) 64.2 / 40.3 / 42.0
+//   524,288 columns, (16, 450) 59.1 / 41.9 / 41.9; (16, 1000) 62.8 / 45.8 / 54.1; (64, 3000) 77.4 / 60.1 / 99.1; (700, 0) 99.3 / 56.6;
+//     2100 entries, (1500, 0) 156 / 73
+// The largest class is ahead everywhere: it is spared a launch and the longest sorts.  The middle class alone, whose
+// sorts run beside those of the small panels, is behind (65,536 columns, 16 panels of 600 10.1 / 12.3; 524,288, 4096 of
+// them 53.7 / 114.7), and with the largest ahead as long as all are one round of workgroups, two a CU.
+// Bitmaps of a million columns leave a CU one workgroup: 640 listed panels 65 us, sorted 40.
 constexpr int kListedThreads = 1024;
 constexpr uint32_t kListedMaxWords = 16384;          // 512 Ki columns: 72 KiB of LDS with the table
+constexpr uint32_t kListedRound = 512;
 
 __global__ __launch_bounds__(kListedThreads) void k_panel_bitmap_census(
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind, int64_t M, int64_t K,
     const uint32_t* __restrict__ mid_list, const uint32_t* __restrict__ big_list, const PlanControl* ctl,
-    uint32_t words, uint32_t* err, uint32_t* __restrict__ ncols_p, uint32_t* __restrict__ order) {
+    bool with_mid, uint32_t words, uint32_t* err, uint32_t* __restrict__ ncols_p, uint32_t* __restrict__ order) {
   extern __shared__ uint32_t lds[];
   __shared__ uint32_t sums[kListedThreads / 64];
   uint32_t *bm = lds, *pre = lds + words;   // [words], [words / kGroupWords, rounded up]
-  const uint32_t n_big = ctl->n_big, n_mid = ctl->n_mid;   // (the host does not know them yet)
+  const uint32_t n_big = ctl->n_big, n_mid = with_mid ? ctl->n_mid : 0u;   // (the host does not know them yet)
   if (blockIdx.x >= n_big + n_mid) return;
   const int64_t p = blockIdx.x < n_big ? big_list[blockIdx.x] : mid_list[blockIdx.x - n_big];
   const PanelRows x(rowptr, M, p);
@@ -1697,7 +1713,7 @@ hipError_t launch_rows_census(const int32_t* rowptr, const int32_t* colind, int6
                               uint32_t* ncols_p, uint32_t* panel_ptr, uint32_t* tmp, PlanControl* ctl,
                               PlanControl* pinned, uint32_t* flag, uint32_t* mid_list, uint32_t* big_list,
                               void* clear, size_t clear_bytes, hipStream_t s) {
-  static_assert(sizeof(PanelTotals) == 40, "ten words of `tmp` each");
+  static_assert(sizeof(PanelTotals) == 48, "twelve words of `tmp` each");
   PanelTotals* totals = reinterpret_cast<PanelTotals*>(tmp);
   const int64_t want = std::max<int64_t>(1, std::min<int64_t>((P + kFirstWaves - 1) / kFirstWaves, kFirstBlocks));
   const int64_t run = std::max<int64_t>(1, (P + want - 1) / want);
@@ -1881,18 +1897,15 @@ bool panel_sort_fits(int64_t P, int64_t nnz, uint32_t max_nnz) {
 int64_t panel_mid_list_elems(int64_t nnz) { return nnz / kSortSmall; }
 int64_t panel_big_list_elems(int64_t nnz) { return nnz / kSortMid; }
 
-// The listed panels go through a bitmap of all columns where they are the few heavy ones of many: at most 128
-// entries a panel in the mean, so at most a quarter of the panels is listed.
-constexpr int64_t kFewListedMean = 128;
-
 hipError_t launch_panel_sort_census(const int32_t* rowptr, const int32_t* colind, int64_t M,
-                                    int64_t K, int64_t P, int64_t nnz, uint32_t max_nnz,
+                                    int64_t K, int64_t P, int64_t nnz, uint32_t max_nnz, uint32_t n_listed,
                                     const uint32_t* mid_list, const uint32_t* big_list, PlanControl* ctl,
                                     uint32_t* ncols_p, uint32_t* order, hipStream_t s) {
   if (P == 0) return hipSuccess;
-  const bool narrow = K < (int64_t(1) << (32 - kMidBits)), narrow_big = K < (int64_t(1) << (32 - kBigBits));
+  const bool narrow = K < (int64_t(1) << (32 - kMidBits));
   const int64_t words = (K + 31) / 32;
-  const bool listed = max_nnz > kSortSmall, bitmap = listed && nnz <= kFewListedMean * P && words <= kListedMaxWords;
+  const bool bitmap = max_nnz > kSortMid && words <= kListedMaxWords;   // (see the kernel)
+  const bool with_mid = bitmap && n_listed <= kListedRound;
   if (bitmap) {
     const size_t lds = (size_t)(words + (words + kGroupWords - 1) / kGroupWords) * 4;
     if (lds > 48 * 1024) {
@@ -1900,11 +1913,11 @@ hipError_t launch_panel_sort_census(const int32_t* rowptr, const int32_t* colind
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
       if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(k_panel_bitmap_census, dim3((unsigned)std::min(P, panel_mid_list_elems(nnz))),
-                       dim3(kListedThreads), lds, s, rowptr, colind, M, K, mid_list, big_list, ctl, (uint32_t)words,
-                       &ctl->err, ncols_p, order);
+    const int64_t at_most = with_mid ? n_listed : std::min<int64_t>(n_listed, panel_big_list_elems(nnz));
+    hipLaunchKernelGGL(k_panel_bitmap_census, dim3((unsigned)at_most), dim3(kListedThreads), lds, s, rowptr, colind, M, K, mid_list, big_list, ctl, with_mid,
+                       (uint32_t)words, &ctl->err, ncols_p, order);
   }
-  const bool mid = listed && !bitmap;
+  const bool mid = max_nnz > kSortSmall && !with_mid;
   const unsigned mid_blocks = mid ? (unsigned)std::min(P, panel_mid_list_elems(nnz)) : 0u;
   const dim3 grid(mid_blocks + grid_for(P, kMidThreads / 64)), block(kMidThreads);
 #define SPMM_LAUNCH_CENSUS(KT, BITS, MID)                                                         \
@@ -1920,12 +1933,8 @@ hipError_t launch_panel_sort_census(const int32_t* rowptr, const int32_t* colind
 #undef SPMM_LAUNCH_CENSUS
   if (max_nnz > kSortMid && !bitmap) {
     const dim3 at_most((unsigned)std::min(P, panel_big_list_elems(nnz))), big(kBigThreads);
-    if (narrow_big)
-      hipLaunchKernelGGL((k_panel_sort_census_big<uint32_t, kBigBits>), at_most, big, 0, s, rowptr,
-                         colind, M, K, big_list, &ctl->n_big, &ctl->err, ncols_p, order);
-    else
-      hipLaunchKernelGGL((k_panel_sort_census_big<unsigned long long, 32>), at_most, big, 0, s, rowptr,
-                         colind, M, K, big_list, &ctl->n_big, &ctl->err, ncols_p, order);
+    hipLaunchKernelGGL(k_panel_sort_census_big, at_most, big, 0, s, rowptr, colind, M, K, big_list, &ctl->n_big,
+                       &ctl->err, ncols_p, order);
   }
   return hipGetLastError();
 }

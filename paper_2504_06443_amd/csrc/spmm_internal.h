@@ -38,7 +38,7 @@ struct PlanControl {        // device, zeroed when a plan begins; read back at i
   uint32_t n_mid, n_big;    // panels in the lists of the sort-based path
   uint32_t counted;         // every panel's columns were counted in the first pass
   uint32_t ended;           // workgroups of k_plan_stats that have ended
-  uint32_t pad;
+  uint32_t n_listed;        // panels of more entries than a wavefront sorts, before the lists are there
   unsigned long long n_active;   // active columns, summed over the panels
   unsigned long long n_blocks;   // blocks of four bricks, every panel rounded up
   unsigned long long spans;      // column spans, summed over the panels
@@ -158,7 +158,7 @@ int64_t panel_mid_list_elems(int64_t nnz);   // room the lists need
 int64_t panel_big_list_elems(int64_t nnz);
 bool panel_sort_fits(int64_t P, int64_t nnz, uint32_t max_nnz);
 hipError_t launch_panel_sort_census(const int32_t* rowptr, const int32_t* colind, int64_t M,
-                                    int64_t K, int64_t P, int64_t nnz, uint32_t max_nnz,
+                                    int64_t K, int64_t P, int64_t nnz, uint32_t max_nnz, uint32_t n_listed,
                                     const uint32_t* mid_list, const uint32_t* big_list,
                                     PlanControl* ctl, uint32_t* ncols_p,
                                     uint32_t* order /* [nnz]; read back by the build from src */,
