@@ -920,7 +920,7 @@ int spmm_plan(int64_t M, int64_t K, int64_t nnz, const int32_t* rowptr, const in
     goto done;
   }
 
-  pl->scattered = (int64_t)h_ctl.spans > kScatteredSpan * pl->n_active_cols;
+  pl->scattered = h_ctl.spans > (float)(kScatteredSpan * pl->n_active_cols);
   h_maxnb = (h_ctl.max_cols + kBrickK - 1) / kBrickK;
   if (path == kPathBitmap && !panel_build_fits(words_cap, std::max<uint32_t>(h_maxnb, 1))) {
     path = kPathSearch;   // a panel with more bricks than fit in LDS: finish on the search-based path

@@ -38,10 +38,11 @@ struct PlanControl {        // device, zeroed when a plan begins; read back at i
   uint32_t n_mid, n_big;    // panels in the lists of the sort-based path
   uint32_t counted;         // every panel's columns were counted in the first pass
   uint32_t ended;           // workgroups of k_plan_stats that have ended
-  uint32_t n_listed;        // panels of more entries than a wavefront sorts, before the lists are there
+  uint32_t n_listed;        // panels of the lists, before these are there, or 65,535
+  float spans;              // column spans, summed over the panels
+  uint32_t pad;
   unsigned long long n_active;   // active columns, summed over the panels
   unsigned long long n_blocks;   // blocks of four bricks, every panel rounded up
-  unsigned long long spans;      // column spans, summed over the panels
   unsigned long long counters[kNumCounters];
 };
 
