@@ -6,15 +6,19 @@ where its arguments are plain tensors, everything else through ctypes.
 Device arrays are torch tensors (PyTorch is used for device memory and
 streams); results of host-side queries come back as plain Python / numpy.
 Importing this module raises if the library has not been built: there is no
-fallback path.
+fallback path.  Without _native, or with one made for another torch, it warns:
+every call then goes through ctypes, to the same library.
 """
 from __future__ import annotations
 
 import ctypes as C
 import os
+import warnings
 
 import numpy as np
 import torch  # first: the library must bind to the HIP runtime torch has already loaded
+
+from .build import NATIVE, native_is_current
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libspmm_brick.so")
@@ -26,14 +30,29 @@ if not os.path.exists(LIB_PATH):
 
 _lib = C.CDLL(LIB_PATH)
 
-# (a product of 4096 rows, N = 32, one behind another: 8.5 us through ctypes, 3.7 so, as when replayed from a graph)
-try:
-    from . import _native
-except ImportError as e:
-    raise ImportError(f"{_HERE}/_native.so not found or not loadable ({e}): build it with "
-                      "`python -m paper_2504_06443_amd.build` (or __graft_entry__.build())") from e
-_native.bind(*(C.cast(f, C.c_void_p).value for f in
-               (_lib.spmm_exec, _lib.spmm_exec_noalloc, _lib.spmm_plan_update_values, _lib.spmm_plan)))
+
+class _ThroughCtypes:
+    """In the place of _native: takes no call."""
+    plan = update = product = staticmethod(lambda *args: None)
+
+
+def _load_native():
+    # (a product of 4096 rows, N = 32, one behind another: 8.5 us through ctypes, 3.7 so, as when replayed from a graph)
+    why = "not built, or for another torch or Python"
+    if native_is_current():
+        try:
+            from . import _native
+            _native.bind(*(C.cast(f, C.c_void_p).value for f in
+                           (_lib.spmm_exec, _lib.spmm_exec_noalloc, _lib.spmm_plan_update_values, _lib.spmm_plan)))
+            return _native
+        except ImportError as e:
+            why = str(e)
+    warnings.warn(f"{NATIVE}: {why}. Calls go through ctypes, which takes 5 us more each: build it with "
+                  "`python -m paper_2504_06443_amd.build` (or __graft_entry__.build())", RuntimeWarning, stacklevel=3)
+    return _ThroughCtypes
+
+
+_native = _load_native()
 
 SPMM_OK, SPMM_EINVAL, SPMM_EFORMAT, SPMM_ENOMEM, SPMM_EHIP, SPMM_ELIMIT = 0, -1, -2, -3, -4, -5
 ROUTE_AUTO, ROUTE_MFMA, ROUTE_VALU, ROUTE_CLASS = 0, 1, 2, 3

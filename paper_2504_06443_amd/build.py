@@ -4,7 +4,9 @@ from __future__ import annotations
 
 import os
 import subprocess
+import sys
 import sysconfig
+import warnings
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -32,12 +34,40 @@ def build_library(verbose: bool = False) -> str:
     return LIB
 
 
+def built_for() -> str:
+    """What _native is tied to, as it stands in the module."""
+    import torch
+    return f"_native for torch {torch.__version__}, Python {sys.version_info[0]}.{sys.version_info[1]}"
+
+
+def native_is_current() -> bool:
+    """_native is there, made for the torch and the Python that run (looked up in the file: to load another is too
+    late)."""
+    if not os.path.exists(NATIVE):
+        return False
+    with open(NATIVE, "rb") as f:
+        return built_for().encode() + b"\0" in f.read()
+
+
+def build_missing() -> None:
+    """What tests and the smoke run load.  The calls of _native have a slower way round it, so not every machine needs
+    to be able to compile it."""
+    if not os.path.exists(LIB):
+        build_library()
+    if not native_is_current():
+        try:
+            build_native()
+        except (OSError, subprocess.CalledProcessError) as e:
+            warnings.warn(f"_native was not built: {e}", RuntimeWarning)
+
+
 def build_native(verbose: bool = False) -> str:
     """Host code only, against the headers of the installed torch."""
     import torch
     from torch.utils import cpp_extension
     lib = os.path.join(os.path.dirname(torch.__file__), "lib")
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f'-DSPMM_BUILT_FOR="{built_for()}"',
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
            *[f for p in cpp_extension.include_paths("cuda") for f in ("-isystem", p)],
            "-isystem", sysconfig.get_paths()["include"],

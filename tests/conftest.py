@@ -11,11 +11,8 @@ if ROOT not in sys.path:
 def pytest_configure(config):
     config.addinivalue_line("markers", "gpu: needs a real MI355X (run with -m gpu)")
     # the tests load what is built; only if nothing is there, build it once
-    from paper_2504_06443_amd.build import LIB, NATIVE, build_library, build_native
-    if not os.path.exists(LIB):
-        build_library(verbose=False)
-    if not os.path.exists(NATIVE):
-        build_native(verbose=False)
+    from paper_2504_06443_amd.build import build_missing
+    build_missing()
 
 
 @pytest.fixture(scope="session")
