@@ -10,10 +10,16 @@ from test_gpu_parity import check_c, gpu, make_plan  # noqa: F401
 pytestmark = pytest.mark.gpu
 
 
-def test_values_beyond_two_gib(gpu):  # noqa: F811
-    """671 M stored entries: byte offsets of values with the top bit of 32 set."""
+def simds():
     import torch
-    M, K = 20480, 1 << 15
+    return 4 * torch.cuda.get_device_properties(0).multi_processor_count
+
+
+def test_values_beyond_two_gib(gpu):  # noqa: F811
+    """599 M stored entries: byte offsets of values with the top bit of 32 set, by index at every width that has it."""
+    import torch
+    M, K = 16 * (7 * simds() // 2 + 16), 10400
+    assert 4 * M * K > 1 << 31
     gen = torch.Generator(device="cuda").manual_seed(3)
     rowptr = torch.arange(M + 1, dtype=torch.int64, device="cuda").mul_(K).to(torch.int32)
     colind = torch.arange(K, dtype=torch.int32, device="cuda").repeat(M)
@@ -26,6 +32,8 @@ def test_values_beyond_two_gib(gpu):  # noqa: F811
         got = gpu.spmm_exec(plan, B)
         print(f"N={N}", flush=True)
         assert torch.equal(got, vals @ B)                     # whole numbers below 2^24
+        names = kernels_of(lambda: gpu.spmm_exec(plan, B))
+        assert ("narrow<%d, true" if N <= 32 else "fast<%d, false, true") % (N // 16) in names, names
 
 
 @pytest.mark.parametrize("N", [17, 32, 64, 100, 128, 256])
