@@ -157,19 +157,24 @@ __device__ inline bool work_item(const ItemMap& m, const uint32_t* panel_ptr, ui
 }
 
 // Whether values are loaded by index (spmm_load_indexed).  It saves an instruction a brick, but a wavefront's first
-// bricks arrive later, so panels have to have as many bricks as each width wants.  us, shift / index:
-//   16 columns, N = 16: bands of 3 a row (10 bricks a panel) 10.8 / 11.1, of 6 (18) 14.0 / 14.2, of 14 (46) 25.9 / 25.8,
-//     of 20 (60) 31.8 / 31.5; cells of fill 0.06 (42) 11.4 / 11.5, of 0.1 (50) 15.05 / 14.9, (100) 24.05 / 23.2
-//   32 columns, N = 32: bands 14.6 / 14.9, 18.5 / 18.4, 37.2 / 36.3, 46.6 / 45.4; cells 16.1 / 16.1, 22.4 / 22.4, 37.8 / 37.3
-//   48 columns, N = 48: bands 19.3 / 20.5, 24.3 / 24.7, 54.5 / 54.3, 73.8 / 73.8; cells 23.3 / 23.7, 32.15 / 32.4, 54.5 / 52.3;
-//     4096 panels of 75 bricks 23.55 / 22.9
-//   64 columns, N = 64: cells 28.4 / 29.0, 40.05 / 41.6, 70.4 / 70.4; 4096 panels of 75 bricks 29.8 / 28.6
-// And as many wavefronts that others hide it, 3.5 a SIMD (cells of 75 bricks, blocks of 30): 1000 panels, N = 16 9.06 / 9.34
-// and 5.90 / 6.07, N = 32 9.94 / 10.2 and 6.93 / 7.13, N = 64 in two tiles 12.3 / 12.7; 3000, N = 16 12.1 / 12.2 and
-// 9.34 / 9.45, N = 32 15.9 / 15.8 and 12.1 / 12.0, N = 64 22.5 / 23.0; 4000, N = 16 14.1 / 14.0, N = 64 29.4 / 28.3.
+// bricks arrive later, so panels have to have as many bricks as each width wants, and SIMDs at least 3.5 wavefronts, of
+// which others hide it.  us, shift / index; matrices of even panels, 12 entries a brick, the columns in a band or anywhere:
+//   16 columns: from 64 bricks a panel, and from 44 with more than 5 wavefronts a SIMD.  4 a SIMD, band, 44 bricks 8.03 / 8.19, 64
+//     10.51 / 10.51, 80 12.56 / 12.47; 5 a SIMD, 44 bricks 9.13 / 9.26; 5.5, 10.39 / 10.40, anywhere 12.18 / 11.96; 8, 13.91 / 13.52,
+//     160 bricks 49.8 / 47.4; 24 a SIMD, 44 bricks 37.2 / 36.0, anywhere 51.2 / 51.1.
+//   32 columns: from 20 bricks.  Blocks of 15 bricks, 8 a SIMD 8.93 / 9.10, of 22, 16 a SIMD 21.69 / 21.61, of 29 26.92 / 26.44;
+//     64 bricks, 4 a SIMD 14.63 / 14.28, anywhere 16.50 / 16.31; 12 a SIMD 40.05 / 39.00, anywhere 62.2 / 61.9.
+//   48 columns: from 64 bricks.  Blocks of 32, 8 a SIMD 21.72 / 21.85, 44 bricks, 10 a SIMD 30.05 / 30.87; 64 bricks, 4 a SIMD 18.23 /
+//     17.91, 8 34.02 / 33.64, anywhere 54.1 / 54.5; 16 a SIMD 62.6 / 61.3; 80 bricks, 8 a SIMD, anywhere 66.2 / 65.0.
+//   64 columns: from 64 bricks, as long as all wavefronts are resident: the kernel with the index takes 60 vector registers and
+//     a SIMD holds six, the other 62 and five.  64 bricks, 4 a SIMD 21.82 / 21.84, anywhere 26.8 / 25.0; 5.5 32.2 / 30.9, 46.5 / 45.2; 6.0
+//     32.6 / 31.2, 50.5 / 48.1; 6.05 35.8 / 36.9, 53.0 / 53.1; 8 41.1 / 43.5, 71.3 / 72.7; 12 64.0 / 63.8, 118.2 / 119.2.
+// Fewer wavefronts a SIMD (cells of 75 bricks): 1, N = 16 9.06 / 9.34, N = 32 9.94 / 10.2; 2 of 64 columns 12.3 / 12.7; 3, N = 16
+// 12.1 / 12.2, N = 64 22.5 / 23.0.
 inline bool values_by_index(const WorkSource& w, int tile, int64_t tiles) {
-  return w.mean_bricks() >= (tile == 32 ? 20 : tile == 16 ? 44 : 64) &&
-         2 * tiles * ((int64_t)w.n_items + w.n_parts) >= 7 * (int64_t)w.simds;
+  const int64_t waves = tiles * ((int64_t)w.n_items + w.n_parts);
+  const int64_t least = tile == 32 ? 20 : tile == 16 && waves > 5 * (int64_t)w.simds ? 44 : 64;
+  return w.mean_bricks() >= least && 2 * waves >= 7 * (int64_t)w.simds && (tile != 64 || waves <= 6 * (int64_t)w.simds);
 }
 
 constexpr int64_t kNarrowLargeB = int64_t(64) << 20;

@@ -60,16 +60,24 @@ def test_split_panels_over_a_large_b(gpu, N, large):  # noqa: F811
         check_c(Cd.cpu().numpy(), Cref, S)
 
 
-@pytest.mark.parametrize("N, least", [(16, 44), (31, 20), (32, 20), (48, 64), (61, 64), (64, 64)])
-@pytest.mark.parametrize("too_few", ["", "bricks", "panels"])
-def test_values_by_index_from_a_mean_of_bricks(gpu, N, least, too_few):  # noqa: F811
-    """Panels of 3 and of 2m - 3 bricks: m on average as each width wants it, or one less; 3.5 panels a SIMD, or one
-    less."""
+RULES = [(16, 64, 3.5, None), (16, 44, 5, None), (31, 20, 3.5, None), (32, 20, 3.5, None), (48, 64, 3.5, None),
+         (61, 64, 3.5, 6), (64, 64, 3.5, 6)]
+
+
+@pytest.mark.parametrize("N, least, fewest, most, outside", [
+    rule + (outside,) for rule in RULES for outside in ("", "bricks", "panels", "many") if rule[3] or outside != "many"])
+def test_values_by_index_from_a_mean_of_bricks(gpu, N, least, fewest, most, outside):  # noqa: F811
+    """Panels of 3 and of 2m - 3 bricks: m on average as each width wants it, or one less; as many panels a SIMD as it
+    wants, or one less, and as many as it may have, or one more."""
     import torch
-    simds = 4 * torch.cuda.get_device_properties(0).multi_processor_count
-    P, rng = 7 * simds // 2 - (too_few == "panels"), np.random.default_rng(N)
-    m = least - (too_few == "bricks")
+    P = int(fewest * simds()) + (fewest == 5) - (outside == "panels")
+    if most is not None and outside != "panels":
+        P = most * simds() + (outside == "many")
+    rng = np.random.default_rng(N)
+    m = least - (outside == "bricks")
     bricks = np.where(np.arange(P) % 2, 3, 2 * m - 3)
+    if P % 2:
+        bricks[-1] = m
     K = 8 * least + 9
     cols = np.concatenate([np.arange(4 * b) * 2 % K for b in bricks])   # (K is odd)
     panel = np.repeat(np.arange(P), 4 * bricks)
@@ -82,5 +90,5 @@ def test_values_by_index_from_a_mean_of_bricks(gpu, N, least, too_few):  # noqa:
     got = []
     names = kernels_of(lambda: got.append(gpu.spmm_exec(plan, torch.from_numpy(B).cuda())))
     kernel = "narrow<%d, %s, false, 4>" if N <= 32 else "fast<%d, false, %s, 4>"
-    assert kernel % ((N + 15) // 16, "false" if too_few else "true") in names, names
+    assert kernel % ((N + 15) // 16, "false" if outside else "true") in names, names
     check_c(got[0].cpu().numpy(), Cref, S)
