@@ -19,7 +19,13 @@ def simds():
     return 4 * torch.cuda.get_device_properties(0).multi_processor_count
 
 
-@pytest.mark.parametrize("per_simd", [0.02, 0.6, 1.5, 1.6, 2.5, 2.6])
+# the tile that even panels run on, by panels a SIMD (2.5: one panel more)
+TILES = {0.02: {64: 16, 96: 16, 128: 16, 256: 16}, 0.6: {64: 16, 96: 32, 128: 32, 256: 64}, 1.5: {64: 32, 96: 96, 128: 64, 256: 128},
+         1.6: {64: 64, 96: 96, 128: 128, 256: 128}, 2.4: {64: 64, 96: 96, 128: 64, 256: 128}, 2.5: {64: 64, 128: 128, 256: 128},
+         2.6: {64: 64, 128: 128, 256: 128}}
+
+
+@pytest.mark.parametrize("per_simd", sorted(TILES))
 @pytest.mark.parametrize("split", [0, 2])
 @pytest.mark.parametrize("scattered", [False, True])
 def test_every_width_on_either_side_of_the_rule(gpu, per_simd, split, scattered):  # noqa: F811
@@ -35,7 +41,7 @@ def test_every_width_on_either_side_of_the_rule(gpu, per_simd, split, scattered)
     Call, S = oracle.spmm_f64(A.rowptr, A.colind, A.vals, Ball)
     for N in WIDTHS:
         print(f"{panels} panels, N={N} split={split} scattered={scattered}", flush=True)
-        offset = N % 4                                      # operands at every dword alignment
+        offset = (N + WIDTHS.index(N)) % 4                  # operands at every dword alignment
         Bd = torch.empty(A.K * N + 4, device="cuda")[offset:offset + A.K * N].view(A.K, N)
         Bd.copy_(torch.from_numpy(Ball[:, :N].copy()))
         whole = torch.full((A.M * N + 8,), 7.0, device="cuda")
@@ -45,6 +51,10 @@ def test_every_width_on_either_side_of_the_rule(gpu, per_simd, split, scattered)
         torch.cuda.synchronize()
         check_c(Cd.cpu().numpy(), Call[:, :N], S[:, :N])
         assert bool((whole[:offset] == 7.0).all()) and bool((whole[offset + A.M * N:] == 7.0).all())
+        if split == 0 and not scattered and N in TILES[per_simd]:
+            names = kernels_of(lambda: gpu.spmm_exec(plan, Bd, Cd))
+            tile = TILES[per_simd][N]
+            assert ("narrow<%d, " if tile <= 32 else "fast<%d, ") % (tile // 16) in names, (N, names)
 
 
 @pytest.mark.parametrize("N", [48, 64, 128])

@@ -77,21 +77,32 @@ def test_split_panels_on_either_side_of_the_rule(gpu, N):  # noqa: F811
     check_c(C.cpu().numpy(), Cref, S)
 
 
-@pytest.mark.parametrize("N", [8, 16, 20, 32, 48])
-def test_infinities_stay_where_the_other_tiles_have_them(gpu, N):  # noqa: F811
+@pytest.mark.parametrize("N, wide", [(8, 0), (16, 0), (20, 0), (32, 0), (48, 0), (48, 3), (64, 4), (77, 5), (96, 6), (100, 7),
+                                     (128, 8), (144, 5)])
+def test_infinities_stay_where_the_other_tiles_have_them(gpu, N, wide):  # noqa: F811
     """A panel's rows with an entry in the column of an infinity are infinite, its other rows NaN (0 * inf), and
-    no other panel has either, whatever place the column's brick has in a load or chunk (N = 48: the wider tiles)."""
+    no other panel has either, whatever place the column's brick has in a load or chunk, on the narrow tiles of few
+    panels and on wide ones."""
     import torch
-    A = panels_of(BRICKS)
-    plan = make_plan(gpu, A)
+    A = more = panels_of(BRICKS)
+    rows = torch.arange(A.M)
+    if wide:
+        from test_gpu_widths import among_empty_panels
+        more, rows = among_empty_panels(A, 3.6)
+    plan = make_plan(gpu, more)
     gpu.spmm_plan_set_split(plan, gpu.SPLIT_NEVER)
+    names = kernels_of(lambda: gpu.spmm_exec(plan, torch.zeros((A.K, N), device="cuda")))
+    assert ("fast<%d, " % wide if wide else "narrow<") in names, names
     dense = np.zeros((A.M, A.K), np.float32)
     dense[np.repeat(np.arange(A.M), np.diff(A.rowptr)), A.colind] = A.vals
     bricks = np.repeat(BRICKS, 16)[:A.M]
     for n in BRICKS[1:]:
         B = W.dense_b(A.K, N, 7)
         B[4 * n - 1] = np.inf                              # the last column of panels of n bricks
-        C = gpu.spmm_exec(plan, torch.from_numpy(B).cuda()).cpu().numpy()
+        C = gpu.spmm_exec(plan, torch.from_numpy(B).cuda())
+        infinite = int(torch.isfinite(C).logical_not().sum())
+        C = C[rows.cuda()].cpu().numpy()
+        assert infinite == np.count_nonzero(~np.isfinite(C))
         entry = dense[:, 4 * n - 1]
         expect = np.where(bricks < n, 0.0, np.where(entry != 0, np.copysign(np.inf, entry), np.nan))
         got = np.where(np.isfinite(C), 0.0, C)
