@@ -31,8 +31,9 @@ def plan_kernels(tmp_path_factory):
 
 
 def instructions(code, kernel):
-    body = re.search(r"^_ZN4spmm\S*%s\S*:.*?^\.Lfunc_end" % kernel, code, re.M | re.S)[0]
-    return [line.split(";")[0].strip() for line in body.splitlines()]
+    bodies = re.findall(r"^_ZN4spmm\S*%s\S*:.*?^\.Lfunc_end" % kernel, code, re.M | re.S)
+    assert len(bodies) == 1, "%d functions are named like %s" % (len(bodies), kernel)
+    return [line.split(";")[0].strip() for line in bodies[0].splitlines()]
 
 
 def test_merge_loads_a_round_of_parts_at_a_time(product_kernels):
@@ -46,10 +47,11 @@ def test_merge_loads_a_round_of_parts_at_a_time(product_kernels):
     assert longest >= 16
 
 
-def test_narrow_tile_enters_its_loop_with_the_ring_full(product_kernels):
+@pytest.mark.parametrize("waves", [4, 1])              # a workgroup
+def test_narrow_tile_enters_its_loop_with_the_ring_full(product_kernels, waves):
     """Four steps of two loads are in flight at the head of the check-free loop, and the loop begins with
     three more: the first operand waits for none of the eight youngest."""
-    code = instructions(product_kernels, "k_spmm_mfma_fastILi1ELb0E")
+    code = instructions(product_kernels, "k_spmm_mfma_fastILi1ELb0ELb0ELi%dE" % waves)
     heads = {i[:-1]: n for n, i in enumerate(code) if i.startswith(".LBB")}
     loops = [code[heads[i.split()[1]]:n] for n, i in enumerate(code)
              if i.startswith("s_cbranch") and heads.get(i.split()[1], n) < n]
