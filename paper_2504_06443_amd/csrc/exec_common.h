@@ -181,16 +181,19 @@ constexpr int64_t kNarrowLargeB = int64_t(64) << 20;
 
 // Workgroups of one wavefront, for graphs (scattered, one panel in 512 and more of them split) where B is large: their
 // panels differ so much that the slots of a workgroup's first wavefronts stay empty until the last one ends.  us, four /
-// one: graphs of 326 k and 800 k rows, N = 64 60.2 / 58.8 and 145 / 140, N = 80 84.8 / 83.1 and 201 / 201, N = 96 88.4 / 86.1 and
-// 216 / 212, N = 112 111 / 107 and 266 / 258, N = 128 115.9 / 111.2 and 276 / 267, N = 144 152 / 151 and 375 / 374, N = 256 221 /
-// 214; narrower ones of 600 k and 1.05 M rows, N = 32 60.1 / 58.0 and 103 / 97, N = 48 97.5 / 96.7 and 169 / 169, N = 16 (the
-// latter) 79.6 / 78.7, N = 17 107.5 / 108.9; 100 k rows 36.7 / 37.6.
+// one, each product with a B of its own: graphs of 326 k and 800 k rows, N = 64 60.5 / 58.7 and 143.5 / 138.2, N = 96 88.6 / 86.8 and
+// 212 / 208, N = 112 109 / 106 and 260 / 255, N = 128 113.8 / 109.8 and 273 / 262, N = 256 216 / 213 and 558 / 535; narrower ones of
+// 400 k and 1.05 M rows, N = 32 45.0 / 43.7 and 101.8 / 96.3, N = 16 (the latter) 80.7 / 80.4; 60 k rows, N = 384 66.2 / 63.7.  With
+// one B for all products, from the Infinity Cache where it fits, four wavefronts are 1 to 5 % ahead there (326 k rows, N = 64
+// 53.4 / 55.2, N = 128 102.1 / 105.0), and behind as ever beyond (N = 384 323 / 311).
+// Tiles of 48 and 80 columns keep four, new B / one B: 326 k rows, N = 80 83.7 / 83.0 and 78.1 / 78.9; 500 k, N = 48 83.1 / 83.1
+// and 78.4 / 79.0; 1.05 M, N = 48 163.6 / 165.7 and 154 / 159, N = 80 261.9 / 261.3 and 259.7 / 258.8.
 // Even panels keep four, whether some are long or not: 400 k rows of blocks, N = 128 181 / 184, with one full row 270 / 272,
 // with two 285 / 293, with 200 of 3000 entries 255 / 264, 800 k rows, N = 32 and one full row 187 / 191; only where the
 // long rows are a quarter of the matrix and more either may win by far (350 k rows, 16 full ones, N = 128 541 / 602, N = 256
 // 1143 / 922).  Cells of 600 k rows with one long row 209 / 212, with 30 215 / 220, with 300 278 / 268.
-inline bool single_waves(const WorkSource& w, int64_t N, int64_t K) {
-  return w.scattered && w.n_split > 0 && 512 * w.n_split >= w.panels && K * N * 4 >= kNarrowLargeB;
+inline bool single_waves(const WorkSource& w, int tile, int64_t N, int64_t K) {
+  return tile != 48 && tile != 80 && w.scattered && w.n_split > 0 && 512 * w.n_split >= w.panels && K * N * 4 >= kNarrowLargeB;
 }
 
 inline bool ptr_aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }

@@ -855,21 +855,25 @@ hipError_t launch_spmm_mfma(const BrickFormat& f, const WorkSource& w, const flo
       return launch_spmm_mfma_narrow(f, w, tile, B, C, partial, M, N, K, s);
     const unsigned gy = (unsigned)((N + tile - 1) / tile);
     const uint32_t k_last = (uint32_t)(K - 1);
-    const bool single = single_waves(w, N, K);
+    const bool single = single_waves(w, tile, N, K);
 #define SPMM_LAUNCH_WAVES(TT, FF, II, W)                                                        \
   hipLaunchKernelGGL((k_spmm_mfma_fast<TT, FF, II, W>), dim3(item_blocks<W>(w), gy), dim3(64 * W), 0, s, \
                      SPMM_ITEM_ARGS(W, w), f.panel_ptr, f.brick_cols,                           \
                      f.brick_mask, f.brick_valptr, f.vals, B, C, partial, M, N, k_last)
+// (single_waves: no tiles of 48 and 80; those of 32 are for a B below its bound)
 #define SPMM_LAUNCH_FAST(TT, FF, II)                                                            \
   do {                                                                                          \
     if (single) SPMM_LAUNCH_WAVES(TT, FF, II, 1); else SPMM_LAUNCH_WAVES(TT, FF, II, kWavesPerBlock); \
   } while (0)
     switch (tile / 16) {
       case 1: SPMM_LAUNCH_FAST(1, false, false); break;   // (split panels: short ones mostly)
-      case 2: SPMM_LAUNCH_FAST(2, false, false); break;
-      case 3: if (values_by_index(w, tile, gy)) SPMM_LAUNCH_FAST(3, false, true); else SPMM_LAUNCH_FAST(3, false, false); break;
+      case 2: SPMM_LAUNCH_WAVES(2, false, false, kWavesPerBlock); break;
+      case 3:
+        if (values_by_index(w, tile, gy)) SPMM_LAUNCH_WAVES(3, false, true, kWavesPerBlock);
+        else SPMM_LAUNCH_WAVES(3, false, false, kWavesPerBlock);
+        break;
       case 4: if (values_by_index(w, tile, gy)) SPMM_LAUNCH_FAST(4, false, true); else SPMM_LAUNCH_FAST(4, false, false); break;
-      case 5: SPMM_LAUNCH_FAST(5, false, false); break;
+      case 5: SPMM_LAUNCH_WAVES(5, false, false, kWavesPerBlock); break;
       case 6: SPMM_LAUNCH_FAST(6, false, false); break;
       case 7: SPMM_LAUNCH_FAST(7, false, false); break;
       default:   // whole 128-column tiles: the second vector of a B row at a constant offset

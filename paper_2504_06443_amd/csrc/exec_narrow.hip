@@ -246,7 +246,7 @@ hipError_t launch_spmm_mfma_narrow(const BrickFormat& f, const WorkSource& w, in
 #define SPMM_LAUNCH_NARROW(TT)                                                                  \
   do {                                                                                          \
     if (gy > 1) SPMM_LAUNCH_WAVES(TT, false, true, kWavesPerBlock);   /* too few for an index */ \
-    else if (single_waves(w, N, K))                                                             \
+    else if (single_waves(w, tile, N, K))                                                             \
       { if (by_index) SPMM_LAUNCH_WAVES(TT, true, false, 1); else SPMM_LAUNCH_WAVES(TT, false, false, 1); } \
     else if (by_index) SPMM_LAUNCH_WAVES(TT, true, false, kWavesPerBlock);                      \
     else SPMM_LAUNCH_WAVES(TT, false, false, kWavesPerBlock);                                   \

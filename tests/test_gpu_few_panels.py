@@ -131,10 +131,10 @@ def test_a_few_long_rows_do_not_make_a_graph(gpu, per_simd, rows, entries, tiles
         check_c(C.cpu().numpy(), Call[:, :N], S[:, :N])
 
 
-@pytest.mark.parametrize("N", [32, 64, 128])
+@pytest.mark.parametrize("N", [32, 48, 64, 80, 128])
 @pytest.mark.parametrize("rows, waves", [(1, 4), (9, 4), ("graph", 1)])
 def test_long_rows_over_a_large_b(gpu, N, rows, waves):  # noqa: F811
-    """Workgroups of one wavefront are for graphs, not for a band with a few long rows."""
+    """Workgroups of one wavefront are for graphs, not for a band with a few long rows, and not for tiles of 48 and 80."""
     import torch
     M = 16 * 4133 - 3
     A = W.power_law(M, target_nnz=int(2.854 * M), seed=3) if rows == "graph" else \
@@ -150,6 +150,6 @@ def test_long_rows_over_a_large_b(gpu, N, rows, waves):  # noqa: F811
     Bd[torch.arange(A.K, device="cuda") * step + 5] = torch.from_numpy(B).cuda()
     C = gpu.spmm_exec(plan, Bd)
     names = kernels_of(lambda: gpu.spmm_exec(plan, Bd))
-    assert ", %d>" % waves in names, names
+    assert ", %d>" % (4 if N in (48, 80) else waves) in names, names
     Cref, S = oracle.spmm_f64(A.rowptr, A.colind, A.vals, B)
     check_c(C.cpu().numpy(), Cref, S)
