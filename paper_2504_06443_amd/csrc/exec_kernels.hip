@@ -774,7 +774,10 @@ int mfma_fp32_tile(int64_t N, int64_t K, int64_t nnz) {
 //     three tiles for two 8.4 / 8.55).
 //   64 -> 32 and 32 -> 16 where the wider one gives at most 1.5 a SIMD, in 16-byte loads (exec_narrow.hip): 256
 //     panels, N = 64 6.8 / 5.3 / 4.7 and 8.5 / 6.5 / 5.6; 1250 panels, N = 64 10.0 / 9.0 / 9.2; 1530, N = 64 11.4 / 10.1 and
-//     18.3 / 15.4, N = 32 7.9 / 7.5 and 13.2 / 11.4; 1024 panels, N = 128 10.4 / 11.0 / 13.4. Cells of 3000 panels lose (22.5 /
+//     18.3 / 15.4; 1024 panels, N = 128 10.4 / 11.0 / 13.4.  Where the wide tile is 32 itself, only as long as each of the
+//     narrower ones has a SIMD to itself: blocks of 30 bricks, 440 panels 4.58 / 4.32, 560 4.71 / 4.96, 850 4.69 / 5.08; of 117
+//     bricks, 390 panels 11.5 / 9.8, 520 11.7 / 11.7, 880 11.9 / 12.2; with split panels 100 11.6 / 9.7, 1087 27.6 / 30.0.
+//     Cells of 3000 panels lose (22.5 /
 //     24.7); graphs gain further (of 2500 panels, N = 64 14.9 / 14.2, N = 96 18.2 / 16.8; of 4000, N = 64 18.4 /
 //     17.9), up to twelve of the narrower a SIMD (of 10,000 31.5 / 31.9), but no matrix with only a few long rows (blocks and
 //     one of 1000 entries, 3750 panels, N = 64 19.0 / 20.9; cells and one of 2000, 4000 panels 15.8 / 17.0).
@@ -798,7 +801,7 @@ int mfma_run_tile(const WorkSource& w, int64_t N, int64_t K, int64_t nnz) {
     const int64_t narrower = 16 * (t > 1 && N % 32 == 0 ? (t + 1) / 2 * 2 : t);
     const int64_t columns = k * narrower, least = tiles(whole) * whole;   // multiplied, with those behind N
     const int64_t waves = items * tiles(2 * width);
-    if (narrower >= tile) continue;
+    if (narrower >= tile || (whole == 32 && 2 * items > w.simds)) continue;
     const int64_t most = k < 2 * tiles(whole) ? 8 : (N % 4 ? 9 : 10);   // narrower wavefronts for two SIMDs
     // columns of the SIMD with most: no gain where that stays, but for wavefronts that were alone
     const int64_t then = (items * k + w.simds - 1) / w.simds * narrower;

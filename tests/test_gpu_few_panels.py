@@ -20,7 +20,8 @@ def simds():
 
 
 # the tile that even panels run on, by panels a SIMD (2.5: one panel more)
-TILES = {0.02: {64: 16, 96: 16, 128: 16, 256: 16}, 0.6: {64: 16, 96: 32, 128: 32, 256: 64}, 1.5: {64: 32, 96: 96, 128: 64, 256: 128},
+TILES = {0.02: {20: 16, 32: 16, 64: 16, 96: 16, 128: 16, 256: 16}, 0.5: {31: 16, 32: 16},
+         0.6: {31: 32, 32: 32, 64: 16, 96: 32, 128: 32, 256: 64}, 1.5: {32: 32, 64: 32, 96: 96, 128: 64, 256: 128},
          1.6: {64: 64, 96: 96, 128: 128, 256: 128}, 2.4: {64: 64, 96: 96, 128: 64, 256: 128}, 2.5: {64: 64, 128: 128, 256: 128},
          2.6: {64: 64, 128: 128, 256: 128}}
 
@@ -106,6 +107,8 @@ def with_long_rows(A, rows, entries):
 
 
 @pytest.mark.parametrize("per_simd, rows, entries, tiles", [
+    (0.4, 1, 600, {24: 16, 32: 16}),            # half as wide as 32 while each wavefront has a SIMD
+    (0.5, 1, 600, {24: 32, 32: 32}),
     (3.66, 0, 0, {64: 64, 128: 128}),            # even panels, more than narrow tiles are for,
     (3.66, 1, 1000, {64: 64, 96: 96, 128: 128}),     # and the same with a long row: neither a graph
     (4.4, 1, 1000, {64: 64, 128: 64}),           # but just over what the device holds
@@ -116,9 +119,12 @@ def with_long_rows(A, rows, entries):
 def test_a_few_long_rows_do_not_make_a_graph(gpu, per_simd, rows, entries, tiles):  # noqa: F811
     import torch
     M = 16 * int(per_simd * simds())
-    A = W.power_law(M, target_nnz=int(2.854 * M), seed=3) if rows == "graph" else W.clustered_blocks(M, 4, 60, seed=7)
-    if rows != "graph" and rows:
-        A = with_long_rows(A, rows, entries)
+    if rows == "graph":
+        A = W.power_law(M, target_nnz=int(2.854 * M), seed=3)
+    else:
+        A = W.clustered_blocks(M, 4, 60, seed=7)
+        if rows:
+            A = with_long_rows(A, rows, entries)
     plan = make_plan(gpu, A)
     Ball = W.dense_b(A.K, max(tiles), 11)
     Call, S = oracle.spmm_f64(A.rowptr, A.colind, A.vals, Ball)
