@@ -760,8 +760,9 @@ int mfma_fp32_tile(int64_t N, int64_t K, int64_t nnz) {
 //     as many (N = 300, 5 tiles for 3: at 3.6 a SIMD 21.3 / 18.3, at 4 a band 13.9 / 14.5), or rows of B are not
 //     aligned (N = 339, at 4.1 a SIMD 23.1 / 21.3, at 4.95 22.0 / 23.0).  Beyond that, as long as B stays in the Infinity
 //     Cache (a graph of 12,288 panels, B of 100 MB, 73.6 / 75.1):
-//     - graphs: scattered panels, bound by memory and not by MFMAs, one in 40 and more of them split (4096 panels 30.3 /
-//       26.6);
+//     - graphs: scattered panels of few bricks, bound by memory and not by MFMAs, one in 40 and more of them split (4096
+//       panels 30.3 / 26.6; not of many: 2500 panels of 120 bricks, N = 64 in tiles of 32 34.7 / 40.5, of 51 19.9 / 21.7, of 27 14.6 /
+//       15.5, of 18 12.7 / 13.2; graphs have 12 to 15);
 //     - scattered panels of many bricks (cells of 8192 panels 112.5 / 107.1; N = 128, 6000 panels of 25 bricks 46.7 / 44.1, of
 //       6 21.2 / 21.8; 4000 of 25, 7.8 a SIMD, 32.2 / 33.0; N = 256, 2800 of 25 44.5 / 41.8);
 //     - any matrix with split panels whose wide wavefronts are more than the device holds (4 a SIMD, 5 of 96 columns), where
@@ -789,7 +790,7 @@ int mfma_run_tile(const WorkSource& w, int64_t N, int64_t K, int64_t nnz) {
   const int64_t items = (int64_t)w.n_items + w.n_parts;
   auto tiles = [&](int64_t width) { return (N + width - 1) / width; };
   const bool whole_lines = N % 32 == 0 && K * N * 4 < kNarrowLargeB;
-  const bool graph = w.scattered && 40 * w.n_split >= w.panels;
+  const bool graph = w.scattered && 40 * w.n_split >= w.panels && w.mean_bricks() <= 16;
   const int64_t wide = items * tiles(whole);
   const int64_t round = (whole > 96 ? 4 : 5) * (int64_t)w.simds;
   const bool second_round = w.n_split > 0 && wide > round &&

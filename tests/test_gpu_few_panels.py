@@ -109,6 +109,7 @@ def with_long_rows(A, rows, entries):
 @pytest.mark.parametrize("per_simd, rows, entries, tiles", [
     (0.4, 1, 600, {24: 16, 32: 16}),            # half as wide as 32 while each wavefront has a SIMD
     (0.5, 1, 600, {24: 32, 32: 32}),
+    (2.0, "wide", 0, {64: 64}),                  # scattered and split, but of many bricks
     (3.66, 0, 0, {64: 64, 128: 128}),            # even panels, more than narrow tiles are for,
     (3.66, 1, 1000, {64: 64, 96: 96, 128: 128}),     # and the same with a long row: neither a graph
     (4.4, 1, 1000, {64: 64, 128: 64}),           # but just over what the device holds
@@ -121,6 +122,8 @@ def test_a_few_long_rows_do_not_make_a_graph(gpu, per_simd, rows, entries, tiles
     M = 16 * int(per_simd * simds())
     if rows == "graph":
         A = W.power_law(M, target_nnz=int(2.854 * M), seed=3)
+    elif rows == "wide":
+        A = with_long_rows(W.uniform_random(M, M, 6 / M, 3), M // 16 // 40 + 1, 1500)
     else:
         A = W.clustered_blocks(M, 4, 60, seed=7)
         if rows:
