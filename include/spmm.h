@@ -316,8 +316,10 @@ typedef struct spmm_worklist_info {
   int64_t n_valu_panels;  /* panels handled by the vector-ALU kernel          */
   int64_t n_split_panels; /* panels split into more than one part             */
   int64_t num_waves;      /* Eq. 7 denominator actually used                  */
-  int32_t n_tile;         /* columns of C per wavefront (16, 32, ... 128); few panels, which
-                             would not fill the device, are multiplied on narrower ones */
+  int32_t n_tile;         /* columns of C per wavefront (16, 32, ... 128) that the items and
+                             Eq. 7 count with.  The kernel runs on these, but for few panels
+                             and scattered ones, which it multiplies item by item on narrower
+                             tiles: no field here depends on those */
   int32_t n_tiles;        /* ceil(N / n_tile)                                 */
   int32_t num_cus;        /* compute units of the plan's device               */
   int32_t resident_waves_per_cu; /* wavefronts of the MFMA kernel, at the
