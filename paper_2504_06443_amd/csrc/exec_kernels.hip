@@ -780,8 +780,12 @@ int mfma_fp32_tile(int64_t N, int64_t K, int64_t nnz) {
 //     bricks, 390 panels 11.5 / 9.8, 520 11.7 / 11.7, 880 11.9 / 12.2; with split panels 100 11.6 / 9.7, 1087 27.6 / 30.0.
 //     Cells of 3000 panels lose (22.5 /
 //     24.7); graphs gain further (of 2500 panels, N = 64 14.9 / 14.2, N = 96 18.2 / 16.8; of 4000, N = 64 18.4 /
-//     17.9), up to twelve of the narrower a SIMD (of 10,000 31.5 / 31.9), but no matrix with only a few long rows (blocks and
-//     one of 1000 entries, 3750 panels, N = 64 19.0 / 20.9; cells and one of 2000, 4000 panels 15.8 / 17.0).
+//     17.9), up to twelve of the narrower a SIMD (of 10,000 31.5 / 31.9).  Matrices with a few long rows, which as graphs
+//     would lose (blocks and one of 1000 entries, 3750 panels, N = 64 19.0 / 20.9; cells and one of 2000, 4000 panels
+//     15.8 / 17.0), gain as far as twelve where the wide tiles multiply columns behind N and these do not (N = 160, 96 / 32:
+//     cells of 850 panels and three rows of 2000 11.7 / 9.9; 1670 of a band and three of 700 11.2 / 9.5; at 2.5 and more a SIMD of 96
+//     0.87 to 0.91; with one panel in 40 and more split up to seven, 0.82 to 0.98, and 1.05 beyond), and any with split panels up to 1.5 wide ones a SIMD where there are no
+//     tiles of 64 between (N = 96, 96 / 32: 0.92 to 1.00 at 0.75 to 1.5 a SIMD, 1.02 beyond).
 // Not where the narrower tiles multiply many columns more than there are: N = 80 as two of 48, 930 panels, 9.1 / 9.7.
 // Work lists and Eq. 7 go by the wide tiles, so which panels are split does not depend on this.
 int mfma_run_tile(const WorkSource& w, int64_t N, int64_t K, int64_t nnz) {
@@ -807,13 +811,15 @@ int mfma_run_tile(const WorkSource& w, int64_t N, int64_t K, int64_t nnz) {
     // columns of the SIMD with most: no gain where that stays, but for wavefronts that were alone
     const int64_t then = (items * k + w.simds - 1) / w.simds * narrower;
     const bool less = then < (wide + w.simds - 1) / w.simds * whole + (wide <= w.simds ? 1 : 0);
+    const int64_t most_32 = graph ? 12 : w.n_split == 0 || columns >= least ? 0 : 40 * w.n_split < w.panels ? 12 : 7;
     if (width == 64 ? 10 * columns <= 11 * least &&
                           ((less && 2 * items * k <= most * w.simds) ||
                            (whole_lines && (graph || second_round ||
                                             (w.scattered && w.mean_bricks() >= 16 && items * k >= 10 * w.simds))))
                     : 4 * columns < 5 * least &&
                           ((less && 2 * waves <= 3 * w.simds) ||
-                           (width == 32 && whole_lines && graph && items * k <= 12 * w.simds)))
+                           (width == 32 && whole_lines &&
+                            (items * k <= most_32 * w.simds || (w.n_split > 0 && tile == whole && 2 * wide <= 3 * w.simds)))))
       tile = (int)narrower;
   }
   return tile;

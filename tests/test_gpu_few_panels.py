@@ -111,7 +111,10 @@ def with_long_rows(A, rows, entries):
     (0.5, 1, 600, {24: 32, 32: 32}),
     (2.0, "wide", 0, {64: 64}),                  # scattered and split, but of many bricks
     (3.66, 0, 0, {64: 64, 128: 128}),            # even panels, more than narrow tiles are for,
-    (3.66, 1, 1000, {64: 64, 96: 96, 128: 128}),     # and the same with a long row: neither a graph
+    (3.66, 1, 1000, {64: 64, 96: 96, 128: 128, 160: 96}),     # and the same with a long row: neither a graph
+    (1.2, 0, 0, {96: 96, 160: 64}),
+    (1.2, 1, 1000, {96: 32, 160: 32}),           # three or five for one or two wide ones
+    (2.3, 1, 1000, {96: 96, 160: 32}),
     (4.4, 1, 1000, {64: 64, 128: 64}),           # but just over what the device holds
     (6.1, 1, 1000, {64: 64, 128: 128}),
     (6.1, 30, 2000, {64: 64, 128: 64}),          # or with much of the matrix in long rows
