@@ -169,12 +169,14 @@ __device__ inline bool work_item(const ItemMap& m, const uint32_t* panel_ptr, ui
 //   64 columns: from 64 bricks, as long as all wavefronts are resident: the kernel with the index takes 60 vector registers and
 //     a SIMD holds six, the other 62 and five.  64 bricks, 4 a SIMD 21.82 / 21.84, anywhere 26.8 / 25.0; 5.5 32.2 / 30.9, 46.5 / 45.2; 6.0
 //     32.6 / 31.2, 50.5 / 48.1; 6.05 35.8 / 36.9, 53.0 / 53.1; 8 41.1 / 43.5, 71.3 / 72.7; 12 64.0 / 63.8, 118.2 / 119.2.
+//     With several tiles of 64 a panel beyond that, too (anywhere, 10 to 16 a SIMD, N = 128 to 256: 64 bricks 0.95 to 1.02 of
+//     the time, 120 0.95 to 1.00; 3500 panels of 120, N = 160 120.6 / 115.3).
 // Fewer wavefronts a SIMD (cells of 75 bricks): 1, N = 16 9.06 / 9.34, N = 32 9.94 / 10.2; 2 of 64 columns 12.3 / 12.7; 3, N = 16
 // 12.1 / 12.2, N = 64 22.5 / 23.0.
 inline bool values_by_index(const WorkSource& w, int tile, int64_t tiles) {
   const int64_t waves = tiles * ((int64_t)w.n_items + w.n_parts);
   const int64_t least = tile == 32 ? 20 : tile == 16 && waves > 5 * (int64_t)w.simds ? 44 : 64;
-  return w.mean_bricks() >= least && 2 * waves >= 7 * (int64_t)w.simds && (tile != 64 || waves <= 6 * (int64_t)w.simds);
+  return w.mean_bricks() >= least && 2 * waves >= 7 * (int64_t)w.simds && (tile != 64 || tiles > 1 || waves <= 6 * (int64_t)w.simds);
 }
 
 constexpr int64_t kNarrowLargeB = int64_t(64) << 20;

@@ -92,3 +92,25 @@ def test_values_by_index_from_a_mean_of_bricks(gpu, N, least, fewest, most, outs
     kernel = "narrow<%d, %s, false, 4>" if N <= 32 else "fast<%d, false, %s, 4>"
     assert kernel % ((N + 15) // 16, "false" if outside else "true") in names, names
     check_c(got[0].cpu().numpy(), Cref, S)
+
+
+def test_values_by_index_in_several_tiles_of_a_panel(gpu):  # noqa: F811
+    """Scattered panels on tiles of 64 columns, more than ten wavefronts a SIMD."""
+    import torch
+    P, bricks, N, rng = 5 * simds() + 1, 64, 128, np.random.default_rng(3)
+    K = 16 * P
+    cols = (rng.integers(0, K // 4, P * bricks)[:, None] * 4 + np.arange(4)).ravel()
+    rows = 16 * np.repeat(np.arange(P), 4 * bricks) + rng.integers(0, 16, len(cols))
+    rows[::4 * bricks], rows[1::4 * bricks] = 16 * np.arange(P), 16 * np.arange(P)
+    cols[::4 * bricks], cols[1::4 * bricks] = 0, K - 1      # (so that no panel has fewer)
+    extra = 16 * np.arange(P) + 1, np.full(P, 8)
+    A = W.csr_from_coo(K, K, np.concatenate([rows] + [extra[0]] * 12), np.concatenate([cols] + [extra[1] + 40 * i for i in range(12)]),
+                       rng.uniform(-1, 1, len(rows) + 12 * P).astype(np.float32))
+    plan = make_plan(gpu, A)
+    assert gpu.spmm_plan_export(plan)["brick_mask"].shape[0] >= 64 * P
+    B = W.dense_b(A.K, N, 3)
+    Cref, S = oracle.spmm_f64(A.rowptr, A.colind, A.vals, B)
+    got = []
+    names = kernels_of(lambda: got.append(gpu.spmm_exec(plan, torch.from_numpy(B).cuda())))
+    assert "fast<4, false, true, 4>" in names, names
+    check_c(got[0].cpu().numpy(), Cref, S)
